@@ -167,6 +167,53 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
     int32_t *zero_point = per_token ? (int32_t *)x_scale + 2 * (size_t)M : (int32_t *)(ws + L.n_outliers) + 2;
     int32_t *cn = (int32_t *)(ws + L.cn);
     const int32_t *w_row_sum = (const int32_t *)(w_q + muxq::wq_rowsum_offset(N, k_pad));
+    // few tokens: the whole layer in one launch (the measurement aid that brackets the GEMM keeps
+    // the separate launches, as does Aux on a scale of its own; X is addressed with 32-bit offsets)
+    if (gemm_start == nullptr && !aux_own && (size_t)M * (size_t)ldx < (1u << 30) &&
+        muxq::few_tokens_fit(M, K, k_pad, r_cap)) {
+        muxq::FewArgs f{};
+        f.x = (const uint16_t *)X;
+        f.M = M; f.K = K; f.ldx = ldx; f.k_pad = k_pad; f.N = N;
+        f.w_q = w_q;
+        f.w_row_sum = w_row_sum;
+        f.w_scale = w_scale;
+        f.bias = (const _Float16 *)bias;
+        f.w_per_channel = w_gran == MUXQ_PER_CHANNEL;
+        f.x_per_token = per_token;
+        f.exp = exp;
+        f.r_cap = r_cap;
+        f.qmax = qmax;
+        f.threshold = threshold;
+        if (absmax_ready) {
+            f.slabs = partial;
+            f.n_slabs = absmax_slabs > 0 ? absmax_slabs : muxq::absmax_slab_count(M, k_pad);
+        }
+        f.static_mask = static_mask;
+        f.col_absmax = col_absmax;
+        f.col_scale = col_scale;
+        f.col_slot = col_slot;
+        f.col_mask = (uint8_t *)(ws + L.col_mask);
+        f.idx = idx;
+        f.n_outliers = (int32_t *)(ws + L.n_outliers);
+        f.x_scale = x_scale;
+        f.zero_point = zero_point;
+        f.body_q = body_q;
+        f.aux_q = aux_q;
+        f.w_aux = gather ? w_aux : nullptr;
+        f.cn = cn;
+        f.cn_bias = per_token ? 0 : muxq::kCnBias;
+        f.y = (_Float16 *)Y;
+        f.ldy = ldy;
+        f.dbg_acc = dbg_acc;
+        f.gelu = gelu;
+        if (gelu && next_slabs != nullptr) {
+            f.next_slabs = (uint16_t *)next_slabs;
+            f.next_ld = kpad(N);
+            f.next_count = muxq_linear_gelu_slabs(M, K, N);
+        }
+        MUXQ_TRY(muxq::launch_linear_few(f, s));
+        return MUXQ_OK;
+    }
     if (!(per_token && static_block != nullptr)) {
         if (absmax_ready)     // a producer of X has left the slab maxima in the workspace
             n_slabs = absmax_slabs > 0 ? absmax_slabs : muxq::absmax_slab_count(M, k_pad);

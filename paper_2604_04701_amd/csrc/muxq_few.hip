@@ -1,0 +1,585 @@
+// The whole MUXQ linear layer for few tokens (a decode step) as ONE launch.
+//
+// With few rows of X every stage of the layer is short, and what a call costs is the launches
+// and the memory round trips between them: a dependent launch takes 4-5 us on this chip however
+// little it does, and a GEMM kernel made of 64 x 64 or 128 x 128 output tiles leaves most CUs
+// without a tile.  So here every workgroup does the activation side of ALL rows for itself --
+// column maxima, outlier selection, codes, kept in LDS -- and then the product for 16 output
+// channels at a time.  What bounds it now: latency up to about 8 K elements of X (1 x 768 -> 2304:
+// 6.5 us inside the kernel, of which 1.6 us until X has arrived and 1.6 us selection), the vector
+// ALU work of the codes, repeated on every CU, beyond (8 x 5120: 3.1 of 10.8 us).
+// Measured, us per call, the separate launches against this kernel: 1 x 768 -> 2304 18.8 / 8.4,
+// 1 x 8192 -> 1024 49.1 / 10.1, 8 x 1280 -> 5120 -> 1280 (an MLP, two launches instead of eight)
+// 61.5 / 24.7, 16 x 2560 -> 2560 28.8 / 11.2, 32 x 1280 -> 5120 per token 24.0 / 16.4,
+// 2 x 4096 -> 16384 36.8 / 20.5.
+//
+// Product.  A block of the packed weight layout is 16 output channels x 64 input channels, 1 KiB
+// contiguous, which is exactly the first operand of one v_mfma_i32_16x16x64_i8: lane l takes the
+// 16 bytes of channel l % 16 at input channels 16 (l / 16).  Weights therefore go from memory
+// straight to registers, each byte once per call, in loads of whole KiB; the waves of the
+// workgroup split K, and their INT32 partial sums meet in LDS (integer adds: any order gives the
+// same sum).  The loads of the first 16 channels are issued before anything else, so that the
+// activation side runs in the shadow of their latency.
+//
+// Everything a caller may read from the workspace afterwards (the muxq_workspace_layout regions)
+// is written as by the separate launches: the selection results by workgroup 0, the codes in
+// shares by all workgroups, w_aux and cn by the workgroup that owns the channels.
+#include "muxq_kernels.h"
+
+namespace muxq {
+namespace {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kFewThreads = 1024, kFewWaves = kFewThreads / 64;
+constexpr int kFewMaxK = 8 * kFewThreads;                    // one 8-channel chunk per thread in the selection
+constexpr int kFewLoads = kFewMaxK / 64 / kFewWaves;         // weight blocks of a wave: all in registers
+constexpr int kFewMaxM = 64;
+
+// What the kernel needs besides FewArgs, worked out on the host: the division of its waves and LDS.
+struct FewPlan {
+    int pieces, groups;      // a row of X is `pieces` pieces of 64 chunks (8 channels each); rows in flight at once
+    int div;                 // wave / pieces == wave * div >> 16
+    int share_parts, share_len;          // codes for the caller: a row in so many parts of so many 16-byte units
+    int codes, aux, waux, red, idx, part, total;     // LDS offsets (X itself at 0)
+};
+
+FewPlan few_plan(int M, int K, int k_pad, int r_cap, int grid)
+{
+    FewPlan P;
+    P.pieces = (k_pad / 8 + 63) / 64;
+    P.groups = kFewWaves / P.pieces;
+    P.div = 65536 / P.pieces + 1;
+    P.share_parts = grid / M > 1 ? grid / M : 1;
+    const int units = k_pad / 16;
+    P.share_len = (units + P.share_parts - 1) / P.share_parts;
+    int off = M * K * 2;                                     // X, row after row
+    P.codes = off; off += M * k_pad;                         // codes of Body, tight rows
+    P.aux = off;   off += M * r_cap;                         // codes of Aux
+    P.waux = off;  off += 16 * r_cap;                        // Aux weight rows of the current 16 channels
+    P.red = off;   off += (M + 15) / 16 * 1024;              // partial sums
+    P.idx = off;   off += r_cap * 4;                         // the list
+    // partial column maxima, before there are codes or sums
+    P.part = P.codes;
+    if (P.part + kFewThreads * 16 > off) off = P.part + kFewThreads * 16;
+    P.total = off;
+    return P;
+}
+
+// Byte of (row, column) in an LDS code matrix of M rows and `cols` columns: blocks of 16 rows x 64
+// columns like the packed layout, the last one with as many rows as there are; the four 16-byte
+// chunks of a row are XOR-swizzled with row bits, so that the 16 rows a fragment read touches at
+// one chunk fall into different banks.
+__device__ __forceinline__ int few_code_pos(int row, int col, int M, int cols)
+{
+    const int mb = row >> 4, r = row & 15, rows = min(16, M - (mb << 4));
+    return (mb << 4) * cols + (col >> 6) * (rows << 6) + (r << 6) + ((((col >> 4) & 3) ^ (r >> 2)) << 4) + (col & 15);
+}
+
+// The largest magnitude among the channels of `raw` (8 fp16) that `listed` does not name, in the
+// low half, and among those it names, in the high half (fp16 magnitudes order like integers).
+__device__ __forceinline__ uint32_t chunk_maxima(uint4 raw, uint32_t listed)
+{
+    uint32_t d[4] = {raw.x & 0x7fff7fffu, raw.y & 0x7fff7fffu, raw.z & 0x7fff7fffu, raw.w & 0x7fff7fffu};
+    uint32_t l = 0;
+    if (__ballot(listed != 0) != 0) {                    // (most waves have no listed channel)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t two = listed >> (2 * i);
+            const uint32_t out = (two & 1u) * 0xffffu | (two >> 1 & 1u) * 0xffff0000u;
+            l = pk_max_u16(l, d[i] & out);
+            d[i] &= ~out;
+        }
+        l = max(l & 0xffffu, l >> 16);
+    }
+    const uint32_t m = pk_max_u16(pk_max_u16(d[0], d[1]), pk_max_u16(d[2], d[3]));
+    return max(m & 0xffffu, m >> 16) | (l << 16);
+}
+
+__device__ __forceinline__ float f32_of_half_bits(uint32_t h)
+{
+    return (float)__builtin_bit_cast(_Float16, (unsigned short)h);
+}
+
+// Scale, multiplier and zero point (Eq. 1; the zero point of the unlisted channels' codes is even,
+// see the selection kernel) from the two maxima of chunk_maxima over a row, or over the call.
+__device__ __forceinline__ void few_scale(uint32_t maxima, float shrink, float qmax, float &sx, float &inv, int &z)
+{
+    const float nm = fmaxf(0.f, f32_of_half_bits(maxima & 0xffffu)), lm = fmaxf(0.f, f32_of_half_bits(maxima >> 16));
+    const float am = fmaxf(nm, lm * shrink);             // exact: max |Body| (Eq. 4)
+    sx = am > 0.f ? am / qmax : 0.f;                     // correctly rounded binary32 divisions
+    inv = am > 0.f ? qmax / am : 0.f;
+    const int c = (int)fminf(__builtin_rintf(nm * inv), qmax);
+    z = min(c + (c & 1), (127 - c) & ~1);
+}
+
+// Maximum (two packed uint16) over the wave, in lane 63; sum of the lanes up to and including this
+// one.  (Cross-lane moves of the vector ALU: a permute through LDS is ten times their latency.)
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ uint32_t dpp_zero(uint32_t v)     // lanes without a source get 0
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_max_u16x2_to_lane63(uint32_t v)
+{
+    v = pk_max_u16(v, dpp_zero<0x111>(v));                   // row_shr 1, 2, 4, 8: lane 15 of a row of 16
+    v = pk_max_u16(v, dpp_zero<0x112>(v));
+    v = pk_max_u16(v, dpp_zero<0x114>(v));
+    v = pk_max_u16(v, dpp_zero<0x118>(v));
+    v = pk_max_u16(v, dpp_zero<0x142, 0xa>(v));              // lane 15 of a row to the next one
+    return pk_max_u16(v, dpp_zero<0x143, 0xc>(v));           // lane 31 to the upper half
+}
+__device__ __forceinline__ int wave_inclusive_sum(int x)
+{
+    uint32_t v = (uint32_t)x;
+    v += dpp_zero<0x111>(v);
+    v += dpp_zero<0x112>(v);
+    v += dpp_zero<0x114>(v);
+    v += dpp_zero<0x118>(v);
+    v += dpp_zero<0x142, 0xa>(v);
+    return (int)(v + dpp_zero<0x143, 0xc>(v));
+}
+
+// MB: 16-row blocks of tokens (1, 2 or 4).  TOKEN: one activation scale per row.
+// (Loops over rows are kept rolled: a kernel starts with a cold instruction cache, and straight-line
+// code for eight rows takes longer to fetch than to run.)
+template <int MB, bool TOKEN>
+__global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, const FewPlan L)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    typedef __attribute__((address_space(3))) void *lptr_t;
+    __shared__ __attribute__((aligned(16))) int s_tot[kFewWaves];
+    __shared__ __attribute__((aligned(16))) uint32_t s_max[kFewWaves];
+    __shared__ uint32_t s_row[kFewMaxM * kFewWaves];     // per token: the maxima of a row's pieces
+    __shared__ float s_sx[kFewMaxM], s_inv[kFewMaxM];
+    __shared__ int s_z[kFewMaxM];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int M = a.M, K = a.K, k_pad = a.k_pad, N = a.N, r_cap = a.r_cap;
+    unsigned char *const codes = lds + L.codes;
+    unsigned char *const aux = lds + L.aux;
+    unsigned char *const waux = lds + L.waux;
+    int *const red = (int *)(lds + L.red);
+    int *const idx_lds = (int *)(lds + L.idx);
+    const int C = K / 8, CA = k_pad / 8;                 // 8-channel chunks: real, with the padding
+    const int KB = k_pad / 64, nblk = (N + 15) >> 4, n_mb = (M + 15) >> 4;
+    const int ln = lane & 15, lq = lane >> 4;            // MFMA lane: row of the block, 16-byte chunk
+
+    // Activation side: a wave owns piece `seg` of the rows p, p + P, ...; a thread its chunk c there.
+    const int S = L.pieces, P = L.groups;
+    const int p = wave * L.div >> 16, seg = wave - p * S, c = seg * 64 + lane;
+    const bool in_c = c < C && p < P;
+    const int row0 = p < P ? p : M;                      // (waves without a row: none)
+    const unsigned char *const xc = lds + c * 16;        // this thread's chunk, + row * 2 K
+
+    // X goes straight to LDS, all of it in flight at once (the wave's 64 x 16 bytes are contiguous)
+    {
+        const __amdgpu_buffer_rsrc_t r_x = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)a.x, 0, (int)(((unsigned)(M - 1) * (unsigned)a.ldx + (unsigned)K) * 2u), 0x00020000);
+        if (in_c)
+            for (int row = row0; row < M; row += P)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(r_x, (lptr_t)(lds + row * K * 2 + seg * 1024), 16,
+                                                         (unsigned)c * 16u, (unsigned)row * (unsigned)a.ldx * 2u, 0, 0);
+    }
+    const bool is_static = a.static_mask != nullptr;
+    const bool want_max = !(TOKEN && is_static);
+    uint32_t listed = 0;                                 // bit i: channel 8 c + i is listed
+    uint4 mx = make_uint4(0, 0, 0, 0);                   // column maxima
+    if (in_c && is_static) listed = a.static_mask[c];
+    if (in_c && a.slabs != nullptr && want_max)          // left by the producer of X; one or two
+        for (int sl = 0; sl < a.n_slabs; ++sl)
+            mx = absmax_step(mx, *(const uint4 *)(a.slabs + (size_t)sl * k_pad + c * 8));
+
+    // the weight blocks of the first 16 channels, on their way during all that follows
+    int nb = blockIdx.x;
+    v4i w[kFewLoads];
+    auto load_weights = [&](int nblock) {
+        const int8_t *src = a.w_q + (size_t)nblock * k_pad * 16 + ln * 64 + lq * 16;
+#pragma unroll
+        for (int i = 0; i < kFewLoads; ++i) {
+            const int kb = wave + i * kFewWaves;
+            if (kb < KB) w[i] = *(const v4i *)(src + (size_t)kb * 1024);
+        }
+    };
+    load_weights(nb);
+    // constants of the epilogue (waves 0 .. n_mb - 1: lane = token ln, channels n .. n + 3)
+    v4i rs = {0, 0, 0, 0};
+    float4 sw = make_float4(0.f, 0.f, 0.f, 0.f);
+    f16x4 bias = {0, 0, 0, 0};
+    auto load_consts = [&](int nblock) {
+        const int n = nblock * 16 + lq * 4;
+        if (wave < n_mb && n < N) {                      // N % 8 == 0: a run of 4 is in or out as a whole
+            rs = *(const v4i *)(a.w_row_sum + n);
+            const int st = a.w_per_channel ? 1 : 0, n0 = a.w_per_channel ? n : 0;
+            sw = make_float4(a.w_scale[n0], a.w_scale[n0 + st], a.w_scale[n0 + 2 * st], a.w_scale[n0 + 3 * st]);
+            if (a.bias != nullptr) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) bias[i] = a.bias[n + i];
+            }
+        }
+    };
+    load_consts(nb);
+
+    // X has landed (and with it the weights: both come from memory at the same time); a wave reads
+    // back only what it loaded itself
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0f70);                  // vmcnt(0)
+    asm volatile("" ::: "memory");
+
+    // ---- column maxima of |X| (Sec. III-C) ----
+    if (want_max && a.slabs == nullptr) {
+        if (in_c)
+            for (int row = row0; row < M; row += P) mx = absmax_step(mx, *(const uint4 *)(xc + row * K * 2));
+        if (P > 1) {                                     // the row groups' parts meet
+            uint4 *const part = (uint4 *)(lds + L.part);
+            part[tid] = mx;
+            lds_barrier();
+            const int groups = min(P, M);
+            mx = part[seg * 64 + lane];
+            for (int g = 1; g < groups; ++g) mx = absmax_step(mx, part[(g * S + seg) * 64 + lane]);
+            if (p >= P) mx = make_uint4(0, 0, 0, 0);
+            lds_barrier();
+        }
+    }
+    for (int i = tid * 4; i < M * r_cap; i += kFewThreads * 4) *(uint32_t *)(aux + i) = 0u;
+    for (int i = tid * 4; i < 16 * r_cap; i += kFewThreads * 4) *(uint32_t *)(waux + i) = 0u;
+    for (int i = tid; i < n_mb * 256; i += kFewThreads) red[i] = 0;
+
+    // ---- selection (Sec. III-C) with the capacity rule; every row group does it for its chunks ----
+    const float shrink = __uint_as_float((uint32_t)(127 - a.exp) << 23);  // 2^-exp
+    if (in_c && !is_static) {
+        float v[8];
+        widen8(mx, v);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) listed |= (v[i] > a.threshold ? 1u : 0u) << i;
+    }
+    const int cnt = __builtin_popcount(listed);
+    const int incl = wave_inclusive_sum(cnt);
+    uint32_t top = TOKEN ? 0u : wave_max_u16x2_to_lane63(chunk_maxima(mx, listed));
+    if (lane == 63) {
+        s_tot[wave] = p == 0 ? incl : 0;
+        s_max[wave] = p == 0 ? top : 0u;
+    }
+    lds_barrier();
+    int first = incl - cnt, found = 0;                   // rank of this chunk's first candidate
+    uint32_t call_max = 0;
+#pragma unroll
+    for (int i = 0; i < kFewWaves; i += 4) {
+        const int4 t = *(const int4 *)(s_tot + i);
+        const uint4 m = *(const uint4 *)(s_max + i);
+        first += (i < seg ? t.x : 0) + (i + 1 < seg ? t.y : 0) + (i + 2 < seg ? t.z : 0) + (i + 3 < seg ? t.w : 0);
+        found += t.x + t.y + t.z + t.w;
+        call_max = pk_max_u16(call_max, pk_max_u16(pk_max_u16(m.x, m.y), pk_max_u16(m.z, m.w)));
+    }
+    const int used = min(found, r_cap);
+    if (found > r_cap) {                                 // the r_cap lowest candidates are listed
+        uint32_t kept = 0;
+        int rank = first;
+        for (uint32_t mm = listed; mm != 0; mm &= mm - 1, ++rank)
+            if (rank < r_cap) kept |= mm & (0u - mm);
+        listed = kept;
+        top = wave_max_u16x2_to_lane63(chunk_maxima(mx, listed));
+        lds_barrier();                                   // s_max is consumed
+        if (lane == 63) s_max[wave] = p == 0 ? top : 0u;
+        lds_barrier();
+        call_max = 0;
+        for (int i = 0; i < kFewWaves; ++i) call_max = pk_max_u16(call_max, s_max[i]);
+    }
+    if (p == 0) {
+        int rank = first;
+        for (uint32_t mm = listed; mm != 0; mm &= mm - 1, ++rank) idx_lds[rank] = c * 8 + __builtin_ctz(mm);
+    }
+    if (!TOKEN) lds_barrier();
+
+    float inv = 0.f, sx_call = 0.f;
+    int z = 0;
+    if (TOKEN) {
+        // ---- max|Body| of every row: a wave's piece first ----
+#pragma unroll 2
+        for (int row = row0; row < M; row += P) {
+            uint4 raw = make_uint4(0, 0, 0, 0);
+            if (in_c) raw = *(const uint4 *)(xc + row * K * 2);
+            const uint32_t m = wave_max_u16x2_to_lane63(chunk_maxima(raw, listed));
+            if (lane == 63) s_row[row * kFewWaves + seg] = m;
+        }
+        lds_barrier();
+        if (tid < M) {
+            uint32_t m = 0;
+            for (int s = 0; s < S; ++s) m = pk_max_u16(m, s_row[tid * kFewWaves + s]);
+            float sx, iv;
+            int zz;
+            few_scale(m, shrink, a.qmax, sx, iv, zz);
+            s_sx[tid] = sx;
+            s_inv[tid] = iv;
+            s_z[tid] = zz;
+            if (blockIdx.x == 0) {
+                a.x_scale[tid] = sx;
+                a.x_scale[M + tid] = iv;
+                a.zero_point[tid] = zz;
+            }
+        }
+        lds_barrier();
+    } else {
+        few_scale(call_max, shrink, a.qmax, sx_call, inv, z);
+    }
+
+    // Eq. 7: the weights of the listed channels, 16 per output channel and step; on their way while
+    // the codes are formed (the lines have just been read, as part of the weight blocks)
+    const int g_row = tid & 15, g_slot = tid >> 4;       // 64 slots at a time
+    int g_w = 0;
+    auto gather_weights = [&](int nblock, int j) -> int {
+        return a.w_q[(size_t)nblock * k_pad * 16 + (size_t)(idx_lds[j] >> 6) * 1024 + g_row * 64 + (idx_lds[j] & 63)];
+    };
+    if (g_slot < used) g_w = gather_weights(nb, g_slot);
+
+    // ---- codes of Body and Aux (Eq. 1, 4, 5) into LDS ----
+    const bool wave_listed = __ballot(listed != 0) != 0;
+    if (p < P && c < CA) {
+        for (int row = row0; row < M; row += P) {
+            if (TOKEN) {
+                inv = s_inv[row];
+                z = s_z[row];
+            }
+            uint4 raw = make_uint4(0, 0, 0, 0);
+            if (c < C) raw = *(const uint4 *)(xc + row * K * 2);
+            const float magic = 12582912.0f + (float)z;
+            const f16x8 h = __builtin_bit_cast(f16x8, raw);
+            uint32_t q[8];
+            if (wave_listed) {
+                // listed channels: Body = x 2^-exp and one rounded product (the factor is a power of
+                // two: its place does not matter), no zero point
+                const float inv_l = inv * shrink;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const bool l = ((listed >> j) & 1u) != 0;
+                    q[j] = quant_word((float)h[j], l ? inv_l : inv, a.qmax, l ? 12582912.0f : magic);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) q[j] = quant_word((float)h[j], inv, a.qmax, magic);
+            }
+            uint2 packed = make_uint2(pack_low_bytes(q[0], q[1], q[2], q[3]), pack_low_bytes(q[4], q[5], q[6], q[7]));
+            if (c >= C) packed = make_uint2(0, 0);       // K padding of Body
+            int slot = first;
+            for (uint32_t mm = listed; mm != 0; mm &= mm - 1, ++slot) {          // Aux (Eq. 5)
+                const int j = __builtin_ctz(mm);
+                aux[few_code_pos(row, slot, M, r_cap)] = (uint8_t)((j < 4 ? packed.x : packed.y) >> ((j & 3) * 8));
+            }
+            *(uint2 *)(codes + few_code_pos(row, c * 8, M, k_pad)) = packed;
+        }
+    }
+    auto keep_weights = [&](int nblock) {                // -> LDS; lists beyond 64 entries: the rest directly
+        if (g_slot < used) waux[few_code_pos(g_row, g_slot, 16, r_cap)] = (uint8_t)g_w;
+        for (int j = g_slot + 64; j < used; j += 64)
+            waux[few_code_pos(g_row, j, 16, r_cap)] = (uint8_t)gather_weights(nblock, j);
+    };
+    keep_weights(nb);
+    // ---- the selection results, for the caller ----
+    if (blockIdx.x == 0 && want_max) {
+        if (p == 0 && c < CA) {
+            int slots[8];
+            int rank = first;
+            float v[8];
+            widen8(mx, v);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const bool l = ((listed >> i) & 1u) != 0;
+                slots[i] = l ? rank : -1;
+                if (l) a.idx[rank] = c * 8 + i;
+                rank += l ? 1 : 0;
+            }
+            int4 *cs = (int4 *)(a.col_slot + c * 8);
+            cs[0] = make_int4(slots[0], slots[1], slots[2], slots[3]);
+            cs[1] = make_int4(slots[4], slots[5], slots[6], slots[7]);
+            a.col_mask[c] = (uint8_t)listed;
+            if (c < C) {
+                float4 *cm = (float4 *)(a.col_absmax + c * 8);
+                cm[0] = make_float4(v[0], v[1], v[2], v[3]);
+                cm[1] = make_float4(v[4], v[5], v[6], v[7]);
+            }
+            if (!TOKEN) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = c < C ? inv * (slots[i] >= 0 ? shrink : 1.0f) : 0.f;
+                float4 *sc = (float4 *)(a.col_scale + c * 8);
+                sc[0] = make_float4(v[0], v[1], v[2], v[3]);
+                sc[1] = make_float4(v[4], v[5], v[6], v[7]);
+            }
+        }
+        for (int j = used + tid; j < max(r_cap, 1); j += kFewThreads) a.idx[j] = -1;
+        if (tid == 0) {
+            a.n_outliers[0] = used;
+            a.n_outliers[1] = found;
+            if (!TOKEN) {
+                a.x_scale[0] = sx_call;
+                a.x_scale[1] = inv;
+                a.zero_point[0] = z;
+            }
+        }
+    }
+    lds_barrier();
+    // ---- this workgroup's share of the codes, for the caller: part of a row, or whole rows ----
+    if ((int)blockIdx.x < M * L.share_parts)
+        for (int row = (int)blockIdx.x % M; row < M; row += gridDim.x) {
+            const int u0 = ((int)blockIdx.x / M) * L.share_len, u1 = min(k_pad / 16, u0 + L.share_len);
+            for (int u = u0 + tid; u < u1; u += kFewThreads)
+                *(uint4 *)(a.body_q + packed_index(row, u * 16, k_pad)) = *(const uint4 *)(codes + few_code_pos(row, u * 16, M, k_pad));
+            if ((int)blockIdx.x < M && tid < r_cap / 16)
+                *(uint4 *)(a.aux_q + packed_index(row, tid * 16, r_cap)) = *(const uint4 *)(aux + few_code_pos(row, tid * 16, M, r_cap));
+        }
+
+    // ---- products, 16 output channels at a time ----
+    const int t_aux = (used + 63) >> 6;
+    auto frag = [&](const unsigned char *m, int cols, int mb, int kb) -> v4i {
+        const int rows = min(16, M - mb * 16), r = min(ln, rows - 1);     // rows past M feed outputs that are not stored
+        return *(const v4i *)(m + mb * 16 * cols + kb * (rows << 6) + (r << 6) + ((lq ^ (r >> 2)) << 4));
+    };
+    for (; nb < nblk; nb += gridDim.x) {
+        const int n = nb * 16 + lq * 4;
+        const bool epi = wave < n_mb && n < N;
+        v4i acc[MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[mb] = v4i{0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < kFewLoads; ++i) {
+            const int kb = wave + i * kFewWaves;
+            if (kb >= KB) break;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+                if (mb < n_mb)
+                    acc[mb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[i], frag(codes, k_pad, mb, kb), acc[mb], 0, 0, 0);
+        }
+        if (nb + (int)gridDim.x < nblk) {
+            load_weights(nb + gridDim.x);
+            if (g_slot < used) g_w = gather_weights(nb + gridDim.x, g_slot);
+        }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+            if (mb < n_mb) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) atomicAdd(&red[(mb * 4 + v) * 64 + lane], acc[mb][v]);
+            }
+        lds_barrier();
+
+        // the Aux weight rows, for the caller (a static block has them already)
+        if (a.w_aux != nullptr)
+            for (int u = tid; u < r_cap; u += kFewThreads) {       // 16 rows x r_cap / 16 pieces
+                const int row = u & 15, col = u & ~15;
+                if (nb * 16 + row < N)
+                    *(uint4 *)(a.w_aux + packed_index(nb * 16 + row, col, r_cap)) =
+                        *(const uint4 *)(waux + few_code_pos(row, col, 16, r_cap));
+            }
+        if (wave < n_mb) {
+            const int mb = wave;
+            // Aux product, and (second operand all ones) each channel's sum over the listed weights
+            v4i ax = {0, 0, 0, 0}, sum = {0, 0, 0, 0};
+            const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+            for (int t = 0; t < t_aux; ++t) {
+                const v4i wa = *(const v4i *)(waux + (t << 10) + (ln << 6) + ((lq ^ (ln >> 2)) << 4));
+                ax = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa, frag(aux, r_cap, mb, t), ax, 0, 0, 0);
+                sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa, ones, sum, 0, 0, 0);
+            }
+            const int m = mb * 16 + ln;
+            const float sx = TOKEN ? s_sx[min(m, M - 1)] : sx_call;
+            if (TOKEN) z = s_z[min(m, M - 1)];
+            const v4i cn = rs - sum;
+            const float swv[4] = {sw.x, sw.y, sw.z, sw.w};
+            f16x4 out;
+            v4i total;
+            uint32_t hmax[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                // Eq. 7 on INT32 accumulators, modulo 2^32 like every form of the GEMM
+                total[i] = (int)((uint32_t)red[(mb * 4 + i) * 64 + lane] + ((uint32_t)ax[i] << a.exp) - (uint32_t)ax[i] -
+                                 (uint32_t)z * (uint32_t)cn[i]);
+                const float sc = sx * swv[i];
+                float y = sc * (float)total[i];          // Eq. 3
+                if (a.bias != nullptr) y = y + (float)bias[i];
+                out[i] = (_Float16)y;
+                // fused activation: on the fp16 value the layer would have stored
+                if (a.gelu) out[i] = (_Float16)gelu_tanh_f32((float)out[i]);
+                hmax[i] = m < M ? (uint32_t)__builtin_bit_cast(unsigned short, (_Float16)out[i]) & 0x7fffu : 0u;
+            }
+            if (epi && m < M) {
+                *(f16x4 *)(a.y + (size_t)m * a.ldy + n) = out;
+                if (a.dbg_acc != nullptr) *(v4i *)(a.dbg_acc + (size_t)m * N + n) = total;
+            }
+            if (a.cn != nullptr && epi && mb == 0 && ln == 0) *(v4i *)(a.cn + n) = cn + a.cn_bias;
+            if (a.next_slabs != nullptr) {               // column maxima over the tokens, for the next layer
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    hmax[i] = max(hmax[i], dpp_zero<0x111>(hmax[i]));
+                    hmax[i] = max(hmax[i], dpp_zero<0x112>(hmax[i]));
+                    hmax[i] = max(hmax[i], dpp_zero<0x114>(hmax[i]));
+                    hmax[i] = max(hmax[i], dpp_zero<0x118>(hmax[i]));
+                }
+                if (ln == 15) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) red[(mb * 4 + i) * 64 + lane] = (int)hmax[i];
+                }
+            }
+        }
+        lds_barrier();
+        if (a.next_slabs != nullptr && tid < 16) {
+            uint32_t m = 0;
+            for (int mb = 0; mb < n_mb; ++mb) m = max(m, (uint32_t)red[(mb * 4 + (tid & 3)) * 64 + (tid >> 2) * 16 + 15]);
+            if (nb * 16 + tid >= N) m = 0;
+            for (int sl = 0; sl < a.next_count; ++sl)              // the whole maximum sits in slab 0
+                a.next_slabs[(size_t)sl * a.next_ld + nb * 16 + tid] = sl == 0 ? (uint16_t)m : (uint16_t)0;
+        }
+        if (nb + (int)gridDim.x < nblk) {
+            load_consts(nb + gridDim.x);
+            keep_weights(nb + gridDim.x);                // (waux is consumed: the barrier above)
+            if (a.next_slabs != nullptr) lds_barrier();
+            for (int i = tid; i < n_mb * 256; i += kFewThreads) red[i] = 0;
+            lds_barrier();
+        }
+    }
+    // the K padding of the next layer's slabs past the last 16 channels of this one
+    if (a.next_slabs != nullptr && blockIdx.x == 0)
+        for (int i = nblk * 16 + tid; i < a.next_ld; i += kFewThreads)
+            for (int sl = 0; sl < a.next_count; ++sl) a.next_slabs[(size_t)sl * a.next_ld + i] = 0;
+}
+
+}  // namespace
+
+// The line is where X and its codes no longer fit LDS together (about 42 K elements): at every size
+// below it the one launch is the faster way, by 1.1 (32 x 1280 -> 5120 with a static list and one scale
+// per token, whose separate way is two launches: 16.4 / 15.0 us) to 4.9 times.
+bool few_tokens_fit(int M, int K, int k_pad, int r_cap)
+{
+    return M <= kFewMaxM && k_pad <= kFewMaxK && few_plan(M, K, k_pad, r_cap, 1).total <= kFewLdsBytes;
+}
+
+typedef void (*few_kernel_t)(const FewArgs, const FewPlan);
+static few_kernel_t few_kernel(int row_blocks, bool token)
+{
+    switch (row_blocks) {
+    case 1: return token ? k_linear_few<1, true> : k_linear_few<1, false>;
+    case 2: return token ? k_linear_few<2, true> : k_linear_few<2, false>;
+    default: return token ? k_linear_few<4, true> : k_linear_few<4, false>;
+    }
+}
+
+hipError_t few_prepare_device()
+{
+    for (int i = 0; i < 6; ++i) {
+        const hipError_t e = hipFuncSetAttribute((const void *)few_kernel(1 + i / 2, i % 2 != 0),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kFewLdsBytes);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_linear_few(const FewArgs &a, hipStream_t s)
+{
+    const hipError_t e = gemm_prepare_device();
+    if (e != hipSuccess) return e;
+    // every workgroup repeats the activation side: no more of them than are resident at once
+    const int nblk = (a.N + 15) / 16, grid = nblk < 256 ? nblk : 256;
+    const FewPlan plan = few_plan(a.M, a.K, a.k_pad, a.r_cap, grid);
+    return launch_kernel(few_kernel((a.M + 15) / 16, a.x_per_token != 0), dim3(grid), dim3(kFewThreads), plan.total, s,
+                         a, plan);
+}
+
+}  // namespace muxq

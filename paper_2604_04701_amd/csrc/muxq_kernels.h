@@ -98,6 +98,54 @@ __device__ __forceinline__ float gelu_tanh_f32(float y)
     return r;
 }
 
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ void widen8(uint4 mx, float (&v)[8])
+{
+    const uint32_t w[4] = {mx.x, mx.y, mx.z, mx.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[2 * i] = (float)__builtin_bit_cast(_Float16, (unsigned short)(w[i] & 0xffffu));
+        v[2 * i + 1] = (float)__builtin_bit_cast(_Float16, (unsigned short)(w[i] >> 16));
+    }
+}
+
+// Workgroup barrier for data exchanged through LDS only: waits for this wave's LDS
+// operations but not for its global stores.  (__syncthreads() also waits until every
+// earlier global store of the wave has been acknowledged, 1-3 us each time in the
+// one-workgroup selection kernels, whose stores nobody reads before the kernel ends.)
+// (The empty asm statements keep the compiler from moving accesses across: to it the barrier
+// touches no memory.)
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0), vmcnt and expcnt unconstrained
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// Eq. 1 code of x * scale, left in the low byte of the returned word: the product is
+// rounded to binary32, clamped to [-qmax, qmax] (v_med3_f32), and adding 1.5 * 2^23 then
+// rounds it to the nearest integer, ties to even, in the adder itself and leaves that
+// integer, two's complement, in the low mantissa bits.  Rounding after the clamp equals
+// clamping after rounding because the bounds are integers.  Three VALU ops per element; the streaming quantisers are not far from ALU-bound.
+__device__ __forceinline__ uint32_t quant_word(float x, float scale, float qmax,
+                                               float magic = 12582912.0f)
+{
+    // x comes from an fp16 value: conversion and product are one mixed-precision fma, whose single
+    // rounding is that of the product (adding +0 is exact; it only turns -0 into +0)
+    const float t = __builtin_amdgcn_fmed3f(__builtin_fmaf(x, scale, 0.0f), -qmax, qmax);
+    return __float_as_uint(t + magic);      // magic = 1.5 * 2^23 (+ a zero point: code + z)
+}
+
+// The low bytes of four such words as one dword (a in byte 0).
+__device__ __forceinline__ uint32_t pack_low_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
+{
+    const uint32_t lo = __builtin_amdgcn_perm(b, a, 0x0c0c0400u);   // {a.byte0, b.byte0, 0, 0}
+    const uint32_t hi = __builtin_amdgcn_perm(d, c, 0x0c0c0400u);
+    return lo | (hi << 16);
+}
+
 struct GemmArgs {
     const int8_t *a_q;      // packed M x k_pad activation codes (Body)
     const int8_t *w_q;      // packed N x k_pad weight codes (row n = output channel n)
@@ -131,6 +179,44 @@ struct GemmArgs {
     long long *wg_ticks;    // measurement aid, or nullptr: workgroup i of a persistent kernel stores
                             // the constant 100 MHz counter at its start in [2 i] and at its end in [2 i + 1]
 };
+
+// One layer in one launch, for few tokens (muxq_few.hip).  Pointers into the workspace as in
+// muxq_ws_layout; slabs (n_slabs x k_pad fp16 magnitudes) when a producer of X has left the column
+// maxima; static_mask (one bit per channel) instead of the threshold test; w_aux null when a
+// static block holds the Aux weight rows already.
+struct FewArgs {
+    const uint16_t *x;
+    int M, K, ldx, k_pad, N;
+    const int8_t *w_q;
+    const int32_t *w_row_sum;
+    const float *w_scale;
+    const _Float16 *bias;
+    int w_per_channel, x_per_token, exp, r_cap;
+    float qmax, threshold;
+    const uint16_t *slabs;
+    int n_slabs;
+    const uint8_t *static_mask;
+    float *col_absmax, *col_scale;
+    int32_t *col_slot;
+    uint8_t *col_mask;
+    int32_t *idx, *n_outliers;
+    float *x_scale;
+    int32_t *zero_point;
+    int8_t *body_q, *aux_q, *w_aux;
+    int32_t *cn;
+    int32_t cn_bias;
+    _Float16 *y;
+    int ldy;
+    int32_t *dbg_acc;
+    int gelu;
+    uint16_t *next_slabs;   // with gelu, or null: the column maxima of |Y|, in next_count slabs of next_ld
+    int next_ld, next_count;
+};
+constexpr int kFewLdsBytes = 128 * 1024;
+// Whether launch_linear_few takes a call (and is the faster way): a function of the sizes only.
+bool few_tokens_fit(int M, int K, int k_pad, int r_cap);
+hipError_t launch_linear_few(const FewArgs &a, hipStream_t s);
+hipError_t few_prepare_device();      // LDS attributes, from gemm_prepare_device
 
 hipError_t launch_fill_u32(uint32_t *p, int n, uint32_t v, hipStream_t s);
 

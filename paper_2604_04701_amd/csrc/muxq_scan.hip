@@ -11,8 +11,6 @@
 namespace muxq {
 namespace {
 
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
 __device__ __forceinline__ uint32_t half_mag_to_f32_bits(uint32_t h)
 {
     float f = (float)__builtin_bit_cast(_Float16, (unsigned short)h);
@@ -303,16 +301,6 @@ __global__ __launch_bounds__(1024) void k_select_scale(
         col_scale[k] = k < K ? inv * (col_slot[k] >= 0 ? shrink : 1.0f) : 0.f;
 }
 
-// Workgroup barrier for data exchanged through LDS only: waits for this wave's LDS
-// operations but not for its global stores.  (__syncthreads() also waits until every
-// earlier global store of the wave has been acknowledged, 1-3 us each time in the
-// one-workgroup selection kernels, whose stores nobody reads before the kernel ends.)
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0), vmcnt and expcnt unconstrained
-    __builtin_amdgcn_s_barrier();
-}
-
 // Selection and scales for one workgroup of NT threads, shared by the kernels
 // below.  A thread owns 8 consecutive channels per round (rounds of 8 * NT
 // channels); `load8(k0, v)` supplies their abs-max values (zero in the K padding).
@@ -496,16 +484,6 @@ __device__ __forceinline__ void select_scale_block(Load8 load8, bool write_absma
     }
 }
 
-__device__ __forceinline__ void widen8(uint4 mx, float (&v)[8])
-{
-    const uint32_t w[4] = {mx.x, mx.y, mx.z, mx.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        v[2 * i] = (float)__builtin_bit_cast(_Float16, (unsigned short)(w[i] & 0xffffu));
-        v[2 * i + 1] = (float)__builtin_bit_cast(_Float16, (unsigned short)(w[i] >> 16));
-    }
-}
-
 // Second launch of muxq_linear and muxq_detect_outliers: fold the slabs (col_absmax[k] = max over
 // slabs, widened to binary32) and select, in one workgroup.  STATIC: the candidates are
 // the channels of `static_mask` (a list fixed offline) instead of those over the threshold.
@@ -571,27 +549,6 @@ __global__ __launch_bounds__(1024) void k_fold_select_scale(
     select_scale_block<1024, STATIC>(load8, true, K, k_pad, threshold, r_cap, exp, qmax, do_scale,
                                      col_absmax, idx, n_outliers, col_slot, col_mask, col_scale, x_scale,
                                      static_mask, zero_point, aux_scale_out);
-}
-
-// Eq. 1 code of x * scale, left in the low byte of the returned word: the product is
-// rounded to binary32, clamped to [-qmax, qmax] (v_med3_f32), and adding 1.5 * 2^23 then
-// rounds it to the nearest integer, ties to even, in the adder itself and leaves that
-// integer, two's complement, in the low mantissa bits.  Rounding after the clamp equals
-// clamping after rounding because the bounds are integers.  Four VALU ops per element
-// with the fp16 -> fp32 conversion; the streaming quantisers are not far from ALU-bound.
-__device__ __forceinline__ uint32_t quant_word(float x, float scale, float qmax,
-                                               float magic = 12582912.0f)
-{
-    const float t = __builtin_amdgcn_fmed3f(x * scale, -qmax, qmax);
-    return __float_as_uint(t + magic);      // magic = 1.5 * 2^23 (+ a zero point: code + z)
-}
-
-// The low bytes of four such words as one dword (a in byte 0).
-__device__ __forceinline__ uint32_t pack_low_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
-{
-    const uint32_t lo = __builtin_amdgcn_perm(b, a, 0x0c0c0400u);   // {a.byte0, b.byte0, 0, 0}
-    const uint32_t hi = __builtin_amdgcn_perm(d, c, 0x0c0c0400u);
-    return lo | (hi << 16);
 }
 
 // Role of the extra workgroups of the two quantiser launches (workgroup `wg` of `n_wgs`,

@@ -1,0 +1,72 @@
+"""Calls with few tokens, which run as one launch (csrc/muxq_few.hip): every workspace region, the
+accumulators and Y against the CPU oracle at the edges of that kernel's ranges -- one row and
+the largest row counts, partial 16-row blocks, the shortest and longest K, fewer and more
+blocks of 16 output channels than workgroups, list capacities, lists fixed offline, and the
+column maxima it hands from layer to layer.  All comparisons are exact (check_mlp states the
+one tolerance, that of the GELU)."""
+import numpy as np
+import pytest
+import torch
+
+import test_gpu_parity as T
+from gpu_common import B, check_case, check_mlp, check_plain_y, orc, synth
+from paper_2604_04701_amd.synth import Case
+
+pytestmark = pytest.mark.gpu
+U = (20.0, 100.0)
+
+SHAPES = [(1, 8, 8), (1, 768, 2304), (1, 8192, 520), (2, 72, 24), (15, 4096, 136), (16, 1280, 1288),
+          (17, 1000, 264), (24, 5120, 264), (31, 512, 8200), (33, 136, 520), (48, 2048, 72), (64, 64, 16),
+          (64, 1024, 264)]
+
+
+@pytest.mark.parametrize("x_gran,w_gran", [("tensor", "tensor"), ("tensor", "channel"), ("token", "channel")])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_few_tokens_all_stages(shape, x_gran, w_gran):
+    M, K, N = shape
+    case = Case("few", M, K, N, min(6, K // 8), U, 600 + M)
+    check_case(case, x_gran=x_gran, w_gran=w_gran, bias_seed=M if M % 2 else None)
+    check_plain_y(case, x_gran=x_gran, w_gran=w_gran, bias_seed=3)
+
+
+@pytest.mark.parametrize("x_gran", ["tensor", "token"])
+@pytest.mark.parametrize("r_cap,r", [(0, 5), (64, 0), (64, 64), (64, 90), (128, 100), (256, 200)])
+def test_few_tokens_list_capacity(r_cap, r, x_gran):
+    for M, e in ((3, 1), (20, 3)):
+        check_case(Case("few_cap", M, 520, 136, r, U, 640 + M), r_cap=r_cap, e=e, x_gran=x_gran)
+
+
+@pytest.mark.parametrize("x_gran,w_gran", [("tensor", "channel"), ("token", "tensor")])
+def test_few_tokens_static_lists(x_gran, w_gran):
+    for M, K, N in ((1, 264, 136), (24, 5120, 72), (50, 1032, 264)):
+        case = Case("few_static", M, K, N, 5, U, 660 + M)
+        _, _, planted = synth.make_case(case)
+        _lists = ([int(k) for k in planted], [], list(range(0, 200, 2)), [3, 7, 7, K + 1])
+        for lst in _lists:
+            T._check_static(case, lst, x_gran, w_gran, with_bias=M > 1)
+
+
+@pytest.mark.parametrize("w_gran,x_gran", [("tensor", "tensor"), ("channel", "token")])
+@pytest.mark.parametrize("M,K,N1,N2", [(1, 64, 256, 64), (8, 1280, 5120, 1280), (17, 264, 1048, 264),
+                                       (64, 768, 1000, 768), (40, 72, 4104, 72)])
+def test_few_tokens_mlp(M, K, N1, N2, w_gran, x_gran):
+    check_mlp(M, K, N1, N2, 700 + M, w_gran=w_gran, x_gran=x_gran)
+
+
+def test_few_tokens_strided_rows_and_the_static_array():
+    """Row strides above the row length; the entry point without a workspace; the same
+    workspace for calls of shrinking size."""
+    dev = "cuda"
+    rng = np.random.default_rng(5)
+    for M, K, N in ((24, 1280, 520), (3, 200, 72)):
+        X, _ = synth.make_x(M, K, 4, U, rng)
+        W = synth.make_w(K, N, rng)
+        Xd = torch.zeros((M, K + 24), dtype=torch.float16, device=dev)[:, :K]
+        Xd.copy_(torch.from_numpy(X))
+        out = torch.full((M, N + 16), 7.0, dtype=torch.float16, device=dev)
+        w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(W).to(dev))
+        B.muxq_linear(Xd, w_q, w_s, N, out=out[:, :N])
+        y = B.muxq_linear_noalloc(Xd, w_q, w_s, N)
+        o = orc.linear(X, W)
+        assert (out[:, :N].cpu().numpy() == o["y16"]).all() and (out[:, N:] == 7.0).all()
+        assert (y.cpu().numpy() == o["y16"]).all()
