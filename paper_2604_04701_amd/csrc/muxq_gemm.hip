@@ -26,7 +26,7 @@
 // through, the epilogue removes it).  The weights are the first MFMA operand and the
 // narrow activation codes the second: the other way round draws more.
 //
-// Three kernels share that scheme:
+// Four kernels share that scheme:
 //   k_gemm_i8_persist8  256 x 256 tile, 8 waves (2 per SIMD), K step 64, one
 //                   persistent workgroup per CU.  Operand tiles go global -> LDS
 //                   directly (buffer_load_dwordx4 ... lds, no staging registers)
@@ -38,8 +38,10 @@
 //   k_gemm_i8_persist4  the same kernel body with a 128 x 128 tile and 4 waves,
 //                   two workgroups per CU, for problems with too few 256 x 256
 //                   tiles to fill 256 CUs but a long K loop.
-//   k_gemm_i8_small register-staged tiles of 128 x 128 or 64 x 64 for short K
-//                   loops and small problems.
+//   k_gemm_i8_direct  small tiles (16 x 16 to 64 x 64), operands from memory straight to
+//                   registers, the waves of a workgroup split K: for problems
+//                   with too few larger tiles to fill the chip.
+//   k_gemm_i8_small register-staged tiles of 64 x 64 for short K loops.
 //
 // LDS rows are 64 bytes (one K step); the four 16-byte chunks of a row are
 // XOR-swizzled with row bits so that a ds_read_b128 of 32 rows x one chunk is
@@ -48,10 +50,12 @@
 // is applied on the global-address side instead).
 //
 // Workgroup -> tile map.  Workgroups are dealt round-robin to the 8 XCDs, each
-// with its own L2.  Tiles are grouped in super-tiles of sup_m x sup_n tiles
-// (<= 32, one per CU of an XCD); workgroup i belongs to XCD i % 8 and the
-// workgroups an XCD runs concurrently form one compact super-tile, so its L2
-// holds (sup_m + sup_n) operand panels for sup_m * sup_n tiles.
+// with its own L2; workgroup i belongs to XCD i % 8.  Tiles are grouped in blocks
+// of sup_m x sup_n, as many as an XCD works on at one time, so that its L2 holds
+// sup_m + sup_n operand panels for sup_m * sup_n tiles.  Blocks are dealt to the
+// XCDs in turn; where ragged blocks would make that take more rounds than the
+// number of tiles needs, the tiles are instead put in one order, block after
+// block, and split evenly.
 #include "muxq_kernels.h"
 
 #include <atomic>
@@ -66,8 +70,26 @@ typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BK = 64;   // K step (bytes of one LDS row)
 
+// Division by a launch constant: one high multiplication and a correction (a division by a run-time
+// value is a chain of some 20 instructions, and the tile map needs several for every tile).
+struct Divisor {
+    unsigned d, m;
+};
+__host__ inline Divisor divisor(int d) { return {(unsigned)d, 0xffffffffu / (unsigned)d}; }
+__device__ __forceinline__ int quotient(int x, const Divisor &v)
+{
+    const unsigned q = __umulhi((unsigned)x, v.m);       // the quotient, or one less
+    return (int)((unsigned)x - q * v.d >= v.d ? q + 1 : q);
+}
+
 struct TileMap {
-    int tiles_m, tiles_n, sup_m, sup_n, super_n, n_super;
+    int tiles_m, tiles_n, sup_m, sup_n;
+    int at_once;          // even split: tiles an XCD works on at a time; 0: blocks dealt in turn
+    int n_super, super_n; // blocks, and blocks per row of blocks
+    int full, rest;       // even split: full rounds, tiles of the last one
+    Divisor by_block, by_sup_n, by_super_n, by_at_once, by_band, by_band_block, by_last_band_block, by_last_cols;
+    // by_block: sup_m sup_n; by_band: sup_m tiles_n; by_band_block: rows of a band x sup_n; `last`: the
+    // last, ragged band of rows or block of columns
 };
 
 // 16-byte chunk position of logical chunk `chunk` in LDS row `row`.
@@ -84,16 +106,46 @@ __device__ __forceinline__ int swizzle(int row, int chunk)
         return chunk;
 }
 
+// Tile j of the share of XCD `xcd`: 1, or 0 past the end of the share, or -1 where a ragged block has
+// no tile (j + 1 may have one).
+// (12288 x 1280 -> 1280 is 240 tiles for 256 CUs; dealt as blocks of 4 x 5 tiles, half of the XCDs had
+// two rounds, 39 us, split evenly one, 23 us.  Where both take the same number of rounds whole blocks
+// are better: 16384 x 1280 -> 3840 84 us, split evenly 87-90 us.)
+__device__ __forceinline__ int tile_of_share(const TileMap &tm, int xcd, int j, int &tile_m, int &tile_n)
+{
+    if (tm.at_once == 0) {
+        const int r = quotient(j, tm.by_block), in_block = j - r * tm.sup_m * tm.sup_n, st = r * 8 + xcd;
+        if (st >= tm.n_super) return 0;
+        const int row = quotient(in_block, tm.by_sup_n), bm = quotient(st, tm.by_super_n);
+        tile_m = bm * tm.sup_m + row;
+        tile_n = (st - bm * tm.super_n) * tm.sup_n + in_block - row * tm.sup_n;
+        return tile_m < tm.tiles_m && tile_n < tm.tiles_n ? 1 : -1;
+    }
+    const int r = quotient(j, tm.by_at_once);
+    int idx;
+    if (r < tm.full) {
+        idx = (r * 8 + xcd) * tm.at_once + (j - r * tm.at_once);
+    } else {
+        const int jr = j - tm.full * tm.at_once;
+        if (jr >= tm.rest / 8 + (xcd < tm.rest % 8 ? 1 : 0)) return 0;
+        idx = tm.full * 8 * tm.at_once + tm.rest / 8 * xcd + min(tm.rest % 8, xcd) + jr;
+    }
+    const int band = quotient(idx, tm.by_band), in_band = idx - band * tm.sup_m * tm.tiles_n;
+    const bool last = (band + 1) * tm.sup_m > tm.tiles_m;
+    const int rows = last ? tm.tiles_m - band * tm.sup_m : tm.sup_m;
+    const int block = last ? quotient(in_band, tm.by_last_band_block) : quotient(in_band, tm.by_band_block);
+    const int in_block = in_band - block * rows * tm.sup_n;
+    const bool last_cols = (block + 1) * tm.sup_n > tm.tiles_n;
+    const int cols = last_cols ? tm.tiles_n - block * tm.sup_n : tm.sup_n;
+    const int row = last_cols ? quotient(in_block, tm.by_last_cols) : quotient(in_block, tm.by_sup_n);
+    tile_m = band * tm.sup_m + row;
+    tile_n = block * tm.sup_n + in_block - row * cols;
+    return 1;
+}
+
 __device__ __forceinline__ bool tile_of_workgroup(const TileMap &tm, int &tile_m, int &tile_n)
 {
-    const int S = tm.sup_m * tm.sup_n;
-    const int wg = blockIdx.x;
-    const int xcd = wg & 7, j = wg >> 3;
-    const int w_in = j % S, st = (j / S) * 8 + xcd;
-    if (st >= tm.n_super) return false;
-    tile_m = (st / tm.super_n) * tm.sup_m + w_in / tm.sup_n;
-    tile_n = (st % tm.super_n) * tm.sup_n + w_in % tm.sup_n;
-    return tile_m < tm.tiles_m && tile_n < tm.tiles_n;
+    return tile_of_share(tm, (int)blockIdx.x & 7, (int)blockIdx.x >> 3, tile_m, tile_n) > 0;
 }
 
 // acc <- c * acc with c = 2^e - 1, as (acc << e) - acc (two full-rate VALU ops).  The
@@ -163,6 +215,22 @@ __device__ __forceinline__ float aux_rho(const GemmArgs &a)
     if (!a.aux_own_scale || a.x_per_token) return 0.f;
     const float sx = a.x_scale[0], sa = a.x_scale[2];
     return sx > 0.f ? ((float)((1 << a.exp_shift) - 1) * sa) / sx : 0.f;
+}
+
+// 16 bytes of Y.  STREAM: non-temporal, for rows that start on 128-byte lines: a store instruction
+// then writes whole lines, and Y, which is not read here again, stays out of the operands' way in
+// L2.  Otherwise the lines at the ends of a piece are completed by the neighbouring piece, which only
+// happens in L2: as a stream they would go out half written (3001 x 1592 -> 4808: 37 us as a stream,
+// 29 us so; 16384 x 1280 -> 3840: 87 us as a stream, 90 us otherwise).  Compile time: a branch at each
+// store costs 1 us per tile.
+template <bool STREAM>
+__device__ __forceinline__ void store_y(const GemmArgs &a, int m, int n, v4i v)
+{
+    v4i *const dst = (v4i *)(a.y + (size_t)m * a.ldy + n);
+    if (STREAM)
+        __builtin_nontemporal_store(v, dst);
+    else
+        *dst = v;
 }
 
 // Eq. 3: Y = fp16((s_x * s_w[n]) * float(acc) + bias[n]).  Lane layout of the
@@ -236,10 +304,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs &a, const v16i (&acc)[FN
             const int piece = lane % LANES_PER_ROW;
             const v4i v = *(const v4i *)(patch + row * ROW_BYTES + piece * 16);
             const int m = m_base + fm * 32 + row, n = n_base + piece * 8;
-            // streaming store: Y is written once and never re-read here, keep it out of
-            // the way of the operand panels in L2
-            if (m < a.M && n < a.N)
-                __builtin_nontemporal_store(v, (v4i *)(a.y + (size_t)m * a.ldy + n));
+            if (m < a.M && n < a.N) store_y<false>(a, m, n, v);
         }
     }
 
@@ -297,8 +362,8 @@ constexpr int kChanFloats = 128 + 64 + 64 + 128 + 64 + 64;   // per-wave LDS for
 // GELU (compile time): the result goes through the tanh GELU, applied to the fp16 value the
 // layer would have stored, and `mx` (FN / 2 entries) collects, per lane, the running maxima of
 // the |fp16| values the lane stores (its 8 channels of each half, over its rows).
-template <int FN, int FM, int ROW_BYTES, int MODE, bool ZC = false, bool SUB = true, int WCH = -1,
-          int TOK = -1, int BIAS = -1, bool GELU = false>
+template <int FN, int FM, int ROW_BYTES, int MODE, bool STREAM, bool ZC = false, bool SUB = true,
+          int WCH = -1, int TOK = -1, int BIAS = -1, bool GELU = false>
 __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&acc)[FN][FM],
                                                int m_base, int n_base, int lane,
                                                unsigned char *patch, float *chan, float sx,
@@ -393,7 +458,7 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
                 const v4i v = *(const v4i *)(patch + row * ROW_BYTES + piece * 16);
                 const int m = m_base + fm * 32 + row, n = n_base + h * 64 + piece * 8;
                 if (m < a.M && n < a.N) {
-                    __builtin_nontemporal_store(v, (v4i *)(a.y + (size_t)m * a.ldy + n));
+                    store_y<STREAM>(a, m, n, v);
                     if (GELU) mx[h] = absmax_step(mx[h], __builtin_bit_cast(uint4, v));
                 }
             }
@@ -456,28 +521,18 @@ constexpr int waitcnt_lds_only() { return waitcnt_vm_lds(63); }
 // stored.
 // --------------------------------------------------------------------------
 struct PersistTile {
-    int v;            // virtual workgroup index of the tile, >= total when exhausted
+    int j;            // index in the XCD's share, see tile_of_share; -1 when exhausted
     int tile_m, tile_n;
 };
 
-__device__ __forceinline__ bool tile_of_virtual(const TileMap &tm, int v, int &tile_m, int &tile_n)
-{
-    const int S = tm.sup_m * tm.sup_n;
-    const int xcd = v & 7, j = v >> 3;
-    const int w_in = j % S, st = (j / S) * 8 + xcd;
-    if (st >= tm.n_super) return false;
-    tile_m = (st / tm.super_n) * tm.sup_m + w_in / tm.sup_n;
-    tile_n = (st % tm.super_n) * tm.sup_n + w_in % tm.sup_n;
-    return tile_m < tm.tiles_m && tile_n < tm.tiles_n;
-}
-
-// First valid tile at or after virtual index v, stepping by the grid size.
-__device__ __forceinline__ PersistTile next_tile(const TileMap &tm, int v, int total, int stride)
+// The first tile of this XCD's share at or after j, in steps of `stride` workgroups of the XCD.
+__device__ __forceinline__ PersistTile tile_at(const TileMap &tm, int j, int stride)
 {
     PersistTile p;
     p.tile_m = p.tile_n = 0;
-    while (v < total && !tile_of_virtual(tm, v, p.tile_m, p.tile_n)) v += stride;
-    p.v = v;
+    int st;
+    while ((st = tile_of_share(tm, (int)blockIdx.x & 7, j, p.tile_m, p.tile_n)) < 0) j += stride;
+    p.j = st > 0 ? j : -1;
     return p;
 }
 
@@ -490,9 +545,8 @@ __device__ __forceinline__ PersistTile next_tile(const TileMap &tm, int v, int t
 // accumulators (nor the per-launch form the per-token factors: 109 spilled registers in one kernel).
 // GELU (compile time): the fused-activation form (GemmArgs::gelu): every epilogue applies the
 // GELU and, with slab_out, the workgroup leaves the column maxima of its tile of Y.
-template <int STAGES, int NWAVES, int FN, int FM, int OWN = 0, bool GELU = false>
-__device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileMap &tm,
-                                                  const int total_virtual)
+template <int STAGES, int NWAVES, int FN, int FM, int OWN, bool GELU, bool STREAM>
+__device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileMap &tm)
 {
     constexpr int WN = 2, WM = NWAVES / WN, TN = WN * FN * 32, TM = WM * FM * 32, SWZ = 1;
     constexpr int NMFMA = FN * FM;           // MFMAs per wave per K sub-step
@@ -521,10 +575,10 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
 
     const int t_aux = aux_tiles(a);
     const int k_tiles = a.k_pad / BK;
-    const int stride = (int)gridDim.x;
+    const int stride = (int)gridDim.x >> 3;  // the grid is a multiple of the 8 XCDs
 
-    PersistTile cur_tile = next_tile(tm, (int)blockIdx.x, total_virtual, stride);
-    if (cur_tile.v >= total_virtual) return;
+    PersistTile cur_tile = tile_at(tm, (int)blockIdx.x >> 3, stride);
+    if (cur_tile.j < 0) return;
     if (a.wg_ticks != nullptr) {             // measurement aid: when this workgroup started
         if (tid == 0) a.wg_ticks[2 * blockIdx.x] = wall_clock64();
         __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // keeps the store out of the loop's load accounting
@@ -562,6 +616,11 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
     __amdgpu_buffer_rsrc_t r_w, r_x;
 
     PersistTile dma_tile = cur_tile;
+    // The tile after the current one, worked out at the end of each epilogue, where the scalar unit has
+    // time: at the phase change all waves would wait for it.  With fewer K steps per tile than the
+    // stream runs ahead, the stream may need the tile after that one and works it out itself.
+    const bool known_next = t_aux + k_tiles > DEPTH;
+    PersistTile nx_tile = tile_at(tm, cur_tile.j + stride, stride);
     bool d_aux;                 // phase of the stream
     int d_left;                 // K steps left in the phase
     unsigned d_w[LH], d_x[LH];  // scalar byte offsets of the next step's blocks
@@ -588,8 +647,8 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
         if (d_aux) {                                                                            \
             MUXQ_DMA_PHASE(false);                                                              \
         } else {                                                                                \
-            const PersistTile nx_ = next_tile(tm, dma_tile.v + stride, total_virtual, stride);  \
-            if (nx_.v < total_virtual) {                                                        \
+            const PersistTile nx_ = known_next ? nx_tile : tile_at(tm, dma_tile.j + stride, stride); \
+            if (nx_.j >= 0) {                                                                   \
                 dma_tile = nx_;                                                                 \
                 MUXQ_DMA_PHASE(t_aux > 0);                                                      \
             } else {                                                                            \
@@ -751,10 +810,10 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
     } while (0)
 
 #define MUXQ_EPI_STAGED(SUB_, WCH_, TOK_, BIAS_)                                                  \
-    epilogue_patch<FN, FM, PATCH_ROW, EPI_STAGED, false, SUB_, WCH_, TOK_, BIAS_>(                  \
+    epilogue_patch<FN, FM, PATCH_ROW, EPI_STAGED, STREAM, false, SUB_, WCH_, TOK_, BIAS_>(                  \
         a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias)
 #define MUXQ_EPI_GELU(MODE_, ZC_, SUB_, WCH_, TOK_, BIAS_)                                        \
-    epilogue_patch<FN, FM, PATCH_ROW, MODE_, ZC_, SUB_, WCH_, TOK_, BIAS_, true>(                   \
+    epilogue_patch<FN, FM, PATCH_ROW, MODE_, STREAM, ZC_, SUB_, WCH_, TOK_, BIAS_, true>(                   \
         a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias, mxh)
     // fused-GELU form: per-wave then per-workgroup column maxima of the tile, behind the
     // waves' epilogue constants in LDS: [WM][TN] fp16 magnitudes
@@ -762,7 +821,7 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
         (unsigned short *)(lds + RING_BYTES + NWAVES * PATCH_BYTES + NWAVES * kChanFloats * 4);
 
     const int t_all = t_aux + k_tiles;
-    while (cur_tile.v < total_virtual) {
+    while (cur_tile.j >= 0) {
         v16i acc[FN][FM];
 #pragma unroll
         for (int fn = 0; fn < FN; ++fn)
@@ -854,11 +913,11 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
             }
         } else
         if (plain && has_zc && sub_bias == 0) {
-            epilogue_patch<FN, FM, PATCH_ROW, EPI_PLAIN, true, false>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, 0);
+            epilogue_patch<FN, FM, PATCH_ROW, EPI_PLAIN, STREAM, true, false>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, 0);
         } else if (plain && has_zc) {
-            epilogue_patch<FN, FM, PATCH_ROW, EPI_PLAIN, true>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias);
+            epilogue_patch<FN, FM, PATCH_ROW, EPI_PLAIN, STREAM, true>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias);
         } else if (plain) {
-            epilogue_patch<FN, FM, PATCH_ROW, EPI_PLAIN>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias);
+            epilogue_patch<FN, FM, PATCH_ROW, EPI_PLAIN, STREAM>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias);
         } else if (staged && !a.x_per_token && sub_bias == 0) {
             // one activation scale, the accumulators' offset folded away: per-channel weight
             // scales with or without a bias, or a bias alone
@@ -875,16 +934,17 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
             if (a.bias != nullptr) MUXQ_EPI_STAGED(true, 1, 1, 1);
             else MUXQ_EPI_STAGED(true, 1, 1, 0);
         } else if (staged) {
-            epilogue_patch<FN, FM, PATCH_ROW, EPI_STAGED>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias);
+            epilogue_patch<FN, FM, PATCH_ROW, EPI_STAGED, STREAM>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias);
         } else {
-            epilogue_patch<FN, FM, PATCH_ROW, EPI_LOADS>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias);
+            epilogue_patch<FN, FM, PATCH_ROW, EPI_LOADS, STREAM>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias);
         }
         if ((plain || staged) && full && (!GELU || a.slab_out != nullptr)) {
             stores_pending = true;           // exactly STORES stores and no loads were issued
         } else {
             __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // unknown number of vector-memory operations: drain
         }
-        cur_tile = next_tile(tm, cur_tile.v + stride, total_virtual, stride);
+        cur_tile = nx_tile;
+        if (cur_tile.j >= 0) nx_tile = tile_at(tm, cur_tile.j + stride, stride);
     }
     // Drain the unused tail loads before the workgroup's LDS is released.
     __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds(0));
@@ -902,25 +962,23 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
 #undef MUXQ_EPI_GELU
 }
 
-template <int STAGES, int OWN = 0, bool GELU = false>
-__global__ __launch_bounds__(512) void k_gemm_i8_persist8(const GemmArgs a, const TileMap tm,
-                                                          const int total_virtual)
+template <int STAGES, int OWN, bool GELU, bool STREAM>
+__global__ __launch_bounds__(512) void k_gemm_i8_persist8(const GemmArgs a, const TileMap tm)
 {
-    gemm_persist_body<STAGES, 8, 4, 2, OWN, GELU>(a, tm, total_virtual);
+    gemm_persist_body<STAGES, 8, 4, 2, OWN, GELU, STREAM>(a, tm);
 }
 
 // 128 x 128 tiles, 4 waves of 64 x 64, a deeper ring: for problems with too few
 // 256 x 256 tiles to fill the chip, where the load latency of a short K loop
 // is what has to be hidden.
-template <int STAGES, int OWN = 0, bool GELU = false>
-__global__ __launch_bounds__(256) void k_gemm_i8_persist4(const GemmArgs a, const TileMap tm,
-                                                          const int total_virtual)
+template <int STAGES, int OWN, bool GELU, bool STREAM>
+__global__ __launch_bounds__(256) void k_gemm_i8_persist4(const GemmArgs a, const TileMap tm)
 {
-    gemm_persist_body<STAGES, 4, 2, 2, OWN, GELU>(a, tm, total_virtual);
+    gemm_persist_body<STAGES, 4, 2, 2, OWN, GELU, STREAM>(a, tm);
 }
 
 // --------------------------------------------------------------------------
-// Small tiles (TN x TM in {128 x 128, 64 x 64}), 4 waves, register staging.
+// Small tiles (64 x 64), 4 waves, register staging.
 // --------------------------------------------------------------------------
 template <int TN, int TM>
 __global__ __launch_bounds__(256) void k_gemm_i8_small(const GemmArgs a, const TileMap tm)
@@ -1180,17 +1238,204 @@ __global__ __launch_bounds__(256) void k_gemm_i8_small_deep(const GemmArgs a, co
     epilogue<FN, FM>(a, acc, m0 + wave_m, n0 + wave_n, lane, lds + wave * (32 * (FN * 64 + 16)), sub_bias);
 }
 
-TileMap make_tile_map(const GemmArgs &a, int TN, int TM, int &grid)
+// --------------------------------------------------------------------------
+// Problems with too few tiles for the forms above: 16 TNB x 16 TMB tiles, and the waves of a
+// workgroup split K.  A block of the packed layout (16 rows x 64 codes, 1 KiB) is one operand of
+// v_mfma_i32_16x16x64_i8 as it lies there -- lane l takes the 16 bytes of row l % 16 at 16 (l / 16)
+// -- so fragments go from memory straight to registers: no LDS image, no barrier in the K loop,
+// and every byte a workgroup reads is read by one wave once.  A wave keeps the loads of DEPTH K
+// steps in flight.  The waves' INT32 partial sums meet in LDS (integer adds: any order gives the
+// same sum).  Bound by what a CU fetches (operands come from L2 at 80-100 GB/s per CU) and by the
+// latencies at its start and end; the matrix pipes, which run this MFMA shape at 60 % of the
+// 32x32x32 rate, do not matter.
+// The Aux K steps all belong to the last wave (which has the fewest Body steps), come first there
+// and are weighted before its Body steps, as in the other forms.
+// --------------------------------------------------------------------------
+template <int TNB, int TMB, int DEPTH, int W>
+__global__ __launch_bounds__(W * 64) void k_gemm_i8_direct(const GemmArgs a, const TileMap tm)
+{
+    constexpr int FRAGS = TNB * TMB, NQ = TNB * 4;       // n quads per tile row
+    __shared__ __attribute__((aligned(16))) v4i part[W * FRAGS * 64];
+    __shared__ uint32_t s_colmax[TNB * 16];
+
+    int tile_m, tile_n;
+    if (!tile_of_workgroup(tm, tile_m, tile_n)) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nblk_n = (a.N + 15) >> 4, nblk_m = (a.M + 15) >> 4;
+    const int k_tiles = a.k_pad / BK;
+    const int lane_off = (lane & 15) * 64 + (lane >> 4) * 16;
+    // ragged edges: the last block again (it only feeds outputs that are not stored)
+    int bn[TNB], bm[TMB];
+#pragma unroll
+    for (int i = 0; i < TNB; ++i) bn[i] = min(tile_n * TNB + i, nblk_n - 1);
+#pragma unroll
+    for (int i = 0; i < TMB; ++i) bm[i] = min(tile_m * TMB + i, nblk_m - 1);
+
+    v4i acc[TNB][TMB];
+#pragma unroll
+    for (int i = 0; i < TNB; ++i)
+#pragma unroll
+        for (int j = 0; j < TMB; ++j) acc[i][j] = v4i{0, 0, 0, 0};
+
+    v4i wf[DEPTH][TNB], xf[DEPTH][TMB];
+    const int8_t *wp[TNB], *xp[TMB];
+#pragma unroll
+    for (int i = 0; i < TNB; ++i) wp[i] = a.w_q + (size_t)bn[i] * k_tiles * 1024 + lane_off;
+#pragma unroll
+    for (int i = 0; i < TMB; ++i) xp[i] = a.a_q + (size_t)bm[i] * k_tiles * 1024 + lane_off;
+    const int nk = (k_tiles - wave + W - 1) / W;          // Body steps of this wave: wave, wave + W, ...
+    auto load = [&](int d, int step) {
+        const int off = (wave + min(step, nk - 1) * W) * 1024;     // past the end: the last step again, unused
+#pragma unroll
+        for (int i = 0; i < TNB; ++i) wf[d][i] = *(const v4i *)(wp[i] + off);
+#pragma unroll
+        for (int i = 0; i < TMB; ++i) xf[d][i] = *(const v4i *)(xp[i] + off);
+    };
+    if (nk > 0) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) load(d, d);
+    }
+
+    // epilogue constants: a thread finishes 4 channels (n quad nq) of the tokens m0, m0 + MSTEP, ...
+    constexpr int MSTEP = W * 64 / NQ;
+    const int nq = tid % NQ, m0 = tid / NQ;
+    const int n = tile_n * TNB * 16 + nq * 4;
+    const bool n_in = n < a.N;                            // N % 8 == 0: a run of 4 is in or out as a whole
+    float4 sw = make_float4(0.f, 0.f, 0.f, 0.f);
+    f16x4 bias = {0, 0, 0, 0};
+    v4i cn = {0, 0, 0, 0};
+    if (n_in) {
+        const int st = a.w_per_channel ? 1 : 0, ns = a.w_per_channel ? n : 0;
+        sw = make_float4(a.w_scale[ns], a.w_scale[ns + st], a.w_scale[ns + 2 * st], a.w_scale[ns + 3 * st]);
+        if (a.bias != nullptr) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) bias[i] = a.bias[n + i];
+        }
+        if (a.cn != nullptr) cn = *(const v4i *)(a.cn + n) - a.cn_bias;
+    }
+    if (tid < TNB * 16) s_colmax[tid] = 0;
+
+    if (wave == W - 1) {
+        const int t_aux = aux_tiles(a), r_tiles = a.r_cap / BK;
+        for (int t = 0; t < t_aux; ++t) {
+            v4i wa[TNB], xa[TMB];
+#pragma unroll
+            for (int i = 0; i < TNB; ++i) wa[i] = *(const v4i *)(a.w_aux + ((size_t)bn[i] * r_tiles + t) * 1024 + lane_off);
+#pragma unroll
+            for (int i = 0; i < TMB; ++i) xa[i] = *(const v4i *)(a.aux_q + ((size_t)bm[i] * r_tiles + t) * 1024 + lane_off);
+#pragma unroll
+            for (int i = 0; i < TNB; ++i)
+#pragma unroll
+                for (int j = 0; j < TMB; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa[i], xa[j], acc[i][j], 0, 0, 0);
+        }
+        if (t_aux > 0) {                                  // acc_aux -> (2^e - 1) acc_aux, or onto Body's scale
+            const float rho = aux_rho(a);
+#pragma unroll
+            for (int j = 0; j < TMB; ++j) {
+                float r = rho;
+                if (a.aux_own_scale && a.x_per_token)
+                    r = aux_rho_tok(a)[min((tile_m * TMB + j) * 16 + (lane & 15), a.M - 1)];
+#pragma unroll
+                for (int i = 0; i < TNB; ++i)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        acc[i][j][v] = a.aux_own_scale
+                                           ? (int)__builtin_rintf(r * (float)acc[i][j][v])
+                                           : (int)(((unsigned)acc[i][j][v] << a.exp_shift) - (unsigned)acc[i][j][v]);
+            }
+        }
+    }
+    for (int t = 0; t < nk; t += DEPTH) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            if (t + d >= nk) break;
+#pragma unroll
+            for (int i = 0; i < TNB; ++i)
+#pragma unroll
+                for (int j = 0; j < TMB; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[d][i], xf[d][j], acc[i][j], 0, 0, 0);
+            if (t + d + DEPTH < nk) load(d, t + d + DEPTH);
+        }
+    }
+
+    // Partial sums to LDS.  A 16 x 16 fragment has its lane (token l % 16, n quad q = l / 16) in slot
+    // 16 q + (token + 4 nb + q) % 16: free of bank conflicts for this store and for the reads below.
+    {
+        const int m = lane & 15, q = lane >> 4;
+#pragma unroll
+        for (int i = 0; i < TNB; ++i)
+#pragma unroll
+            for (int j = 0; j < TMB; ++j)
+                part[(wave * FRAGS + i * TMB + j) * 64 + q * 16 + ((m + 4 * i + q) & 15)] = acc[i][j];
+    }
+    lds_barrier();
+    uint32_t mx[4] = {0, 0, 0, 0};
+    for (int mt = m0; mt < TMB * 16; mt += MSTEP) {
+        const int nb = nq >> 2, q = nq & 3, j = mt >> 4, m = tile_m * TMB * 16 + mt;
+        const v4i *src = part + (nb * TMB + j) * 64 + q * 16 + (((mt & 15) + 4 * nb + q) & 15);
+        v4i sum = src[0];
+#pragma unroll
+        for (int w = 1; w < W; ++w) sum += src[w * FRAGS * 64];
+        if (!n_in || m >= a.M) continue;
+        const int tok = a.x_per_token ? m : 0;
+        if (a.cn != nullptr) sum -= cn * a.zero_point[tok];
+        const float sx = a.x_scale[tok];
+        const float swv[4] = {sw.x, sw.y, sw.z, sw.w};
+        f16x4 out;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float y = (sx * swv[i]) * (float)sum[i];      // Eq. 3
+            if (a.bias != nullptr) y = y + (float)bias[i];
+            out[i] = (_Float16)y;
+            if (a.gelu) {
+                out[i] = (_Float16)gelu_tanh_f32((float)out[i]);
+                mx[i] = max(mx[i], (uint32_t)__builtin_bit_cast(unsigned short, (_Float16)out[i]) & 0x7fffu);
+            }
+        }
+        *(f16x4 *)(a.y + (size_t)m * a.ldy + n) = out;
+        if (a.dbg_acc != nullptr) *(v4i *)(a.dbg_acc + (size_t)m * a.N + n) = sum;
+    }
+    if (a.slab_out != nullptr) {                          // the tile's column maxima, for the next layer
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (mx[i] != 0) atomicMax(&s_colmax[nq * 4 + i], mx[i]);
+        lds_barrier();
+        const int ch = tile_n * TNB * 16 + tid;
+        if (tid < TNB * 16 && ch < a.slab_ld) a.slab_out[(size_t)tile_m * a.slab_ld + ch] = (uint16_t)s_colmax[tid];
+        // zeros in the K padding past the last tile
+        if (tile_n == tm.tiles_n - 1)
+            for (int i = tm.tiles_n * TNB * 16 + tid; i < a.slab_ld; i += W * 64) a.slab_out[(size_t)tile_m * a.slab_ld + i] = 0;
+    }
+}
+
+// at_once: tiles an XCD works on at a time.  grid: workgroups for one tile each, a multiple of 8.
+TileMap make_tile_map(const GemmArgs &a, int TN, int TM, int &grid, int at_once = 32)
 {
     TileMap tm;
     tm.tiles_m = (a.M + TM - 1) / TM;
     tm.tiles_n = (a.N + TN - 1) / TN;
-    tm.sup_m = min(4, tm.tiles_m);
-    tm.sup_n = min(32 / tm.sup_m, tm.tiles_n);
+    tm.sup_m = min(at_once > 32 ? 8 : 4, tm.tiles_m);
+    tm.sup_n = min(at_once / tm.sup_m, tm.tiles_n);
     const int super_m = (tm.tiles_m + tm.sup_m - 1) / tm.sup_m;
     tm.super_n = (tm.tiles_n + tm.sup_n - 1) / tm.sup_n;
     tm.n_super = super_m * tm.super_n;
-    grid = ((tm.n_super + 7) / 8) * 8 * tm.sup_m * tm.sup_n;
+    const int total = tm.tiles_m * tm.tiles_n;
+    // whole blocks if they fill at least one round and no XCD's CUs (32) get a tile more by them
+    const int block_rounds = (tm.n_super + 7) / 8, most = block_rounds * tm.sup_m * tm.sup_n, even = (total + 7) / 8;
+    tm.at_once = total < at_once * 8 || (most + 31) / 32 > (even + 31) / 32 ? at_once : 0;
+    tm.full = total / (at_once * 8);
+    tm.rest = total - tm.full * at_once * 8;
+    const int last_rows = tm.tiles_m - (super_m - 1) * tm.sup_m, last_cols = tm.tiles_n - (tm.super_n - 1) * tm.sup_n;
+    tm.by_block = divisor(tm.sup_m * tm.sup_n);
+    tm.by_sup_n = divisor(tm.sup_n);
+    tm.by_super_n = divisor(tm.super_n);
+    tm.by_at_once = divisor(at_once);
+    tm.by_band = divisor(tm.sup_m * tm.tiles_n);
+    tm.by_band_block = divisor(tm.sup_m * tm.sup_n);
+    tm.by_last_band_block = divisor(last_rows * tm.sup_n);
+    tm.by_last_cols = divisor(last_cols);
+    grid = tm.at_once ? (total + 7) / 8 * 8 : block_rounds * 8 * tm.sup_m * tm.sup_n;
     return tm;
 }
 
@@ -1207,6 +1452,35 @@ constexpr int persist_lds_bytes()
 // 64 KiB of LDS).
 constexpr int kDeepSteps = 8;
 
+typedef void (*persist_kernel_t)(const GemmArgs, const TileMap);
+
+// The persistent kernels of one tile size: Aux on Body's scale / on its own / on its own per token /
+// the fused GELU, each with streaming and with plain stores of Y.
+constexpr int kPersistForms = 8;
+template <int STAGES, int NWAVES>
+persist_kernel_t persist_kernel(int form)
+{
+#define MUXQ_FORM(OWN_, GELU_, STREAM_) \
+    (NWAVES == 8 ? k_gemm_i8_persist8<STAGES, OWN_, GELU_, STREAM_> : k_gemm_i8_persist4<STAGES, OWN_, GELU_, STREAM_>)
+    switch (form) {
+    case 0: return MUXQ_FORM(0, false, false);
+    case 1: return MUXQ_FORM(0, false, true);
+    case 2: return MUXQ_FORM(1, false, false);
+    case 3: return MUXQ_FORM(1, false, true);
+    case 4: return MUXQ_FORM(2, false, false);
+    case 5: return MUXQ_FORM(2, false, true);
+    case 6: return MUXQ_FORM(0, true, false);
+    default: return MUXQ_FORM(0, true, true);
+    }
+#undef MUXQ_FORM
+}
+
+int persist_form(const GemmArgs &a)
+{
+    const bool stream = (((uintptr_t)a.y | (uintptr_t)a.ldy * 2) % 128) == 0;
+    return 2 * (a.gelu ? 3 : !a.aux_own_scale ? 0 : a.x_per_token ? 2 : 1) + (stream ? 1 : 0);
+}
+
 // What the launcher needs to know about a device, found once per device (gemm_prepare_device).
 constexpr int kMaxDevices = 64;
 std::atomic<int> g_device_cus[kMaxDevices];      // 0 = not prepared yet
@@ -1216,30 +1490,15 @@ hipError_t prepare_current_device(int dev)
 {
     std::lock_guard<std::mutex> lock(g_prepare_mutex);
     if (g_device_cus[dev].load(std::memory_order_acquire) != 0) return hipSuccess;
-    hipError_t e = hipFuncSetAttribute((const void *)k_gemm_i8_persist8<3>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, persist_lds_bytes<3, 8>());
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void *)k_gemm_i8_persist4<3>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, persist_lds_bytes<3, 4>());
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void *)k_gemm_i8_persist8<3, 1>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, persist_lds_bytes<3, 8>());
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void *)k_gemm_i8_persist4<3, 1>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, persist_lds_bytes<3, 4>());
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void *)k_gemm_i8_persist8<3, 2>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, persist_lds_bytes<3, 8>());
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void *)k_gemm_i8_persist4<3, 2>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, persist_lds_bytes<3, 4>());
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void *)k_gemm_i8_persist8<3, 0, true>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, persist_lds_bytes<3, 8>());
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void *)k_gemm_i8_persist4<3, 0, true>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, persist_lds_bytes<3, 4>());
-    if (e != hipSuccess) return e;
+    hipError_t e;
+    for (int form = 0; form < kPersistForms; ++form) {
+        e = hipFuncSetAttribute((const void *)persist_kernel<3, 8>(form), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                persist_lds_bytes<3, 8>());
+        if (e != hipSuccess) return e;
+        e = hipFuncSetAttribute((const void *)persist_kernel<3, 4>(form), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                persist_lds_bytes<3, 4>());
+        if (e != hipSuccess) return e;
+    }
     e = hipFuncSetAttribute((const void *)k_gemm_i8_small_deep<64, 64, kDeepSteps>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, kDeepSteps * 128 * BK);
     if (e != hipSuccess) return e;
@@ -1273,40 +1532,37 @@ hipError_t launch_persist(const GemmArgs &a, hipStream_t s)
     static_assert(NWAVES == 8 || NWAVES == 4, "built forms");
     constexpr int TILE = NWAVES == 8 ? 256 : 128;
     int total;
-    const TileMap tm = make_tile_map(a, TILE, TILE, total);
+    const TileMap tm = make_tile_map(a, TILE, TILE, total, NWAVES == 8 ? 32 : 64);
     constexpr int lds_bytes = persist_lds_bytes<STAGES, NWAVES>();
     constexpr int wgs_per_cu = 160 * 1024 / lds_bytes;     // by LDS; registers allow at least as many
     static_assert(wgs_per_cu >= 1, "ring too deep");
-    void (*kern)(const GemmArgs, const TileMap, const int);
-    if constexpr (NWAVES == 8)
-        kern = a.gelu ? k_gemm_i8_persist8<STAGES, 0, true>
-               : !a.aux_own_scale ? k_gemm_i8_persist8<STAGES>
-               : a.x_per_token ? k_gemm_i8_persist8<STAGES, 2> : k_gemm_i8_persist8<STAGES, 1>;
-    else
-        kern = a.gelu ? k_gemm_i8_persist4<STAGES, 0, true>
-               : !a.aux_own_scale ? k_gemm_i8_persist4<STAGES>
-               : a.x_per_token ? k_gemm_i8_persist4<STAGES, 2> : k_gemm_i8_persist4<STAGES, 1>;
+    const persist_kernel_t kern = persist_kernel<STAGES, NWAVES>(persist_form(a));
     int n_cu = 0;
     const hipError_t e = current_device_cus(n_cu);
     if (e != hipSuccess) return e;
     const int grid = total < n_cu * wgs_per_cu ? total : n_cu * wgs_per_cu;
-    return launch_kernel(kern, dim3(grid), dim3(NWAVES * 64), lds_bytes, s, a, tm, total);
+    return launch_kernel(kern, dim3(grid), dim3(NWAVES * 64), lds_bytes, s, a, tm);
 }
 
-template <int TN, int TM>
 hipError_t launch_small(const GemmArgs &a, hipStream_t s)
 {
     int grid;
-    const TileMap tm = make_tile_map(a, TN, TM, grid);
-    if constexpr (TN == 64) {
-        int n_cu = 0;                             // (prepares the device on first use: LDS attribute)
-        const hipError_t e = current_device_cus(n_cu);
-        if (e != hipSuccess) return e;
-        if ((long)tm.tiles_m * tm.tiles_n <= n_cu)
-            return launch_kernel(k_gemm_i8_small_deep<64, 64, kDeepSteps>, dim3(grid), dim3(256),
-                                 kDeepSteps * 128 * BK, s, a, tm);
-    }
-    return launch_kernel(k_gemm_i8_small<TN, TM>, dim3(grid), dim3(256), 0, s, a, tm);
+    const TileMap tm = make_tile_map(a, 64, 64, grid);
+    int n_cu = 0;                             // (prepares the device on first use: LDS attribute)
+    const hipError_t e = current_device_cus(n_cu);
+    if (e != hipSuccess) return e;
+    if ((long)tm.tiles_m * tm.tiles_n <= n_cu)
+        return launch_kernel(k_gemm_i8_small_deep<64, 64, kDeepSteps>, dim3(grid), dim3(256),
+                             kDeepSteps * 128 * BK, s, a, tm);
+    return launch_kernel(k_gemm_i8_small<64, 64>, dim3(grid), dim3(256), 0, s, a, tm);
+}
+
+template <int TNB, int TMB, int DEPTH, int W>
+hipError_t launch_direct(const GemmArgs &a, hipStream_t s)
+{
+    int grid;
+    const TileMap tm = make_tile_map(a, TNB * 16, TMB * 16, grid);
+    return launch_kernel(k_gemm_i8_direct<TNB, TMB, DEPTH, W>, dim3(grid), dim3(W * 64), 0, s, a, tm);
 }
 
 }  // namespace
@@ -1317,38 +1573,70 @@ hipError_t gemm_prepare_device()
     return current_device_cus(n_cu);
 }
 
-// 0: register-staged 64 x 64, 1: register-staged 128 x 128, 2: persistent 128 x 128,
-// 3: persistent 256 x 256.
-static int gemm_form(int M, int N, int k_pad)
+enum GemmForm {
+    kSmall64,         // register-staged 64 x 64
+    kPersist128, kPersist256,
+    kDirect16x16, kDirect16x32, kDirect32x32, kDirect32x64, kDirect64x64       // channels x tokens
+};
+
+// Which form runs a shape fastest was measured over 300 shapes (M 32..16384, K 256..5120, N 256..16384,
+// each form forced in turn).  us per call, by form:
+//   32 x 768 -> 2304     16x32 4.1,  32x32 4.7,  small 7.8,  persistent 128 9.3
+//   24 x 5120 -> 1280    16x16 5.3,  16x32 6.0,  32x32 8.2,  small 24.0,  persistent 128 27.6
+//   512 x 1024 -> 1024   32x32 6.4,  32x64 6.6,  64x64 8.4,  small 9.3,  persistent 128 10.0
+//   512 x 4096 -> 1024   32x64 9.0,  32x32 10.2,  64x64 12.1,  small 20.5,  persistent 128 23.3
+//   1024 x 4096 -> 1024  64x64 12.3,  32x64 14.7,  persistent 128 22.5
+//   512 x 1024 -> 3072   persistent 128 10.4,  small 10.8,  32x32 13.0,  64x64 15.7
+//   1024 x 320 -> 1000   small 6.2,  64x64 8.2,  persistent 128 8.9
+static GemmForm gemm_form(int M, int N, int k_pad)
 {
-    // Which form runs a shape fastest was measured over a grid of 168 GPT-2-scale shapes
-    // (M 128..16384, K 768..4096, N 768..5120, each form forced in turn); this rule loses
-    // 1 % to the best form on average and at most about 15 %.  The 256 x 256 form wins as
-    // soon as its tiles give more than half of the CUs work; below that the 128 x 128
-    // DMA-ring form wins when the K loop is long enough for its ring to matter, and plain
-    // register-staged workgroups, several per CU, when it is short.
-    const long t256 = (long)((M + 255) / 256) * ((N + 255) / 256);
-    const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
-    if (t256 >= 144) return 3;
-    if (k_pad >= 2048) return 2;
-    if (k_pad < 1024) return t128 <= 320 ? 0 : 1;
-    if (t128 < 128) return 0;
-    return t128 <= 384 ? 2 : 1;
+    const auto tiles = [&](int tn, int tm) { return (long)((N + tn - 1) / tn) * ((M + tm - 1) / tm); };
+    const long t64 = tiles(64, 64), t128 = tiles(128, 128), t256 = tiles(256, 256);
+    // Too few tiles for the others: the smallest tile that gives no more workgroups than CUs, or, while
+    // K is short, than are resident at once (a long K is bound by what the CUs fetch, and two small
+    // tiles on a CU fetch more than one large one).
+    const bool short_k = k_pad <= 1536;
+    if (!short_k && tiles(16, 16) <= 256) return kDirect16x16;
+    if (tiles(16, 32) <= (short_k ? 320 : 256)) return kDirect16x32;
+    if (k_pad <= 512) {
+        if (t64 <= 96) return kDirect32x32;
+        if (t128 <= 192) return kSmall64;       // a few K steps: the ring of the persistent forms hides nothing
+    } else {
+        if (tiles(32, 32) <= (short_k ? 800 : 256)) return kDirect32x32;
+        if (!short_k && tiles(32, 64) <= 256) return kDirect32x64;
+        if (t64 <= 256) return kDirect64x64;
+    }
+    // A round of 256 tiles of 256 x 256 takes as long as three of 256 tiles of 128 x 128 (1024 channels:
+    // 20-23 us and 5.3 us + 5.3 us each; the ratio holds from K = 768 to 5120), so the larger tile
+    // wins where its last round is full enough: 8192 x 1024 -> 1024 14 us against 19 us,
+    // 16384 x 1024 -> 1024 24 us against 21 us.
+    const long rounds128 = (t128 + 255) / 256, rounds256 = (t256 + 255) / 256;
+    return rounds128 < 3 * rounds256 || (rounds256 >= 3 && rounds128 == 3 * rounds256) ? kPersist128 : kPersist256;
 }
 
-int gemm_persistent_tile_rows(int M, int N, int k_pad)
+int gemm_tile_rows(int M, int N, int k_pad)
 {
-    const int f = gemm_form(M, N, k_pad);
-    return f == 3 ? 256 : f == 2 ? 128 : 0;
+    switch (gemm_form(M, N, k_pad)) {
+    case kPersist256: return 256;
+    case kPersist128: return 128;
+    case kDirect64x64: case kDirect32x64: return 64;
+    case kDirect32x32: case kDirect16x32: return 32;
+    case kDirect16x16: return 16;
+    default: return 0;
+    }
 }
 
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
 {
     switch (gemm_form(a.M, a.N, a.k_pad)) {
-    case 3: return launch_persist<3, 8>(a, s);
-    case 2: return launch_persist<3, 4>(a, s);
-    case 1: return launch_small<128, 128>(a, s);
-    default: return launch_small<64, 64>(a, s);
+    case kPersist256: return launch_persist<3, 8>(a, s);
+    case kPersist128: return launch_persist<3, 4>(a, s);
+    case kDirect16x16: return launch_direct<1, 1, 8, 8>(a, s);
+    case kDirect16x32: return launch_direct<1, 2, 6, 4>(a, s);
+    case kDirect32x32: return launch_direct<2, 2, 6, 4>(a, s);
+    case kDirect32x64: return launch_direct<2, 4, 6, 4>(a, s);
+    case kDirect64x64: return launch_direct<4, 4, 4, 4>(a, s);
+    default: return launch_small(a, s);
     }
 }
 

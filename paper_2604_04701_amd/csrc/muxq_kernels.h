@@ -167,7 +167,7 @@ struct GemmArgs {
     int w_per_channel;
     int x_per_token;        // one activation scale per row of a_q (per-vector setting)
     int gelu;               // the layer's output goes through the tanh GELU: Y = fp16(gelu(fp16(y)))
-    uint16_t *slab_out;     // with gelu, persistent kernels only, or nullptr: workgroups write the
+    uint16_t *slab_out;     // with gelu, not the register-staged form, or nullptr: workgroups write the
                             // column maxima |Y| of their tile, fp16 bits, to
                             // slab_out[tile_m][n] (row stride slab_ld, zeros for n >= N): the slab
                             // maxima the next layer's selection step folds
@@ -316,9 +316,9 @@ hipError_t launch_wquant_transpose(const void *w_fp16, int K, int N, int ldw,
 hipError_t launch_wscale_finalize(float *w_scale, int n, float qmax, hipStream_t s);
 
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s);
-// Rows per output tile of the persistent form launch_gemm picks for this problem (256 or 128),
-// or 0 when it picks the register-staged form (which does not write slab_out).
-int gemm_persistent_tile_rows(int M, int N, int k_pad);
+// Rows per output tile of the form launch_gemm picks for this problem, or 0 when it picks the
+// register-staged form (which does not write slab_out).
+int gemm_tile_rows(int M, int N, int k_pad);
 
 // Per-device set-up of the GEMM kernels for the CURRENT device: the LDS attribute of the
 // persistent kernels and the CU count their grid is sized by.  Thread-safe, idempotent, and

@@ -1,0 +1,49 @@
+"""The forms of the GEMM and its tile map at the sizes where they can go wrong: ragged last tiles
+and blocks in both directions, fewer K steps than waves, several Aux steps, rows of Y on and off
+128-byte lines, even splits of the tiles over the XCDs.  Accumulators and Y against the CPU
+oracle, all exact (Aux on its own scale: check_own_scale states the bound)."""
+import numpy as np
+import pytest
+
+from gpu_common import check_case, check_mlp, check_own_scale, check_plain_y
+from paper_2604_04701_amd.synth import Case
+
+pytestmark = pytest.mark.gpu
+U = (20.0, 100.0)
+
+FORMS = {
+    "direct 16x16": (100, 2112, 264), "direct 16x32": (130, 520, 1000), "direct 16x32, one K step": (70, 64, 72),
+    "direct 32x32": (333, 1032, 1096), "direct 32x64": (500, 2112, 776), "direct 64x64": (700, 1600, 1400),
+    "direct 64x64, long K": (390, 3008, 1992), "register-staged": (2049, 264, 776),
+    "persistent 128, even split": (2100, 520, 1544), "persistent 256, even split": (3077, 136, 4808),
+    "persistent 256, blocks": (4100, 72, 2560),
+}
+
+
+@pytest.mark.parametrize("x_gran,w_gran,bias_seed", [("tensor", "tensor", None), ("tensor", "channel", 5),
+                                                     ("token", "channel", 6)])
+@pytest.mark.parametrize("form", FORMS)
+def test_gemm_forms(form, x_gran, w_gran, bias_seed):
+    M, K, N = FORMS[form]
+    case = Case("form", M, K, N, min(6, K // 8), U, 800 + M)
+    if M * N <= 2000 * 1600:
+        check_case(case, x_gran=x_gran, w_gran=w_gran, bias_seed=bias_seed)
+    check_plain_y(case, x_gran=x_gran, w_gran=w_gran, bias_seed=bias_seed)
+
+
+@pytest.mark.parametrize("x_gran", ["tensor", "token"])
+@pytest.mark.parametrize("shape", [(100, 2112, 264), (130, 520, 1000), (333, 1032, 1096), (500, 2112, 776)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_direct_forms_several_aux_steps_and_own_scale(shape, x_gran):
+    M, K, N = shape
+    check_case(Case("form_aux", M, K, N, 150, U, 820 + M), r_cap=192, e=3, x_gran=x_gran)
+    X = np.random.default_rng(M).uniform(-5.0, 5.0, size=(M, K)).astype(np.float32)
+    X[:, ::K // 8] *= 1.5
+    W = (0.05 * np.random.default_rng(N).standard_normal((K, N))).astype(np.float16)
+    check_own_scale(Case("form_own", M, K, N, 0, U, 0), X.astype(np.float16), W, x_gran=x_gran, w_gran="channel")
+
+
+@pytest.mark.parametrize("shape", [(100, 2112, 264, 72), (333, 1032, 1096, 136), (700, 1600, 1400, 264)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_direct_forms_hand_the_column_maxima_over(shape):
+    check_mlp(*shape, 840 + shape[0])
