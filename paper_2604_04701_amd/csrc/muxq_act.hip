@@ -1,0 +1,429 @@
+// The activation side with the selection inside the quantisers.
+//
+// The selection (Sec. III-C: which channels are outlier channels; Eq. 1: the scale taken on Body)
+// needs the column maxima of all of X and very little work, and as a kernel of its own it cost 6-8 us
+// between two streaming kernels: one workgroup reading up to 320 KB of slab maxima at what one CU
+// can fetch (~100 GB/s), and the launch.  Here the abs-max pass leaves few slabs (narrow blocks of
+// columns, 64 KB in all), and every workgroup of the quantiser folds them and selects for itself,
+// while its first rows of X are on their way.  With few tokens the abs-max pass goes as well: the
+// workgroups fold X itself (`slabs` are its rows).  Workgroup 0 leaves the results in the workspace.
+//
+// Bound by memory: X twice (the second time mostly out of the memory-side cache), the codes once.
+#include "muxq_select.h"
+
+namespace muxq {
+namespace {
+
+constexpr int kActThreads = 1024, kActWaves = kActThreads / 64;
+constexpr int kActMaxK = 8 * kActThreads;              // one chunk of 8 channels per thread in the selection
+constexpr int kActMaxCap = 1024;
+
+// Column maxima of |X| per row slab, like k_col_absmax_partial, but a workgroup covers only 128
+// columns and many rows: the same number of workgroups leaves a quarter of the slabs.  (64 columns leave
+// an eighth, but 16384 x 5120 from HBM then takes 5 us more; 256 columns, 64-128 KB to fold, cost the
+// quantisers 1-2 us.)
+constexpr int kNarrowLanes = 16;
+__global__ __launch_bounds__(512) void k_col_absmax_narrow(const uint16_t *__restrict__ x, int rows, int cols, int ld,
+                                                           int k_pad, int rows_per_block,
+                                                           uint16_t *__restrict__ partial)
+{
+    constexpr int LANES = kNarrowLanes, RW = 64 / LANES, RB = 8 * RW;    // rows of a wave's load, of a workgroup's
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col0 = blockIdx.x * LANES * 8 + (lane % LANES) * 8;
+    const int r0 = blockIdx.y * rows_per_block, r1 = min(rows, r0 + rows_per_block);
+    uint4 mx = make_uint4(0, 0, 0, 0);
+    if (col0 < cols) {
+        const uint16_t *p = x + col0;
+        int row = r0 + wave * RW + lane / LANES;
+        for (; row + 3 * RB < r1; row += 4 * RB) {
+            const uint4 v0 = *(const uint4 *)(p + (size_t)row * ld);
+            const uint4 v1 = *(const uint4 *)(p + (size_t)(row + RB) * ld);
+            const uint4 v2 = *(const uint4 *)(p + (size_t)(row + 2 * RB) * ld);
+            const uint4 v3 = *(const uint4 *)(p + (size_t)(row + 3 * RB) * ld);
+            mx = absmax_step(absmax_step(absmax_step(absmax_step(mx, v0), v1), v2), v3);
+        }
+        for (; row < r1; row += RB) mx = absmax_step(mx, *(const uint4 *)(p + (size_t)row * ld));
+    }
+    __shared__ uint4 red[512];
+    red[threadIdx.x] = mx;
+    lds_barrier();
+    if (wave != 0) return;
+    for (int w = 1; w < 8; ++w) mx = absmax_step(mx, red[w * 64 + lane]);
+#pragma unroll
+    for (int off = LANES; off < 64; off <<= 1)
+        mx = absmax_step(mx, make_uint4(__shfl_xor((int)mx.x, off), __shfl_xor((int)mx.y, off),
+                                        __shfl_xor((int)mx.z, off), __shfl_xor((int)mx.w, off)));
+    if (lane < LANES && col0 < k_pad) *(uint4 *)(partial + (size_t)blockIdx.y * k_pad + col0) = mx;  // zeros in the K padding
+}
+
+struct ActShared {
+    uint4 part[kActThreads];
+    uint16_t slot[kActMaxK];             // list position of each listed channel
+    int idx[kActMaxCap];                 // the list
+    uint8_t mask[kActThreads];           // per chunk of 8 channels: which are listed
+    __attribute__((aligned(16))) int tot[kActWaves];
+    __attribute__((aligned(16))) uint32_t max[kActWaves];
+    float amax, nmax;                    // given list only
+};
+
+// Fold, selection and list for the whole workgroup.  want_max: false where neither the candidates (a
+// list fixed offline) nor the scale (one per token) need the column maxima.
+__device__ __forceinline__ Selected act_select(const ActArgs &a, ActShared &sh, bool want_max, bool want_scale, uint4 &mx)
+{
+    const int tid = threadIdx.x, C = a.K / 8, CA = a.k_pad / 8;
+    mx = make_uint4(0, 0, 0, 0);
+    if (want_max) {
+        const int P = quotient(kActThreads, a.by_chunks), p = quotient(tid, a.by_chunks), c = tid - p * CA;
+        if (p < P && c < C) {
+            const uint16_t *src = a.slabs + (size_t)c * 8;
+            int sl = p;
+            for (; sl + 7 * P < a.n_slabs; sl += 8 * P) {
+                uint4 q[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) q[j] = *(const uint4 *)(src + (size_t)(sl + j * P) * a.slab_ld);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) mx = absmax_step(mx, q[j]);
+            }
+            // (past the end the last slab again: a branch per load would serialise the loads)
+            if (sl < a.n_slabs) {
+                uint4 q[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) q[j] = *(const uint4 *)(src + (size_t)min(sl + j * P, a.n_slabs - 1) * a.slab_ld);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) mx = absmax_step(mx, q[j]);
+            }
+        }
+        if (P > 1) {
+            sh.part[tid] = mx;
+            lds_barrier();
+            mx = make_uint4(0, 0, 0, 0);
+            if (tid < CA)
+                for (int g = 0; g < min(P, a.n_slabs); ++g) mx = absmax_step(mx, sh.part[g * CA + tid]);
+        }
+    }
+    uint32_t cand = 0;
+    if (tid < C) {
+        if (a.static_mask != nullptr) {
+            cand = a.static_mask[tid];
+        } else {
+            float v[8];
+            widen8(mx, v);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) cand |= (v[i] > a.threshold ? 1u : 0u) << i;
+        }
+    }
+    const Selected r = select_channels<kActWaves>(mx, cand, true, tid >> 6, a.r_cap, want_scale, sh.tot, sh.max);
+    if (tid < CA) sh.mask[tid] = (uint8_t)r.listed;
+    int rank = r.first;
+    for (uint32_t mm = r.listed; mm != 0; mm &= mm - 1, ++rank) {
+        const int k = tid * 8 + __builtin_ctz(mm);
+        sh.slot[k] = (uint16_t)rank;
+        sh.idx[rank] = k;
+    }
+    lds_barrier();
+    return r;
+}
+
+// Eq. 7: the weight rows that meet Aux, w_aux[n][j] = w_q[n][idx[j]], and cn[n], the sum of channel n's
+// other weight codes (+ cn_bias): 16 lanes per output channel, 64 channels per workgroup and step.  The
+// bytes of the first step are requested before the rows of X are worked on and written after it.
+struct ActGather {
+    int v[4], row_sum;
+};
+__device__ __forceinline__ ActGather gather_request(const ActArgs &a, const ActShared &sh, int n, int used)
+{
+    ActGather g;
+    g.row_sum = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) g.v[i] = 0;
+    if (a.cn == nullptr || n >= a.N) return g;
+    g.row_sum = a.w_row_sum[n];
+    const int sub = threadIdx.x & 15;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (sub + 16 * i < used) g.v[i] = a.w_q[packed_index(n, sh.idx[sub + 16 * i], a.k_pad)];
+    return g;
+}
+__device__ __forceinline__ void gather_finish(const ActArgs &a, const ActShared &sh, int n, int used, const ActGather &g)
+{
+    if (a.cn == nullptr) return;
+    const int sub = threadIdx.x & 15;
+    int sum = 0;
+    if (n < a.N) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int j = sub + 16 * i;
+            if (a.w_aux != nullptr && j < a.r_cap) a.w_aux[packed_index(n, j, a.r_cap)] = (int8_t)g.v[i];
+            sum += g.v[i];
+        }
+        for (int j = sub + 64; j < a.r_cap; j += 16) {           // lists beyond 64 entries
+            const int v = j < used ? a.w_q[packed_index(n, sh.idx[j], a.k_pad)] : 0;
+            if (a.w_aux != nullptr) a.w_aux[packed_index(n, j, a.r_cap)] = (int8_t)v;
+            sum += v;
+        }
+    }
+    for (int off = 8; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+    if (sub == 0 && n < a.N) a.cn[n] = g.row_sum - sum + a.cn_bias;
+}
+__device__ __forceinline__ void gather_rest(const ActArgs &a, const ActShared &sh, int used, const ActGather &first)
+{
+    const int n0 = blockIdx.x * 64 + (threadIdx.x >> 4);
+    gather_finish(a, sh, n0, used, first);
+    if (a.cn == nullptr) return;
+    for (int nb = ((int)blockIdx.x + (int)gridDim.x) * 64; nb < a.N; nb += (int)gridDim.x * 64) {     // (N in the ten thousands)
+        const int n = nb + (threadIdx.x >> 4);
+        gather_finish(a, sh, n, used, gather_request(a, sh, n, used));
+    }
+}
+
+// Codes of one chunk of 8 channels of a row: Body (Eq. 1, 4; unlisted channels as code + z, which
+// rides on `magic`), and the Aux codes of the channels in `mask` (Eq. 5).
+__device__ __forceinline__ void quantize_chunk(const ActArgs &a, const ActShared &sh, int row, int c, uint4 raw, uint32_t mask,
+                                               float inv, float inv_listed, float magic)
+{
+    const f16x8 h = __builtin_bit_cast(f16x8, raw);
+    uint32_t q[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) q[i] = quant_word((float)h[i], inv, a.qmax, magic);
+    uint2 packed = make_uint2(pack_low_bytes(q[0], q[1], q[2], q[3]), pack_low_bytes(q[4], q[5], q[6], q[7]));
+    for (uint32_t mm = mask; mm != 0; mm &= mm - 1) {              // few lanes: listed channels again, shrunk, no z
+        const int i = __builtin_ctz(mm), d = i >> 1;
+        const uint32_t word = d == 0 ? raw.x : d == 1 ? raw.y : d == 2 ? raw.z : raw.w;
+        const float xi = (float)__builtin_bit_cast(_Float16, (unsigned short)(word >> ((i & 1) * 16)));
+        const uint32_t code = quant_word(xi, inv_listed, a.qmax) & 0xffu, sh8 = (uint32_t)(i & 3) * 8u;
+        if (i < 4)
+            packed.x = (packed.x & ~(0xffu << sh8)) | (code << sh8);
+        else
+            packed.y = (packed.y & ~(0xffu << sh8)) | (code << sh8);
+        a.aux_q[packed_index(row, sh.slot[c * 8 + i], a.r_cap)] = (int8_t)code;
+    }
+    *(uint2 *)(a.body_q + packed_index(row, c * 8, a.k_pad)) = packed;
+}
+
+// One activation scale for the call.  A wave owns a piece of 64 chunks of a row, a thread one chunk
+// (its mask and every address but the row's part, which is scalar, are fixed: the work per code is the
+// quantisation itself, 4 vector instructions), and takes it in row after row, up to U rows in flight.  All
+// workgroups walk X together: what is in flight at one time is one contiguous piece of memory.  (A
+// range of rows for each workgroup puts all of them on the same few memory channels where a range
+// is a multiple of a large power of two: 16384 x 5120 from HBM 65 us instead of 45 us.)
+// GIVEN: the list and the column maxima are the caller's (muxq_build_aux): any list of channels, each
+// named once, and any binary32 maxima.
+template <bool GIVEN>
+__global__ __launch_bounds__(kActThreads) void k_quantize_select(const ActArgs a)
+{
+    __shared__ ActShared sh;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int C = a.K / 8, CA = a.k_pad / 8;
+    constexpr int U = 4;
+    const int S = a.pieces, P = a.groups, p = quotient(wave, a.by_pieces), seg = wave - p * S;
+    const int c = seg * 64 + lane;
+    const bool in_c = c < C && p < P;
+    const int deep = a.deep;                         // rows in flight, at most U
+    const int stride = (int)gridDim.x * P * deep;
+    int row = p < P ? (int)blockIdx.x * P * deep + p : a.M;    // (waves without a piece: no row)
+    uint4 raw[U];
+    auto load = [&](int r) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            raw[u] = make_uint4(0, 0, 0, 0);
+            if (u < deep && r + u * P < a.M && in_c) raw[u] = *(const uint4 *)(a.x + (size_t)(r + u * P) * a.ldx + c * 8);
+        }
+    };
+    load(row);
+
+    const float shrink = __uint_as_float((uint32_t)(127 - a.exp) << 23);  // 2^-exp
+    float sx, inv;
+    int z = 0, used;
+    if (GIVEN) {
+        used = max(0, min(a.n_outliers[0], a.r_cap));
+        if (tid < CA) sh.mask[tid] = 0;
+        if (tid == 0) sh.amax = 0.f;
+        lds_barrier();
+        for (int j = tid; j < used; j += kActThreads) {
+            const int k = a.idx[j];
+            if (k >= 0 && k < a.K) {
+                sh.slot[k] = (uint16_t)j;
+                atomicOr((uint32_t *)(sh.mask + ((k >> 3) & ~3)), 1u << ((k & 7) + 8 * ((k >> 3) & 3)));
+            }
+        }
+        lds_barrier();
+        float amax = 0.f;
+        if (tid < C) {
+            const uint32_t m = sh.mask[tid];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) amax = fmaxf(amax, a.col_absmax[tid * 8 + i] * ((m >> i) & 1u ? shrink : 1.0f));
+        }
+        for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+        if ((tid & 63) == 0) atomicMax((uint32_t *)&sh.amax, __float_as_uint(amax));
+        lds_barrier();
+        amax = sh.amax;
+        sx = amax > 0.f ? amax / a.qmax : 0.f;       // correctly rounded binary32 divisions (Eq. 1)
+        inv = amax > 0.f ? a.qmax / amax : 0.f;
+        if (blockIdx.x == 0 && tid == 0) {
+            a.x_scale[0] = sx;
+            a.x_scale[1] = inv;
+        }
+    } else {
+        uint4 mx;
+        const Selected sel = act_select(a, sh, true, true, mx);
+        used = sel.used;
+        call_scale(sel.maxima, shrink, a.qmax, sx, inv, z);
+        if (blockIdx.x == 0) {
+            store_selection(sel, mx, tid, C, CA, true, a.r_cap, true, inv, shrink, a.col_absmax, a.col_scale, a.col_slot,
+                            a.col_mask, a.idx, a.n_outliers);
+            if (tid == 0) {
+                a.x_scale[0] = sx;
+                a.x_scale[1] = inv;
+                a.zero_point[0] = z;
+            }
+        }
+    }
+    const ActGather g = gather_request(a, sh, blockIdx.x * 64 + (tid >> 4), used);
+
+    // Aux columns past the list, in equal shares of the rows
+    if (used < a.r_cap) {
+        const int per = (a.M + (int)gridDim.x - 1) / (int)gridDim.x, r1 = min(a.M, ((int)blockIdx.x + 1) * per);
+        for (int r = blockIdx.x * per + (tid >> 6); r < r1; r += kActWaves)
+            for (int j = used + (tid & 63); j < a.r_cap; j += 64) a.aux_q[packed_index(r, j, a.r_cap)] = 0;
+    }
+    const float inv_listed = inv * shrink, magic = 12582912.0f + (float)z;
+    const uint32_t mask = in_c ? sh.mask[c] : 0u;
+    for (; row < a.M; row += stride) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = row + u * P;
+            if (u >= deep || r >= a.M) break;
+            if (in_c)
+                quantize_chunk(a, sh, r, c, raw[u], mask, inv, inv_listed, magic);
+            else if (c < CA)                         // K padding of Body
+                *(uint2 *)(a.body_q + packed_index(r, c * 8, a.k_pad)) = make_uint2(0, 0);
+        }
+        load(row + stride);
+    }
+    gather_rest(a, sh, used, g);
+}
+
+// One activation scale per row.  A row is `pieces` pieces of 64 NC chunks; a wave takes a piece, a lane
+// the chunks lane, lane + 64, ... of it, in registers from the row's maximum to the codes; the next
+// rows are on their way meanwhile.  The pieces' maxima meet in LDS (one barrier per step of all rows
+// in flight; the two halves of `s_piece` take turns).
+template <int NC>
+__global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
+{
+    __shared__ ActShared sh;
+    __shared__ uint32_t s_piece[2][kActWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int C = a.K / 8, CA = a.k_pad / 8;
+    const int S = a.pieces, P = a.groups, p = quotient(wave, a.by_pieces), seg = wave - p * S;
+    const int c0 = seg * 64 * NC + lane;
+    uint4 raw[NC];
+    auto load = [&](int row, uint4 (&v)[NC]) {
+        const uint16_t *src = a.x + (size_t)row * a.ldx + c0 * 8;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            v[i] = make_uint4(0, 0, 0, 0);
+            if (row < a.M && p < P && c0 + 64 * i < C) v[i] = *(const uint4 *)(src + 512 * i);
+        }
+    };
+    // (P rows of every workgroup in turn: see k_quantize_select)
+    const int stride = (int)gridDim.x * P;
+    int row = (int)blockIdx.x * P + p;
+    load(row, raw);
+
+    const float shrink = __uint_as_float((uint32_t)(127 - a.exp) << 23);  // 2^-exp
+    const bool want_max = a.static_mask == nullptr;
+    uint4 mx;
+    const Selected sel = act_select(a, sh, want_max, false, mx);
+    if (blockIdx.x == 0 && want_max)
+        store_selection(sel, mx, tid, C, CA, true, a.r_cap, false, 0.f, shrink, a.col_absmax, a.col_scale, a.col_slot,
+                        a.col_mask, a.idx, a.n_outliers);
+    const ActGather g = gather_request(a, sh, blockIdx.x * 64 + (tid >> 4), sel.used);
+    uint32_t mk = 0;                                 // this lane's chunk masks, one to a byte
+    static_assert(NC <= 4, "four masks to a word");
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+        if (c0 + 64 * i < C) mk |= (uint32_t)sh.mask[c0 + 64 * i] << (8 * i);
+
+    // (the same number of steps for all waves: they meet at the barrier)
+    for (int step = 0, r0 = (int)blockIdx.x * P; r0 < a.M; ++step, r0 += stride, row += stride) {
+        uint4 nx[NC];
+        load(row + stride, nx);
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) m = pk_max_u16(m, chunk_maxima(raw[i], (mk >> (8 * i)) & 0xffu));
+        m = wave_max_u16x2_to_lane63(m);
+        if (S > 1) {
+            if (lane == 63) s_piece[step & 1][wave] = m;
+            lds_barrier();
+            m = 0;
+            for (int i = 0; i < S; ++i) m = pk_max_u16(m, s_piece[step & 1][min(p, P - 1) * S + i]);
+        } else {
+            m = (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+        }
+        if (p < P && row < a.M) {
+            float sx, inv;
+            int z;
+            call_scale(m, shrink, a.qmax, sx, inv, z);
+            if (lane == 0 && seg == 0) {
+                a.x_scale[row] = sx;
+                a.x_scale[a.M + row] = inv;
+                ((int32_t *)a.x_scale)[2 * (size_t)a.M + row] = z;
+            }
+            const float inv_listed = inv * shrink, magic = 12582912.0f + (float)z;
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+                const int c = c0 + 64 * i;
+                if (c < C)
+                    quantize_chunk(a, sh, row, c, raw[i], (mk >> (8 * i)) & 0xffu, inv, inv_listed, magic);
+                else if (c < CA)                     // K padding of Body
+                    *(uint2 *)(a.body_q + packed_index(row, c * 8, a.k_pad)) = make_uint2(0, 0);
+            }
+            if (seg == S - 1)
+                for (int j = sel.used + lane; j < a.r_cap; j += 64) a.aux_q[packed_index(row, j, a.r_cap)] = 0;
+        }
+#pragma unroll
+        for (int i = 0; i < NC; ++i) raw[i] = nx[i];
+    }
+    gather_rest(a, sh, sel.used, g);
+}
+
+}  // namespace
+
+bool act_select_fits(int k_pad, int r_cap) { return k_pad <= kActMaxK && r_cap <= kActMaxCap; }
+
+hipError_t launch_col_absmax_narrow(const void *x_fp16, int rows, int cols, int ld, int k_pad, uint16_t *partial,
+                                    int *n_slabs, hipStream_t s)
+{
+    // about one workgroup per CU, at least 64 rows each
+    const int gx = (k_pad / 8 + kNarrowLanes - 1) / kNarrowLanes;
+    int gy = max(1, min(kMaxSlabs, 256 / gx));
+    gy = max(1, min(gy, (rows + 63) / 64));
+    const int rpb = ((rows + gy - 1) / gy + 63) & ~63;
+    gy = (rows + rpb - 1) / rpb;
+    *n_slabs = gy;
+    return launch_kernel(k_col_absmax_narrow, dim3(gx, gy), dim3(512), 0, s,
+                         (const uint16_t *)x_fp16, rows, cols, ld, k_pad, rpb, partial);
+}
+
+hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool given, hipStream_t s)
+{
+    ActArgs a = args;
+    a.by_chunks = divisor(a.k_pad / 8);
+    // pieces of a row: of 64 chunks, or with one scale per row of as many as a wave keeps in registers
+    a.pieces = !per_token ? (a.k_pad / 8 + 63) / 64 : a.k_pad <= 1024 ? 1 : (a.k_pad + 2047) / 2048;
+    a.by_pieces = divisor(a.pieces);
+    // every workgroup selects for itself, so no more of them than are resident at once, but enough for
+    // a share of the weight side each (64 output channels)
+    a.groups = min(kActWaves / a.pieces, (a.M + 255) / 256);       // rows of a workgroup at a time
+    a.deep = per_token ? 1 : max(1, min(4, a.M / (256 * a.groups)));
+    const int rows = a.groups * a.deep;
+    const int grid = min(max((a.M + rows - 1) / rows, a.cn != nullptr ? (a.N + 63) / 64 : 1), 256);
+    void (*kern)(const ActArgs);
+    if (!per_token)
+        kern = given ? k_quantize_select<true> : k_quantize_select<false>;
+    else
+        kern = a.k_pad <= 1024 ? k_rows_select<2> : k_rows_select<4>;
+    return launch_kernel(kern, dim3(grid), dim3(kActThreads), 0, s, a);
+}
+
+}  // namespace muxq

@@ -167,6 +167,7 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
     int32_t *zero_point = per_token ? (int32_t *)x_scale + 2 * (size_t)M : (int32_t *)(ws + L.n_outliers) + 2;
     int32_t *cn = (int32_t *)(ws + L.cn);
     const int32_t *w_row_sum = (const int32_t *)(w_q + muxq::wq_rowsum_offset(N, k_pad));
+    const int ready_slabs = absmax_slabs > 0 ? absmax_slabs : muxq::absmax_slab_count(M, k_pad);
     // few tokens: the whole layer in one launch (the measurement aid that brackets the GEMM keeps
     // the separate launches, as does Aux on a scale of its own; X is addressed with 32-bit offsets)
     if (gemm_start == nullptr && !aux_own && (size_t)M * (size_t)ldx < (1u << 30) &&
@@ -186,7 +187,7 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
         f.threshold = threshold;
         if (absmax_ready) {
             f.slabs = partial;
-            f.n_slabs = absmax_slabs > 0 ? absmax_slabs : muxq::absmax_slab_count(M, k_pad);
+            f.n_slabs = ready_slabs;
         }
         f.static_mask = static_mask;
         f.col_absmax = col_absmax;
@@ -214,9 +215,48 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
         MUXQ_TRY(muxq::launch_linear_few(f, s));
         return MUXQ_OK;
     }
+    // the selection inside the quantiser, where every workgroup can fold the column maxima for itself
+    if (!aux_own && muxq::act_select_fits(k_pad, r_cap) &&
+        !(absmax_ready && (size_t)ready_slabs * k_pad * 2 > muxq::kFoldSlabBytes)) {
+        muxq::ActArgs q{};
+        q.x = (const uint16_t *)X;
+        q.M = M; q.K = K; q.ldx = ldx; q.k_pad = k_pad; q.N = N;
+        q.exp = exp;
+        q.r_cap = r_cap;
+        q.qmax = qmax;
+        q.threshold = threshold;
+        q.static_mask = static_mask;
+        q.slabs = partial;
+        q.slab_ld = k_pad;
+        if (absmax_ready) {
+            q.n_slabs = ready_slabs;
+        } else if ((size_t)M * K * 2 <= muxq::kFoldXBytes) {      // X is small: its rows are the slabs
+            q.slabs = (const uint16_t *)X;
+            q.slab_ld = ldx;
+            q.n_slabs = M;
+        } else if (!(per_token && static_block != nullptr)) {
+            MUXQ_TRY(muxq::launch_col_absmax_narrow(X, M, K, ldx, k_pad, partial, &q.n_slabs, s));
+        }
+        q.col_absmax = col_absmax;
+        q.col_scale = col_scale;
+        q.col_slot = col_slot;
+        q.col_mask = (uint8_t *)(ws + L.col_mask);
+        q.idx = idx;
+        q.n_outliers = (int32_t *)(ws + L.n_outliers);
+        q.x_scale = x_scale;
+        q.zero_point = zero_point;
+        q.body_q = body_q;
+        q.aux_q = aux_q;
+        q.w_aux = gather ? w_aux : nullptr;
+        q.w_q = w_q;
+        q.w_row_sum = w_row_sum;
+        q.cn = cn;
+        q.cn_bias = per_token ? 0 : muxq::kCnBias;
+        MUXQ_TRY(muxq::launch_quantize_select(q, per_token, false, s));
+    } else {
     if (!(per_token && static_block != nullptr)) {
         if (absmax_ready)     // a producer of X has left the slab maxima in the workspace
-            n_slabs = absmax_slabs > 0 ? absmax_slabs : muxq::absmax_slab_count(M, k_pad);
+            n_slabs = ready_slabs;
         else
             MUXQ_TRY(muxq::launch_col_absmax_partial(X, M, K, ldx, k_pad, partial, &n_slabs, s));
         MUXQ_TRY(muxq::launch_fold_select_scale(partial, n_slabs, K, k_pad, threshold, r_cap, exp, qmax,
@@ -238,6 +278,7 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
                                             gather ? nullptr : (r_cap ? w_aux : nullptr), zero_point,
                                             w_row_sum, cn, muxq::kCnBias, aux_own ? x_scale + 2 : nullptr,
                                             exp));
+    }
 
     muxq::GemmArgs g{};
     g.a_q = body_q;
@@ -505,7 +546,10 @@ int muxq_detect_outliers(const void *X, int M, int K, int ldx, float threshold, 
         return MUXQ_ERR_ALIGN;
     hipStream_t s = (hipStream_t)stream;
     int n_slabs = 0;
-    MUXQ_TRY(muxq::launch_col_absmax_partial(X, M, K, ldx, kpad(K), (uint16_t *)scratch, &n_slabs, s));
+    if (muxq::act_select_fits(kpad(K), 0))           // few slabs for the fold, see muxq_act.hip
+        MUXQ_TRY(muxq::launch_col_absmax_narrow(X, M, K, ldx, kpad(K), (uint16_t *)scratch, &n_slabs, s));
+    else
+        MUXQ_TRY(muxq::launch_col_absmax_partial(X, M, K, ldx, kpad(K), (uint16_t *)scratch, &n_slabs, s));
     MUXQ_TRY(muxq::launch_fold_select_scale((const uint16_t *)scratch, n_slabs, K, kpad(K), threshold,
                                             r_cap, 0, 127.0f, 0, col_absmax, outlier_idx, n_outliers, nullptr,
                                             nullptr, nullptr, nullptr, s));
@@ -529,6 +573,22 @@ int muxq_build_aux(const void *X, int M, int K, int ldx, const float *col_absmax
         (aux_q && !aligned(aux_q, 16)) || !aligned(x_scale, 4))
         return MUXQ_ERR_ALIGN;
     hipStream_t s = (hipStream_t)stream;
+    if (muxq::act_select_fits(k_pad, r_cap)) {       // the scale inside the quantiser: one launch
+        muxq::ActArgs q{};
+        q.x = (const uint16_t *)X;
+        q.M = M; q.K = K; q.ldx = ldx; q.k_pad = k_pad;
+        q.exp = exp;
+        q.r_cap = r_cap;
+        q.qmax = 127.0f;
+        q.col_absmax = const_cast<float *>(col_absmax);
+        q.idx = const_cast<int32_t *>(outlier_idx);
+        q.n_outliers = const_cast<int32_t *>(n_outliers);
+        q.x_scale = x_scale;
+        q.body_q = body_q;
+        q.aux_q = aux_q;
+        MUXQ_TRY(muxq::launch_quantize_select(q, false, true, s));
+        return MUXQ_OK;
+    }
     float *col_scale = (float *)scratch;
     int32_t *col_slot = (int32_t *)scratch + k_pad;
     MUXQ_TRY(muxq::launch_select_scale(col_absmax, K, k_pad, 0.f, r_cap, exp, 127.0f, 0, 1,

@@ -24,7 +24,7 @@
 // Everything a caller may read from the workspace afterwards (the muxq_workspace_layout regions)
 // is written as by the separate launches: the selection results by workgroup 0, the codes in
 // shares by all workgroups, w_aux and cn by the workgroup that owns the channels.
-#include "muxq_kernels.h"
+#include "muxq_select.h"
 
 namespace muxq {
 namespace {
@@ -77,70 +77,6 @@ __device__ __forceinline__ int few_code_pos(int row, int col, int M, int cols)
     return (mb << 4) * cols + (col >> 6) * (rows << 6) + (r << 6) + ((((col >> 4) & 3) ^ (r >> 2)) << 4) + (col & 15);
 }
 
-// The largest magnitude among the channels of `raw` (8 fp16) that `listed` does not name, in the
-// low half, and among those it names, in the high half (fp16 magnitudes order like integers).
-__device__ __forceinline__ uint32_t chunk_maxima(uint4 raw, uint32_t listed)
-{
-    uint32_t d[4] = {raw.x & 0x7fff7fffu, raw.y & 0x7fff7fffu, raw.z & 0x7fff7fffu, raw.w & 0x7fff7fffu};
-    uint32_t l = 0;
-    if (__ballot(listed != 0) != 0) {                    // (most waves have no listed channel)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t two = listed >> (2 * i);
-            const uint32_t out = (two & 1u) * 0xffffu | (two >> 1 & 1u) * 0xffff0000u;
-            l = pk_max_u16(l, d[i] & out);
-            d[i] &= ~out;
-        }
-        l = max(l & 0xffffu, l >> 16);
-    }
-    const uint32_t m = pk_max_u16(pk_max_u16(d[0], d[1]), pk_max_u16(d[2], d[3]));
-    return max(m & 0xffffu, m >> 16) | (l << 16);
-}
-
-__device__ __forceinline__ float f32_of_half_bits(uint32_t h)
-{
-    return (float)__builtin_bit_cast(_Float16, (unsigned short)h);
-}
-
-// Scale, multiplier and zero point (Eq. 1; the zero point of the unlisted channels' codes is even,
-// see the selection kernel) from the two maxima of chunk_maxima over a row, or over the call.
-__device__ __forceinline__ void few_scale(uint32_t maxima, float shrink, float qmax, float &sx, float &inv, int &z)
-{
-    const float nm = fmaxf(0.f, f32_of_half_bits(maxima & 0xffffu)), lm = fmaxf(0.f, f32_of_half_bits(maxima >> 16));
-    const float am = fmaxf(nm, lm * shrink);             // exact: max |Body| (Eq. 4)
-    sx = am > 0.f ? am / qmax : 0.f;                     // correctly rounded binary32 divisions
-    inv = am > 0.f ? qmax / am : 0.f;
-    const int c = (int)fminf(__builtin_rintf(nm * inv), qmax);
-    z = min(c + (c & 1), (127 - c) & ~1);
-}
-
-// Maximum (two packed uint16) over the wave, in lane 63; sum of the lanes up to and including this
-// one.  (Cross-lane moves of the vector ALU: a permute through LDS is ten times their latency.)
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ uint32_t dpp_zero(uint32_t v)     // lanes without a source get 0
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
-}
-__device__ __forceinline__ uint32_t wave_max_u16x2_to_lane63(uint32_t v)
-{
-    v = pk_max_u16(v, dpp_zero<0x111>(v));                   // row_shr 1, 2, 4, 8: lane 15 of a row of 16
-    v = pk_max_u16(v, dpp_zero<0x112>(v));
-    v = pk_max_u16(v, dpp_zero<0x114>(v));
-    v = pk_max_u16(v, dpp_zero<0x118>(v));
-    v = pk_max_u16(v, dpp_zero<0x142, 0xa>(v));              // lane 15 of a row to the next one
-    return pk_max_u16(v, dpp_zero<0x143, 0xc>(v));           // lane 31 to the upper half
-}
-__device__ __forceinline__ int wave_inclusive_sum(int x)
-{
-    uint32_t v = (uint32_t)x;
-    v += dpp_zero<0x111>(v);
-    v += dpp_zero<0x112>(v);
-    v += dpp_zero<0x114>(v);
-    v += dpp_zero<0x118>(v);
-    v += dpp_zero<0x142, 0xa>(v);
-    return (int)(v + dpp_zero<0x143, 0xc>(v));
-}
-
 // MB: 16-row blocks of tokens (1, 2 or 4).  TOKEN: one activation scale per row.
 // (Loops over rows are kept rolled: a kernel starts with a cold instruction cache, and straight-line
 // code for eight rows takes longer to fetch than to run.)
@@ -149,7 +85,7 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     typedef __attribute__((address_space(3))) void *lptr_t;
-    __shared__ __attribute__((aligned(16))) int s_tot[kFewWaves];
+    __shared__ __attribute__((aligned(16))) int s_tot[kFewWaves];       // (each row group selects for itself)
     __shared__ __attribute__((aligned(16))) uint32_t s_max[kFewWaves];
     __shared__ uint32_t s_row[kFewMaxM * kFewWaves];     // per token: the maxima of a row's pieces
     __shared__ float s_sx[kFewMaxM], s_inv[kFewMaxM];
@@ -254,38 +190,10 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
 #pragma unroll
         for (int i = 0; i < 8; ++i) listed |= (v[i] > a.threshold ? 1u : 0u) << i;
     }
-    const int cnt = __builtin_popcount(listed);
-    const int incl = wave_inclusive_sum(cnt);
-    uint32_t top = TOKEN ? 0u : wave_max_u16x2_to_lane63(chunk_maxima(mx, listed));
-    if (lane == 63) {
-        s_tot[wave] = p == 0 ? incl : 0;
-        s_max[wave] = p == 0 ? top : 0u;
-    }
-    lds_barrier();
-    int first = incl - cnt, found = 0;                   // rank of this chunk's first candidate
-    uint32_t call_max = 0;
-#pragma unroll
-    for (int i = 0; i < kFewWaves; i += 4) {
-        const int4 t = *(const int4 *)(s_tot + i);
-        const uint4 m = *(const uint4 *)(s_max + i);
-        first += (i < seg ? t.x : 0) + (i + 1 < seg ? t.y : 0) + (i + 2 < seg ? t.z : 0) + (i + 3 < seg ? t.w : 0);
-        found += t.x + t.y + t.z + t.w;
-        call_max = pk_max_u16(call_max, pk_max_u16(pk_max_u16(m.x, m.y), pk_max_u16(m.z, m.w)));
-    }
-    const int used = min(found, r_cap);
-    if (found > r_cap) {                                 // the r_cap lowest candidates are listed
-        uint32_t kept = 0;
-        int rank = first;
-        for (uint32_t mm = listed; mm != 0; mm &= mm - 1, ++rank)
-            if (rank < r_cap) kept |= mm & (0u - mm);
-        listed = kept;
-        top = wave_max_u16x2_to_lane63(chunk_maxima(mx, listed));
-        lds_barrier();                                   // s_max is consumed
-        if (lane == 63) s_max[wave] = p == 0 ? top : 0u;
-        lds_barrier();
-        call_max = 0;
-        for (int i = 0; i < kFewWaves; ++i) call_max = pk_max_u16(call_max, s_max[i]);
-    }
+    const Selected sel = select_channels<kFewWaves>(mx, listed, p == 0, seg, r_cap, !TOKEN, s_tot, s_max);
+    listed = sel.listed;
+    const int first = sel.first, used = sel.used, found = sel.found;
+    const uint32_t call_max = sel.maxima;
     if (p == 0) {
         int rank = first;
         for (uint32_t mm = listed; mm != 0; mm &= mm - 1, ++rank) idx_lds[rank] = c * 8 + __builtin_ctz(mm);
@@ -309,7 +217,7 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
             for (int s = 0; s < S; ++s) m = pk_max_u16(m, s_row[tid * kFewWaves + s]);
             float sx, iv;
             int zz;
-            few_scale(m, shrink, a.qmax, sx, iv, zz);
+            call_scale(m, shrink, a.qmax, sx, iv, zz);
             s_sx[tid] = sx;
             s_inv[tid] = iv;
             s_z[tid] = zz;
@@ -321,7 +229,7 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
         }
         lds_barrier();
     } else {
-        few_scale(call_max, shrink, a.qmax, sx_call, inv, z);
+        call_scale(call_max, shrink, a.qmax, sx_call, inv, z);
     }
 
     // Eq. 7: the weights of the listed channels, 16 per output channel and step; on their way while
@@ -377,39 +285,9 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
     keep_weights(nb);
     // ---- the selection results, for the caller ----
     if (blockIdx.x == 0 && want_max) {
-        if (p == 0 && c < CA) {
-            int slots[8];
-            int rank = first;
-            float v[8];
-            widen8(mx, v);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const bool l = ((listed >> i) & 1u) != 0;
-                slots[i] = l ? rank : -1;
-                if (l) a.idx[rank] = c * 8 + i;
-                rank += l ? 1 : 0;
-            }
-            int4 *cs = (int4 *)(a.col_slot + c * 8);
-            cs[0] = make_int4(slots[0], slots[1], slots[2], slots[3]);
-            cs[1] = make_int4(slots[4], slots[5], slots[6], slots[7]);
-            a.col_mask[c] = (uint8_t)listed;
-            if (c < C) {
-                float4 *cm = (float4 *)(a.col_absmax + c * 8);
-                cm[0] = make_float4(v[0], v[1], v[2], v[3]);
-                cm[1] = make_float4(v[4], v[5], v[6], v[7]);
-            }
-            if (!TOKEN) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = c < C ? inv * (slots[i] >= 0 ? shrink : 1.0f) : 0.f;
-                float4 *sc = (float4 *)(a.col_scale + c * 8);
-                sc[0] = make_float4(v[0], v[1], v[2], v[3]);
-                sc[1] = make_float4(v[4], v[5], v[6], v[7]);
-            }
-        }
-        for (int j = used + tid; j < max(r_cap, 1); j += kFewThreads) a.idx[j] = -1;
+        store_selection(sel, mx, c, C, CA, p == 0, r_cap, !TOKEN, inv, shrink, a.col_absmax, a.col_scale, a.col_slot,
+                        a.col_mask, a.idx, a.n_outliers);
         if (tid == 0) {
-            a.n_outliers[0] = used;
-            a.n_outliers[1] = found;
             if (!TOKEN) {
                 a.x_scale[0] = sx_call;
                 a.x_scale[1] = inv;

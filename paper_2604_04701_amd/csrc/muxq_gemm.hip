@@ -70,18 +70,6 @@ typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BK = 64;   // K step (bytes of one LDS row)
 
-// Division by a launch constant: one high multiplication and a correction (a division by a run-time
-// value is a chain of some 20 instructions, and the tile map needs several for every tile).
-struct Divisor {
-    unsigned d, m;
-};
-__host__ inline Divisor divisor(int d) { return {(unsigned)d, 0xffffffffu / (unsigned)d}; }
-__device__ __forceinline__ int quotient(int x, const Divisor &v)
-{
-    const unsigned q = __umulhi((unsigned)x, v.m);       // the quotient, or one less
-    return (int)((unsigned)x - q * v.d >= v.d ? q + 1 : q);
-}
-
 struct TileMap {
     int tiles_m, tiles_n, sup_m, sup_n;
     int at_once;          // even split: tiles an XCD works on at a time; 0: blocks dealt in turn

@@ -180,6 +180,55 @@ struct GemmArgs {
                             // the constant 100 MHz counter at its start in [2 i] and at its end in [2 i + 1]
 };
 
+// Division by a launch constant: one high multiplication and a correction (a division by a run-time
+// value is a chain of some 20 instructions; the tile map of the GEMM needs several for every tile).
+struct Divisor {
+    unsigned d, m;
+};
+inline Divisor divisor(int d) { return {(unsigned)d, 0xffffffffu / (unsigned)d}; }
+__device__ __forceinline__ int quotient(int x, const Divisor &v)
+{
+    const unsigned q = __umulhi((unsigned)x, v.m);       // the quotient, or one less
+    return (int)((unsigned)x - q * v.d >= v.d ? q + 1 : q);
+}
+
+// The quantisers with the selection inside (muxq_act.hip).  slabs: rows of column maxima, fp16
+// (n_slabs of slab_ld entries; signs do not matter, so X itself will do); static_mask: one bit per
+// channel instead of the threshold test; otherwise as FewArgs below.  With a list given by the caller
+// (muxq_build_aux) col_absmax, idx and n_outliers are inputs.  cn null: no weight side.
+struct ActArgs {
+    const uint16_t *x;
+    int M, K, ldx, k_pad, N;
+    int exp, r_cap;
+    float qmax, threshold;
+    const uint16_t *slabs;
+    int n_slabs, slab_ld;
+    const uint8_t *static_mask;
+    float *col_absmax, *col_scale;
+    int32_t *col_slot;
+    uint8_t *col_mask;
+    int32_t *idx, *n_outliers;
+    float *x_scale;
+    int32_t *zero_point;
+    int8_t *body_q, *aux_q, *w_aux;
+    const int8_t *w_q;
+    const int32_t *w_row_sum;
+    int32_t *cn;
+    int32_t cn_bias;
+    Divisor by_chunks, by_pieces;        // these are set by the launch
+    int pieces, groups, deep;
+};
+// What every workgroup of the quantisers may as well read to select for itself, in bytes: the slabs a
+// producer of X left (against 6-8 us for the selection kernel; 256 KB, the 32 slabs of 4096 channels of
+// an MLP's second layer, already take longer: 37.7 us against 7.8 + 26.3 us), and X itself (against
+// 4-5 us for the abs-max pass).
+constexpr size_t kFoldSlabBytes = 128 * 1024, kFoldXBytes = 128 * 1024;
+bool act_select_fits(int k_pad, int r_cap);
+// The abs-max pass that leaves few slabs (see muxq_act.hip); partial and *n_slabs as launch_col_absmax_partial.
+hipError_t launch_col_absmax_narrow(const void *x_fp16, int rows, int cols, int ld, int k_pad, uint16_t *partial,
+                                    int *n_slabs, hipStream_t s);
+hipError_t launch_quantize_select(const ActArgs &a, bool per_token, bool given, hipStream_t s);
+
 // One layer in one launch, for few tokens (muxq_few.hip).  Pointers into the workspace as in
 // muxq_ws_layout; slabs (n_slabs x k_pad fp16 magnitudes) when a producer of X has left the column
 // maxima; static_mask (one bit per channel) instead of the threshold test; w_aux null when a

@@ -1,0 +1,177 @@
+// Device code shared by the kernels that select the outlier channels for themselves: every
+// workgroup folds the column maxima, selects (Sec. III-C) and derives the scale (Eq. 1 on Body), a
+// thread per chunk of 8 channels, instead of reading the results of a selection kernel.
+#pragma once
+#include "muxq_kernels.h"
+
+namespace muxq {
+namespace {
+
+// The largest magnitude among the channels of `raw` (8 fp16) that `listed` does not name, in the
+// low half, and among those it names, in the high half (fp16 magnitudes order like integers).
+__device__ __forceinline__ uint32_t chunk_maxima(uint4 raw, uint32_t listed)
+{
+    uint32_t d[4] = {raw.x & 0x7fff7fffu, raw.y & 0x7fff7fffu, raw.z & 0x7fff7fffu, raw.w & 0x7fff7fffu};
+    uint32_t l = 0;
+    if (__ballot(listed != 0) != 0) {                    // (most waves have no listed channel)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t two = listed >> (2 * i);
+            const uint32_t out = (two & 1u) * 0xffffu | (two >> 1 & 1u) * 0xffff0000u;
+            l = pk_max_u16(l, d[i] & out);
+            d[i] &= ~out;
+        }
+        l = max(l & 0xffffu, l >> 16);
+    }
+    const uint32_t m = pk_max_u16(pk_max_u16(d[0], d[1]), pk_max_u16(d[2], d[3]));
+    return max(m & 0xffffu, m >> 16) | (l << 16);
+}
+
+__device__ __forceinline__ float f32_of_half_bits(uint32_t h)
+{
+    return (float)__builtin_bit_cast(_Float16, (unsigned short)h);
+}
+
+// Scale, multiplier and zero point (Eq. 1; the zero point of the unlisted channels' codes is even,
+// see the selection kernel) from the two maxima of chunk_maxima over a row, or over the call.
+__device__ __forceinline__ void call_scale(uint32_t maxima, float shrink, float qmax, float &sx, float &inv, int &z)
+{
+    const float nm = fmaxf(0.f, f32_of_half_bits(maxima & 0xffffu)), lm = fmaxf(0.f, f32_of_half_bits(maxima >> 16));
+    const float am = fmaxf(nm, lm * shrink);             // exact: max |Body| (Eq. 4)
+    sx = am > 0.f ? am / qmax : 0.f;                     // correctly rounded binary32 divisions
+    inv = am > 0.f ? qmax / am : 0.f;
+    const int c = (int)fminf(__builtin_rintf(nm * inv), qmax);
+    z = min(c + (c & 1), (127 - c) & ~1);
+}
+
+// Maximum (two packed uint16) over the wave, in lane 63; sum of the lanes up to and including this
+// one.  (Cross-lane moves of the vector ALU: a permute through LDS is ten times their latency.)
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ uint32_t dpp_zero(uint32_t v)     // lanes without a source get 0
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_max_u16x2_to_lane63(uint32_t v)
+{
+    v = pk_max_u16(v, dpp_zero<0x111>(v));                   // row_shr 1, 2, 4, 8: lane 15 of a row of 16
+    v = pk_max_u16(v, dpp_zero<0x112>(v));
+    v = pk_max_u16(v, dpp_zero<0x114>(v));
+    v = pk_max_u16(v, dpp_zero<0x118>(v));
+    v = pk_max_u16(v, dpp_zero<0x142, 0xa>(v));              // lane 15 of a row to the next one
+    return pk_max_u16(v, dpp_zero<0x143, 0xc>(v));           // lane 31 to the upper half
+}
+__device__ __forceinline__ int wave_inclusive_sum(int x)
+{
+    uint32_t v = (uint32_t)x;
+    v += dpp_zero<0x111>(v);
+    v += dpp_zero<0x112>(v);
+    v += dpp_zero<0x114>(v);
+    v += dpp_zero<0x118>(v);
+    v += dpp_zero<0x142, 0xa>(v);
+    return (int)(v + dpp_zero<0x143, 0xc>(v));
+}
+
+// What select_channels returns for this thread's chunk and for the call.
+struct Selected {
+    uint32_t listed;     // bit i: channel i of the chunk is listed
+    int first;           // rank of the chunk's first candidate
+    int used, found;     // listed channels, candidates
+    uint32_t maxima;     // chunk_maxima over all channels (want_max)
+};
+
+// Sec. III-C with the capacity rule: the r_cap lowest candidates are listed.  All NW waves of the
+// workgroup call it; a thread brings the column maxima `mx` of its chunk and its candidates, one
+// bit per channel.  Chunks are numbered 64 seg + lane; waves with `counted` false hold copies of chunks
+// that others bring.  Two barriers at least; the caller's LDS writes before are visible after.
+template <int NW>
+__device__ __forceinline__ Selected select_channels(uint4 mx, uint32_t cand, bool counted, int seg, int r_cap,
+                                                    bool want_max, int *s_tot, uint32_t *s_max)
+{
+    static_assert(NW % 4 == 0, "read four at a time");
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    Selected r;
+    const int cnt = __builtin_popcount(cand);
+    const int incl = wave_inclusive_sum(cnt);
+    uint32_t top = want_max ? wave_max_u16x2_to_lane63(chunk_maxima(mx, cand)) : 0u;
+    if (lane == 63) {
+        s_tot[wave] = counted ? incl : 0;
+        s_max[wave] = counted ? top : 0u;
+    }
+    lds_barrier();
+    r.listed = cand;
+    r.first = incl - cnt;
+    r.found = 0;
+    r.maxima = 0;
+#pragma unroll
+    for (int i = 0; i < NW; i += 4) {
+        const int4 t = *(const int4 *)(s_tot + i);
+        const uint4 m = *(const uint4 *)(s_max + i);
+        r.first += (i < seg ? t.x : 0) + (i + 1 < seg ? t.y : 0) + (i + 2 < seg ? t.z : 0) + (i + 3 < seg ? t.w : 0);
+        r.found += t.x + t.y + t.z + t.w;
+        r.maxima = pk_max_u16(r.maxima, pk_max_u16(pk_max_u16(m.x, m.y), pk_max_u16(m.z, m.w)));
+    }
+    r.used = min(r.found, r_cap);
+    if (r.found > r_cap) {
+        uint32_t kept = 0;
+        int rank = r.first;
+        for (uint32_t mm = cand; mm != 0; mm &= mm - 1, ++rank)
+            if (rank < r_cap) kept |= mm & (0u - mm);
+        r.listed = kept;
+        if (want_max) {
+            top = wave_max_u16x2_to_lane63(chunk_maxima(mx, kept));
+            lds_barrier();                               // s_max is consumed
+            if (lane == 63) s_max[wave] = counted ? top : 0u;
+            lds_barrier();
+            r.maxima = 0;
+            for (int i = 0; i < NW; ++i) r.maxima = pk_max_u16(r.maxima, s_max[i]);
+        }
+    }
+    return r;
+}
+
+// The selection results of the call as the workspace keeps them, by the threads of one workgroup
+// (one chunk each): col_absmax, col_slot, col_mask and, with one scale per call, col_scale; the list,
+// its padding and counts.
+__device__ __forceinline__ void store_selection(const Selected &r, uint4 mx, int c, int C, int CA, bool mine, int r_cap,
+                                                bool with_scale, float inv, float shrink, float *col_absmax,
+                                                float *col_scale, int32_t *col_slot, uint8_t *col_mask, int32_t *idx,
+                                                int32_t *n_outliers)
+{
+    if (mine && c < CA) {
+        int slots[8];
+        int rank = r.first;
+        float v[8];
+        widen8(mx, v);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const bool l = ((r.listed >> i) & 1u) != 0;
+            slots[i] = l ? rank : -1;
+            if (l) idx[rank] = c * 8 + i;
+            rank += l ? 1 : 0;
+        }
+        int4 *cs = (int4 *)(col_slot + c * 8);
+        cs[0] = make_int4(slots[0], slots[1], slots[2], slots[3]);
+        cs[1] = make_int4(slots[4], slots[5], slots[6], slots[7]);
+        col_mask[c] = (uint8_t)r.listed;
+        if (c < C) {
+            float4 *cm = (float4 *)(col_absmax + c * 8);
+            cm[0] = make_float4(v[0], v[1], v[2], v[3]);
+            cm[1] = make_float4(v[4], v[5], v[6], v[7]);
+        }
+        if (with_scale) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = c < C ? inv * (slots[i] >= 0 ? shrink : 1.0f) : 0.f;
+            float4 *sc = (float4 *)(col_scale + c * 8);
+            sc[0] = make_float4(v[0], v[1], v[2], v[3]);
+            sc[1] = make_float4(v[4], v[5], v[6], v[7]);
+        }
+    }
+    for (int j = r.used + (int)threadIdx.x; j < max(r_cap, 1); j += (int)blockDim.x) idx[j] = -1;
+    if (threadIdx.x == 0) {
+        n_outliers[0] = r.used;
+        n_outliers[1] = r.found;
+    }
+}
+
+}  // namespace
+}  // namespace muxq

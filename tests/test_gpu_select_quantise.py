@@ -1,0 +1,83 @@
+"""The quantisers that select the outlier channels for themselves (csrc/muxq_act.hip): pieces of a row
+for 1 to 16 waves, rows fewer and more than the workgroups take at once, the abs-max pass with
+narrow column blocks or X itself in its place, slabs of a producer below and above the limit,
+lists fixed offline and lists the caller gives to the stage entry point.  All exact."""
+import numpy as np
+import pytest
+import torch
+
+import test_gpu_parity as T
+from gpu_common import B, check_case, check_plain_y, orc, synth
+from paper_2604_04701_amd.synth import Case
+
+pytestmark = pytest.mark.gpu
+U = (20.0, 100.0)
+
+SHAPES = [(65, 1032, 72), (66, 8192, 24), (300, 64, 72), (513, 520, 136), (700, 2056, 72), (1000, 1024, 264),
+          (2100, 200, 72), (5000, 1032, 40), (257, 4104, 8200), (70, 8200, 24)]     # the last one: the separate kernels
+
+
+@pytest.mark.parametrize("x_gran", ["tensor", "token"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_select_and_quantise_all_stages(shape, x_gran):
+    M, K, N = shape
+    check_case(Case("act", M, K, N, min(9, K // 8), U, 900 + M), x_gran=x_gran, w_gran="channel")
+
+
+@pytest.mark.parametrize("x_gran", ["tensor", "token"])
+@pytest.mark.parametrize("r_cap,r", [(0, 5), (64, 0), (64, 64), (64, 90), (128, 100), (256, 200)])
+def test_select_and_quantise_capacity(r_cap, r, x_gran):
+    check_case(Case("act_cap", 333, 712, 136, r, U, 940 + r), r_cap=r_cap, e=3, x_gran=x_gran)
+
+
+@pytest.mark.parametrize("x_gran", ["tensor", "token"])
+def test_select_and_quantise_static_lists(x_gran):
+    for M, K, N in ((70, 2056, 72), (900, 264, 264)):
+        case = Case("act_static", M, K, N, 5, U, 960 + M)
+        _, _, planted = synth.make_case(case)
+        for lst in ([int(k) for k in planted], [], list(range(0, 200, 2))):
+            T._check_static(case, lst, x_gran, "channel", with_bias=True)
+
+
+def test_given_lists_need_not_ascend_and_any_binary32_maxima():
+    """muxq_build_aux: the list in any order, maxima that are no fp16 values."""
+    rng = np.random.default_rng(3)
+    for M, K in ((5, 72), (300, 1032), (1030, 4096), (130, 8192), (40, 8200)):
+        X, ch = synth.make_x(M, K, 6, U, rng)
+        lst = np.array([ch[3], ch[0], 1, ch[5]], dtype=np.int32)
+        _, first = np.unique(lst, return_index=True)
+        lst = lst[np.sort(first)]
+        Xd = torch.from_numpy(X).cuda()
+        cm, _, _ = B.muxq_detect_outliers(Xd)
+        cm = cm * 1.0009765
+        idx = torch.full((64,), -1, dtype=torch.int32, device="cuda")
+        idx[:len(lst)] = torch.from_numpy(lst).cuda()
+        n = torch.tensor([len(lst), len(lst)], dtype=torch.int32, device="cuda")
+        body, aux, xs = B.muxq_build_aux(Xd, cm, idx, n, 64, 2)
+        mult = np.ones(K, np.float32)
+        mult[lst] = 0.25
+        amax = (cm.cpu().numpy()[:K] * mult).max()
+        inv = np.float32(127.0) / amax
+        assert xs.cpu().numpy().tolist() == [amax / np.float32(127.0), inv]
+        want = np.clip(np.rint((X.astype(np.float32) * mult) * inv), -127, 127).astype(np.int8)
+        got = B.unpack(body, M, B.k_pad(K)).cpu().numpy()
+        assert (got[:, :K] == want).all() and (got[:, K:] == 0).all()
+        ga = B.unpack(aux, M, 64).cpu().numpy()
+        assert (ga[:, :len(lst)] == want[:, lst]).all() and (ga[:, len(lst):] == 0).all()
+
+
+@pytest.mark.parametrize("M,K,N", [(333, 200, 264), (2049, 1032, 72), (700, 4096, 72)])
+def test_slabs_of_a_producer(M, K, N):
+    """The maxima left by the GELU kernel, few enough to be folded by every workgroup or not."""
+    rng = np.random.default_rng(M)
+    Y = torch.from_numpy((3.0 * rng.standard_normal((M, K))).astype(np.float16)).cuda()
+    W = synth.make_w(K, N, rng)
+    w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(W).cuda())
+    ws, lay = B.alloc_workspace(M, K, N, 64), B.workspace_layout(M, K, N, 64)
+    ws.fill_(0xCD)
+    X = B.muxq_gelu_absmax(Y, ws, lay)
+    for x_gran in ("tensor", "token"):
+        Yg = B.muxq_linear(X, w_q, w_s, N, workspace=ws, absmax_ready=True, x_gran=x_gran)
+        o = orc.linear(X.cpu().numpy(), W, x_gran=x_gran)
+        assert (Yg.cpu().numpy() == o["y16"]).all()
+        B.muxq_gelu_absmax(Y, ws, lay)
