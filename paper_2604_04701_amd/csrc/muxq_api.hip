@@ -515,13 +515,22 @@ int muxq_quantize_weight_smooth(const void *W, int K, int N, int ldw, int gran, 
     hipStream_t s = (hipStream_t)stream;
     const int per_channel = gran == MUXQ_PER_CHANNEL;
     const int n_scales = per_channel ? N : 1;
+    int32_t *const row_sums = (int32_t *)(w_q + muxq::wq_rowsum_offset(N, kpad(K)));
+    const bool strips = muxq::wquant_in_strips(K, N, per_channel != 0);
+    if (strips && per_channel) {
+        MUXQ_TRY(muxq::launch_wquant_strip(W, K, N, ldw, kpad(K), nullptr, qmax, w_q, row_sums, w_scale, s, factors));
+        return MUXQ_OK;
+    }
     // w_scale first holds the abs-max values (as binary32), then the scales.
     MUXQ_TRY(muxq::launch_fill_u32((uint32_t *)w_scale, n_scales, 0u, s));
     MUXQ_TRY(muxq::launch_col_absmax(W, K, N, ldw, !per_channel, (uint32_t *)w_scale, s, factors));
-    int32_t *row_sum = (int32_t *)(w_q + muxq::wq_rowsum_offset(N, kpad(K)));
-    MUXQ_TRY(muxq::launch_fill_u32((uint32_t *)row_sum, N, 0u, s));
-    MUXQ_TRY(muxq::launch_wquant_transpose(W, K, N, ldw, kpad(K), w_scale, per_channel, qmax, w_q,
-                                           row_sum, s, factors));
+    if (strips) {
+        MUXQ_TRY(muxq::launch_wquant_strip(W, K, N, ldw, kpad(K), w_scale, qmax, w_q, row_sums, nullptr, s, factors));
+    } else {
+        MUXQ_TRY(muxq::launch_fill_u32((uint32_t *)row_sums, N, 0u, s));
+        MUXQ_TRY(muxq::launch_wquant_transpose(W, K, N, ldw, kpad(K), w_scale, per_channel, qmax, w_q,
+                                               row_sums, s, factors));
+    }
     MUXQ_TRY(muxq::launch_wscale_finalize(w_scale, n_scales, qmax, s));
     return MUXQ_OK;
 }

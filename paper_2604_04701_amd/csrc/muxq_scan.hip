@@ -1202,6 +1202,135 @@ __global__ __launch_bounds__(256) void k_wquant_transpose(const uint16_t *__rest
     if (chunk == 0 && n0 + nl < N && part != 0) atomicAdd(row_sum + n0 + nl, part);
 }
 
+// The same for whole strips of 64 output channels: a workgroup owns its channels over all of K, so it
+// takes their abs-max itself (per-channel scales: the whole weight quantiser is this one launch), sums
+// their codes in registers and writes their scales; nothing is accumulated with atomics or cleared
+// before.  K goes by in steps of 512: a thread reads 4 rows x 8 channels, packs the four codes of a
+// channel into one word for the transposing LDS tile and takes 16 codes of one channel out of it per
+// store, a wave one 1 KiB block of the packed layout.  The 16-byte pieces of the tile are
+// XOR-swizzled with the channel, which keeps both sides free of bank conflicts.
+// Bound by memory: W twice (the second time mostly from the memory-side cache), the codes once:
+// 4096 x 16384 53 us, from HBM 65 us, against 93 us for abs-max with atomics, transposition in 64 x 64
+// tiles and three small launches.
+// amax (device, one value): the whole matrix's abs-max with one scale per tensor, else null.
+constexpr int kStripCh = 64, kStripK = 512, kStripThreads = 1024;
+__global__ __launch_bounds__(kStripThreads) void k_wquant_strip(const uint16_t *__restrict__ w, int K, int N, int ldw,
+                                                               int k_pad, const float *__restrict__ amax, float qmax,
+                                                               int8_t *__restrict__ w_q, int32_t *__restrict__ row_sum,
+                                                               float *__restrict__ w_scale,
+                                                               const float *__restrict__ row_factor)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t tile[kStripCh * kStripK / 4];
+    __shared__ float s_amax[kStripCh];
+    __shared__ int s_sum[kStripCh];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n0 = blockIdx.x * kStripCh, nc = tid & 7, kr = tid >> 3;     // 8 channels, one of 128 row groups
+    const bool in_n = n0 + nc * 8 < N;                                     // (N is a multiple of 8)
+    const uint16_t *const src = w + n0 + nc * 8;
+    auto row = [&](int k) -> uint4 {
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (in_n && k < K) {
+            v = *(const uint4 *)(src + (size_t)k * ldw);
+            if (row_factor != nullptr) v = scale8_fp16(v, row_factor[k]);  // W' = fp16(W f[k])
+        }
+        return v;
+    };
+    if (tid < kStripCh) s_sum[tid] = 0;
+    float inv[8];
+    if (amax == nullptr) {
+        uint4 mx = make_uint4(0, 0, 0, 0);
+        int k = kr;
+        for (; k + 7 * 128 < K; k += 8 * 128) {
+            uint4 v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = row(k + i * 128);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) mx = absmax_step(mx, v[i]);
+        }
+        {
+            uint4 v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = row(k + i * 128);           // (zeros past K)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) mx = absmax_step(mx, v[i]);
+        }
+        uint4 *const red = (uint4 *)tile;
+        red[tid] = mx;
+        lds_barrier();
+        if (wave == 0) {
+            for (int j = 1; j < kStripThreads / 64; ++j) mx = absmax_step(mx, red[j * 64 + lane]);
+#pragma unroll
+            for (int off = 8; off < 64; off <<= 1)
+                mx = absmax_step(mx, make_uint4(__shfl_xor((int)mx.x, off), __shfl_xor((int)mx.y, off),
+                                                __shfl_xor((int)mx.z, off), __shfl_xor((int)mx.w, off)));
+            if (lane < 8) {
+                float v[8];
+                widen8(mx, v);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    s_amax[lane * 8 + i] = v[i];
+                    // (the output only after its own abs-max: scales are not read here)
+                    if (in_n) w_scale[n0 + lane * 8 + i] = v[i] > 0.f ? v[i] / qmax : 0.f;
+                }
+            }
+        }
+        lds_barrier();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float a = s_amax[nc * 8 + i];
+            inv[i] = a > 0.f ? qmax / a : 0.f;
+        }
+    } else {
+        const float a = amax[0];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) inv[i] = a > 0.f ? qmax / a : 0.f;
+        lds_barrier();                                   // (s_sum is cleared)
+    }
+
+    const int nl = (wave & 3) * 16 + (lane >> 2);        // the channel this thread stores
+    int sum = 0;
+    uint4 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = row(kr * 4 + i);
+    for (int k0 = 0; k0 < k_pad; k0 += kStripK) {
+        uint32_t q[4][8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const f16x8 h = __builtin_bit_cast(f16x8, v[i]);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) q[i][j] = quant_word((float)h[j], inv[j], qmax);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = row(k0 + kStripK + kr * 4 + i);         // the next step's, on their way
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int n = nc * 8 + j, piece = (kr >> 2) ^ (nc * 2) ^ (j * 4);
+            tile[n * (kStripK / 4) + piece * 4 + (kr & 3)] = pack_low_bytes(q[0][j], q[1][j], q[2][j], q[3][j]);
+        }
+        lds_barrier();
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int kb = (wave + 16 * i) >> 2;         // block of 64 input channels within the step
+            if (k0 + kb * 64 < k_pad) {
+                const int piece = (kb * 4 + (lane & 3)) ^ ((nl >> 3) * 2) ^ ((nl & 7) * 4);
+                const uint4 c = *(const uint4 *)(tile + nl * (kStripK / 4) + piece * 4);
+                if (n0 + nl < N) *(uint4 *)(w_q + packed_index(n0 + nl, k0 + kb * 64 + (lane & 3) * 16, k_pad)) = c;
+                sum = __builtin_amdgcn_sdot4((int)c.x, 0x01010101, sum, false);
+                sum = __builtin_amdgcn_sdot4((int)c.y, 0x01010101, sum, false);
+                sum = __builtin_amdgcn_sdot4((int)c.z, 0x01010101, sum, false);
+                sum = __builtin_amdgcn_sdot4((int)c.w, 0x01010101, sum, false);
+            }
+        }
+        lds_barrier();
+    }
+    // the constant of the activation zero-point correction: each channel's sum of codes
+    sum += __shfl_xor(sum, 1);
+    sum += __shfl_xor(sum, 2);
+    if ((lane & 3) == 0) atomicAdd(&s_sum[nl], sum);
+    lds_barrier();
+    if (tid < kStripCh && n0 + tid < N) row_sum[n0 + tid] = s_sum[tid];
+}
+
 __global__ void k_wscale_finalize(float *w_scale, int n, float qmax)
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1391,6 +1520,23 @@ hipError_t launch_wquant_transpose(const void *w_fp16, int K, int N, int ldw, in
     dim3 grid(k_pad / 64, (N + 63) / 64);
     return launch_kernel(k_wquant_transpose, grid, dim3(256), 0, s, (const uint16_t *)w_fp16, K, N,
                        ldw, k_pad, amax, per_channel, qmax, w_q, row_sum, row_factor);
+}
+
+// Whether the weight quantiser works in strips of 64 output channels.  A strip streams K x 128 bytes
+// through one CU (~100 GB/s), with a scale per channel twice; that wins where it saves four launches
+// (per channel: up to K = 8192 at any N, 768 x 768 21.8 / 10.6 us, 5120 x 1280 41 / 27 us, 8192 x 64
+// 50 / 39 us; one scale per tensor saves one launch only: 1280 x 5120 20.9 / 18.6 us, but 5120 x 1280
+// 21.0 / 33.7 us) or where there are strips for most CUs (4096 x 16384 82 / 52 us and 77 / 72 us).
+bool wquant_in_strips(int K, int N, bool per_channel)
+{
+    return K <= (per_channel ? 8192 : 2048) || N >= 192 * kStripCh;
+}
+
+hipError_t launch_wquant_strip(const void *w_fp16, int K, int N, int ldw, int k_pad, const float *amax, float qmax,
+                               int8_t *w_q, int32_t *row_sum, float *w_scale, hipStream_t s, const float *row_factor)
+{
+    return launch_kernel(k_wquant_strip, dim3((N + kStripCh - 1) / kStripCh), dim3(kStripThreads), 0, s,
+                         (const uint16_t *)w_fp16, K, N, ldw, k_pad, amax, qmax, w_q, row_sum, w_scale, row_factor);
 }
 
 hipError_t launch_wscale_finalize(float *w_scale, int n, float qmax, hipStream_t s)
