@@ -143,11 +143,17 @@ def _check(status: int, what: str):
 
 
 def _p(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+# The raw handle of the current stream of the current device.  (current_stream() builds a Stream object
+# on the way, 2.9 us of the 9 us a call of one token takes on the host.)
+if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+    def _stream():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+else:
+    def _stream():
+        return torch.cuda.current_stream().cuda_stream
 
 
 def k_pad(K: int) -> int:
