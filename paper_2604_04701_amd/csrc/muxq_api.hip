@@ -143,10 +143,10 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
     uint16_t *partial = (uint16_t *)(ws + L.absmax_partial);
     const int k_pad = L.k_pad;
 
-    // four launches: slab maxima -> fold + select (+ scales) -> quantise (+ Aux weight
-    // gather in the same launch) -> GEMM.  With a static block the channel list and the Aux
-    // weight rows are given: no gather, and in the per-token setting no pass for the
-    // channel maxima either (two launches).
+    // The stages are: slab maxima -> fold + select (+ scales) -> quantise (+ Aux weight gather) -> GEMM.
+    // One launch does all of them for few tokens; the quantisers select for themselves while K <= 8192
+    // (two or three launches); four launches otherwise.  With a static block the channel list and the
+    // Aux weight rows are given: no gather, and in the per-token setting no pass for the channel maxima.
     int n_slabs = 0;
     const bool per_token = x_gran == MUXQ_X_PER_TOKEN;
     const uint8_t *static_mask = nullptr;
@@ -170,7 +170,10 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
     const int ready_slabs = absmax_slabs > 0 ? absmax_slabs : muxq::absmax_slab_count(M, k_pad);
     // few tokens: the whole layer in one launch (the measurement aid that brackets the GEMM keeps
     // the separate launches, as does Aux on a scale of its own; X is addressed with 32-bit offsets)
-    if (gemm_start == nullptr && !aux_own && (size_t)M * (size_t)ldx < (1u << 30) &&
+    // (a Y that shares memory with X is written while other workgroups still read X: separate launches)
+    const char *const xb = (const char *)X, *const yb = (const char *)Y;
+    const bool apart = yb >= xb + ((size_t)(M - 1) * ldx + K) * 2 || xb >= yb + ((size_t)(M - 1) * ldy + N) * 2;
+    if (gemm_start == nullptr && !aux_own && apart && (size_t)M * (size_t)ldx < (1u << 30) &&
         muxq::few_tokens_fit(M, K, k_pad, r_cap)) {
         muxq::FewArgs f{};
         f.x = (const uint16_t *)X;

@@ -71,6 +71,19 @@ __device__ __forceinline__ int wave_inclusive_sum(int x)
     return (int)(v + dpp_zero<0x143, 0xc>(v));
 }
 
+// Channel maxima without those that are NaN (magnitudes above infinity's): a NaN in X must not hide the
+// other channels from the scale of the call.
+__device__ __forceinline__ uint4 drop_nan(uint4 mx)
+{
+    uint32_t d[4] = {mx.x, mx.y, mx.z, mx.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if ((d[i] & 0xffffu) > 0x7c00u) d[i] &= 0xffff0000u;
+        if ((d[i] >> 16) > 0x7c00u) d[i] &= 0xffffu;
+    }
+    return make_uint4(d[0], d[1], d[2], d[3]);
+}
+
 // What select_channels returns for this thread's chunk and for the call.
 struct Selected {
     uint32_t listed;     // bit i: channel i of the chunk is listed
@@ -92,7 +105,7 @@ __device__ __forceinline__ Selected select_channels(uint4 mx, uint32_t cand, boo
     Selected r;
     const int cnt = __builtin_popcount(cand);
     const int incl = wave_inclusive_sum(cnt);
-    uint32_t top = want_max ? wave_max_u16x2_to_lane63(chunk_maxima(mx, cand)) : 0u;
+    uint32_t top = want_max ? wave_max_u16x2_to_lane63(chunk_maxima(drop_nan(mx), cand)) : 0u;
     if (lane == 63) {
         s_tot[wave] = counted ? incl : 0;
         s_max[wave] = counted ? top : 0u;
@@ -118,7 +131,7 @@ __device__ __forceinline__ Selected select_channels(uint4 mx, uint32_t cand, boo
             if (rank < r_cap) kept |= mm & (0u - mm);
         r.listed = kept;
         if (want_max) {
-            top = wave_max_u16x2_to_lane63(chunk_maxima(mx, kept));
+            top = wave_max_u16x2_to_lane63(chunk_maxima(drop_nan(mx), kept));
             lds_barrier();                               // s_max is consumed
             if (lane == 63) s_max[wave] = counted ? top : 0u;
             lds_barrier();

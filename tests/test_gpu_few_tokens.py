@@ -70,3 +70,32 @@ def test_few_tokens_strided_rows_and_the_static_array():
         o = orc.linear(X, W)
         assert (out[:, :N].cpu().numpy() == o["y16"]).all() and (out[:, N:] == 7.0).all()
         assert (y.cpu().numpy() == o["y16"]).all()
+
+
+def test_y_in_the_place_of_x():
+    """Y may take X's memory (K = N): no workgroup may store before all have read."""
+    rng = np.random.default_rng(9)
+    M, K = 16, 1280
+    X, _ = synth.make_x(M, K, 4, U, rng)
+    W = synth.make_w(K, K, rng)
+    w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(W).cuda())
+    o = orc.linear(X, W)
+    for _ in range(5):
+        Xd = torch.from_numpy(X).cuda()
+        assert (B.muxq_linear(Xd, w_q, w_s, K, out=Xd).cpu().numpy() == o["y16"]).all()
+
+
+@pytest.mark.parametrize("M,K,N", [(8, 1280, 264), (300, 1032, 136), (70, 4096, 72)])
+def test_a_nan_does_not_hide_the_other_channels(M, K, N):
+    """One scale per call: a NaN in one row of a quiet channel leaves the other rows as they are
+    with a zero in its place (its channel's maximum is not a number and sets no scale)."""
+    X, ch = synth.make_x(M, K, 4, U, np.random.default_rng(M))
+    c = next(k for k in range(5, K) if k not in set(ch.tolist()))
+    X[0, c] = 0
+    W = synth.make_w(K, N, np.random.default_rng(K))
+    o = orc.linear(X, W)
+    Xn = X.copy()
+    Xn[0, c] = np.nan
+    w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(W).cuda())
+    y = B.muxq_linear(torch.from_numpy(Xn).cuda(), w_q, w_s, N).cpu().numpy()
+    assert (y[1:] == o["y16"][1:]).all()
