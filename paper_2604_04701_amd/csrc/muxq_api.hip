@@ -219,8 +219,7 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
         return MUXQ_OK;
     }
     // the selection inside the quantiser, where every workgroup can fold the column maxima for itself
-    if (!aux_own && muxq::act_select_fits(k_pad, r_cap) &&
-        !(absmax_ready && (size_t)ready_slabs * k_pad * 2 > muxq::kFoldSlabBytes)) {
+    if (!aux_own && muxq::act_select_fits(k_pad, r_cap)) {
         muxq::ActArgs q{};
         q.x = (const uint16_t *)X;
         q.M = M; q.K = K; q.ldx = ldx; q.k_pad = k_pad; q.N = N;
@@ -233,6 +232,10 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
         q.slab_ld = k_pad;
         if (absmax_ready) {
             q.n_slabs = ready_slabs;
+            if ((size_t)ready_slabs * k_pad * 2 > muxq::kFoldSlabBytes && !(per_token && static_block != nullptr)) {
+                MUXQ_TRY(muxq::launch_fold_slabs(partial, ready_slabs, k_pad, s));
+                q.n_slabs = 1;
+            }
         } else if ((size_t)M * K * 2 <= muxq::kFoldXBytes) {      // X is small: its rows are the slabs
             q.slabs = (const uint16_t *)X;
             q.slab_ld = ldx;

@@ -219,11 +219,12 @@ struct ActArgs {
     int pieces, groups, deep;
 };
 // What every workgroup of the quantisers may as well read to select for itself, in bytes: the slabs a
-// producer of X left (against 6-8 us for the selection kernel; 256 KB, the 32 slabs of 4096 channels of
-// an MLP's second layer, already take longer: 37.7 us against 7.8 + 26.3 us), and X itself (against
-// 4-5 us for the abs-max pass).
+// producer of X left (more are folded into one by a launch of their own first: the quantiser of an MLP's
+// second layer, 32 slabs of 4096 channels = 256 KB, takes 37.7 us on all of them), and X itself
+// (against 4-5 us for the abs-max pass).
 constexpr size_t kFoldSlabBytes = 128 * 1024, kFoldXBytes = 128 * 1024;
 bool act_select_fits(int k_pad, int r_cap);
+hipError_t launch_fold_slabs(uint16_t *partial, int n_slabs, int k_pad, hipStream_t s);      // into slab 0
 // The abs-max pass that leaves few slabs (see muxq_act.hip); partial and *n_slabs as launch_col_absmax_partial.
 hipError_t launch_col_absmax_narrow(const void *x_fp16, int rows, int cols, int ld, int k_pad, uint16_t *partial,
                                     int *n_slabs, hipStream_t s);
