@@ -383,7 +383,8 @@ __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
     if (blockIdx.x == 0 && want_max)
         store_selection(sel, mx, tid, C, CA, true, a.r_cap, false, 0.f, shrink, a.col_absmax, a.col_scale, a.col_slot,
                         a.col_mask, a.idx, a.n_outliers);
-    const ActGather g = gather_request(a, sh, blockIdx.x * 64 + (tid >> 4), sel.used);
+    const int used = __builtin_amdgcn_readfirstlane(sel.used);       // (the same in every lane)
+    const ActGather g = gather_request(a, sh, blockIdx.x * 64 + (tid >> 4), used);
     uint32_t mk = 0;                                 // this lane's chunk masks, one to a byte
     static_assert(NC <= 4, "four masks to a word");
 #pragma unroll
@@ -394,10 +395,7 @@ __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
     for (int step = 0, r0 = (int)blockIdx.x * P; r0 < a.M; ++step, r0 += stride, row += stride) {
         uint4 nx[NC];
         load(row + stride, nx);
-        uint32_t m = 0;
-#pragma unroll
-        for (int i = 0; i < NC; ++i) m = pk_max_u16(m, chunk_maxima(raw[i], (mk >> (8 * i)) & 0xffu));
-        m = wave_max_u16x2_to_lane63(m);
+        uint32_t m = wave_row_maxima(raw, mk);
         if (S > 1) {
             if (lane == 63) s_piece[step & 1][wave] = m;
             lds_barrier();
@@ -425,12 +423,12 @@ __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
                     *(uint2 *)(a.body_q + packed_index(row, c * 8, a.k_pad)) = make_uint2(0, 0);
             }
             if (seg == S - 1)
-                for (int j = sel.used + lane; j < a.r_cap; j += 64) a.aux_q[packed_index(row, j, a.r_cap)] = 0;
+                for (int j = used + lane; j < a.r_cap; j += 64) a.aux_q[packed_index(row, j, a.r_cap)] = 0;
         }
 #pragma unroll
         for (int i = 0; i < NC; ++i) raw[i] = nx[i];
     }
-    gather_rest(a, sh, sel.used, g);
+    gather_rest(a, sh, used, g);
 }
 
 }  // namespace

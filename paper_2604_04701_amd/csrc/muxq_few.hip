@@ -204,11 +204,10 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
     int z = 0;
     if (TOKEN) {
         // ---- max|Body| of every row: a wave's piece first ----
-#pragma unroll 2
         for (int row = row0; row < M; row += P) {
-            uint4 raw = make_uint4(0, 0, 0, 0);
-            if (in_c) raw = *(const uint4 *)(xc + row * K * 2);
-            const uint32_t m = wave_max_u16x2_to_lane63(chunk_maxima(raw, listed));
+            uint4 raw[1] = {make_uint4(0, 0, 0, 0)};
+            if (in_c) raw[0] = *(const uint4 *)(xc + row * K * 2);
+            const uint32_t m = wave_row_maxima(raw, listed);
             if (lane == 63) s_row[row * kFewWaves + seg] = m;
         }
         lds_barrier();

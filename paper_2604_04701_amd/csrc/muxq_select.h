@@ -71,17 +71,39 @@ __device__ __forceinline__ int wave_inclusive_sum(int x)
     return (int)(v + dpp_zero<0x143, 0xc>(v));
 }
 
-// Channel maxima without those that are NaN (magnitudes above infinity's): a NaN in X must not hide the
-// other channels from the scale of the call.
+// Eight fp16 values, or their magnitudes, with those that are NaN (magnitudes above infinity's) zeroed: a
+// NaN in X must not hide the other channels from the scale of the call, or of its row.
 __device__ __forceinline__ uint4 drop_nan(uint4 mx)
 {
     uint32_t d[4] = {mx.x, mx.y, mx.z, mx.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        if ((d[i] & 0xffffu) > 0x7c00u) d[i] &= 0xffff0000u;
-        if ((d[i] >> 16) > 0x7c00u) d[i] &= 0xffffu;
+        if ((d[i] & 0x7fffu) > 0x7c00u) d[i] &= 0xffff0000u;
+        if ((d[i] >> 16 & 0x7fffu) > 0x7c00u) d[i] &= 0xffffu;
     }
     return make_uint4(d[0], d[1], d[2], d[3]);
+}
+
+// chunk_maxima over the NC chunks that each lane of a wave holds of a row, in lane 63, without NaNs.
+// (`mk`: the chunks' masks of listed channels, one to a byte; every lane of the wave calls.)  A NaN wins
+// the integer comparison, so it shows in the result, and only then -- one scalar test per row in the
+// streaming kernels -- the maxima are taken again without it, chunk by chunk to need few registers.
+template <int NC>
+__device__ __forceinline__ uint32_t wave_row_maxima(const uint4 (&raw)[NC], uint32_t mk)
+{
+    uint32_t m = 0;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) m = pk_max_u16(m, chunk_maxima(raw[i], (mk >> (8 * i)) & 0xffu));
+    m = wave_max_u16x2_to_lane63(m);
+    const uint32_t top = (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+    if ((top & 0xffffu) <= 0x7c00u && (top >> 16) <= 0x7c00u) return m;
+    m = 0;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        m = pk_max_u16(m, chunk_maxima(drop_nan(raw[i]), (mk >> (8 * i)) & 0xffu));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return wave_max_u16x2_to_lane63(m);
 }
 
 // What select_channels returns for this thread's chunk and for the call.

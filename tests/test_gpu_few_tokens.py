@@ -9,7 +9,7 @@ import pytest
 import torch
 
 import test_gpu_parity as T
-from gpu_common import B, check_case, check_mlp, check_plain_y, orc, synth
+from gpu_common import B, check_case, check_mlp, check_plain_y, orc, run_gpu, synth
 from paper_2604_04701_amd.synth import Case
 
 pytestmark = pytest.mark.gpu
@@ -99,3 +99,27 @@ def test_a_nan_does_not_hide_the_other_channels(M, K, N):
     w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(W).cuda())
     y = B.muxq_linear(torch.from_numpy(Xn).cuda(), w_q, w_s, N).cpu().numpy()
     assert (y[1:] == o["y16"][1:]).all()
+
+
+@pytest.mark.parametrize("M,K,N", [(8, 1280, 264), (40, 520, 72), (300, 1032, 136), (70, 4096, 72), (300, 200, 72)])
+@pytest.mark.parametrize("r", [0, 4])
+def test_a_nan_does_not_hide_the_other_channels_of_its_row(M, K, N, r):
+    """One scale per token: a NaN in a quiet channel sets no scale itself, and its row keeps the scale
+    and the codes of the other channels, with listed channels in the row and without."""
+    X, ch = synth.make_x(M, K, r, U, np.random.default_rng(M + r))
+    W = synth.make_w(K, N, np.random.default_rng(K))
+    quiet = [k for k in range(K) if k not in set(ch.tolist())]
+    where = [(0, quiet[5]), (M - 1, quiet[-3])]
+    X0, Xn = X.copy(), X.copy()
+    for m, k in where:
+        X0[m, k] = 0
+        Xn[m, k] = -np.float16("nan") if m else np.float16("nan")
+    g = run_gpu(Xn, W, x_gran="token", finite=False)
+    o = orc.linear(X0, W, x_gran="token")
+    assert g["n_outliers"].tolist() == [o["n_used"], o["n_total"]]
+    assert (g["x_scale"][0] == o["s_x"]).all() and (g["x_scale"][1] == o["inv_x"]).all()
+    keep = np.ones((M, K), bool)
+    for m, k in where:
+        keep[m, k] = False
+    assert (g["body_q"][:, :K] == o["body_q"])[keep].all()
+    assert (g["Y"][1:M - 1] == o["y16"][1:M - 1]).all()
