@@ -66,6 +66,12 @@ bool acc_fits(int K, int r_cap, int exp)
     return bound < 2147483647.0;
 }
 
+inline bool touch(const void *p, size_t p_bytes, const void *q, size_t q_bytes)
+{
+    const char *const a = (const char *)p, *const b = (const char *)q;
+    return a < b + q_bytes && b < a + p_bytes;
+}
+
 inline float qmax_of(int bits) { return (float)((1 << (bits - 1)) - 1); }
 
 // Address of `scratch` on the current device, looked up once per device.
@@ -168,12 +174,20 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
     int32_t *cn = (int32_t *)(ws + L.cn);
     const int32_t *w_row_sum = (const int32_t *)(w_q + muxq::wq_rowsum_offset(N, k_pad));
     const int ready_slabs = absmax_slabs > 0 ? absmax_slabs : muxq::absmax_slab_count(M, k_pad);
+    // next_slabs may lie in this call's own workspace (one workspace for both layers, whose layouts differ):
+    // not where the launch that writes them still reads, or other workgroups of it write.
+    const int k_pad_next = kpad(N), next_count = gelu && next_slabs != nullptr ? muxq_linear_gelu_slabs(M, K, N) : 0;
+    auto next_in = [&](size_t from, size_t to) {
+        return next_count > 0 && touch(next_slabs, (size_t)next_count * k_pad_next * 2, ws + from, to - from);
+    };
+    const bool next_hits_gemm = next_in(L.n_outliers, L.absmax_partial) || next_in(L.body_q, L.total);
+    const bool next_hits_few = next_in(0, L.absmax_partial) || next_in(L.body_q, L.total) ||
+                               (absmax_ready && next_in(L.absmax_partial, L.body_q));
     // few tokens: the whole layer in one launch (the measurement aid that brackets the GEMM keeps
     // the separate launches, as does Aux on a scale of its own; X is addressed with 32-bit offsets)
     // (a Y that shares memory with X is written while other workgroups still read X: separate launches)
-    const char *const xb = (const char *)X, *const yb = (const char *)Y;
-    const bool apart = yb >= xb + ((size_t)(M - 1) * ldx + K) * 2 || xb >= yb + ((size_t)(M - 1) * ldy + N) * 2;
-    if (gemm_start == nullptr && !aux_own && apart && (size_t)M * (size_t)ldx < (1u << 30) &&
+    const bool apart = !touch(X, ((size_t)(M - 1) * ldx + K) * 2, Y, ((size_t)(M - 1) * ldy + N) * 2);
+    if (gemm_start == nullptr && !aux_own && apart && !next_hits_few && (size_t)M * (size_t)ldx < (1u << 30) &&
         muxq::few_tokens_fit(M, K, k_pad, r_cap)) {
         muxq::FewArgs f{};
         f.x = (const uint16_t *)X;
@@ -212,8 +226,8 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
         f.gelu = gelu;
         if (gelu && next_slabs != nullptr) {
             f.next_slabs = (uint16_t *)next_slabs;
-            f.next_ld = kpad(N);
-            f.next_count = muxq_linear_gelu_slabs(M, K, N);
+            f.next_ld = k_pad_next;
+            f.next_count = next_count;
         }
         MUXQ_TRY(muxq::launch_linear_few(f, s));
         return MUXQ_OK;
@@ -309,19 +323,16 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
     g.gelu = gelu;
     // the column maxima of the output, for the next layer: from the GEMM's own tiles when its
     // form takes them and it has at most kMaxSlabs rows of tiles, else by a pass over Y
-    const int k_pad_next = kpad(N);
     const int tile_rows = muxq::gemm_tile_rows(M, N, k_pad);
-    const bool slabs_from_gemm = gelu && next_slabs != nullptr && tile_rows > 0 &&
+    const bool slabs_from_gemm = next_count > 0 && !next_hits_gemm && tile_rows > 0 &&
                                  (M + tile_rows - 1) / tile_rows <= muxq::kMaxSlabs;
     if (slabs_from_gemm) {
         g.slab_out = (uint16_t *)next_slabs;
         g.slab_ld = k_pad_next;
     }
     MUXQ_TRY(gemm_with_events(g, s, gemm_start, gemm_stop));
-    if (gelu && next_slabs != nullptr && !slabs_from_gemm) {
-        int n_next = 0;
-        MUXQ_TRY(muxq::launch_col_absmax_partial(Y, M, N, ldy, k_pad_next, (uint16_t *)next_slabs, &n_next, s));
-    }
+    if (next_count > 0 && !slabs_from_gemm)
+        MUXQ_TRY(muxq::launch_col_absmax_counted(Y, M, N, ldy, k_pad_next, (uint16_t *)next_slabs, next_count, s));
     return MUXQ_OK;
 }
 

@@ -294,6 +294,9 @@ hipError_t launch_gelu_absmax_partial(const void *y_fp16, int rows, int cols, in
                                       const float *col_factor = nullptr);
 hipError_t launch_col_absmax_partial(const void *x_fp16, int rows, int cols, int ld, int k_pad,
                                     uint16_t *partial, int *n_slabs, hipStream_t s);
+// The same in exactly n_slabs slabs.
+hipError_t launch_col_absmax_counted(const void *x_fp16, int rows, int cols, int ld, int k_pad,
+                                     uint16_t *partial, int n_slabs, hipStream_t s);
 
 // qmax below is the largest code magnitude, 2^(bits-1) - 1 (127 for the INT8 of
 // Eq. 1-2), passed as a float.

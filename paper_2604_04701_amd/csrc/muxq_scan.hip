@@ -1403,6 +1403,14 @@ hipError_t launch_col_absmax_partial(const void *x_fp16, int rows, int cols, int
                        (const uint16_t *)x_fp16, rows, cols, ld, k_pad, rpb, partial);
 }
 
+hipError_t launch_col_absmax_counted(const void *x_fp16, int rows, int cols, int ld, int k_pad,
+                                     uint16_t *partial, int n_slabs, hipStream_t s)
+{
+    // (slabs past the last row are zeros)
+    return launch_kernel(k_col_absmax_partial, dim3((k_pad / 8 + 63) / 64, n_slabs), dim3(512), 0, s,
+                         (const uint16_t *)x_fp16, rows, cols, ld, k_pad, (rows + n_slabs - 1) / n_slabs, partial);
+}
+
 int absmax_slab_count(int rows, int k_pad)
 {
     int gx, gy, rpb;

@@ -123,3 +123,29 @@ def test_a_nan_does_not_hide_the_other_channels_of_its_row(M, K, N, r):
         keep[m, k] = False
     assert (g["body_q"][:, :K] == o["body_q"])[keep].all()
     assert (g["Y"][1:M - 1] == o["y16"][1:M - 1]).all()
+
+
+@pytest.mark.parametrize("x_gran", ["tensor", "token"])
+@pytest.mark.parametrize("M,K,N1,N2", [(8, 2560, 1280, 264), (8, 64, 1000, 72), (8, 264, 1048, 264),
+                                       (333, 64, 1000, 136), (333, 1032, 520, 72), (2100, 64, 3000, 72)])
+def test_one_workspace_for_both_layers(M, K, N1, N2, x_gran):
+    """The column maxima for the next layer may lie inside the workspace of this one, on whatever its
+    layout has there: results as with two workspaces."""
+    rng = np.random.default_rng(M + K)
+    X, _ = synth.make_x(M, K, 4, U, rng)
+    Xd = torch.from_numpy(X).cuda()
+    wq1, ws1 = B.muxq_quantize_weight(torch.from_numpy(synth.make_w(K, N1, rng)).cuda())
+    wq2, ws2 = B.muxq_quantize_weight(torch.from_numpy(synth.make_w(N1, N2, rng)).cuda())
+    lay2 = B.workspace_layout(M, N1, N2, 64)
+    n1, n2 = B.workspace_bytes(M, K, N1, 64), B.workspace_bytes(M, N1, N2, 64)
+
+    def run(first, second):
+        H, n = B.muxq_linear_gelu(Xd, wq1, ws1, N1, workspace=first, next_workspace=second, next_layout=lay2, x_gran=x_gran)
+        return H, B.muxq_linear(H, wq2, ws2, N2, workspace=second, absmax_ready=True, absmax_slabs=n, x_gran=x_gran)
+
+    H, Y = run(torch.empty(n1, dtype=torch.uint8, device="cuda"), torch.empty(n2, dtype=torch.uint8, device="cuda"))
+    one = torch.empty(max(n1, n2), dtype=torch.uint8, device="cuda")
+    for _ in range(5):
+        one.fill_(0x5A)
+        H1, Y1 = run(one, one)
+        assert torch.equal(H, H1) and torch.equal(Y, Y1)
