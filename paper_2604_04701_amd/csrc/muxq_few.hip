@@ -34,8 +34,11 @@ typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kFewThreads = 1024, kFewWaves = kFewThreads / 64;
 constexpr int kFewMaxK = 8 * kFewThreads;                    // one 8-channel chunk per thread in the selection
-constexpr int kFewLoads = kFewMaxK / 64 / kFewWaves;         // weight blocks of a wave: all in registers
 constexpr int kFewMaxM = 64;
+// Weight blocks of a wave, all in registers, by 16-row blocks of tokens: enough for the K that X and its
+// codes leave room for in LDS (17 tokens: 2512, 33 tokens: 1280 with a list of 64).  Eight for all
+// of them made the forms above 16 tokens spill to scratch (68 and 52 bytes per lane).
+constexpr int few_loads(int row_blocks) { return row_blocks == 1 ? kFewMaxK / 64 / kFewWaves : row_blocks == 2 ? 3 : 2; }
 
 // What the kernel needs besides FewArgs, worked out on the host: the division of its waves and LDS.
 struct FewPlan {
@@ -85,6 +88,7 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     typedef __attribute__((address_space(3))) void *lptr_t;
+    constexpr int LOADS = few_loads(MB);
     __shared__ __attribute__((aligned(16))) int s_tot[kFewWaves];       // (each row group selects for itself)
     __shared__ __attribute__((aligned(16))) uint32_t s_max[kFewWaves];
     __shared__ uint32_t s_row[kFewMaxM * kFewWaves];     // per token: the maxima of a row's pieces
@@ -129,11 +133,11 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
 
     // the weight blocks of the first 16 channels, on their way during all that follows
     int nb = blockIdx.x;
-    v4i w[kFewLoads];
+    v4i w[LOADS];
     auto load_weights = [&](int nblock) {
         const int8_t *src = a.w_q + (size_t)nblock * k_pad * 16 + ln * 64 + lq * 16;
 #pragma unroll
-        for (int i = 0; i < kFewLoads; ++i) {
+        for (int i = 0; i < LOADS; ++i) {
             const int kb = wave + i * kFewWaves;
             if (kb < KB) w[i] = *(const v4i *)(src + (size_t)kb * 1024);
         }
@@ -192,7 +196,7 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
     }
     const Selected sel = select_channels<kFewWaves>(mx, listed, p == 0, seg, r_cap, !TOKEN, s_tot, s_max);
     listed = sel.listed;
-    const int first = sel.first, used = sel.used, found = sel.found;
+    const int first = sel.first, used = sel.used;
     const uint32_t call_max = sel.maxima;
     if (p == 0) {
         int rank = first;
@@ -318,7 +322,7 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[mb] = v4i{0, 0, 0, 0};
 #pragma unroll
-        for (int i = 0; i < kFewLoads; ++i) {
+        for (int i = 0; i < LOADS; ++i) {
             const int kb = wave + i * kFewWaves;
             if (kb >= KB) break;
 #pragma unroll
@@ -425,7 +429,7 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
 // per token, whose separate way is two launches: 16.4 / 15.0 us) to 4.9 times.
 bool few_tokens_fit(int M, int K, int k_pad, int r_cap)
 {
-    return M <= kFewMaxM && k_pad <= kFewMaxK && few_plan(M, K, k_pad, r_cap, 1).total <= kFewLdsBytes;
+    return M <= kFewMaxM && k_pad <= 64 * kFewWaves * few_loads((M + 15) / 16) && few_plan(M, K, k_pad, r_cap, 1).total <= kFewLdsBytes;
 }
 
 typedef void (*few_kernel_t)(const FewArgs, const FewPlan);

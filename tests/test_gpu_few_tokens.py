@@ -149,3 +149,10 @@ def test_one_workspace_for_both_layers(M, K, N1, N2, x_gran):
         one.fill_(0x5A)
         H1, Y1 = run(one, one)
         assert torch.equal(H, H1) and torch.equal(Y, Y1)
+
+
+@pytest.mark.parametrize("x_gran", ["tensor", "token"])
+@pytest.mark.parametrize("M,K", [(16, 2624), (17, 2432), (32, 1280), (33, 1216), (48, 848), (64, 600)])
+def test_longest_rows_of_each_form(M, K, x_gran):
+    """The longest K that LDS leaves each number of 16-row blocks: every weight block of a wave is held."""
+    check_case(Case("few_longest", M, K, 4360, 5, U, 680 + M), x_gran=x_gran, w_gran="channel", bias_seed=2)
