@@ -188,7 +188,7 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
     // (a Y that shares memory with X is written while other workgroups still read X: separate launches)
     const bool apart = !touch(X, ((size_t)(M - 1) * ldx + K) * 2, Y, ((size_t)(M - 1) * ldy + N) * 2);
     if (gemm_start == nullptr && !aux_own && apart && !next_hits_few && (size_t)M * (size_t)ldx < (1u << 30) &&
-        muxq::few_tokens_fit(M, K, k_pad, r_cap)) {
+        muxq::few_tokens_fit(M, K, N, k_pad, r_cap, per_token)) {
         muxq::FewArgs f{};
         f.x = (const uint16_t *)X;
         f.M = M; f.K = K; f.ldx = ldx; f.k_pad = k_pad; f.N = N;

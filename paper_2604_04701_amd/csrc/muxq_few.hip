@@ -8,10 +8,10 @@
 // channels at a time.  What bounds it now: latency up to about 8 K elements of X (1 x 768 -> 2304:
 // 6.5 us inside the kernel, of which 1.6 us until X has arrived and 1.6 us selection), the vector
 // ALU work of the codes, repeated on every CU, beyond (8 x 5120: 3.1 of 10.8 us).
-// Measured, us per call, the separate launches against this kernel: 1 x 768 -> 2304 18.8 / 8.4,
+// Measured, us per call, four launches with a selection kernel against this kernel: 1 x 768 -> 2304 18.8 / 8.4,
 // 1 x 8192 -> 1024 49.1 / 10.1, 8 x 1280 -> 5120 -> 1280 (an MLP, two launches instead of eight)
-// 61.5 / 24.7, 16 x 2560 -> 2560 28.8 / 11.2, 32 x 1280 -> 5120 per token 24.0 / 16.4,
-// 2 x 4096 -> 16384 36.8 / 20.5.
+// 61.5 / 24.7, 16 x 2560 -> 2560 28.8 / 11.2, 2 x 4096 -> 16384 36.8 / 20.5; against the launches that
+// would run here without it, see few_tokens_fit.
 //
 // Product.  A block of the packed weight layout is 16 output channels x 64 input channels, 1 KiB
 // contiguous, which is exactly the first operand of one v_mfma_i32_16x16x64_i8: lane l takes the
@@ -35,10 +35,9 @@ typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 constexpr int kFewThreads = 1024, kFewWaves = kFewThreads / 64;
 constexpr int kFewMaxK = 8 * kFewThreads;                    // one 8-channel chunk per thread in the selection
 constexpr int kFewMaxM = 64;
-// Weight blocks of a wave, all in registers, by 16-row blocks of tokens: enough for the K that X and its
-// codes leave room for in LDS (17 tokens: 2512, 33 tokens: 1280 with a list of 64).  Eight for all
-// of them made the forms above 16 tokens spill to scratch (68 and 52 bytes per lane).
-constexpr int few_loads(int row_blocks) { return row_blocks == 1 ? kFewMaxK / 64 / kFewWaves : row_blocks == 2 ? 3 : 2; }
+// Weight blocks of a wave, all in registers, by 16-row blocks of tokens: enough for the K that
+// few_tokens_fit lets through.  (Eight for all of them made the forms above 16 tokens spill to scratch.)
+constexpr int few_loads(int row_blocks) { return row_blocks == 1 ? kFewMaxK / 64 / kFewWaves : row_blocks == 2 ? 3 : 1; }
 
 // What the kernel needs besides FewArgs, worked out on the host: the division of its waves and LDS.
 struct FewPlan {
@@ -424,12 +423,27 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
 
 }  // namespace
 
-// The line is where X and its codes no longer fit LDS together (about 42 K elements): at every size
-// below it the one launch is the faster way, by 1.1 (32 x 1280 -> 5120 with a static list and one scale
-// per token, whose separate way is two launches: 16.4 / 15.0 us) to 4.9 times.
-bool few_tokens_fit(int M, int K, int k_pad, int r_cap)
+// X and its codes have to fit LDS together (about 42 K elements); below that the line against the separate
+// launches (selecting quantiser and GEMM) lies where two things that grow here outweigh the launch
+// saved: the walk over N, 16 channels per workgroup at a time with barriers between, and the
+// codes, which every CU forms for all rows.  us per call, the separate launches / this kernel:
+//   N      1 x 768 -> 12288 12.5 / 11.4, -> 32768 17.7 / 19.6, -> 131072 39.6 / 65.7;  8 x 4096 -> 24576 34.5 / 29.8,
+//          -> 65536 59.5 / 65.4 (a longer K gives the walk more to hide its barriers behind);  1 x 8192 -> 32768 65.9 /
+//          51.3;  64 x 248 -> 4096 12.8 / 11.5, -> 12288 14.2 / 15.6;  8 x 1280 -> 16384 per token 15.4 / 14.2
+//   codes  20 x 2000 -> 2048 12.3 / 11.0;  32 x 1000 -> 2048 11.8 / 10.7, with one scale per token 12.4 / 12.5;  32 x 1248
+//          -> 2048 11.8 / 11.7 and 13.4 / 14.3;  40 x 800 -> 4096 12.1 / 11.7 and 12.7 / 13.6;  64 x 560 -> 2048 11.6 / 13.0
+// Long lists move it the other way (8 x 1280 -> 4096, 160 channels of at most 1024 listed: 19.6 / 11.0), which only
+// the line over N takes in.
+bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token)
 {
-    return M <= kFewMaxM && k_pad <= 64 * kFewWaves * few_loads((M + 15) / 16) && few_plan(M, K, k_pad, r_cap, 1).total <= kFewLdsBytes;
+    if (M > kFewMaxM || k_pad > 64 * kFewWaves * few_loads((M + 15) / 16) || few_plan(M, K, k_pad, r_cap, 1).total > kFewLdsBytes)
+        return false;
+    const bool fewest = M <= 8;
+    if (N > (M > 32 ? 8192 : K > 1536 ? (fewest && K > 3072 ? 32768 : 24576) : fewest && (per_token || r_cap > 64) ? 16384 : 12288))
+        return false;
+    if (M <= 20) return true;
+    if (M <= 32) return M * K <= (M <= 24 ? 36 : 32) * 1024;
+    return K <= 512 ? M <= (per_token ? 48 : 64) : M <= 40 && M * K <= 32 * 1024 && !per_token;
 }
 
 typedef void (*few_kernel_t)(const FewArgs, const FewPlan);

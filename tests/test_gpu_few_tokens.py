@@ -152,7 +152,13 @@ def test_one_workspace_for_both_layers(M, K, N1, N2, x_gran):
 
 
 @pytest.mark.parametrize("x_gran", ["tensor", "token"])
-@pytest.mark.parametrize("M,K", [(16, 2624), (17, 2432), (32, 1280), (33, 1216), (48, 848), (64, 600)])
-def test_longest_rows_of_each_form(M, K, x_gran):
-    """The longest K that LDS leaves each number of 16-row blocks: every weight block of a wave is held."""
-    check_case(Case("few_longest", M, K, 4360, 5, U, 680 + M), x_gran=x_gran, w_gran="channel", bias_seed=2)
+@pytest.mark.parametrize("M,K,N", [(16, 2624, 4360), (20, 2048, 24576), (24, 1536, 4360), (32, 1024, 12288), (33, 992, 264),
+                                   (40, 816, 264), (48, 512, 8192), (64, 512, 8192)])
+def test_longest_rows_and_widest_outputs(M, K, N, x_gran):
+    """The longest rows that each number of tokens runs with (every weight block of a wave is held), the
+    widest outputs; one row more, eight channels more of either, take the separate launches."""
+    check_case(Case("few_longest", M, K, N, 5, U, 680 + M), x_gran=x_gran, w_gran="channel", bias_seed=2)
+    if N in (8192, 12288, 24576):
+        check_plain_y(Case("few_wider", M, K, N + 8, 5, U, 690 + M), x_gran=x_gran, w_gran="channel")
+    else:
+        check_case(Case("few_longer", M + 1, K + 8, N, 5, U, 690 + M), x_gran=x_gran, w_gran="channel")
