@@ -533,7 +533,7 @@ int muxq_quantize_weight_smooth(const void *W, int K, int N, int ldw, int gran, 
     const int per_channel = gran == MUXQ_PER_CHANNEL;
     const int n_scales = per_channel ? N : 1;
     int32_t *const row_sums = (int32_t *)(w_q + muxq::wq_rowsum_offset(N, kpad(K)));
-    const bool strips = muxq::wquant_in_strips(K, N, per_channel != 0);
+    const bool strips = muxq::wquant_in_strips(W, K, N, ldw, per_channel != 0);
     if (strips && per_channel) {
         MUXQ_TRY(muxq::launch_wquant_strip(W, K, N, ldw, kpad(K), nullptr, qmax, w_q, row_sums, w_scale, s, factors));
         return MUXQ_OK;

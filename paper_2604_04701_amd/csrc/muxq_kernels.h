@@ -369,7 +369,7 @@ hipError_t launch_wquant_transpose(const void *w_fp16, int K, int N, int ldw,
 // The same in strips of 64 output channels, which need no cleared row_sum: amax null, per-channel scales,
 // takes the abs-max of the channels and writes w_scale as well (one launch in all); else amax[0] is the
 // matrix's, and w_scale is left alone.
-bool wquant_in_strips(int K, int N, bool per_channel);
+bool wquant_in_strips(const void *w_fp16, int K, int N, int ldw, bool per_channel);
 hipError_t launch_wquant_strip(const void *w_fp16, int K, int N, int ldw, int k_pad, const float *amax, float qmax,
                                int8_t *w_q, int32_t *row_sum, float *w_scale, hipStream_t s, const float *row_factor);
 hipError_t launch_wscale_finalize(float *w_scale, int n, float qmax, hipStream_t s);

@@ -1531,13 +1531,26 @@ hipError_t launch_wquant_transpose(const void *w_fp16, int K, int N, int ldw, in
 }
 
 // Whether the weight quantiser works in strips of 64 output channels.  A strip streams K x 128 bytes
-// through one CU (~100 GB/s), with a scale per channel twice; that wins where it saves four launches
-// (per channel: up to K = 8192 at any N, 768 x 768 21.8 / 10.6 us, 5120 x 1280 41 / 27 us, 8192 x 64
-// 50 / 39 us; one scale per tensor saves one launch only: 1280 x 5120 20.9 / 18.6 us, but 5120 x 1280
-// 21.0 / 33.7 us) or where there are strips for most CUs (4096 x 16384 82 / 52 us and 77 / 72 us).
-bool wquant_in_strips(int K, int N, bool per_channel)
+// through one CU (~100 GB/s), with a scale per channel twice, the second time from the memory-side
+// cache.  us, 64 x 64 tiles / strips:
+//   per channel, saves four launches: 768 x 768 14.4 / 8.0, 5120 x 1280 40 / 27, 8192 x 64 51 / 40, 4096 x 16384 92 / 53.
+//     Not where one strip has few channels (8192 x 8 34.3 / 37.7), K is a fraction of the 512 rows of a step and
+//     there are many strips (64 x 50304 14.7 / 20.4), or W outgrows the cache with K beyond 8192
+//     (16384 x 12288 229 / 244; 8704 x 16384 181 / 150).
+//   one scale per tensor, saves one launch: 512 x 512 13.9 / 13.1, 1280 x 5120 18.2 / 18.6, 2048 x 1280 13.7 / 16.7; with
+//     a strip for every other CU or more 4096 x 16384 76 / 71, 4096 x 5120 39 / 43, 6144 x 24576 153 / 162.
+//   Rows of W off 128-byte lines: the pieces of a strip share lines with its neighbours', on other XCDs, which then
+//     fetch them as well: 3072 x 16392 1.09 times as fast, 4096 x 16392 0.97, 2048 x 50264 113 / 137 us.
+bool wquant_in_strips(const void *w_fp16, int K, int N, int ldw, bool per_channel)
 {
-    return K <= (per_channel ? 8192 : 2048) || N >= 192 * kStripCh;
+    const size_t bytes = (size_t)K * N * 2;
+    const bool whole_lines = (((uintptr_t)w_fp16 | (uintptr_t)ldw * 2) % 128) == 0;
+    if (!per_channel)
+        return (K <= 512 && N <= 16384) || (K <= 1024 && N <= 1280) ||
+               (whole_lines && K <= 8192 && N >= 128 * kStripCh && N <= 256 * kStripCh);
+    if ((N < kStripCh && K > 4096) || (N > 512 * kStripCh && K < 256)) return false;
+    if (!whole_lines) return K <= 8192 && bytes <= ((size_t)96 << 20);
+    return K <= 8192 || (N >= 192 * kStripCh && bytes <= ((size_t)288 << 20));
 }
 
 hipError_t launch_wquant_strip(const void *w_fp16, int K, int N, int ldw, int k_pad, const float *amax, float qmax,

@@ -29,3 +29,20 @@ def test_weight_codes_sums_and_scales(K, N, gran):
         assert (got[:, :K] == o["w_q"].T).all() and (got[:, K:] == 0).all()
         assert (w_s.cpu().numpy() == o["s_w"]).all()
         assert (B.wq_row_sums(w_q, K, N).cpu().numpy() == got.astype(np.int64).sum(axis=1)).all()
+
+
+@pytest.mark.parametrize("gran", ["tensor", "channel"])
+@pytest.mark.parametrize("K,N,ldw", [(1032, 8192, 8192), (1032, 8192, 8200), (1032, 8200, 8200), (72, 32768, 32768),
+                                     (72, 32776, 32832), (4104, 24, 24), (1024, 1280, 1280), (1024, 1288, 1288), (40, 50304, 50304)])
+def test_weight_codes_on_both_sides_of_the_line(K, N, ldw, gran):
+    """Rows on and off 128-byte lines, few and many strips, short and long K: strips and 64 x 64 tiles."""
+    rng = np.random.default_rng(K + ldw)
+    W = synth.make_w(K, N, rng)
+    ld = torch.zeros((K, ldw), dtype=torch.float16, device="cuda")
+    ld[:, :N] = torch.from_numpy(W).cuda()
+    w_q, w_s = B.muxq_quantize_weight(ld[:, :N], gran)
+    o = orc.quantize_weight(W, gran)
+    got = B.unpack(w_q, N, B.k_pad(K)).cpu().numpy()
+    assert (got[:, :K] == o["w_q"].T).all() and (got[:, K:] == 0).all()
+    assert (w_s.cpu().numpy() == o["s_w"]).all()
+    assert (B.wq_row_sums(w_q, K, N).cpu().numpy() == got.astype(np.int64).sum(axis=1)).all()
