@@ -205,12 +205,8 @@ __device__ __forceinline__ float aux_rho(const GemmArgs &a)
     return sx > 0.f ? ((float)((1 << a.exp_shift) - 1) * sa) / sx : 0.f;
 }
 
-// 16 bytes of Y.  STREAM: non-temporal, for rows that start on 128-byte lines: a store instruction
-// then writes whole lines, and Y, which is not read here again, stays out of the operands' way in
-// L2.  Otherwise the lines at the ends of a piece are completed by the neighbouring piece, which only
-// happens in L2: as a stream they would go out half written (3001 x 1592 -> 4808: 37 us as a stream,
-// 29 us so; 16384 x 1280 -> 3840: 87 us as a stream, 90 us otherwise).  Compile time: a branch at each
-// store costs 1 us per tile.
+// 16 bytes of Y.  STREAM: non-temporal (chosen by stream_rows).  Compile time: a branch at each store costs
+// 1 us per tile.
 template <bool STREAM>
 __device__ __forceinline__ void store_y(const GemmArgs &a, int m, int n, v4i v)
 {
@@ -1463,10 +1459,23 @@ persist_kernel_t persist_kernel(int form)
 #undef MUXQ_FORM
 }
 
+// Whether Y goes out as a stream.  Rows on 128-byte lines: a store instruction writes whole lines, and Y, which
+// is not read here again, stays out of the operands' way in L2 (16384 x 1280 -> 3840 90 us through L2, 87 us as a
+// stream).  Rows on 64-byte boundaries: whole transfers still, but half lines, which L2 would join.  That is worth
+// more while the memory-side cache takes Y in, and less once it does not, or while the L2s themselves hold it (768
+// input channels, us through L2 / as a stream: 1000 -> 20000 24.5 / 22.5, 2000 -> 20000 43 / 47, 12000 -> 20000
+// 250 / 202).  Other rows: the transfers at the ends of a piece are completed by the neighbouring piece, which only
+// happens in L2 (3001 -> 4808 19 / 27, 12000 -> 10000 111 / 145).
+bool stream_rows(const GemmArgs &a)
+{
+    const uintptr_t start = (uintptr_t)a.y | (uintptr_t)a.ldy * 2;
+    const size_t mib = ((size_t)a.M * a.N * 2) >> 20;
+    return start % 128 == 0 || (start % 64 == 0 && (mib < 48 || mib >= 256));
+}
+
 int persist_form(const GemmArgs &a)
 {
-    const bool stream = (((uintptr_t)a.y | (uintptr_t)a.ldy * 2) % 128) == 0;
-    return 2 * (a.gelu ? 3 : !a.aux_own_scale ? 0 : a.x_per_token ? 2 : 1) + (stream ? 1 : 0);
+    return 2 * (a.gelu ? 3 : !a.aux_own_scale ? 0 : a.x_per_token ? 2 : 1) + (stream_rows(a) ? 1 : 0);
 }
 
 // What the launcher needs to know about a device, found once per device (gemm_prepare_device).

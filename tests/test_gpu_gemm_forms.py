@@ -1,11 +1,12 @@
 """The forms of the GEMM and its tile map at the sizes where they can go wrong: ragged last tiles
 and blocks in both directions, fewer K steps than waves, several Aux steps, rows of Y on and off
-128-byte lines, even splits of the tiles over the XCDs.  Accumulators and Y against the CPU
+64-byte boundaries, even splits of the tiles over the XCDs.  Accumulators and Y against the CPU
 oracle, all exact (Aux on its own scale: check_own_scale states the bound)."""
 import numpy as np
 import pytest
+import torch
 
-from gpu_common import check_case, check_mlp, check_own_scale, check_plain_y
+from gpu_common import B, check_case, check_mlp, check_own_scale, check_plain_y, orc, sample_rows, synth
 from paper_2604_04701_amd.synth import Case
 
 pytestmark = pytest.mark.gpu
@@ -47,3 +48,18 @@ def test_direct_forms_several_aux_steps_and_own_scale(shape, x_gran):
                          ids=lambda s: "x".join(map(str, s)))
 def test_direct_forms_hand_the_column_maxima_over(shape):
     check_mlp(*shape, 840 + shape[0])
+
+
+@pytest.mark.parametrize("N,ldy", [(4808, 4808), (4816, 4816), (4832, 4832), (4864, 4864), (4808, 4832), (4832, 4840)])
+def test_rows_of_y_on_every_boundary(N, ldy):
+    """Rows that start on 16-, 32-, 64- and 128-byte boundaries, by N and by the row stride; nothing past N."""
+    rng = np.random.default_rng(N + ldy)
+    M, K = 3077, 136
+    X, _ = synth.make_x(M, K, 5, U, rng)
+    W = synth.make_w(K, N, rng)
+    out = torch.full((M, ldy), 7.0, dtype=torch.float16, device="cuda")
+    w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(W).cuda())
+    B.muxq_linear(torch.from_numpy(X).cuda(), w_q, w_s, N, out=out[:, :N])
+    rows = sample_rows(M, 200, 3)
+    assert (out[:, :N].cpu().numpy()[rows] == orc.linear(X, W, rows=rows)["y16"]).all()
+    assert (out[:, N:] == 7.0).all()
