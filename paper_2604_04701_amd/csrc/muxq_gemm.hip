@@ -53,9 +53,9 @@
 // with its own L2; workgroup i belongs to XCD i % 8.  Tiles are grouped in blocks
 // of sup_m x sup_n, as many as an XCD works on at one time, so that its L2 holds
 // sup_m + sup_n operand panels for sup_m * sup_n tiles.  Blocks are dealt to the
-// XCDs in turn; where ragged blocks would make that take more rounds than the
-// number of tiles needs, the tiles are instead put in one order, block after
-// block, and split evenly.
+// XCDs in turn, one to each where there are no more tiles than CUs; where ragged
+// blocks would make that take more rounds than the number of tiles needs, the
+// tiles are instead put in one order, block after block, and split evenly.
 #include "muxq_kernels.h"
 
 #include <atomic>
@@ -92,6 +92,18 @@ __device__ __forceinline__ int swizzle(int row, int chunk)
         return chunk ^ (row & 3);
     else
         return chunk;
+}
+
+// Brings all cache lines of the kernel's arguments in at once.  The tile map reads its fields behind
+// branches, and each first touch of a 64-byte line of arguments is a round trip to memory
+// (24 x 5120 -> 1280 4.84 -> 4.65 us, 512 x 1024 -> 1024 5.60 -> 5.39 us; the persistent forms have no use for it).
+__device__ __forceinline__ void fetch_arguments()
+{
+    constexpr int LINES = (sizeof(GemmArgs) + sizeof(TileMap) + 63) / 64;
+    static_assert(LINES == 5, "one operand below for each line");
+    const __attribute__((address_space(4))) int *const p =
+        (const __attribute__((address_space(4))) int *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" ::"s"(p[0]), "s"(p[16]), "s"(p[32]), "s"(p[48]), "s"(p[64]));
 }
 
 // Tile j of the share of XCD `xcd`: 1, or 0 past the end of the share, or -1 where a ragged block has
@@ -967,6 +979,7 @@ __global__ __launch_bounds__(256) void k_gemm_i8_persist4(const GemmArgs a, cons
 template <int TN, int TM>
 __global__ __launch_bounds__(256) void k_gemm_i8_small(const GemmArgs a, const TileMap tm)
 {
+    fetch_arguments();
     constexpr int WN = 2, WM = 2, NT = 256, CH = BK / 16, SWZ = 1;
     constexpr int FN = TN / WN / 32, FM = TM / WM / 32;
     constexpr int ROWS_PER_PASS = NT / CH;
@@ -1092,6 +1105,7 @@ __global__ __launch_bounds__(256) void k_gemm_i8_small(const GemmArgs a, const T
 template <int TN, int TM, int CS>
 __global__ __launch_bounds__(256) void k_gemm_i8_small_deep(const GemmArgs a, const TileMap tm)
 {
+    fetch_arguments();
     constexpr int WN = 2, WM = 2, NT = 256, CH = BK / 16, SWZ = 1;
     constexpr int FN = TN / WN / 32, FM = TM / WM / 32;
     constexpr int ROWS_PER_PASS = NT / CH;
@@ -1238,6 +1252,7 @@ __global__ __launch_bounds__(256) void k_gemm_i8_small_deep(const GemmArgs a, co
 template <int TNB, int TMB, int DEPTH, int W>
 __global__ __launch_bounds__(W * 64) void k_gemm_i8_direct(const GemmArgs a, const TileMap tm)
 {
+    fetch_arguments();
     constexpr int FRAGS = TNB * TMB, NQ = TNB * 4;       // n quads per tile row
     __shared__ __attribute__((aligned(16))) v4i part[W * FRAGS * 64];
     __shared__ uint32_t s_colmax[TNB * 16];
@@ -1394,20 +1409,36 @@ __global__ __launch_bounds__(W * 64) void k_gemm_i8_direct(const GemmArgs a, con
 }
 
 // at_once: tiles an XCD works on at a time.  grid: workgroups for one tile each, a multiple of 8.
-TileMap make_tile_map(const GemmArgs &a, int TN, int TM, int &grid, int at_once = 32)
+TileMap make_tile_map(const GemmArgs &a, int TN, int TM, int &grid, bool persistent = false, int at_once = 32)
 {
     TileMap tm;
     tm.tiles_m = (a.M + TM - 1) / TM;
     tm.tiles_n = (a.N + TN - 1) / TN;
-    tm.sup_m = min(at_once > 32 ? 8 : 4, tm.tiles_m);
-    tm.sup_n = min(at_once / tm.sup_m, tm.tiles_n);
+    const int total = tm.tiles_m * tm.tiles_n, even = (total + 7) / 8;
+    // No more tiles than the chip works on at one time: eight blocks, one for each XCD, as square as there are,
+    // if no XCD's CUs (32) get a tile more by them than by an even split, whose shares straddle blocks
+    // (300 x 2560 -> 7680, 3 x 60 tiles: 16.2 us split evenly, 13.5 us in blocks of 3 x 8; 256 x 2048 -> 16384 15.7, 14.3 us).
+    int square = 0;
+    if (persistent && total <= at_once * 8)
+        for (int bands = 1; bands <= 8; ++bands) {
+            const int strips = 8 / bands, m = (tm.tiles_m + bands - 1) / bands, n = (tm.tiles_n + strips - 1) / strips;
+            if ((m * n + 31) / 32 <= (even + 31) / 32 && (square == 0 || m + n < square)) {
+                square = m + n;
+                tm.sup_m = m;
+                tm.sup_n = n;
+            }
+        }
+    if (square == 0) {
+        tm.sup_m = min(at_once > 32 ? 8 : 4, tm.tiles_m);
+        tm.sup_n = min(at_once / tm.sup_m, tm.tiles_n);
+    }
     const int super_m = (tm.tiles_m + tm.sup_m - 1) / tm.sup_m;
     tm.super_n = (tm.tiles_n + tm.sup_n - 1) / tm.sup_n;
     tm.n_super = super_m * tm.super_n;
-    const int total = tm.tiles_m * tm.tiles_n;
-    // whole blocks if they fill at least one round and no XCD's CUs (32) get a tile more by them
-    const int block_rounds = (tm.n_super + 7) / 8, most = block_rounds * tm.sup_m * tm.sup_n, even = (total + 7) / 8;
-    tm.at_once = total < at_once * 8 || (most + 31) / 32 > (even + 31) / 32 ? at_once : 0;
+    // otherwise whole blocks if they fill at least one round and no XCD's CUs get a tile more
+    const int block_rounds = (tm.n_super + 7) / 8, most = block_rounds * tm.sup_m * tm.sup_n;
+    const bool blocks = square != 0 || (total >= at_once * 8 && (most + 31) / 32 <= (even + 31) / 32);
+    tm.at_once = blocks ? 0 : at_once;
     tm.full = total / (at_once * 8);
     tm.rest = total - tm.full * at_once * 8;
     const int last_rows = tm.tiles_m - (super_m - 1) * tm.sup_m, last_cols = tm.tiles_n - (tm.super_n - 1) * tm.sup_n;
@@ -1529,7 +1560,7 @@ hipError_t launch_persist(const GemmArgs &a, hipStream_t s)
     static_assert(NWAVES == 8 || NWAVES == 4, "built forms");
     constexpr int TILE = NWAVES == 8 ? 256 : 128;
     int total;
-    const TileMap tm = make_tile_map(a, TILE, TILE, total, NWAVES == 8 ? 32 : 64);
+    const TileMap tm = make_tile_map(a, TILE, TILE, total, true, NWAVES == 8 ? 32 : 64);
     constexpr int lds_bytes = persist_lds_bytes<STAGES, NWAVES>();
     constexpr int wgs_per_cu = 160 * 1024 / lds_bytes;     // by LDS; registers allow at least as many
     static_assert(wgs_per_cu >= 1, "ring too deep");

@@ -63,3 +63,11 @@ def test_rows_of_y_on_every_boundary(N, ldy):
     rows = sample_rows(M, 200, 3)
     assert (out[:, :N].cpu().numpy()[rows] == orc.linear(X, W, rows=rows)["y16"]).all()
     assert (out[:, N:] == 7.0).all()
+
+
+@pytest.mark.parametrize("M,K,N", [(300, 520, 7688), (500, 520, 7680), (129, 712, 16384), (1500, 520, 2056), (3000, 520, 776),
+                                   (1000, 520, 3848), (2049, 520, 2056)])
+def test_one_block_of_tiles_for_each_xcd(M, K, N):
+    """The 128 x 128 form with no more tiles than CUs: eight blocks, ragged in either direction, and sizes
+    with no such blocks."""
+    check_plain_y(Case("xcd_blocks", M, K, N, 6, U, 860 + M), w_gran="channel", bias_seed=3)
