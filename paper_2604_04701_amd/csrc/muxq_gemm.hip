@@ -521,9 +521,24 @@ struct PersistTile {
     int tile_m, tile_n;
 };
 
-// The first tile of this XCD's share at or after j, in steps of `stride` workgroups of the XCD.
-__device__ __forceinline__ PersistTile tile_at(const TileMap &tm, int j, int stride)
+// The tile map of a persistent kernel, read from its arguments anew: its 26 fields kept in scalar registers all
+// through the K loop make the forms with Aux on its own scale spill 110 more of them (8192 x 1280 -> 3840 69.0 us,
+// read anew once per tile 67.1 us).  The other forms have the room, and the reads cost them 0.4 us a tile
+// (16384 x 1280 -> 3840 per token).  The kernels' parameters are (GemmArgs, TileMap).
+__device__ __forceinline__ TileMap tile_map_argument()
 {
+    static_assert(sizeof(GemmArgs) % alignof(TileMap) == 0, "the second parameter follows the first");
+    typedef const __attribute__((address_space(4))) char *arg_ptr_t;
+    arg_ptr_t p = (arg_ptr_t)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(GemmArgs);
+    asm volatile("" : "+s"(p));              // (the compiler no longer knows that it has read these before)
+    return *(const TileMap *)p;
+}
+
+// The first tile of this XCD's share at or after j, in steps of `stride` workgroups of the XCD.
+template <bool ANEW>
+__device__ __forceinline__ PersistTile tile_at(const TileMap &map, int j, int stride)
+{
+    const TileMap tm = ANEW ? tile_map_argument() : map;
     PersistTile p;
     p.tile_m = p.tile_n = 0;
     int st;
@@ -573,7 +588,7 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
     const int k_tiles = a.k_pad / BK;
     const int stride = (int)gridDim.x >> 3;  // the grid is a multiple of the 8 XCDs
 
-    PersistTile cur_tile = tile_at(tm, (int)blockIdx.x >> 3, stride);
+    PersistTile cur_tile = tile_at<OWN != 0>(tm, (int)blockIdx.x >> 3, stride);
     if (cur_tile.j < 0) return;
     if (a.wg_ticks != nullptr) {             // measurement aid: when this workgroup started
         if (tid == 0) a.wg_ticks[2 * blockIdx.x] = wall_clock64();
@@ -616,7 +631,7 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
     // time: at the phase change all waves would wait for it.  With fewer K steps per tile than the
     // stream runs ahead, the stream may need the tile after that one and works it out itself.
     const bool known_next = t_aux + k_tiles > DEPTH;
-    PersistTile nx_tile = tile_at(tm, cur_tile.j + stride, stride);
+    PersistTile nx_tile = tile_at<OWN != 0>(tm, cur_tile.j + stride, stride);
     bool d_aux;                 // phase of the stream
     int d_left;                 // K steps left in the phase
     unsigned d_w[LH], d_x[LH];  // scalar byte offsets of the next step's blocks
@@ -643,7 +658,7 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
         if (d_aux) {                                                                            \
             MUXQ_DMA_PHASE(false);                                                              \
         } else {                                                                                \
-            const PersistTile nx_ = known_next ? nx_tile : tile_at(tm, dma_tile.j + stride, stride); \
+            const PersistTile nx_ = known_next ? nx_tile : tile_at<OWN != 0>(tm, dma_tile.j + stride, stride); \
             if (nx_.j >= 0) {                                                                   \
                 dma_tile = nx_;                                                                 \
                 MUXQ_DMA_PHASE(t_aux > 0);                                                      \
@@ -940,7 +955,7 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
             __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // unknown number of vector-memory operations: drain
         }
         cur_tile = nx_tile;
-        if (cur_tile.j >= 0) nx_tile = tile_at(tm, cur_tile.j + stride, stride);
+        if (cur_tile.j >= 0) nx_tile = tile_at<OWN != 0>(tm, cur_tile.j + stride, stride);
     }
     // Drain the unused tail loads before the workgroup's LDS is released.
     __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds(0));
