@@ -12,12 +12,18 @@ from paper_2604_04701_amd.synth import Case
 pytestmark = pytest.mark.gpu
 U = (20.0, 100.0)
 
+# Rows of the output tile of each form; the register-staged form takes no column maxima, so the count
+# it leaves is that of a pass over the output.
 FORMS = {
-    "direct 16x16": (100, 2112, 264), "direct 16x32": (130, 520, 1000), "direct 16x32, one K step": (70, 64, 72),
-    "direct 32x32": (333, 1032, 1096), "direct 32x64": (500, 2112, 776), "direct 64x64": (700, 1600, 1400),
-    "direct 64x64, long K": (390, 3008, 1992), "register-staged": (2049, 264, 776),
-    "persistent 128, even split": (2100, 520, 1544), "persistent 256, even split": (3077, 136, 4808),
-    "persistent 256, blocks": (4100, 72, 2560),
+    "direct 16x16": (100, 2112, 264, 16), "direct 16x32": (130, 520, 1000, 32), "direct 16x32, one K step": (70, 64, 72, 32),
+    "direct 32x32": (333, 1032, 1096, 32), "direct 32x64": (500, 2112, 776, 64), "direct 64x64": (700, 1600, 1400, 64),
+    "direct 64x64, long K": (390, 3008, 1992, 64), "register-staged": (2049, 264, 776, None),
+    # no more tiles than are worked on at one time: split evenly, or one block per XCD
+    "persistent 128, even split": (2100, 520, 1544, 128), "persistent 128, block per XCD": (2245, 72, 1288, 128),
+    "persistent 256, even split": (3077, 136, 4808, 256), "persistent 256, block per XCD": (4100, 72, 2560, 256),
+    # several tiles per workgroup: blocks ragged in both directions (places without a tile are skipped), even splits
+    "persistent 256, ragged blocks": (4743, 72, 4272, 256), "persistent 256, even split, more": (5222, 72, 4112, 256),
+    "persistent 128, even split, more": (6607, 72, 2312, 128),
 }
 
 
@@ -25,11 +31,23 @@ FORMS = {
                                                      ("token", "channel", 6)])
 @pytest.mark.parametrize("form", FORMS)
 def test_gemm_forms(form, x_gran, w_gran, bias_seed):
-    M, K, N = FORMS[form]
+    M, K, N, tile_rows = FORMS[form]
+    if tile_rows is not None:
+        assert B.lib().muxq_linear_gelu_slabs(M, K, N) == (M + tile_rows - 1) // tile_rows
     case = Case("form", M, K, N, min(6, K // 8), U, 800 + M)
     if M * N <= 2000 * 1600:
         check_case(case, x_gran=x_gran, w_gran=w_gran, bias_seed=bias_seed)
     check_plain_y(case, x_gran=x_gran, w_gran=w_gran, bias_seed=bias_seed)
+
+
+@pytest.mark.parametrize("M,N,tile_rows", [(4743, 4272, 256), (4096, 4104, 128)])
+@pytest.mark.parametrize("x_gran,w_gran", [("tensor", "tensor"), ("token", "channel")])
+def test_one_k_step_per_tile_and_several_tiles_per_workgroup(M, N, tile_rows, x_gran, w_gran):
+    """The stream of K steps runs more than a tile ahead of the products: without Aux steps it needs the tile
+    after the next, with one Aux step it changes phase at every step."""
+    assert B.lib().muxq_linear_gelu_slabs(M, 64, N) == (M + tile_rows - 1) // tile_rows
+    for r_cap in (0, 64):
+        check_plain_y(Case("one_step", M, 64, N, 3, U, 880 + r_cap), x_gran=x_gran, w_gran=w_gran, r_cap=r_cap)
 
 
 @pytest.mark.parametrize("x_gran", ["tensor", "token"])

@@ -32,8 +32,8 @@ def test_ragged_shapes(case, w_gran):
     check_case(case, w_gran=w_gran, bias_seed=case.seed)
 
 
-# Shapes with at least 192 tiles of 256 x 256: these take the persistent large-tile GEMM
-# (several tiles per workgroup, ragged last tile row and column, one- and two-step K loops).
+# Shapes with close to 256 tiles of 256 x 256: these take the persistent large-tile GEMM, about one
+# tile per workgroup (ragged last tile row and column, one- and two-step K loops).
 LARGE = [
     Case("large_ragged", 3333, 200, 4104, 5, U, 27),
     Case("large_k64", 4096, 64, 4096, 2, U, 28),
@@ -359,9 +359,10 @@ def test_large_tile_path_several_aux_steps(r_cap, r):
     check_plain_y(case, r_cap=r_cap, w_gran="channel", bias_seed=3)
 
 
-# The 128 x 128 form of the DMA-ring GEMM: chosen below 144 tiles of 256 x 256 for long K
-# loops (K >= 2048) and, with 1024 <= K < 2048, for 128..384 tiles of 128 x 128.  The third
-# case (K = 64) runs the register-staged form on the same tiling.
+# Middle sizes.  The 128 x 128 form of the DMA-ring GEMM runs where its rounds of 256 tiles are fewer than
+# three times those of the 256 x 256 form and there are too many tiles for the direct forms: here the
+# second case (one tile per workgroup).  The first runs direct 16 x 32 tiles, the third (K = 64) the
+# register-staged form.
 MID = [
     Case("mid_long_k", 300, 2112, 264, 7, U, 41),
     Case("mid_one_round", 1500, 1032, 1544, 5, U, 42),
@@ -394,19 +395,21 @@ def test_mid_tile_path_several_aux_steps(r_cap, r):
 
 def test_mid_tile_path_several_tiles_per_workgroup():
     # more 128 x 128 tiles than resident workgroups: the K-step stream runs across tiles
-    case = Case("mid_stream", 2690, 2048, 3000, 9, U, 47)     # 132 tiles of 256^2, 528 of 128^2
+    case = Case("mid_stream", 4096, 712, 4104, 9, U, 47)      # 1056 tiles of 128^2, 512 workgroups
+    assert B.lib().muxq_linear_gelu_slabs(case.M, case.K, case.N) == case.M // 128
     rows = sample_rows(case.M, 40, 11)
     check_case(case, rows=rows)
     check_plain_y(case, rows=rows)
     check_plain_y(case, rows=rows, w_gran="channel", bias_seed=4, x_gran="token")
 
 
-def test_muxq_linear_recorded_in_a_graph_replays_correctly():
-    # A call launches its four kernels on the given stream and nothing else (no allocation,
-    # no memset, no host synchronisation), so it can be recorded into a HIP graph.  Every
-    # replay, on fresh inputs and with eager work in between, must equal the eager call.
+@pytest.mark.parametrize("M", [300, 8])
+def test_muxq_linear_recorded_in_a_graph_replays_correctly(M):
+    # A call launches its kernels (three here, one with few tokens) on the given stream and nothing
+    # else (no allocation, no memset, no host synchronisation), so it can be recorded into a HIP graph.
+    # Every replay, on fresh inputs and with eager work in between, must equal the eager call.
     import dataclasses
-    case = Case("graph", 300, 256, 264, 5, U, 77)
+    case = Case("graph", M, 256, 264, 5, U, 77)
     X, W, _ = synth.make_case(case)
     dev = "cuda"
     w_q, w_scale = B.muxq_quantize_weight(torch.from_numpy(W).to(dev), "channel")
@@ -800,23 +803,26 @@ def test_own_scale_aux_per_token_full_size_and_loud_outliers():
 
 # ---- the MLP pair: GELU fused into the first projection's GEMM, maxima handed to the second ----
 
-@pytest.mark.parametrize("shape,form", [
-    ((3333, 200, 4104, 264), "persistent 256, ragged tiles"),
-    ((1000, 2112, 1096, 520), "persistent 128"),
-    ((300, 264, 520, 136), "register-staged: maxima by a pass over H"),
-    ((2049, 512, 2048, 512), "register-staged 128"),
-    ((4096, 64, 4096, 72), "persistent 256, one-step K loop"),
-], ids=lambda v: v if isinstance(v, str) else "x".join(map(str, v)))
+@pytest.mark.parametrize("shape,tile_rows", [
+    ((3333, 200, 4104, 264), 256),
+    ((1000, 2112, 1096, 520), 128),
+    ((300, 264, 520, 136), 32),                            # direct 32 x 32
+    ((2049, 512, 2048, 512), 128),
+    ((4096, 64, 4096, 72), 256),                           # one-step K loop
+    ((4096, 520, 4104, 72), 128),                          # several tiles per workgroup
+    ((1500, 512, 1544, 136), None),                        # register-staged: maxima by a pass over H
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else f"tile_rows_{v}")
 @pytest.mark.parametrize("w_gran,x_gran", [("tensor", "tensor"), ("channel", "token")])
-def test_mlp_gelu_fused_into_the_first_gemm(shape, form, w_gran, x_gran):
+def test_mlp_gelu_fused_into_the_first_gemm(shape, tile_rows, w_gran, x_gran):
     M, K, N1, N2 = shape
-    check_mlp(M, K, N1, N2, seed=M + K, w_gran=w_gran, x_gran=x_gran)
+    n = check_mlp(M, K, N1, N2, seed=M + K, w_gran=w_gran, x_gran=x_gran)
+    if tile_rows is not None:                              # one slab per row of tiles
+        assert n == (M + tile_rows - 1) // tile_rows
 
 
 def test_mlp_full_size_gpt2_medium():
     n = check_mlp(8192, 1024, 4096, 1024, seed=3100)       # configuration 3: c_fc, GELU, c_proj
     assert n == 32                                         # one slab per row of 256 x 256 tiles
-    assert B.lib().muxq_linear_gelu_slabs(16384 * 2, 1024, 4096) == B.lib().muxq_linear_gelu_slabs(16384 * 2, 1024, 4096)
     # more than 64 rows of tiles: the maxima come from a pass over H, at that pass's slab count
     assert 1 <= B.lib().muxq_linear_gelu_slabs(32768, 1024, 4096) <= 64
 
