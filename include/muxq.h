@@ -219,8 +219,8 @@ int muxq_detect_outliers(const void *X_fp16, int M, int K, int ldx,
  *      aux_q, packed M x r_cap (not touched when r_cap == 0, may then be
  *      NULL), columns past the kept count zeroed;
  *      x_scale float[2] = {s_x, 127/max|Body|}.
- * scratch: caller-provided device memory of 2 * muxq_k_pad(K) * 4 bytes
- *      (per-channel multiplier and list position), 16-byte aligned. */
+ * scratch: caller-provided device memory of 2 * muxq_k_pad(K) * 4 bytes, 16-byte aligned
+ *      (per-channel multiplier and list position, for K above 8192). */
 int muxq_build_aux(const void *X_fp16, int M, int K, int ldx,
                    const float *col_absmax, const int32_t *outlier_idx,
                    const int32_t *n_outliers, int r_cap, int exp,
@@ -332,8 +332,10 @@ int muxq_gelu_absmax(const void *Y_fp16, int M, int K, int ldy, void *X_fp16, in
  * maxima of H, so that the next muxq_linear_opts / muxq_linear_static starts at its selection
  * step with opts.absmax_ready = 1 and opts.absmax_slabs = muxq_linear_gelu_slabs(M, K, N).
  * The GEMM's workgroups take those maxima from the tiles they store (one slab per row of
- * tiles); where the problem is too small for that form of the GEMM, or has more than 64 rows of
- * tiles, one plain pass over H takes them instead (same result, same interface).
+ * tiles); where the problem runs on a form of the GEMM that does not, or has more than 64 rows of
+ * tiles, one plain pass over H takes them instead (same result, same interface).  One workspace may
+ * serve both layers (large enough for either): next_slabs then lies inside `workspace`, and the
+ * maxima come from that pass where its layout has something there that the GEMM still needs.
  * opts: as muxq_linear_opts (aux_own_scale is not combined with the fused GELU: MUXQ_ERR_PARAM). */
 int muxq_linear_gelu_slabs(int M, int K, int N);   /* 0 on bad shapes */
 int muxq_linear_gelu(const void *X_fp16, int M, int K, int ldx, const int8_t *w_q,

@@ -86,7 +86,7 @@ struct ActShared {
     uint8_t mask[kActThreads];           // per chunk of 8 channels: which are listed
     __attribute__((aligned(16))) int tot[kActWaves];
     __attribute__((aligned(16))) uint32_t max[kActWaves];
-    float amax, nmax;                    // given list only
+    float amax;                          // given list only
 };
 
 // Fold, selection and list for the whole workgroup.  want_max: false where neither the candidates (a
@@ -225,7 +225,7 @@ __device__ __forceinline__ void quantize_chunk(const ActArgs &a, const ActShared
 
 // One activation scale for the call.  A wave owns a piece of 64 chunks of a row, a thread one chunk
 // (its mask and every address but the row's part, which is scalar, are fixed: the work per code is the
-// quantisation itself, 4 vector instructions), and takes it in row after row, up to U rows in flight.  All
+// quantisation itself, 3 vector instructions and a share of the packing), and takes it in row after row, up to U rows in flight.  All
 // workgroups walk X together: what is in flight at one time is one contiguous piece of memory.  (A
 // range of rows for each workgroup puts all of them on the same few memory channels where a range
 // is a multiple of a large power of two: 16384 x 5120 from HBM 65 us instead of 45 us.)

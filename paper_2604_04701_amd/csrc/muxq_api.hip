@@ -274,30 +274,30 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
         q.cn_bias = per_token ? 0 : muxq::kCnBias;
         MUXQ_TRY(muxq::launch_quantize_select(q, per_token, false, s));
     } else {
-    if (!(per_token && static_block != nullptr)) {
-        if (absmax_ready)     // a producer of X has left the slab maxima in the workspace
-            n_slabs = ready_slabs;
+        if (!(per_token && static_block != nullptr)) {
+            if (absmax_ready)     // a producer of X has left the slab maxima in the workspace
+                n_slabs = ready_slabs;
+            else
+                MUXQ_TRY(muxq::launch_col_absmax_partial(X, M, K, ldx, k_pad, partial, &n_slabs, s));
+            MUXQ_TRY(muxq::launch_fold_select_scale(partial, n_slabs, K, k_pad, threshold, r_cap, exp, qmax,
+                                                    per_token ? 0 : 1, col_absmax, idx, n_out, col_slot,
+                                                    (uint8_t *)(ws + L.col_mask), col_scale, x_scale, s,
+                                                    static_mask, per_token ? nullptr : zero_point,
+                                                    aux_own && !per_token ? x_scale + 2 : nullptr));
+        }
+        if (per_token)
+            MUXQ_TRY(muxq::launch_quantize_rows_token(X, M, K, ldx, k_pad, qmax, exp, col_mask, n_out, r_cap,
+                                                      body_q, aux_q, x_scale, w_q, N, idx,
+                                                      gather ? w_aux : nullptr, s,
+                                                      gather ? nullptr : (r_cap ? w_aux : nullptr),
+                                                      w_row_sum, cn, aux_own ? 1 : 0));
         else
-            MUXQ_TRY(muxq::launch_col_absmax_partial(X, M, K, ldx, k_pad, partial, &n_slabs, s));
-        MUXQ_TRY(muxq::launch_fold_select_scale(partial, n_slabs, K, k_pad, threshold, r_cap, exp, qmax,
-                                                per_token ? 0 : 1, col_absmax, idx, n_out, col_slot,
-                                                (uint8_t *)(ws + L.col_mask), col_scale, x_scale, s,
-                                                static_mask, per_token ? nullptr : zero_point,
-                                                aux_own && !per_token ? x_scale + 2 : nullptr));
-    }
-    if (per_token)
-        MUXQ_TRY(muxq::launch_quantize_rows_token(X, M, K, ldx, k_pad, qmax, exp, col_mask, n_out, r_cap,
-                                                  body_q, aux_q, x_scale, w_q, N, idx,
-                                                  gather ? w_aux : nullptr, s,
-                                                  gather ? nullptr : (r_cap ? w_aux : nullptr),
-                                                  w_row_sum, cn, aux_own ? 1 : 0));
-    else
-        MUXQ_TRY(muxq::launch_quantize_body(X, M, K, ldx, k_pad, qmax, col_scale, col_slot, n_out,
-                                            r_cap, body_q, aux_q, w_q, N, idx,
-                                            gather ? w_aux : nullptr, s,
-                                            gather ? nullptr : (r_cap ? w_aux : nullptr), zero_point,
-                                            w_row_sum, cn, muxq::kCnBias, aux_own ? x_scale + 2 : nullptr,
-                                            exp));
+            MUXQ_TRY(muxq::launch_quantize_body(X, M, K, ldx, k_pad, qmax, col_scale, col_slot, n_out,
+                                                r_cap, body_q, aux_q, w_q, N, idx,
+                                                gather ? w_aux : nullptr, s,
+                                                gather ? nullptr : (r_cap ? w_aux : nullptr), zero_point,
+                                                w_row_sum, cn, muxq::kCnBias, aux_own ? x_scale + 2 : nullptr,
+                                                exp));
     }
 
     muxq::GemmArgs g{};

@@ -36,8 +36,8 @@
 //                   workgroup barrier per K step, placed between the two
 //                   sub-steps so that it never waits on data.
 //   k_gemm_i8_persist4  the same kernel body with a 128 x 128 tile and 4 waves,
-//                   two workgroups per CU, for problems with too few 256 x 256
-//                   tiles to fill 256 CUs but a long K loop.
+//                   two workgroups per CU, where its rounds of tiles are fewer
+//                   than three times those of the 256 x 256 form (gemm_form).
 //   k_gemm_i8_direct  small tiles (16 x 16 to 64 x 64), operands from memory straight to
 //                   registers, the waves of a workgroup split K: for problems
 //                   with too few larger tiles to fill the chip.
@@ -979,9 +979,8 @@ __global__ __launch_bounds__(512) void k_gemm_i8_persist8(const GemmArgs a, cons
     gemm_persist_body<STAGES, 8, 4, 2, OWN, GELU, STREAM>(a, tm);
 }
 
-// 128 x 128 tiles, 4 waves of 64 x 64, a deeper ring: for problems with too few
-// 256 x 256 tiles to fill the chip, where the load latency of a short K loop
-// is what has to be hidden.
+// 128 x 128 tiles, 4 waves of 64 x 64: for problems whose 256 x 256 tiles would leave the last, or the
+// only, round on the chip half empty.
 template <int STAGES, int OWN, bool GELU, bool STREAM>
 __global__ __launch_bounds__(256) void k_gemm_i8_persist4(const GemmArgs a, const TileMap tm)
 {
@@ -991,11 +990,10 @@ __global__ __launch_bounds__(256) void k_gemm_i8_persist4(const GemmArgs a, cons
 // --------------------------------------------------------------------------
 // Small tiles (64 x 64), 4 waves, register staging.
 // --------------------------------------------------------------------------
-template <int TN, int TM>
 __global__ __launch_bounds__(256) void k_gemm_i8_small(const GemmArgs a, const TileMap tm)
 {
     fetch_arguments();
-    constexpr int WN = 2, WM = 2, NT = 256, CH = BK / 16, SWZ = 1;
+    constexpr int TN = 64, TM = 64, WN = 2, WM = 2, NT = 256, CH = BK / 16, SWZ = 1;
     constexpr int FN = TN / WN / 32, FM = TM / WM / 32;
     constexpr int ROWS_PER_PASS = NT / CH;
     constexpr int W_LD = TN / ROWS_PER_PASS, X_LD = TM / ROWS_PER_PASS;
@@ -1117,11 +1115,11 @@ __global__ __launch_bounds__(256) void k_gemm_i8_small(const GemmArgs a, const T
 // steps instead of once per step.  It costs registers and LDS (two workgroups per CU), which
 // is why problems with several workgroups per CU keep the kernel above.
 // --------------------------------------------------------------------------
-template <int TN, int TM, int CS>
+template <int CS>
 __global__ __launch_bounds__(256) void k_gemm_i8_small_deep(const GemmArgs a, const TileMap tm)
 {
     fetch_arguments();
-    constexpr int WN = 2, WM = 2, NT = 256, CH = BK / 16, SWZ = 1;
+    constexpr int TN = 64, TM = 64, WN = 2, WM = 2, NT = 256, CH = BK / 16, SWZ = 1;
     constexpr int FN = TN / WN / 32, FM = TM / WM / 32;
     constexpr int ROWS_PER_PASS = NT / CH;
     constexpr int W_LD = TN / ROWS_PER_PASS, X_LD = TM / ROWS_PER_PASS;
@@ -1542,7 +1540,7 @@ hipError_t prepare_current_device(int dev)
                                 persist_lds_bytes<3, 4>());
         if (e != hipSuccess) return e;
     }
-    e = hipFuncSetAttribute((const void *)k_gemm_i8_small_deep<64, 64, kDeepSteps>,
+    e = hipFuncSetAttribute((const void *)k_gemm_i8_small_deep<kDeepSteps>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, kDeepSteps * 128 * BK);
     if (e != hipSuccess) return e;
     if ((e = few_prepare_device()) != hipSuccess) return e;
@@ -1595,9 +1593,9 @@ hipError_t launch_small(const GemmArgs &a, hipStream_t s)
     const hipError_t e = current_device_cus(n_cu);
     if (e != hipSuccess) return e;
     if ((long)tm.tiles_m * tm.tiles_n <= n_cu)
-        return launch_kernel(k_gemm_i8_small_deep<64, 64, kDeepSteps>, dim3(grid), dim3(256),
+        return launch_kernel(k_gemm_i8_small_deep<kDeepSteps>, dim3(grid), dim3(256),
                              kDeepSteps * 128 * BK, s, a, tm);
-    return launch_kernel(k_gemm_i8_small<64, 64>, dim3(grid), dim3(256), 0, s, a, tm);
+    return launch_kernel(k_gemm_i8_small, dim3(grid), dim3(256), 0, s, a, tm);
 }
 
 template <int TNB, int TMB, int DEPTH, int W>
@@ -1622,7 +1620,7 @@ enum GemmForm {
     kDirect16x16, kDirect16x32, kDirect32x32, kDirect32x64, kDirect64x64       // channels x tokens
 };
 
-// Which form runs a shape fastest was measured over 300 shapes (M 32..16384, K 256..5120, N 256..16384,
+// Which form runs a shape fastest was measured over 289 shapes (M up to 16384, K 256..5120, N 256..16384,
 // each form forced in turn).  us per call, by form:
 //   32 x 768 -> 2304     16x32 4.1,  32x32 4.7,  small 7.8,  persistent 128 9.3
 //   24 x 5120 -> 1280    16x16 5.3,  16x32 6.0,  32x32 8.2,  small 24.0,  persistent 128 27.6

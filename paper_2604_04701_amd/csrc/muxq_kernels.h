@@ -128,7 +128,8 @@ __device__ __forceinline__ void lds_barrier()
 // rounded to binary32, clamped to [-qmax, qmax] (v_med3_f32), and adding 1.5 * 2^23 then
 // rounds it to the nearest integer, ties to even, in the adder itself and leaves that
 // integer, two's complement, in the low mantissa bits.  Rounding after the clamp equals
-// clamping after rounding because the bounds are integers.  Three VALU ops per element; the streaming quantisers are not far from ALU-bound.
+// clamping after rounding because the bounds are integers.  Three VALU ops per element, and 3 for each four to
+// pack their bytes; the streaming quantisers are not far from ALU-bound.
 __device__ __forceinline__ uint32_t quant_word(float x, float scale, float qmax,
                                                float magic = 12582912.0f)
 {
