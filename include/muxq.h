@@ -220,7 +220,7 @@ int muxq_detect_outliers(const void *X_fp16, int M, int K, int ldx,
  *      NULL), columns past the kept count zeroed;
  *      x_scale float[2] = {s_x, 127/max|Body|}.
  * scratch: caller-provided device memory of 2 * muxq_k_pad(K) * 4 bytes, 16-byte aligned
- *      (per-channel multiplier and list position, for K above 8192). */
+ *      (per-channel multiplier and list position, where they are not kept in LDS). */
 int muxq_build_aux(const void *X_fp16, int M, int K, int ldx,
                    const float *col_absmax, const int32_t *outlier_idx,
                    const int32_t *n_outliers, int r_cap, int exp,

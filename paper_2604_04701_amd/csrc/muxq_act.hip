@@ -435,6 +435,26 @@ __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
 
 bool act_select_fits(int k_pad, int r_cap) { return k_pad <= kActMaxK && r_cap <= kActMaxCap; }
 
+// With one scale per call and X beyond what the 256 MB memory-side cache keeps, both passes stream from HBM, and the
+// 2048 small workgroups of the separate kernels do that better than 256 large ones; the selection kernel between
+// them no longer weighs.  us a layer, separate kernels / these, 64 output channels: 20505 x 4096 (168 MB) 97 / 98, 24409 x
+// 4096 (200 MB) 138 / 140, 146481 x 4096 (1.2 GB) 707 / 777, 78121 x 1280 (200 MB) 133 / 145; up to 1024 channels these
+// win at any size: 97657 x 1024 (200 MB) 133 / 131; so do they with very long rows (73241 x 8192 765 / 734).  (With one scale per row the separate kernel is always the slower one.)
+bool act_select_pays(int M, int K) { return K <= 1024 || K > 6144 || (size_t)M * K * 2 < ((size_t)176 << 20); }
+
+// The same for muxq_build_aux, whose list and maxima come from outside: 40000 x 4096 (328 MB) 100 / 116 us, 50000 x 5120
+// (512 MB) 175 / 152, 97657 x 1024 (200 MB) 66 / 58; short rows 250001 x 256 (128 MB) 54 / 68, 500001 x 256 (256 MB)
+// 135 / 120, 312497 x 512 (320 MB) 113 / 120.
+bool act_given_pays(int M, int K)
+{
+    const size_t mib = ((size_t)M * K * 2) >> 20;
+    return !(mib >= 288 && K >= 1024 && K < 5120) && !(mib >= 60 && (K <= 256 ? mib < 200 : K <= 512));
+}
+
+// And for the abs-max pass by itself, blocks of 512 columns / narrow ones: 262144 x 4096 (2 GB) 332 / 353 us, 256 MB of 4096
+// channels narrow 4 % faster, 400000 x 256 84 / 34.
+bool absmax_narrow_pays(int M, int K) { return K < 2048 || (size_t)M * K * 2 < ((size_t)480 << 20); }
+
 hipError_t launch_col_absmax_narrow(const void *x_fp16, int rows, int cols, int ld, int k_pad, uint16_t *partial,
                                     int *n_slabs, hipStream_t s)
 {

@@ -150,8 +150,8 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
     const int k_pad = L.k_pad;
 
     // The stages are: slab maxima -> fold + select (+ scales) -> quantise (+ Aux weight gather) -> GEMM.
-    // One launch does all of them for few tokens; the quantisers select for themselves while K <= 8192
-    // (two or three launches); four launches otherwise.  With a static block the channel list and the
+    // One launch does all of them for few tokens; the quantisers select for themselves while K <= 8192, and
+    // with one scale per call X no larger than the caches (two or three launches); four launches otherwise.  With a static block the channel list and the
     // Aux weight rows are given: no gather, and in the per-token setting no pass for the channel maxima.
     int n_slabs = 0;
     const bool per_token = x_gran == MUXQ_X_PER_TOKEN;
@@ -233,7 +233,7 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
         return MUXQ_OK;
     }
     // the selection inside the quantiser, where every workgroup can fold the column maxima for itself
-    if (!aux_own && muxq::act_select_fits(k_pad, r_cap)) {
+    if (!aux_own && muxq::act_select_fits(k_pad, r_cap) && (per_token || muxq::act_select_pays(M, K))) {
         muxq::ActArgs q{};
         q.x = (const uint16_t *)X;
         q.M = M; q.K = K; q.ldx = ldx; q.k_pad = k_pad; q.N = N;
@@ -572,7 +572,7 @@ int muxq_detect_outliers(const void *X, int M, int K, int ldx, float threshold, 
         return MUXQ_ERR_ALIGN;
     hipStream_t s = (hipStream_t)stream;
     int n_slabs = 0;
-    if (muxq::act_select_fits(kpad(K), 0))           // few slabs for the fold, see muxq_act.hip
+    if (muxq::act_select_fits(kpad(K), 0) && muxq::absmax_narrow_pays(M, K))     // few slabs for the fold
         MUXQ_TRY(muxq::launch_col_absmax_narrow(X, M, K, ldx, kpad(K), (uint16_t *)scratch, &n_slabs, s));
     else
         MUXQ_TRY(muxq::launch_col_absmax_partial(X, M, K, ldx, kpad(K), (uint16_t *)scratch, &n_slabs, s));
@@ -599,7 +599,7 @@ int muxq_build_aux(const void *X, int M, int K, int ldx, const float *col_absmax
         (aux_q && !aligned(aux_q, 16)) || !aligned(x_scale, 4))
         return MUXQ_ERR_ALIGN;
     hipStream_t s = (hipStream_t)stream;
-    if (muxq::act_select_fits(k_pad, r_cap)) {       // the scale inside the quantiser: one launch
+    if (muxq::act_select_fits(k_pad, r_cap) && muxq::act_given_pays(M, K)) {      // the scale inside the quantiser: one launch
         muxq::ActArgs q{};
         q.x = (const uint16_t *)X;
         q.M = M; q.K = K; q.ldx = ldx; q.k_pad = k_pad;

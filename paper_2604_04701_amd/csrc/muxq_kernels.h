@@ -225,6 +225,10 @@ struct ActArgs {
 // (against 4-5 us for the abs-max pass).
 constexpr size_t kFoldSlabBytes = 128 * 1024, kFoldXBytes = 128 * 1024;
 bool act_select_fits(int k_pad, int r_cap);
+// Whether it is the faster way: for one scale per call, for muxq_build_aux, for the abs-max pass by itself.
+bool act_select_pays(int M, int K);
+bool act_given_pays(int M, int K);
+bool absmax_narrow_pays(int M, int K);
 hipError_t launch_fold_slabs(uint16_t *partial, int n_slabs, int k_pad, hipStream_t s);      // into slab 0
 // The abs-max pass that leaves few slabs (see muxq_act.hip); partial and *n_slabs as launch_col_absmax_partial.
 hipError_t launch_col_absmax_narrow(const void *x_fp16, int rows, int cols, int ld, int k_pad, uint16_t *partial,

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import test_gpu_parity as T
-from gpu_common import B, check_case, check_plain_y, orc, synth
+from gpu_common import B, check_case, check_plain_y, orc, sample_rows, synth
 from paper_2604_04701_amd.synth import Case
 
 pytestmark = pytest.mark.gpu
@@ -81,3 +81,37 @@ def test_slabs_of_a_producer(M, K, N):
         o = orc.linear(X.cpu().numpy(), W, x_gran=x_gran)
         assert (Yg.cpu().numpy() == o["y16"]).all()
         B.muxq_gelu_absmax(Y, ws, lay)
+
+
+@pytest.mark.parametrize("M,K", [(96_001, 968), (96_001, 1032), (24_001, 4096)])
+def test_x_beyond_the_caches(M, K):
+    """X of 186 to 198 MB, on both sides of the line to the separate kernels; codes, lists and scales over all
+    rows, accumulators and Y on a sample."""
+    case = Case("act_big", M, K, 24, 7, U, 970)
+    check_case(case, rows=sample_rows(M, 40, 2))
+
+
+@pytest.mark.parametrize("M,K", [(140_001, 1032), (150_001, 1032), (61_001, 4096), (62_001, 4096), (30_001, 5128), (140_001, 248)])
+def test_stages_on_x_beyond_the_caches(M, K):
+    """The stage entry points on both sides of their lines, against the same formulas in binary32 (every step is exact
+    or correctly rounded here as well: the scales by numpy, the codes by torch on the GPU)."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + K)
+    X = torch.randn(M, K, generator=g, device="cuda", dtype=torch.float16).clamp_(-5.5, 5.5)      # none over 6 by chance
+    lst = torch.tensor([3, 40, K - 2], device="cuda")
+    X[:, lst] *= 30
+    cm, idx, n = B.muxq_detect_outliers(X)
+    assert torch.equal(cm, X.abs().amax(0).float())
+    assert n.tolist() == [3, 3] and idx[:3].tolist() == lst.tolist() and (idx[3:] == -1).all()
+    body, aux, xs = B.muxq_build_aux(X, cm, idx, n, 64, 2)
+    mult = torch.ones(K, device="cuda")
+    mult[lst] = 0.25
+    amax = np.float32((cm * mult).amax().item())
+    inv = float(np.float32(127.0) / amax)
+    assert xs.tolist() == [float(amax / np.float32(127.0)), inv]
+    got = B.unpack(body, M, B.k_pad(K))
+    for r0 in range(0, M, 16384):
+        want = ((X[r0:r0 + 16384].float() * mult) * inv).round_().clamp_(-127, 127).to(torch.int8)
+        assert torch.equal(got[r0:r0 + 16384, :K], want)
+        assert torch.equal(B.unpack(aux, M, 64)[r0:r0 + 16384, :3], want[:, lst])
+    assert (got[:, K:] == 0).all() and (B.unpack(aux, M, 64)[:, 3:] == 0).all()
