@@ -33,7 +33,9 @@ def test_weight_codes_sums_and_scales(K, N, gran):
 
 @pytest.mark.parametrize("gran", ["tensor", "channel"])
 @pytest.mark.parametrize("K,N,ldw", [(1032, 8192, 8192), (1032, 8192, 8200), (1032, 8200, 8200), (72, 32768, 32768),
-                                     (72, 32776, 32832), (4104, 24, 24), (1024, 1280, 1280), (1024, 1288, 1288), (40, 50304, 50304)])
+                                     (72, 32776, 32832), (4104, 24, 24), (1024, 1280, 1280), (1024, 1288, 1288),
+                                     (1032, 1280, 1280), (1024, 8184, 8184), (264, 16448, 16448), (520, 32704, 32704),
+                                     (520, 16448, 16448), (40, 50304, 50304)])
 def test_weight_codes_on_both_sides_of_the_line(K, N, ldw, gran):
     """Rows on and off 128-byte lines, few and many strips, short and long K: strips and 64 x 64 tiles."""
     rng = np.random.default_rng(K + ldw)
@@ -46,3 +48,20 @@ def test_weight_codes_on_both_sides_of_the_line(K, N, ldw, gran):
     assert (got[:, :K] == o["w_q"].T).all() and (got[:, K:] == 0).all()
     assert (w_s.cpu().numpy() == o["s_w"]).all()
     assert (B.wq_row_sums(w_q, K, N).cpu().numpy() == got.astype(np.int64).sum(axis=1)).all()
+
+
+@pytest.mark.parametrize("K,N", [(5128, 16448), (5128, 16512), (8200, 15936), (8200, 16000), (4104, 33024),
+                                 (9224, 16448), (5120, 12296), (3072, 18440)])
+def test_weight_codes_by_rounds_of_strips(K, N):
+    """Strips in one round and in several, the last one short, a single strip or full, rows on and off 128-byte lines, and
+    the separate launches beside them (the channels are independent: the oracle takes some of each strip, all of the last)."""
+    g = torch.Generator(device="cuda").manual_seed(K + N)
+    W = (0.02 * torch.randn(K, N, generator=g, device="cuda")).half()
+    w_q, w_s = B.muxq_quantize_weight(W, "channel")
+    cols = np.unique(np.concatenate([np.arange(0, N, 37), np.arange(N - 64, N)]))
+    o = orc.quantize_weight(W[:, torch.from_numpy(cols).cuda()].cpu().numpy(), "channel")
+    codes = B.unpack(w_q, N, B.k_pad(K))
+    got = codes[torch.from_numpy(cols).cuda()].cpu().numpy()
+    assert (got[:, :K] == o["w_q"].T).all() and (got[:, K:] == 0).all()
+    assert (w_s.cpu().numpy()[cols] == o["s_w"]).all()
+    assert (B.wq_row_sums(w_q, K, N) == codes.sum(dim=1, dtype=torch.int64)).all()
