@@ -161,7 +161,7 @@ __device__ __forceinline__ void scale_acc(v16i (&acc)[FN][FM], int e, int fix)
         {
 #pragma unroll
             for (int v = 0; v < 16; ++v)
-                acc[fn][fm][v] = (int)(((unsigned)acc[fn][fm][v] << e) - (unsigned)acc[fn][fm][v] - (unsigned)fix);
+                acc[fn][fm][v] = (int)(((unsigned)acc[fn][fm][v] << e) + (0u - (unsigned)fix - (unsigned)acc[fn][fm][v]));
             // one fragment at a time: keeps the number of temporaries small when the
             // accumulators live in the accumulation registers
             __builtin_amdgcn_sched_barrier(0);
@@ -328,57 +328,74 @@ __device__ __forceinline__ void epilogue(const GemmArgs &a, const v16i (&acc)[FN
 // Epilogue of the persistent kernel, with a smaller patch: the wave's LDS patch
 // holds 32 tokens x 64 channels (two fragments), so a tile's epilogue runs
 // FM x FN/2 rounds of { 8 ds_write_b64, 4 ds_read_b128, 4 stores of 8 rows x 128 B }.
-// Exactly FM * (FN / 2) * 4 store instructions are issued for a full tile.
+// Exactly FM * (FN / 2) * 4 store instructions are issued for a tile, partial or not.
+// Bound by its vector ALU work and by the latency of reading the constants: a group of 4 channels is read once
+// for the FM tokens of a lane, one group ahead, and the later token's results stay in the registers of the
+// accumulators they replace until the patch is free.
 // The vector-memory counter completes in issue order, so a vector load issued
-// here would have to wait for every operand load still in flight; three forms:
-//   EPI_PLAIN   per-tensor weight scale, no bias: the only scale is the launch
-//               constant `s_tensor`; no loads at all.
-//   EPI_STAGED  per-channel weight scales, a bias and/or per-token activation
-//               scales: the wave's constants were fetched straight into `chan`
-//               (LDS) by direct-to-LDS loads issued with the tile's first K step
-//               (raw values: FN * 32 weight scales, then FN * 32 fp16 bias values,
-//               then FM * 32 token scales); again no loads here.
-//   EPI_LOADS   the wave loads its constants itself (one batch) and also exports
-//               the raw accumulators when asked: the debugging path, which
-//               drains the memory queue once per tile.
-enum { EPI_PLAIN = 0, EPI_STAGED = 1, EPI_LOADS = 2 };
+// here would have to wait for every operand load still in flight.  So the wave's constants come straight into
+// `chan` (LDS) by direct-to-LDS loads issued with the tile's first K step (raw values: FN * 32 weight scales, then
+// FN * 32 fp16 bias values, then FM * 32 token scales, the channels' cn, the tokens' z and rho), and what a launch
+// has of them is known at compile time (Epi): a run-time flag costs a select or an add of zero per output, and this
+// epilogue is bound by its vector ALU work (seven operations per output in the per-vector setting).  One kernel for
+// each, chosen on the host: with eleven epilogues behind one K loop the compiler spilled scalar registers all
+// through them, and left no vector registers for reading the constants ahead.
+// (one kernel each and the reads ahead, us a call: 1024 x 768 -> 3072 19.9 -> 18.1, 8192 x 1024 -> 1024 30.5 -> 28.0, 3001 x
+// 1592 -> 4808 per vector 43.3 -> 41.6, 16384 x 1280 -> 3840 per vector 113.3 -> 108.4, 8192 x 4096 -> 16384 428 -> 422)
+enum Epi {
+    kEpiLoads,        // the wave loads its constants itself and also exports the raw accumulators when asked
+                      // (debugging; drains the memory queue once per tile), and takes any row stride of Y
+    kEpiGeneral,      // flags at run time
+    kEpiPlain, kEpiBias, kEpiChan, kEpiChanBias,          // one activation scale, no zero point (the naive pipeline)
+    kEpiPlainZ, kEpiBiasZ, kEpiChanZ, kEpiChanBiasZ,      // one activation scale, zero point
+    kEpiToken, kEpiTokenBias,                             // scales per token, zero points per token
+    kEpiVector, kEpiVectorBias,                           // the same with a scale per channel as well
+    kEpis
+};
 constexpr int kChanFloats = 128 + 64 + 64 + 128 + 64 + 64;   // per-wave LDS for the tile's constants
 
-// ZC (compile time, PLAIN form only; the other forms test a.cn): the accumulators carry a
-// zero-point term z * cn[n] (cn per channel, int32, staged behind the other constants; z
-// per launch, or per token, staged as well), which is taken off first -- in integers
-// (one 24-bit multiply-add), so the result is the accumulator of Eq. 7 exactly.
-// SUB (compile time): the accumulators started at an offset that no zero-point term removes
-// (see kAccBias); `sub_bias` comes off.  false: the caller knows it is zero.
-// WCH, TOK, BIAS (compile time, STAGED form; -1 = decided at run time from `a`): per-channel
-// weight scales, per-token activation scales, a bias.  The common combinations are compiled
-// separately: a run-time flag costs a select or an add of zero per output, and this epilogue
-// is bound by its vector ALU work (seven operations per output in the general form, four in
-// the plain one).
+// -1: decided at run time from the arguments
+constexpr bool epi_flags(int e) { return e <= kEpiGeneral; }
+constexpr int epi_chan(int e)
+{
+    return epi_flags(e) ? -1 : e == kEpiChan || e == kEpiChanBias || e == kEpiChanZ || e == kEpiChanBiasZ || e >= kEpiVector;
+}
+constexpr int epi_bias(int e)
+{
+    return epi_flags(e) ? -1 : e == kEpiBias || e == kEpiChanBias || e == kEpiBiasZ || e == kEpiChanBiasZ || e == kEpiTokenBias ||
+                                   e == kEpiVectorBias;
+}
+constexpr int epi_token(int e) { return epi_flags(e) ? -1 : e >= kEpiToken; }
+constexpr int epi_zero(int e) { return epi_flags(e) ? -1 : e >= kEpiPlainZ; }
+
+// The accumulators carry a zero-point term z * cn[n] (cn per channel, int32; z per launch or per token), which is
+// taken off in integers (one 24-bit multiply-add), so the result is the accumulator of Eq. 7 exactly; `sub_bias`
+// (see kAccBias) comes off as well, and is known to be zero with one zero point per launch.
 // GELU (compile time): the result goes through the tanh GELU, applied to the fp16 value the
 // layer would have stored, and `mx` (FN / 2 entries) collects, per lane, the running maxima of
 // the |fp16| values the lane stores (its 8 channels of each half, over its rows).
-template <int FN, int FM, int ROW_BYTES, int MODE, bool STREAM, bool ZC = false, bool SUB = true,
-          int WCH = -1, int TOK = -1, int BIAS = -1, bool GELU = false>
+template <int FN, int FM, int ROW_BYTES, int EPI, bool STREAM, bool GELU>
 __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&acc)[FN][FM],
                                                int m_base, int n_base, int lane,
                                                unsigned char *patch, float *chan, float sx,
-                                               float sw0, float s_tensor, int z_launch, int sub_bias,
-                                               uint4 *mx = nullptr)
+                                               float sw0, int z_launch, int sub_bias, uint4 *mx)
 {
-    if (!SUB) sub_bias = 0;
+    constexpr int WCH = epi_chan(EPI), TOK = epi_token(EPI), BIAS = epi_bias(EPI), ZC = epi_zero(EPI);
     const bool w_chan = WCH < 0 ? a.w_per_channel != 0 : WCH != 0;
     const bool x_tok = TOK < 0 ? a.x_per_token != 0 : TOK != 0;
     const bool has_bias = BIAS < 0 ? a.bias != nullptr : BIAS != 0;
+    const bool has_zc = ZC < 0 ? a.cn != nullptr : ZC != 0;
+    if (ZC == 1 && TOK == 0) sub_bias = 0;
+    const float s_tensor = sx * sw0;
     static_assert((FN == 4 || FN == 2) && FM == 2, "the constants' layout holds up to 128 channels and 64 tokens per wave");
-    constexpr bool PLAIN = MODE == EPI_PLAIN;
+    // (what follows from the lane number is worked out anew for each tile: kept through the K loop it would spill)
+    asm volatile("" : "+v"(lane));
     const int fr = lane & 31, fh = lane >> 5;
     _Float16 *const chan_bias = (_Float16 *)(chan + 128);
     float *const chan_tok = chan + 128 + 64;
     int *const chan_zc = (int *)(chan + 256);      // cn of the wave's 128 channels
     int *const chan_ztok = (int *)(chan + 384);    // z of the wave's 64 tokens (per-token setting)
-    const bool has_zc = PLAIN ? ZC : a.cn != nullptr;
-    if (MODE == EPI_LOADS) {                   // same raw layout as the staged form
+    if (EPI == kEpiLoads) {                    // same raw layout as the loads of the first K step
         const int n = n_base + 2 * lane;
         float2 sw = make_float2(0.f, 0.f);
         _Float16 b0 = (_Float16)0.f, b1 = (_Float16)0.f;
@@ -400,68 +417,94 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
         chan_ztok[lane] = zt;
     }
 
+    int negz[FM];                                  // this lane's tokens
+    float sxt[FM];
 #pragma unroll
     for (int fm = 0; fm < FM; ++fm) {
-        int negz = 0;                              // this lane's token
-        if (has_zc) negz = -((!PLAIN && x_tok) ? chan_ztok[fm * 32 + fr] : z_launch);
+        negz[fm] = !has_zc ? 0 : -(x_tok ? chan_ztok[fm * 32 + fr] : z_launch);
+        sxt[fm] = x_tok ? chan_tok[fm * 32 + fr] : sx;
+    }
+    // Y of the wave's rows of one fragment, as a buffer that ends with row M - 1: a store needs one 32-bit add, and
+    // rows past M are dropped by the range check.
+    const int piece = lane & 7;
+    unsigned y_off[4];
 #pragma unroll
-        for (int h = 0; h < FN / 2; ++h) {
+    for (int p = 0; p < 4; ++p) y_off[p] = (unsigned)(p * 8 + (lane >> 3)) * (unsigned)a.ldy * 2u + (unsigned)(n_base + piece * 8) * 2u;
+    // constants of the 4 channels of group e (fragment e / 4, run e % 4), read one group ahead of their use
+    struct Group { float4 w; f16x4 b; v4i z; };
+    const auto group = [&](int e) {
+        const int at = e * 8 + 4 * fh;
+        Group c;
+        c.w = make_float4(sw0, sw0, sw0, sw0);
+        c.b = f16x4{0, 0, 0, 0};
+        c.z = v4i{0, 0, 0, 0};
+        if (w_chan) c.w = *(const float4 *)(chan + at);
+        if (has_bias) c.b = *(const f16x4 *)(chan_bias + at);
+        if (has_zc) c.z = *(const v4i *)(chan_zc + at);
+        return c;
+    };
+    Group cst = group(0);
 #pragma unroll
-            for (int f2 = 0; f2 < 2; ++f2) {
-                // the four corrections of this fragment in one batch of LDS reads: read one
-                // by one inside the pinned loop below, each would expose its latency
-                v4i zq[4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}};
-                if (has_zc) {
+    for (int h = 0; h < FN / 2; ++h) {
+        f16x4 held[FM - 1][8];                     // the later tokens' results wait for the patch
 #pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        zq[g] = *(const v4i *)(chan_zc + h * 64 + f2 * 32 + 8 * g + 4 * fh);
+        for (int e = 0; e < 8; ++e) {
+            const Group nxt = h * 8 + e + 1 < FN * 4 ? group(h * 8 + e + 1) : cst;
+            const int fn = 2 * h + e / 4, g = e % 4;
+            const float wv[4] = {cst.w.x, cst.w.y, cst.w.z, cst.w.w};
+#pragma unroll
+            for (int fm = 0; fm < FM; ++fm) {
+                f16x4 out;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    // Eq. 3: one binary32 product of the two scales, whichever granularity
+                    const float sc = WCH == 0 && TOK == 0 ? s_tensor : sxt[fm] * wv[i];
+                    int t = acc[fn][fm][4 * g + i];
+                    if (has_zc) t = __mul24(cst.z[i], negz[fm]) + t;
+                    float y = sc * (float)(t - sub_bias);
+                    if (BIAS != 0) y = y + (float)cst.b[i];   // + 0 without a bias: changes no finite value
+                    out[i] = (_Float16)y;
+                    if (GELU) out[i] = (_Float16)gelu_tanh_f32((float)out[i]);
                 }
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int fn = 2 * h + f2;
-                    const int nl = f2 * 32 + 8 * g + 4 * fh;          // channel inside the pair
-                    float4 sc = make_float4(s_tensor, s_tensor, s_tensor, s_tensor);
-                    float4 bs = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (!PLAIN) {
-                        // Eq. 3: one binary32 product of the two scales, whichever granularity
-                        float4 w = make_float4(sw0, sw0, sw0, sw0);
-                        if (w_chan) w = *(const float4 *)(chan + h * 64 + nl);
-                        const float sxx = x_tok ? chan_tok[fm * 32 + fr] : sx;
-                        sc = make_float4(sxx * w.x, sxx * w.y, sxx * w.z, sxx * w.w);
-                        if (has_bias) {
-                            const f16x4 b4 = *(const f16x4 *)(chan_bias + h * 64 + nl);
-                            bs = make_float4((float)b4[0], (float)b4[1], (float)b4[2], (float)b4[3]);
-                        }
-                    }
-                    const float scv[4] = {sc.x, sc.y, sc.z, sc.w}, bsv[4] = {bs.x, bs.y, bs.z, bs.w};
-                    const v4i z4 = zq[g];
-                    f16x4 out;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        float y = scv[i] * (float)(__mul24(z4[i], negz) + (acc[fn][fm][4 * g + i] - sub_bias));
-                        if (!PLAIN && BIAS != 0) y = y + bsv[i];   // + 0 without a bias: changes no finite value
-                        out[i] = (_Float16)y;
-                        if (GELU) out[i] = (_Float16)gelu_tanh_f32((float)out[i]);
-                    }
-                    *(f16x4 *)(patch + fr * ROW_BYTES + nl * 2) = out;
-                    __builtin_amdgcn_sched_barrier(0);   // bounds the live temporaries (see scale_acc)
-                }
+                if (fm == 0) *(f16x4 *)(patch + fr * ROW_BYTES + (e * 8 + 4 * fh) * 2) = out;
+                else held[fm - 1][e] = out;
             }
+            cst = nxt;
+            __builtin_amdgcn_sched_barrier(0);     // bounds the live temporaries (see scale_acc)
+        }
+        // (no branch at a store: lanes past N get an offset past the end)
+        const bool n_in = n_base + h * 64 + piece * 8 < a.N;
+        unsigned off[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) off[p] = n_in ? y_off[p] + h * 128 : 1u << 31;
+#pragma unroll
+        for (int fm = 0; fm < FM; ++fm) {
+            if (fm > 0) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) *(f16x4 *)(patch + fr * ROW_BYTES + (e * 8 + 4 * fh) * 2) = held[fm - 1][e];
+            }
+            const int rows = __builtin_amdgcn_readfirstlane(min(max(a.M - m_base - fm * 32, 0), 32));
+            const __amdgpu_buffer_rsrc_t r_y = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(a.y + (size_t)(m_base + fm * 32) * a.ldy), 0, (int)((unsigned)rows * (unsigned)a.ldy * 2u), 0x00020000);
             // patch -> Y: 8 lanes cover the 128 bytes of one token, 8 tokens per instruction
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
-                const int row = p * 8 + (lane >> 3), piece = lane & 7;
+                const int row = p * 8 + (lane >> 3);
                 const v4i v = *(const v4i *)(patch + row * ROW_BYTES + piece * 16);
-                const int m = m_base + fm * 32 + row, n = n_base + h * 64 + piece * 8;
-                if (m < a.M && n < a.N) {
-                    store_y<STREAM>(a, m, n, v);
-                    if (GELU) mx[h] = absmax_step(mx[h], __builtin_bit_cast(uint4, v));
+                if (EPI != kEpiLoads)
+                    __builtin_amdgcn_raw_buffer_store_b128(v, r_y, off[p], 0, STREAM ? 2 : 0);
+                else if (n_in && row < rows)
+                    store_y<STREAM>(a, m_base + fm * 32 + row, n_base + h * 64 + piece * 8, v);
+                if (GELU) {
+                    const unsigned keep = n_in && row < rows ? ~0u : 0u;
+                    const uint4 u = __builtin_bit_cast(uint4, v);
+                    mx[h] = absmax_step(mx[h], make_uint4(u.x & keep, u.y & keep, u.z & keep, u.w & keep));
                 }
             }
         }
     }
 
-    if (MODE == EPI_LOADS && a.dbg_acc != nullptr) {   // raw accumulators, debugging aid: plain per-lane stores
+    if (EPI == kEpiLoads && a.dbg_acc != nullptr) {   // raw accumulators, debugging aid: plain per-lane stores
 #pragma unroll
         for (int fn = 0; fn < FN; ++fn)
 #pragma unroll
@@ -506,7 +549,7 @@ constexpr int waitcnt_lds_only() { return waitcnt_vm_lds(63); }
 // tile is already being computed.  The epilogue's LDS patches lie behind the
 // ring, so the ring keeps filling during an epilogue.
 //
-// The four DMA instructions of a K step are spread over the first eight MFMAs
+// The DMA instructions of a K step (four, in the 256 x 256 form) are spread over the first eight MFMAs
 // (one per two MFMAs) instead of being issued back to back: a burst of 32 DMA
 // instructions per CU backs up the texture-address unit, and a wave blocked on
 // issuing a load cannot issue its MFMAs either.
@@ -547,33 +590,36 @@ __device__ __forceinline__ PersistTile tile_at(const TileMap &map, int j, int st
     return p;
 }
 
-// The tile is 2 x NWAVES/2 waves of FN x FM fragments of 32 x 32.  Built as
-// NWAVES = 8, FN = 4, FM = 2 (256 x 256, two waves per SIMD, each 128 (n) x 64 (m))
-// and NWAVES = 4, FN = 2, FM = 2 (128 x 128, for problems with few tiles).
+// The tile is WN x WM waves of FN x FM fragments of 32 x 32.  Built as 2 x 4 waves of
+// 4 x 2 (256 x 256, two waves per SIMD, each 128 (n) x 64 (m))
+// and 2 x 2 of 2 x 2 (128 x 128, for problems with few tiles).
 // OWN (compile time): the launch's Aux codes have a scale of their own (GemmArgs::aux_own_scale),
 // 1 with one activation scale per launch, 2 with one per token; forms of their own so that the
 // usual kernel's register allocation does not carry the floating-point rescale of the
 // accumulators (nor the per-launch form the per-token factors: 109 spilled registers in one kernel).
 // GELU (compile time): the fused-activation form (GemmArgs::gelu): every epilogue applies the
 // GELU and, with slab_out, the workgroup leaves the column maxima of its tile of Y.
-template <int STAGES, int NWAVES, int FN, int FM, int OWN, bool GELU, bool STREAM>
+template <int STAGES, int WN, int WM, int FN, int FM, int EPI, int OWN, bool GELU, bool STREAM>
 __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileMap &tm)
 {
-    constexpr int WN = 2, WM = NWAVES / WN, TN = WN * FN * 32, TM = WM * FM * 32, SWZ = 1;
+    constexpr int NWAVES = WN * WM, TN = WN * FN * 32, TM = WM * FM * 32, SWZ = 1;
     constexpr int NMFMA = FN * FM;           // MFMAs per wave per K sub-step
     constexpr int NFRAG = FN + FM;           // fragment reads per wave per K sub-step
     constexpr int STAGE_BYTES = (TN + TM) * BK;
     constexpr int RING_BYTES = STAGES * STAGE_BYTES;
     constexpr int DEPTH = STAGES - 1;        // K steps in flight ahead of the one being computed
-    constexpr int LH = TN / 16 / NWAVES;     // DMA instructions per wave per K step and operand
-    static_assert(TN == TM && TN % (16 * NWAVES) == 0, "the waves share the blocks of both operands evenly");
-    constexpr int LOADS = 2 * LH;
+    constexpr int LHN = TN / 16 / NWAVES, LHM = TM / 16 / NWAVES;   // DMA instructions per wave, K step and operand
+    static_assert(TN % (32 * NWAVES) == 0 && TM % (32 * NWAVES) == 0 && FN * 2 % LHN == 0 && FM * 2 % LHM == 0,
+                  "the waves share the blocks of both operands evenly, a fragment's two blocks with one wave");
+    constexpr int LOADS = LHN + LHM;
     constexpr int DMA_EVERY = NMFMA / LOADS; // one DMA instruction per this many MFMAs
+    constexpr int REGION = LOADS * 1024;     // a wave's part of a stage: what it loads itself
     constexpr int PATCH_ROW = 2 * 64 + 16;   // epilogue patch: 32 tokens x 64 channels fp16 (+ pad)
     constexpr int PATCH_BYTES = 32 * PATCH_ROW;
     // global stores per wave per full tile (with the fused GELU one more: the column maxima)
     constexpr int STORES = FM * (FN / 2) * 4 + (GELU ? 1 : 0);
-    static_assert(NMFMA % LOADS == 0 && NFRAG <= NMFMA, "schedule does not fit");
+    static_assert(LOADS <= NMFMA && NFRAG <= NMFMA, "schedule does not fit");
+
     static_assert((DEPTH - 1) * LOADS + STORES + 8 < 64, "vmcnt has 6 bits");
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     typedef __attribute__((address_space(3))) void *lptr_t;
@@ -581,8 +627,8 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave_n = (wave % WN) * (FN * 32), wave_m = (wave / WN) * (FM * 32);
-    unsigned char *const patch = lds + RING_BYTES + wave * PATCH_BYTES;
-    float *const chan = (float *)(lds + RING_BYTES + NWAVES * PATCH_BYTES) + wave * kChanFloats;
+    constexpr int CONST_AT = RING_BYTES + NWAVES * PATCH_BYTES;
+    float *const chan = (float *)(lds + CONST_AT) + wave * kChanFloats;
 
     const int t_aux = aux_tiles(a);
     const int k_tiles = a.k_pad / BK;
@@ -597,18 +643,19 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
     // launch constants of the epilogue, fetched before any operand load is in flight
     const float sx = a.x_scale[0];
     const float sw0 = a.w_scale[0];
-    const float s_tensor = sx * sw0;
-    const bool plain = !a.w_per_channel && !a.x_per_token && a.bias == nullptr && a.dbg_acc == nullptr;
-    const bool has_zc = a.cn != nullptr;
-    const int z_launch = has_zc && !a.x_per_token ? a.zero_point[0] : 0;
-    // where the accumulators start (see kCnBias), and what the Aux weighting has to take off
-    const int fold_bias = z_launch * a.cn_bias;            // comes off with z * cn[n]
-    const int sub_bias = fold_bias != 0 ? 0 : kAccBias;    // comes off by itself (see kAccBias)
-    const int acc_bias = fold_bias + sub_bias, acc_fix = ((1 << a.exp_shift) - 2) * acc_bias;
+    const bool has_zc = epi_zero(EPI) < 0 ? a.cn != nullptr : epi_zero(EPI) != 0;
+    const bool x_tok = epi_token(EPI) < 0 ? a.x_per_token != 0 : epi_token(EPI) != 0;
+    const int z_launch = has_zc && !x_tok ? a.zero_point[0] : 0;
+    // where the accumulators start (see kCnBias): what comes off with z * cn[n], or by itself (see kAccBias), and
+    // what the Aux weighting has to take off
+    const int sub_bias = has_zc && !x_tok ? 0 : kAccBias;
+    const int acc_bias = has_zc && !x_tok ? z_launch * a.cn_bias : kAccBias, acc_fix = ((1 << a.exp_shift) - 2) * acc_bias;
     const float rho = OWN == 1 ? aux_rho(a) : 0.f;
-    const bool staged = !plain && a.dbg_acc == nullptr;
-    const bool consts = staged || (plain && has_zc);     // the tile's constants come by DMA
-    constexpr int CONST_LOADS = 8;           // weight scales (2), bias, token scales, cn (2), token z, token rho: always all eight
+    // the tile's constants that come by DMA: weight scales (2 loads), bias, token scales, cn (2), z and rho per token
+    constexpr bool CONSTS = EPI != kEpiLoads;
+    constexpr bool L_W = CONSTS && epi_chan(EPI) != 0, L_B = CONSTS && epi_bias(EPI) != 0, L_T = CONSTS && epi_token(EPI) != 0,
+                   L_Z = CONSTS && epi_zero(EPI) != 0, L_ZT = L_T && L_Z, L_RHO = CONSTS && OWN == 2;
+    constexpr int CONST_LOADS = 2 * L_W + L_B + L_T + 2 * L_Z + L_ZT + L_RHO;
 
     // ---- DMA side -------------------------------------------------------------
     // One buffer_load ... lds instruction moves one 1 KiB block of the packed layout
@@ -634,15 +681,15 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
     PersistTile nx_tile = tile_at<OWN != 0>(tm, cur_tile.j + stride, stride);
     bool d_aux;                 // phase of the stream
     int d_left;                 // K steps left in the phase
-    unsigned d_w[LH], d_x[LH];  // scalar byte offsets of the next step's blocks
+    unsigned d_w[LHN], d_x[LHM];  // scalar byte offsets of the next step's blocks
 #define MUXQ_DMA_PHASE(aux_)                                                                    \
     do {                                                                                        \
         const bool ax_ = (aux_);                                                                \
         const unsigned rb_ = ax_ ? aux_rowblock : body_rowblock;                                \
-        _Pragma("unroll") for (int i_ = 0; i_ < LH; ++i_) {                                     \
-            d_w[i_] = rb_ * (unsigned)min(dma_tile.tile_n * (TN / 16) + i_ * NWAVES + wave, nblk_n - 1); \
-            d_x[i_] = rb_ * (unsigned)min(dma_tile.tile_m * (TM / 16) + i_ * NWAVES + wave, nblk_m - 1); \
-        }                                                                                       \
+        _Pragma("unroll") for (int i_ = 0; i_ < LHN; ++i_)                                      \
+            d_w[i_] = rb_ * (unsigned)min(dma_tile.tile_n * (TN / 16) + wave * LHN + i_, nblk_n - 1); \
+        _Pragma("unroll") for (int i_ = 0; i_ < LHM; ++i_)                                      \
+            d_x[i_] = rb_ * (unsigned)min(dma_tile.tile_m * (TM / 16) + wave * LHM + i_, nblk_m - 1); \
         r_w = __builtin_amdgcn_make_buffer_rsrc((void *)(ax_ ? a.w_aux : a.w_q), 0,             \
                                                 (int)((unsigned)nblk_n * rb_), RSRC_FLAGS);     \
         r_x = __builtin_amdgcn_make_buffer_rsrc((void *)(ax_ ? a.aux_q : a.a_q), 0,             \
@@ -663,26 +710,28 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
                 dma_tile = nx_;                                                                 \
                 MUXQ_DMA_PHASE(t_aux > 0);                                                      \
             } else {                                                                            \
-                _Pragma("unroll") for (int i_ = 0; i_ < LH; ++i_) { d_w[i_] -= 1024u; d_x[i_] -= 1024u; } \
+                _Pragma("unroll") for (int i_ = 0; i_ < LHN; ++i_) d_w[i_] -= 1024u;            \
+                _Pragma("unroll") for (int i_ = 0; i_ < LHM; ++i_) d_x[i_] -= 1024u;            \
                 d_left = 1;                                                                     \
             }                                                                                   \
         }                                                                                       \
     } while (0)
     MUXQ_DMA_PHASE(t_aux > 0);
     int st_dma = 0;                            // byte offset of the stage the next DMA fills
-    // DMA instruction j of a step: j even -> weight block j / 2, j odd -> activation block j / 2
+    // DMA instruction j of a step: the wave's weight blocks, then its activation blocks
 #define MUXQ_DMA(j_)                                                                            \
     do {                                                                                        \
-        if ((j_) % 2 == 0)                                                                      \
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(r_w,                      \
-                (lptr_t)(lds + st_dma + (((j_) / 2) * NWAVES + wave) * 1024), 16, lane_off, d_w[(j_) / 2], 0, 0); \
+        if ((j_) < LHN)                                                                         \
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r_w,                                       \
+                (lptr_t)(lds + st_dma + wave * REGION + (j_) * 1024), 16, lane_off, d_w[(j_) < LHN ? (j_) : 0], 0, 0); \
         else                                                                                    \
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(r_x,                      \
-                (lptr_t)(lds + st_dma + TN * BK + (((j_) / 2) * NWAVES + wave) * 1024), 16, lane_off, d_x[(j_) / 2], 0, 0); \
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r_x,                                       \
+                (lptr_t)(lds + st_dma + wave * REGION + (j_) * 1024), 16, lane_off, d_x[(j_) < LHN ? 0 : (j_) - LHN], 0, 0); \
     } while (0)
 #define MUXQ_DMA_STEP_DONE                                                                      \
     do {                                                                                        \
-        _Pragma("unroll") for (int i_ = 0; i_ < LH; ++i_) { d_w[i_] += 1024u; d_x[i_] += 1024u; } \
+        _Pragma("unroll") for (int i_ = 0; i_ < LHN; ++i_) d_w[i_] += 1024u;                    \
+        _Pragma("unroll") for (int i_ = 0; i_ < LHM; ++i_) d_x[i_] += 1024u;                    \
         --d_left;                                                                               \
         st_dma = st_dma + STAGE_BYTES == RING_BYTES ? 0 : st_dma + STAGE_BYTES;                 \
     } while (0)
@@ -691,18 +740,19 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
     const int fr = lane & 31, fh = lane >> 5;
     int w_rd[2], x_rd[2];                      // [kk]
     {
-        const int rw = wave_n + fr, rx = wave_m + fr;   // + 32 * f keeps the swizzle bits
+        // (whole blocks of 16 rows behind row fr keep the swizzle bits)
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
-            w_rd[kk] = rw * BK + swizzle<SWZ>(rw, kk * 2 + fh) * 16;
-            x_rd[kk] = TN * BK + rx * BK + swizzle<SWZ>(rx, kk * 2 + fh) * 16;
+            const int in_frag = fr * BK + swizzle<SWZ>(fr, kk * 2 + fh) * 16;
+            w_rd[kk] = wave_n / (16 * LHN) * REGION + in_frag;
+            x_rd[kk] = wave_m / (16 * LHM) * REGION + LHN * 1024 + in_frag;
         }
     }
     // fragment read q of a K sub-step: q < FN -> weight fragment q, else activation fragment q - FN
 #define MUXQ_RD(wf_, xf_, stage_base_, kk_, q_)                                                 \
     do {                                                                                        \
-        if ((q_) < FN) wf_[(q_)] = *(const v4i *)((stage_base_) + w_rd[kk_] + (q_) * 32 * BK);  \
-        else xf_[(q_) - FN] = *(const v4i *)((stage_base_) + x_rd[kk_] + ((q_) - FN) * 32 * BK); \
+        if ((q_) < FN) wf_[(q_)] = *(const v4i *)((stage_base_) + w_rd[kk_] + ((q_) * 2 / LHN) * REGION + ((q_) * 2 % LHN) * 1024); \
+        else xf_[(q_) - FN] = *(const v4i *)((stage_base_) + x_rd[kk_] + (((q_) - FN) * 2 / LHM) * REGION + (((q_) - FN) * 2 % LHM) * 1024); \
     } while (0)
 #define MUXQ_MFMA(q_, wf_, xf_)                                                                 \
     acc[(q_) / FM][(q_) % FM] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf_[(q_) / FM], xf_[(q_) % FM], acc[(q_) / FM][(q_) % FM], 0, 0, 0)
@@ -754,22 +804,16 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
         _Pragma("unroll") for (int q = 0; q < NMFMA; ++q) {                                     \
             MUXQ_MFMA(q, wfA, xfA);                                                             \
             if (q < NFRAG) MUXQ_RD(wfB, xfB, cur_, 1, q);                                       \
-            if (q % DMA_EVERY == 0) MUXQ_DMA(q / DMA_EVERY);                                    \
+            if (q % DMA_EVERY == 0 && q / DMA_EVERY < LOADS) MUXQ_DMA(q / DMA_EVERY);           \
             if (q == NMFMA - 1) MUXQ_DMA_STEP_DONE;                                             \
             MUXQ_PIN;                                                                           \
         }                                                                                       \
         if (FIRST_) {                                                                           \
-            if (consts) {                                                                       \
-                MUXQ_CONST_LOADS;                                                               \
-                if (stores_pending)                                                             \
-                    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds((DEPTH - 1) * LOADS + STORES + CONST_LOADS)); \
-                else                                                                            \
-                    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds((DEPTH - 1) * LOADS + CONST_LOADS)); \
-            } else if (stores_pending) {                                                        \
-                __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds((DEPTH - 1) * LOADS + STORES));       \
-            } else {                                                                            \
-                __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds((DEPTH - 1) * LOADS));                \
-            }                                                                                   \
+            MUXQ_CONST_LOADS;                                                                   \
+            if (stores_pending)                                                                 \
+                __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds((DEPTH - 1) * LOADS + STORES + CONST_LOADS)); \
+            else                                                                                \
+                __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds((DEPTH - 1) * LOADS + CONST_LOADS));  \
             stores_pending = false;                                                             \
         } else {                                                                                \
             __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds((DEPTH - 1) * LOADS));                    \
@@ -792,44 +836,34 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
     // zero-sized resource, whose loads return zeros without touching memory).  Whole
     // offsets go into the per-lane operand: that is the part the buffer range check
     // covers, so channels past N and tokens past M read zeros.
+#define MUXQ_CONST_LOAD(base_, on_, size_, chan_, at_)                                          \
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(                                                   \
+        __builtin_amdgcn_make_buffer_rsrc((on_) ? (void *)(base_) : (void *)a.w_scale, 0, (on_) ? (size_) : 0, RSRC_FLAGS), \
+        (lptr_t)(chan + (chan_)), 4, (at_), 0, 0, 0)
 #define MUXQ_CONST_LOADS                                                                        \
     do {                                                                                        \
-        const __amdgpu_buffer_rsrc_t r_ws_ = __builtin_amdgcn_make_buffer_rsrc(                 \
-            (void *)a.w_scale, 0, a.w_per_channel ? a.N * 4 : 0, RSRC_FLAGS);                   \
-        const __amdgpu_buffer_rsrc_t r_bias_ = __builtin_amdgcn_make_buffer_rsrc(               \
-            a.bias != nullptr ? (void *)a.bias : (void *)a.w_scale, 0,                          \
-            a.bias != nullptr ? a.N * 2 : 0, RSRC_FLAGS);                                       \
-        const __amdgpu_buffer_rsrc_t r_xs_ = __builtin_amdgcn_make_buffer_rsrc(                 \
-            (void *)a.x_scale, 0, a.x_per_token ? a.M * 4 : 0, RSRC_FLAGS);                     \
-        const __amdgpu_buffer_rsrc_t r_zc_ = __builtin_amdgcn_make_buffer_rsrc(                 \
-            has_zc ? (void *)a.cn : (void *)a.w_scale, 0, has_zc ? a.N * 4 : 0, RSRC_FLAGS);    \
-        const bool ztok_ = has_zc && a.x_per_token;                                             \
-        const __amdgpu_buffer_rsrc_t r_zt_ = __builtin_amdgcn_make_buffer_rsrc(                 \
-            ztok_ ? (void *)a.zero_point : (void *)a.w_scale, 0, ztok_ ? a.M * 4 : 0, RSRC_FLAGS); \
         const int n_w_ = cur_tile.tile_n * TN + wave_n, m_w_ = cur_tile.tile_m * TM + wave_m;   \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r_ws_, (lptr_t)chan, 4, (n_w_ + lane) * 4, 0, 0, 0); \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r_ws_, (lptr_t)(chan + 64), 4, (n_w_ + 64 + lane) * 4, 0, 0, 0); \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r_bias_, (lptr_t)(chan + 128), 4, (n_w_ + 2 * lane) * 2, 0, 0, 0); \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r_xs_, (lptr_t)(chan + 192), 4, (m_w_ + lane) * 4, 0, 0, 0); \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r_zc_, (lptr_t)(chan + 256), 4, (n_w_ + lane) * 4, 0, 0, 0); \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r_zc_, (lptr_t)(chan + 320), 4, (n_w_ + 64 + lane) * 4, 0, 0, 0); \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r_zt_, (lptr_t)(chan + 384), 4, (m_w_ + lane) * 4, 0, 0, 0); \
-        const bool rtok_ = OWN == 2;                                                            \
-        const __amdgpu_buffer_rsrc_t r_rho_ = __builtin_amdgcn_make_buffer_rsrc(                \
-            rtok_ ? (void *)aux_rho_tok(a) : (void *)a.w_scale, 0, rtok_ ? a.M * 4 : 0, RSRC_FLAGS); \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r_rho_, (lptr_t)(chan + 448), 4, (m_w_ + lane) * 4, 0, 0, 0); \
+        if constexpr (L_W) {                                                                    \
+            MUXQ_CONST_LOAD(a.w_scale, a.w_per_channel, a.N * 4, 0, (n_w_ + lane) * 4);         \
+            MUXQ_CONST_LOAD(a.w_scale, a.w_per_channel, a.N * 4, 64, (n_w_ + 64 + lane) * 4);   \
+        }                                                                                       \
+        if constexpr (L_B) MUXQ_CONST_LOAD(a.bias, a.bias != nullptr, a.N * 2, 128, (n_w_ + 2 * lane) * 2); \
+        if constexpr (L_T) MUXQ_CONST_LOAD(a.x_scale, a.x_per_token, a.M * 4, 192, (m_w_ + lane) * 4); \
+        if constexpr (L_Z) {                                                                    \
+            MUXQ_CONST_LOAD(a.cn, a.cn != nullptr, a.N * 4, 256, (n_w_ + lane) * 4);            \
+            MUXQ_CONST_LOAD(a.cn, a.cn != nullptr, a.N * 4, 320, (n_w_ + 64 + lane) * 4);       \
+        }                                                                                       \
+        if constexpr (L_ZT)                                                                     \
+            MUXQ_CONST_LOAD(a.zero_point, a.cn != nullptr && a.x_per_token, a.M * 4, 384, (m_w_ + lane) * 4); \
+        if constexpr (L_RHO) MUXQ_CONST_LOAD(aux_rho_tok(a), true, a.M * 4, 448, (m_w_ + lane) * 4); \
     } while (0)
 
-#define MUXQ_EPI_STAGED(SUB_, WCH_, TOK_, BIAS_)                                                  \
-    epilogue_patch<FN, FM, PATCH_ROW, EPI_STAGED, STREAM, false, SUB_, WCH_, TOK_, BIAS_>(                  \
-        a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias)
-#define MUXQ_EPI_GELU(MODE_, ZC_, SUB_, WCH_, TOK_, BIAS_)                                        \
-    epilogue_patch<FN, FM, PATCH_ROW, MODE_, STREAM, ZC_, SUB_, WCH_, TOK_, BIAS_, true>(                   \
-        a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias, mxh)
-    // fused-GELU form: per-wave then per-workgroup column maxima of the tile, behind the
-    // waves' epilogue constants in LDS: [WM][TN] fp16 magnitudes
-    unsigned short *const wg_colmax =
-        (unsigned short *)(lds + RING_BYTES + NWAVES * PATCH_BYTES + NWAVES * kChanFloats * 4);
+    // fused-GELU form: per-wave column maxima of the tile (fp16 magnitudes of the wave's FN * 32 channels), in
+    // the place that only the forms with a factor per token use among the wave's constants
+    static_assert(FN * 32 * 2 <= 64 * 4, "column maxima do not fit");
+    const auto wave_colmax = [&](int wm, int wn) {
+        return (unsigned short *)((float *)(lds + CONST_AT) + (wm * WN + wn) * kChanFloats + 448);
+    };
 
     const int t_all = t_aux + k_tiles;
     while (cur_tile.j >= 0) {
@@ -853,14 +887,14 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
                     // the form that loads its constants itself
                     float rho_t[FM];
                     const float *rho_g = aux_rho_tok(a);
-                    if (!consts) {
+                    if (!CONSTS) {
 #pragma unroll
                         for (int fm = 0; fm < FM; ++fm)
                             rho_t[fm] = rho_g[min(cur_tile.tile_m * TM + wave_m + fm * 32 + (lane & 31), a.M - 1)];
                     }
                     __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds(0));
                     asm volatile("" ::: "memory");       // the reads below stay behind the wait
-                    if (consts) {
+                    if (CONSTS) {
 #pragma unroll
                         for (int fm = 0; fm < FM; ++fm) rho_t[fm] = chan[448 + fm * 32 + (lane & 31)];
                     }
@@ -872,21 +906,16 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
         }
 
         // ---- epilogue of this tile; the ring keeps its loads in flight meanwhile ----
+        unsigned char *const patch = lds + RING_BYTES + wave * PATCH_BYTES;
         const int m_base = cur_tile.tile_m * TM + wave_m, n_base = cur_tile.tile_n * TN + wave_n;
-        const bool full = cur_tile.tile_m * TM + TM <= a.M && cur_tile.tile_n * TN + TN <= a.N;
+        [[maybe_unused]] const bool full = cur_tile.tile_m * TM + TM <= a.M && cur_tile.tile_n * TN + TN <= a.N;
         // a one-step tile has not yet waited past its constants' loads
-        if (consts && t_all == 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+        if (CONST_LOADS > 0 && t_all == 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
         if constexpr (GELU) {
             uint4 mxh[FN / 2];
 #pragma unroll
             for (int h = 0; h < FN / 2; ++h) mxh[h] = make_uint4(0, 0, 0, 0);
-            if (plain && has_zc && sub_bias == 0) MUXQ_EPI_GELU(EPI_PLAIN, true, false, -1, -1, -1);
-            else if (plain && has_zc) MUXQ_EPI_GELU(EPI_PLAIN, true, true, -1, -1, -1);
-            else if (plain) MUXQ_EPI_GELU(EPI_PLAIN, false, true, -1, -1, -1);
-            else if (staged && !a.x_per_token && !a.w_per_channel && sub_bias == 0)
-                MUXQ_EPI_GELU(EPI_STAGED, false, false, 0, 0, 1);      // the usual c_fc: a bias, one scale each
-            else if (staged) MUXQ_EPI_GELU(EPI_STAGED, false, true, -1, -1, -1);
-            else MUXQ_EPI_GELU(EPI_LOADS, false, true, -1, -1, -1);
+            epilogue_patch<FN, FM, PATCH_ROW, EPI, STREAM, true>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, z_launch, sub_bias, mxh);
             if (a.slab_out != nullptr) {
                 // A lane holds the maxima of its 8 channels of each half over the rows it stored;
                 // the 8 lane groups of a wave hold different rows: fold them through the wave's
@@ -906,7 +935,7 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
                         uint4 m = make_uint4(0, 0, 0, 0);
 #pragma unroll
                         for (int g = 0; g < 8; ++g) m = absmax_step(m, *(const uint4 *)(patch + (g * 8 + lane) * 16));
-                        *(uint4 *)(wg_colmax + (wave / WN) * TN + wave_n + h * 64 + lane * 8) = m;
+                        *(uint4 *)(wave_colmax(wave / WN, wave % WN) + h * 64 + lane * 8) = m;
                     }
                 }
                 __builtin_amdgcn_s_waitcnt(waitcnt_lds_only());
@@ -918,38 +947,15 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
                 if (lane < CH_PER_WAVE / 8 && n < a.slab_ld) {
                     uint4 m = make_uint4(0, 0, 0, 0);
 #pragma unroll
-                    for (int wm = 0; wm < WM; ++wm) m = absmax_step(m, *(const uint4 *)(wg_colmax + wm * TN + c0));
+                    for (int wm = 0; wm < WM; ++wm) m = absmax_step(m, *(const uint4 *)(wave_colmax(wm, c0 / (FN * 32)) + c0 % (FN * 32)));
                     *(uint4 *)(a.slab_out + (size_t)cur_tile.tile_m * a.slab_ld + n) = m;
                 }
             }
-        } else
-        if (plain && has_zc && sub_bias == 0) {
-            epilogue_patch<FN, FM, PATCH_ROW, EPI_PLAIN, STREAM, true, false>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, 0);
-        } else if (plain && has_zc) {
-            epilogue_patch<FN, FM, PATCH_ROW, EPI_PLAIN, STREAM, true>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias);
-        } else if (plain) {
-            epilogue_patch<FN, FM, PATCH_ROW, EPI_PLAIN, STREAM>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias);
-        } else if (staged && !a.x_per_token && sub_bias == 0) {
-            // one activation scale, the accumulators' offset folded away: per-channel weight
-            // scales with or without a bias, or a bias alone
-            if (!a.w_per_channel) MUXQ_EPI_STAGED(false, 0, 0, 1);
-            else if (a.bias != nullptr) MUXQ_EPI_STAGED(false, 1, 0, 1);
-            else MUXQ_EPI_STAGED(false, 1, 0, 0);
-        } else if (staged && !a.x_per_token) {
-            // the same with the offset taken off here (no zero point: the naive pipeline)
-            if (!a.w_per_channel) MUXQ_EPI_STAGED(true, 0, 0, 1);
-            else if (a.bias != nullptr) MUXQ_EPI_STAGED(true, 1, 0, 1);
-            else MUXQ_EPI_STAGED(true, 1, 0, 0);
-        } else if (staged && a.w_per_channel && a.x_per_token) {
-            // the per-vector setting
-            if (a.bias != nullptr) MUXQ_EPI_STAGED(true, 1, 1, 1);
-            else MUXQ_EPI_STAGED(true, 1, 1, 0);
-        } else if (staged) {
-            epilogue_patch<FN, FM, PATCH_ROW, EPI_STAGED, STREAM>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias);
         } else {
-            epilogue_patch<FN, FM, PATCH_ROW, EPI_LOADS, STREAM>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, s_tensor, z_launch, sub_bias);
+            epilogue_patch<FN, FM, PATCH_ROW, EPI, STREAM, false>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, z_launch, sub_bias, nullptr);
         }
-        if ((plain || staged) && full && (!GELU || a.slab_out != nullptr)) {
+        // (a store is issued for a partial tile as well; only the store of the column maxima is not)
+        if (EPI != kEpiLoads && (!GELU || (full && a.slab_out != nullptr))) {
             stores_pending = true;           // exactly STORES stores and no loads were issued
         } else {
             __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // unknown number of vector-memory operations: drain
@@ -969,22 +975,21 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
 #undef MUXQ_RD
 #undef MUXQ_MFMA
 #undef MUXQ_PIN
-#undef MUXQ_EPI_STAGED
-#undef MUXQ_EPI_GELU
+#undef MUXQ_CONST_LOAD
 }
 
-template <int STAGES, int OWN, bool GELU, bool STREAM>
+template <int STAGES, int EPI, int OWN, bool GELU, bool STREAM>
 __global__ __launch_bounds__(512) void k_gemm_i8_persist8(const GemmArgs a, const TileMap tm)
 {
-    gemm_persist_body<STAGES, 8, 4, 2, OWN, GELU, STREAM>(a, tm);
+    gemm_persist_body<STAGES, 2, 4, 4, 2, EPI, OWN, GELU, STREAM>(a, tm);
 }
 
 // 128 x 128 tiles, 4 waves of 64 x 64: for problems whose 256 x 256 tiles would leave the last, or the
 // only, round on the chip half empty.
-template <int STAGES, int OWN, bool GELU, bool STREAM>
+template <int STAGES, int EPI, int OWN, bool GELU, bool STREAM>
 __global__ __launch_bounds__(256) void k_gemm_i8_persist4(const GemmArgs a, const TileMap tm)
 {
-    gemm_persist_body<STAGES, 4, 2, 2, OWN, GELU, STREAM>(a, tm);
+    gemm_persist_body<STAGES, 2, 2, 2, 2, EPI, OWN, GELU, STREAM>(a, tm);
 }
 
 // --------------------------------------------------------------------------
@@ -1468,12 +1473,15 @@ TileMap make_tile_map(const GemmArgs &a, int TN, int TM, int &grid, bool persist
 }
 
 // LDS bytes of a persistent kernel: the operand ring, the waves' epilogue patches and constants.
-template <int STAGES, int NWAVES>
+enum PersistTileForm { kTile256, kTile128 };
+constexpr int tile_n_of(int t) { return t == kTile256 ? 256 : 128; }
+constexpr int tile_m_of(int t) { return t == kTile128 ? 128 : 256; }
+constexpr int waves_of(int t) { return t == kTile256 ? 8 : 4; }
+template <int STAGES, int TILE>
 constexpr int persist_lds_bytes()
 {
-    constexpr int TILE = NWAVES == 8 ? 256 : 128;
-    return STAGES * 2 * TILE * BK + NWAVES * (32 * (2 * 64 + 16) + kChanFloats * 4) +
-           (NWAVES / 2) * TILE * 2;          // + the fused-GELU form's column maxima [WM][TN] fp16
+    return STAGES * (tile_n_of(TILE) + tile_m_of(TILE)) * BK +
+           waves_of(TILE) * (32 * (2 * 64 + 16) + kChanFloats * 4);
 }
 
 // K steps whose loads a workgroup of k_gemm_i8_small_deep issues together (64 staging registers,
@@ -1482,25 +1490,60 @@ constexpr int kDeepSteps = 8;
 
 typedef void (*persist_kernel_t)(const GemmArgs, const TileMap);
 
-// The persistent kernels of one tile size: Aux on Body's scale / on its own / on its own per token /
-// the fused GELU, each with streaming and with plain stores of Y.
-constexpr int kPersistForms = 8;
-template <int STAGES, int NWAVES>
-persist_kernel_t persist_kernel(int form)
+// The persistent kernels of one tile: what is fused or rescaled x what the epilogue applies x how Y is stored.
+// nullptr: not built, kEpiGeneral does it.
+enum PersistKind { kKindUsual, kKindOwn, kKindOwnToken, kKindGelu, kKinds };
+template <int TILE, int EPI, int OWN, bool GELU>
+persist_kernel_t persist_kernel_of(bool stream)
 {
-#define MUXQ_FORM(OWN_, GELU_, STREAM_) \
-    (NWAVES == 8 ? k_gemm_i8_persist8<STAGES, OWN_, GELU_, STREAM_> : k_gemm_i8_persist4<STAGES, OWN_, GELU_, STREAM_>)
-    switch (form) {
-    case 0: return MUXQ_FORM(0, false, false);
-    case 1: return MUXQ_FORM(0, false, true);
-    case 2: return MUXQ_FORM(1, false, false);
-    case 3: return MUXQ_FORM(1, false, true);
-    case 4: return MUXQ_FORM(2, false, false);
-    case 5: return MUXQ_FORM(2, false, true);
-    case 6: return MUXQ_FORM(0, true, false);
-    default: return MUXQ_FORM(0, true, true);
-    }
+    constexpr int STAGES = 3;
+#define MUXQ_FORM(STREAM_)                                                         \
+    (TILE == kTile256 ? k_gemm_i8_persist8<STAGES, EPI, OWN, GELU, STREAM_> : k_gemm_i8_persist4<STAGES, EPI, OWN, GELU, STREAM_>)
+    return stream ? MUXQ_FORM(true) : MUXQ_FORM(false);
 #undef MUXQ_FORM
+}
+template <int TILE>
+persist_kernel_t persist_kernel(int kind, int epi, bool stream)
+{
+#define MUXQ_CASE(KIND_, EPI_, OWN_, GELU_) \
+    case KIND_ * kEpis + EPI_: return persist_kernel_of<TILE, EPI_, OWN_, GELU_>(stream)
+    switch (kind * kEpis + epi) {
+        MUXQ_CASE(kKindUsual, kEpiLoads, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiGeneral, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiPlain, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiBias, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiChan, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiChanBias, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiPlainZ, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiBiasZ, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiChanZ, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiChanBiasZ, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiToken, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiTokenBias, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiVector, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiVectorBias, 0, false);
+        MUXQ_CASE(kKindOwn, kEpiLoads, 1, false);
+        MUXQ_CASE(kKindOwn, kEpiGeneral, 1, false);
+        MUXQ_CASE(kKindOwn, kEpiPlainZ, 1, false);
+        MUXQ_CASE(kKindOwn, kEpiBiasZ, 1, false);
+        MUXQ_CASE(kKindOwn, kEpiChanZ, 1, false);
+        MUXQ_CASE(kKindOwn, kEpiChanBiasZ, 1, false);
+        MUXQ_CASE(kKindOwnToken, kEpiLoads, 2, false);
+        MUXQ_CASE(kKindOwnToken, kEpiGeneral, 2, false);
+        MUXQ_CASE(kKindOwnToken, kEpiToken, 2, false);
+        MUXQ_CASE(kKindOwnToken, kEpiTokenBias, 2, false);
+        MUXQ_CASE(kKindOwnToken, kEpiVector, 2, false);
+        MUXQ_CASE(kKindOwnToken, kEpiVectorBias, 2, false);
+        MUXQ_CASE(kKindGelu, kEpiLoads, 0, true);
+        MUXQ_CASE(kKindGelu, kEpiGeneral, 0, true);
+        MUXQ_CASE(kKindGelu, kEpiPlainZ, 0, true);
+        MUXQ_CASE(kKindGelu, kEpiBiasZ, 0, true);
+        MUXQ_CASE(kKindGelu, kEpiChanBiasZ, 0, true);
+        MUXQ_CASE(kKindGelu, kEpiTokenBias, 0, true);
+        MUXQ_CASE(kKindGelu, kEpiVectorBias, 0, true);
+    default: return nullptr;
+    }
+#undef MUXQ_CASE
 }
 
 // Whether Y goes out as a stream.  Rows on 128-byte lines: a store instruction writes whole lines, and Y, which
@@ -1517,9 +1560,33 @@ bool stream_rows(const GemmArgs &a)
     return start % 128 == 0 || (start % 64 == 0 && (mib < 48 || mib >= 256));
 }
 
-int persist_form(const GemmArgs &a)
+template <int TILE>
+persist_kernel_t persist_kernel_for(const GemmArgs &a)
 {
-    return 2 * (a.gelu ? 3 : !a.aux_own_scale ? 0 : a.x_per_token ? 2 : 1) + (stream_rows(a) ? 1 : 0);
+    const int kind = a.gelu ? kKindGelu : !a.aux_own_scale ? kKindUsual : a.x_per_token ? kKindOwnToken : kKindOwn;
+    const bool stream = stream_rows(a);
+    int epi = kEpiGeneral;
+    // rows of Y so far apart that 32 of them are beyond a buffer's 32-bit offsets are stored by address
+    if (a.dbg_acc != nullptr || a.ldy >= 1 << 25) epi = kEpiLoads;
+    else if (!a.x_per_token)
+        epi = (a.cn != nullptr ? kEpiPlainZ : kEpiPlain) + (a.w_per_channel ? 2 : 0) + (a.bias != nullptr ? 1 : 0);
+    else if (a.cn != nullptr)
+        epi = (a.w_per_channel ? kEpiVector : kEpiToken) + (a.bias != nullptr ? 1 : 0);
+    const persist_kernel_t k = persist_kernel<TILE>(kind, epi, stream);
+    return k != nullptr ? k : persist_kernel<TILE>(kind, kEpiGeneral, stream);
+}
+
+template <int STAGES, int TILE>
+hipError_t persist_lds_attributes()
+{
+    for (int i = 0; i < kKinds * kEpis * 2; ++i) {
+        const persist_kernel_t k = persist_kernel<TILE>(i / 2 / kEpis, i / 2 % kEpis, i % 2 != 0);
+        if (k == nullptr) continue;
+        const hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 persist_lds_bytes<STAGES, TILE>());
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // What the launcher needs to know about a device, found once per device (gemm_prepare_device).
@@ -1532,14 +1599,8 @@ hipError_t prepare_current_device(int dev)
     std::lock_guard<std::mutex> lock(g_prepare_mutex);
     if (g_device_cus[dev].load(std::memory_order_acquire) != 0) return hipSuccess;
     hipError_t e;
-    for (int form = 0; form < kPersistForms; ++form) {
-        e = hipFuncSetAttribute((const void *)persist_kernel<3, 8>(form), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                persist_lds_bytes<3, 8>());
-        if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute((const void *)persist_kernel<3, 4>(form), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                persist_lds_bytes<3, 4>());
-        if (e != hipSuccess) return e;
-    }
+    if ((e = persist_lds_attributes<3, kTile256>()) != hipSuccess) return e;
+    if ((e = persist_lds_attributes<3, kTile128>()) != hipSuccess) return e;
     e = hipFuncSetAttribute((const void *)k_gemm_i8_small_deep<kDeepSteps>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, kDeepSteps * 128 * BK);
     if (e != hipSuccess) return e;
@@ -1566,23 +1627,21 @@ hipError_t current_device_cus(int &n_cu)
     return hipSuccess;
 }
 
-template <int STAGES, int NWAVES>
+template <int STAGES, int TILE>
 hipError_t launch_persist(const GemmArgs &a, hipStream_t s)
 {
     static_assert(STAGES == 3, "gemm_prepare_device sets the LDS attribute of the 3-stage forms");
-    static_assert(NWAVES == 8 || NWAVES == 4, "built forms");
-    constexpr int TILE = NWAVES == 8 ? 256 : 128;
     int total;
-    const TileMap tm = make_tile_map(a, TILE, TILE, total, true, NWAVES == 8 ? 32 : 64);
-    constexpr int lds_bytes = persist_lds_bytes<STAGES, NWAVES>();
+    const TileMap tm = make_tile_map(a, tile_n_of(TILE), tile_m_of(TILE), total, true, TILE == kTile256 ? 32 : 64);
+    constexpr int lds_bytes = persist_lds_bytes<STAGES, TILE>();
     constexpr int wgs_per_cu = 160 * 1024 / lds_bytes;     // by LDS; registers allow at least as many
     static_assert(wgs_per_cu >= 1, "ring too deep");
-    const persist_kernel_t kern = persist_kernel<STAGES, NWAVES>(persist_form(a));
+    const persist_kernel_t kern = persist_kernel_for<TILE>(a);
     int n_cu = 0;
     const hipError_t e = current_device_cus(n_cu);
     if (e != hipSuccess) return e;
     const int grid = total < n_cu * wgs_per_cu ? total : n_cu * wgs_per_cu;
-    return launch_kernel(kern, dim3(grid), dim3(NWAVES * 64), lds_bytes, s, a, tm);
+    return launch_kernel(kern, dim3(grid), dim3(waves_of(TILE) * 64), lds_bytes, s, a, tm);
 }
 
 hipError_t launch_small(const GemmArgs &a, hipStream_t s)
@@ -1670,8 +1729,8 @@ int gemm_tile_rows(int M, int N, int k_pad)
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
 {
     switch (gemm_form(a.M, a.N, a.k_pad)) {
-    case kPersist256: return launch_persist<3, 8>(a, s);
-    case kPersist128: return launch_persist<3, 4>(a, s);
+    case kPersist256: return launch_persist<3, kTile256>(a, s);
+    case kPersist128: return launch_persist<3, kTile128>(a, s);
     case kDirect16x16: return launch_direct<1, 1, 8, 8>(a, s);
     case kDirect16x32: return launch_direct<1, 2, 6, 4>(a, s);
     case kDirect32x32: return launch_direct<2, 2, 6, 4>(a, s);

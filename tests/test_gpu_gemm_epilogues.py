@@ -1,0 +1,61 @@
+"""The epilogues of the persistent GEMM, one kernel for each combination of scales, bias, zero point, GELU and way
+of storing Y, on partial tiles in both directions and several tiles per workgroup.  Y against the CPU oracle, exact
+(the order of binary32 operations is the same on both sides)."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import B, check_mlp, check_own_scale, check_plain_y, orc, rows_every_block, sample_rows, synth
+from paper_2604_04701_amd.synth import Case
+
+pytestmark = pytest.mark.gpu
+U = (20.0, 100.0)
+FORMS = {"128x128": (2100, 520, 1544), "256x256": (3077, 136, 4808)}
+
+
+@pytest.mark.parametrize("bias_seed", [None, 7])
+@pytest.mark.parametrize("w_gran", ["tensor", "channel"])
+@pytest.mark.parametrize("x_gran", ["tensor", "token", "naive"])
+@pytest.mark.parametrize("form", FORMS)
+def test_every_combination_of_scales_and_bias(form, x_gran, w_gran, bias_seed):
+    """naive: the plain INT8 pipeline, which has no zero point."""
+    M, K, N = FORMS[form]
+    rows = rows_every_block(M, 11)
+    case = Case("epilogue", M, K, N, 5, U, 900 + M)
+    if x_gran != "naive":
+        check_plain_y(case, rows=rows, w_gran=w_gran, bias_seed=bias_seed, x_gran=x_gran)
+        return
+    X, W, _ = synth.make_case(case)
+    bias = None if bias_seed is None else np.random.default_rng(bias_seed).standard_normal(N).astype(np.float16)
+    w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(W).cuda(), w_gran)
+    Y = B.muxq_linear_naive_int8(torch.from_numpy(X).cuda(), w_q, w_s, N, w_gran,
+                                 bias=None if bias is None else torch.from_numpy(bias).cuda())
+    o = orc.linear(X, W, r_cap=0, w_gran=w_gran, bias16=bias, rows=rows)
+    assert (Y.cpu().numpy()[rows] == o["y16"]).all()
+
+
+@pytest.mark.parametrize("w_gran,x_gran", [("tensor", "tensor"), ("channel", "tensor"), ("tensor", "token"), ("channel", "token")])
+def test_gelu_with_every_kind_of_scales(w_gran, x_gran):
+    check_mlp(1500, 264, 2056, 136, 910, w_gran=w_gran, x_gran=x_gran)
+
+
+@pytest.mark.parametrize("w_gran,x_gran", [("tensor", "tensor"), ("channel", "tensor"), ("tensor", "token"), ("channel", "token")])
+@pytest.mark.parametrize("bias_seed", [None, 8])
+def test_aux_on_its_own_scale_with_every_kind_of_scales(w_gran, x_gran, bias_seed):
+    check_own_scale(Case("epilogue_own", 1500, 264, 2056, 6, U, 920), w_gran=w_gran, x_gran=x_gran, bias_seed=bias_seed)
+
+
+@pytest.mark.parametrize("ldy", [(1 << 25) - 8, 1 << 25])
+def test_rows_of_y_far_apart(ldy):
+    """Row strides at the end of what a buffer's 32-bit offsets reach, and one beyond it."""
+    M, K, N = 129, 712, 16384
+    rng = np.random.default_rng(ldy)
+    X, _ = synth.make_x(M, K, 5, U, rng)
+    W = synth.make_w(K, N, rng)
+    out = torch.empty((M, ldy), dtype=torch.float16, device="cuda")
+    out[:, N:N + 64] = 7.0
+    w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(W).cuda())
+    B.muxq_linear(torch.from_numpy(X).cuda(), w_q, w_s, N, out=out[:, :N])
+    rows = sample_rows(M, 60, 3)
+    assert (out[:, :N].cpu().numpy()[rows] == orc.linear(X, W, rows=rows)["y16"]).all()
+    assert (out[:, N:N + 64] == 7.0).all()
