@@ -26,7 +26,7 @@
 // through, the epilogue removes it).  The weights are the first MFMA operand and the
 // narrow activation codes the second: the other way round draws more.
 //
-// Four kernels share that scheme:
+// Five kernels share that scheme:
 //   k_gemm_i8_persist8  256 x 256 tile, 8 waves (2 per SIMD), K step 64, one
 //                   persistent workgroup per CU.  Operand tiles go global -> LDS
 //                   directly (buffer_load_dwordx4 ... lds, no staging registers)
@@ -38,6 +38,8 @@
 //   k_gemm_i8_persist4  the same kernel body with a 128 x 128 tile and 4 waves,
 //                   two workgroups per CU, where its rounds of tiles are fewer
 //                   than three times those of the 256 x 256 form (gemm_form).
+//   k_gemm_i8_persist_half  the same with a 128 (n) x 256 (m) tile and 4 waves, two workgroups per
+//                   CU, each with its own barriers: one computes under the other's epilogue.
 //   k_gemm_i8_direct  small tiles (16 x 16 to 64 x 64), operands from memory straight to
 //                   registers, the waves of a workgroup split K: for problems
 //                   with too few larger tiles to fill the chip.
@@ -547,7 +549,8 @@ constexpr int waitcnt_lds_only() { return waitcnt_vm_lds(63); }
 // during the last K steps of the current tile, so there is no load latency at
 // tile boundaries, and the stores of a tile's epilogue drain while the next
 // tile is already being computed.  The epilogue's LDS patches lie behind the
-// ring, so the ring keeps filling during an epilogue.
+// ring, so the ring keeps filling during an epilogue (or, OVERLAY, in the one stage
+// that nothing is loaded into meanwhile).
 //
 // The DMA instructions of a K step (four, in the 256 x 256 form) are spread over the first eight MFMAs
 // (one per two MFMAs) instead of being issued back to back: a burst of 32 DMA
@@ -591,7 +594,7 @@ __device__ __forceinline__ PersistTile tile_at(const TileMap &map, int j, int st
 }
 
 // The tile is WN x WM waves of FN x FM fragments of 32 x 32.  Built as 2 x 4 waves of
-// 4 x 2 (256 x 256, two waves per SIMD, each 128 (n) x 64 (m))
+// 4 x 2 (256 x 256, two waves per SIMD, each 128 (n) x 64 (m)), 1 x 4 of 4 x 2 (128 x 256)
 // and 2 x 2 of 2 x 2 (128 x 128, for problems with few tiles).
 // OWN (compile time): the launch's Aux codes have a scale of their own (GemmArgs::aux_own_scale),
 // 1 with one activation scale per launch, 2 with one per token; forms of their own so that the
@@ -619,7 +622,7 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
     // global stores per wave per full tile (with the fused GELU one more: the column maxima)
     constexpr int STORES = FM * (FN / 2) * 4 + (GELU ? 1 : 0);
     static_assert(LOADS <= NMFMA && NFRAG <= NMFMA, "schedule does not fit");
-
+    constexpr bool OVERLAY = REGION >= PATCH_BYTES;
     static_assert((DEPTH - 1) * LOADS + STORES + 8 < 64, "vmcnt has 6 bits");
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     typedef __attribute__((address_space(3))) void *lptr_t;
@@ -627,7 +630,7 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave_n = (wave % WN) * (FN * 32), wave_m = (wave / WN) * (FM * 32);
-    constexpr int CONST_AT = RING_BYTES + NWAVES * PATCH_BYTES;
+    constexpr int CONST_AT = RING_BYTES + (OVERLAY ? 0 : NWAVES * PATCH_BYTES);
     float *const chan = (float *)(lds + CONST_AT) + wave * kChanFloats;
 
     const int t_aux = aux_tiles(a);
@@ -906,7 +909,8 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
         }
 
         // ---- epilogue of this tile; the ring keeps its loads in flight meanwhile ----
-        unsigned char *const patch = lds + RING_BYTES + wave * PATCH_BYTES;
+        unsigned char *const patch = OVERLAY ? lds + (st_cur == 0 ? RING_BYTES - STAGE_BYTES : st_cur - STAGE_BYTES) + wave * REGION
+                                             : lds + RING_BYTES + wave * PATCH_BYTES;
         const int m_base = cur_tile.tile_m * TM + wave_m, n_base = cur_tile.tile_n * TN + wave_n;
         [[maybe_unused]] const bool full = cur_tile.tile_m * TM + TM <= a.M && cur_tile.tile_n * TN + TN <= a.N;
         // a one-step tile has not yet waited past its constants' loads
@@ -982,6 +986,15 @@ template <int STAGES, int EPI, int OWN, bool GELU, bool STREAM>
 __global__ __launch_bounds__(512) void k_gemm_i8_persist8(const GemmArgs a, const TileMap tm)
 {
     gemm_persist_body<STAGES, 2, 4, 4, 2, EPI, OWN, GELU, STREAM>(a, tm);
+}
+
+// 128 (n) x 256 (m) tiles, 4 waves of 128 x 64, two workgroups per CU.  The epilogue's patches lie in the ring, in the
+// stage that was computed last: every wave's in the part that it will load itself, so that its own loads follow its own
+// stores to Y, and no wave still reads operands there (the barrier of the tile's last step came after the last read).
+template <int STAGES, int EPI, int OWN, bool GELU, bool STREAM>
+__global__ __launch_bounds__(256, 2) void k_gemm_i8_persist_half(const GemmArgs a, const TileMap tm)
+{
+    gemm_persist_body<STAGES, 1, 4, 4, 2, EPI, OWN, GELU, STREAM>(a, tm);
 }
 
 // 128 x 128 tiles, 4 waves of 64 x 64: for problems whose 256 x 256 tiles would leave the last, or the
@@ -1473,7 +1486,7 @@ TileMap make_tile_map(const GemmArgs &a, int TN, int TM, int &grid, bool persist
 }
 
 // LDS bytes of a persistent kernel: the operand ring, the waves' epilogue patches and constants.
-enum PersistTileForm { kTile256, kTile128 };
+enum PersistTileForm { kTile256, kTile128, kTileHalf };
 constexpr int tile_n_of(int t) { return t == kTile256 ? 256 : 128; }
 constexpr int tile_m_of(int t) { return t == kTile128 ? 128 : 256; }
 constexpr int waves_of(int t) { return t == kTile256 ? 8 : 4; }
@@ -1481,7 +1494,7 @@ template <int STAGES, int TILE>
 constexpr int persist_lds_bytes()
 {
     return STAGES * (tile_n_of(TILE) + tile_m_of(TILE)) * BK +
-           waves_of(TILE) * (32 * (2 * 64 + 16) + kChanFloats * 4);
+           waves_of(TILE) * ((TILE == kTileHalf ? 0 : 32 * (2 * 64 + 16)) + kChanFloats * 4);
 }
 
 // K steps whose loads a workgroup of k_gemm_i8_small_deep issues together (64 staging registers,
@@ -1498,7 +1511,9 @@ persist_kernel_t persist_kernel_of(bool stream)
 {
     constexpr int STAGES = 3;
 #define MUXQ_FORM(STREAM_)                                                         \
-    (TILE == kTile256 ? k_gemm_i8_persist8<STAGES, EPI, OWN, GELU, STREAM_> : k_gemm_i8_persist4<STAGES, EPI, OWN, GELU, STREAM_>)
+    (TILE == kTile256   ? k_gemm_i8_persist8<STAGES, EPI, OWN, GELU, STREAM_>      \
+     : TILE == kTile128 ? k_gemm_i8_persist4<STAGES, EPI, OWN, GELU, STREAM_>      \
+                        : k_gemm_i8_persist_half<STAGES, EPI, OWN, GELU, STREAM_>)
     return stream ? MUXQ_FORM(true) : MUXQ_FORM(false);
 #undef MUXQ_FORM
 }
@@ -1601,6 +1616,7 @@ hipError_t prepare_current_device(int dev)
     hipError_t e;
     if ((e = persist_lds_attributes<3, kTile256>()) != hipSuccess) return e;
     if ((e = persist_lds_attributes<3, kTile128>()) != hipSuccess) return e;
+    if ((e = persist_lds_attributes<3, kTileHalf>()) != hipSuccess) return e;
     e = hipFuncSetAttribute((const void *)k_gemm_i8_small_deep<kDeepSteps>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, kDeepSteps * 128 * BK);
     if (e != hipSuccess) return e;
@@ -1675,7 +1691,7 @@ hipError_t gemm_prepare_device()
 
 enum GemmForm {
     kSmall64,         // register-staged 64 x 64
-    kPersist128, kPersist256,
+    kPersist128, kPersist256, kPersistHalf,
     kDirect16x16, kDirect16x32, kDirect32x32, kDirect32x64, kDirect64x64       // channels x tokens
 };
 
@@ -1711,13 +1727,30 @@ static GemmForm gemm_form(int M, int N, int k_pad)
     // wins where its last round is full enough: 8192 x 1024 -> 1024 14 us against 19 us,
     // 16384 x 1024 -> 1024 24 us against 21 us.
     const long rounds128 = (t128 + 255) / 256, rounds256 = (t256 + 255) / 256;
-    return rounds128 < 3 * rounds256 || (rounds256 >= 3 && rounds128 == 3 * rounds256) ? kPersist128 : kPersist256;
+    const bool square128 = rounds128 < 3 * rounds256 || (rounds256 >= 3 && rounds128 == 3 * rounds256);
+    // 128 x 256, two workgroups per CU.  A round of 512 tiles does the work of one of 256 tiles of 256 x 256 and
+    // computes one tile under the other's epilogue, but fetches half as much again per K step: by the sweep (in K steps) 1.15
+    // steps + 4 against steps + 7, and a last round of at most 256 tiles, one to a CU, is 0.62 of a full one.  us, 256 x 256 /
+    // 128 x 256: 8192 x 1024 -> 4096 55.3 / 53.5, 5239 x 1728 -> 7224 122 / 108, 10796 x 1480 -> 3664 with GELU 123 / 110,
+    // 16384 x 1280 -> 3840 111 / 117, 8192 x 4096 -> 16384 434 / 480 (K below 512 was not in the sweep).
+    // Against 128 x 128 it reads a quarter less through LDS, which pays with a long K: a round 0.415 steps - 0.3 (16384 x 5120
+    // -> 1280 203 / 191, 4352 x 5120 -> 4680 142 / 132, 16059 x 1432 -> 2152 107 / 102), and in two nearly full rounds
+    // from K = 2048 on (8192 x 4096 -> 1024 80.3 / 76.5; 8192 x 1024 -> 1024 31.2 / 31.9; with 384 tiles even, with 270 7 %
+    // slower).
+    const long t_half = tiles(128, 256), last = t_half % 512, steps = k_pad / 64 + 1;
+    const long half = (100 * (t_half / 512) + (last == 0 ? 0 : last <= 256 ? 62 : 100)) * (115 * steps + 400) / 100;
+    if (square128) {
+        if (rounds128 == 2 ? k_pad >= 2048 && t128 > 448
+                           : rounds128 >= 5 && k_pad >= 1024 && 10 * half < rounds128 * (415 * steps - 300)) return kPersistHalf;
+        return kPersist128;
+    }
+    return k_pad >= 512 && half < rounds256 * 100 * (steps + 7) ? kPersistHalf : kPersist256;
 }
 
 int gemm_tile_rows(int M, int N, int k_pad)
 {
     switch (gemm_form(M, N, k_pad)) {
-    case kPersist256: return 256;
+    case kPersist256: case kPersistHalf: return 256;
     case kPersist128: return 128;
     case kDirect64x64: case kDirect32x64: return 64;
     case kDirect32x32: case kDirect16x32: return 32;
@@ -1731,6 +1764,7 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
     switch (gemm_form(a.M, a.N, a.k_pad)) {
     case kPersist256: return launch_persist<3, kTile256>(a, s);
     case kPersist128: return launch_persist<3, kTile128>(a, s);
+    case kPersistHalf: return launch_persist<3, kTileHalf>(a, s);
     case kDirect16x16: return launch_direct<1, 1, 8, 8>(a, s);
     case kDirect16x32: return launch_direct<1, 2, 6, 4>(a, s);
     case kDirect32x32: return launch_direct<2, 2, 6, 4>(a, s);

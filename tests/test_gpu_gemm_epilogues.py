@@ -5,12 +5,12 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_common import B, check_mlp, check_own_scale, check_plain_y, orc, rows_every_block, sample_rows, synth
+from gpu_common import B, check_case, check_mlp, check_own_scale, check_plain_y, orc, rows_every_block, sample_rows, synth
 from paper_2604_04701_amd.synth import Case
 
 pytestmark = pytest.mark.gpu
 U = (20.0, 100.0)
-FORMS = {"128x128": (2100, 520, 1544), "256x256": (3077, 136, 4808)}
+FORMS = {"128x128": (2100, 520, 1544), "256x256": (3077, 136, 4808), "128x256": (3400, 520, 6304)}
 
 
 @pytest.mark.parametrize("bias_seed", [None, 7])
@@ -34,9 +34,18 @@ def test_every_combination_of_scales_and_bias(form, x_gran, w_gran, bias_seed):
     assert (Y.cpu().numpy()[rows] == o["y16"]).all()
 
 
+@pytest.mark.parametrize("M,K,N", [(1500, 264, 2056), (3400, 520, 6304)])
 @pytest.mark.parametrize("w_gran,x_gran", [("tensor", "tensor"), ("channel", "tensor"), ("tensor", "token"), ("channel", "token")])
-def test_gelu_with_every_kind_of_scales(w_gran, x_gran):
-    check_mlp(1500, 264, 2056, 136, 910, w_gran=w_gran, x_gran=x_gran)
+def test_gelu_with_every_kind_of_scales(w_gran, x_gran, M, K, N):
+    check_mlp(M, K, N, 136, 910, w_gran=w_gran, x_gran=x_gran)
+
+
+@pytest.mark.parametrize("M,K,N", [(8190, 2120, 1016), (3400, 520, 6304), (8300, 4104, 2312)])
+def test_128x256_tiles(M, K, N):
+    """One tile per CU, ragged in both directions; several Aux steps; two tiles for some workgroups and K = 65 steps."""
+    rows = rows_every_block(M, 12)
+    check_plain_y(Case("half", M, K, N, 150, U, 930 + K), rows=rows, w_gran="channel", bias_seed=3, r_cap=192)
+    check_case(Case("half", M, K, N, 3, U, 931 + K), rows=sample_rows(M, 40, 2))
 
 
 @pytest.mark.parametrize("w_gran,x_gran", [("tensor", "tensor"), ("channel", "tensor"), ("tensor", "token"), ("channel", "token")])
