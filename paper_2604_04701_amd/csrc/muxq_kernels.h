@@ -83,13 +83,15 @@ __device__ __forceinline__ uint4 absmax_step(uint4 mx, uint4 v)
 }
 
 // The activation between the two projections of the GPT-2 MLP (the modules of Sec. IV-C), tanh
-// form: gelu(y) = 0.5 y (1 + tanh(sqrt(2/pi) (y + 0.044715 y^3))) = y / (1 + exp(-2 u)),
-// evaluated in binary32.  One definition for the stand-alone producer kernel and the GEMM's
+// form: gelu(y) = 0.5 y (1 + tanh(u)) = y / (1 + exp(-2 u)), u = sqrt(2/pi) (y + 0.044715 y^3), as
+// y / (1 + 2^t) with t = y (k1 + k2 y^2), k1 = -2 sqrt(2/pi) log2(e), k2 = 0.044715 k1, in binary32: seven
+// instructions, two of them transcendental (step by step as written above it is eleven, and one rounding more in t for
+// each).  One definition for the stand-alone producer kernel and the GEMM's
 // fused epilogue, so that the two give the same fp16 values.
 __device__ __forceinline__ float gelu_tanh_f32(float y)
 {
-    const float u = 0.7978845608028654f * (y + 0.044715f * y * y * y);
-    float r = y * __builtin_amdgcn_rcpf(1.0f + __expf(-2.0f * u));
+    const float t = y * __builtin_fmaf(-0.10294324f, y * y, -2.3022082f);
+    float r = y * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
     // The product is a binary32 value in every caller: without this the compiler may fold the
     // multiply and a following conversion to fp16 into one mixed-precision instruction with a
     // single rounding, and the same input would then give different fp16 results in different
