@@ -1202,26 +1202,19 @@ __global__ __launch_bounds__(256) void k_wquant_transpose(const uint16_t *__rest
     if (chunk == 0 && n0 + nl < N && part != 0) atomicAdd(row_sum + n0 + nl, part);
 }
 
-// The same for whole strips of 64 output channels: a workgroup owns its channels over all of K, so it
-// takes their abs-max itself (per-channel scales: the whole weight quantiser is this one launch), sums
-// their codes in registers and writes their scales; nothing is accumulated with atomics or cleared
-// before.  K goes by in steps of 512: a thread reads 4 rows x 8 channels, packs the four codes of a
+// The same for whole strips of 64 output channels: a workgroup owns its channels over all of K.  K goes by in steps of
+// 512: a thread reads 4 rows x 8 channels, packs the four codes of a
 // channel into one word for the transposing LDS tile and takes 16 codes of one channel out of it per
 // store, a wave one 1 KiB block of the packed layout.  The 16-byte pieces of the tile are
 // XOR-swizzled with the channel, which keeps both sides free of bank conflicts.
-// Bound by memory: W twice (the second time mostly from the memory-side cache), the codes once:
-// 4096 x 16384 53 us, from HBM 65 us, against 93 us for abs-max with atomics, transposition in 64 x 64
-// tiles and three small launches.
-// amax (device, one value): the whole matrix's abs-max with one scale per tensor, else null.
+// One scale per tensor, from the whole matrix's abs-max `amax` (device, one value).
 constexpr int kStripCh = 64, kStripK = 512, kStripThreads = 1024;
 __global__ __launch_bounds__(kStripThreads) void k_wquant_strip(const uint16_t *__restrict__ w, int K, int N, int ldw,
                                                                int k_pad, const float *__restrict__ amax, float qmax,
                                                                int8_t *__restrict__ w_q, int32_t *__restrict__ row_sum,
-                                                               float *__restrict__ w_scale,
                                                                const float *__restrict__ row_factor)
 {
     __shared__ __attribute__((aligned(16))) uint32_t tile[kStripCh * kStripK / 4];
-    __shared__ float s_amax[kStripCh];
     __shared__ int s_sum[kStripCh];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n0 = blockIdx.x * kStripCh, nc = tid & 7, kr = tid >> 3;     // 8 channels, one of 128 row groups
@@ -1236,56 +1229,8 @@ __global__ __launch_bounds__(kStripThreads) void k_wquant_strip(const uint16_t *
         return v;
     };
     if (tid < kStripCh) s_sum[tid] = 0;
-    float inv[8];
-    if (amax == nullptr) {
-        uint4 mx = make_uint4(0, 0, 0, 0);
-        int k = kr;
-        for (; k + 7 * 128 < K; k += 8 * 128) {
-            uint4 v[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = row(k + i * 128);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) mx = absmax_step(mx, v[i]);
-        }
-        {
-            uint4 v[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = row(k + i * 128);           // (zeros past K)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) mx = absmax_step(mx, v[i]);
-        }
-        uint4 *const red = (uint4 *)tile;
-        red[tid] = mx;
-        lds_barrier();
-        if (wave == 0) {
-            for (int j = 1; j < kStripThreads / 64; ++j) mx = absmax_step(mx, red[j * 64 + lane]);
-#pragma unroll
-            for (int off = 8; off < 64; off <<= 1)
-                mx = absmax_step(mx, make_uint4(__shfl_xor((int)mx.x, off), __shfl_xor((int)mx.y, off),
-                                                __shfl_xor((int)mx.z, off), __shfl_xor((int)mx.w, off)));
-            if (lane < 8) {
-                float v[8];
-                widen8(mx, v);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    s_amax[lane * 8 + i] = v[i];
-                    // (the output only after its own abs-max: scales are not read here)
-                    if (in_n) w_scale[n0 + lane * 8 + i] = v[i] > 0.f ? v[i] / qmax : 0.f;
-                }
-            }
-        }
-        lds_barrier();
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float a = s_amax[nc * 8 + i];
-            inv[i] = a > 0.f ? qmax / a : 0.f;
-        }
-    } else {
-        const float a = amax[0];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) inv[i] = a > 0.f ? qmax / a : 0.f;
-        lds_barrier();                                   // (s_sum is cleared)
-    }
+    const float a = amax[0], inv = a > 0.f ? qmax / a : 0.f;
+    lds_barrier();                                       // (s_sum is cleared)
 
     const int nl = (wave & 3) * 16 + (lane >> 2);        // the channel this thread stores
     int sum = 0;
@@ -1298,7 +1243,7 @@ __global__ __launch_bounds__(kStripThreads) void k_wquant_strip(const uint16_t *
         for (int i = 0; i < 4; ++i) {
             const f16x8 h = __builtin_bit_cast(f16x8, v[i]);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) q[i][j] = quant_word((float)h[j], inv[j], qmax);
+            for (int j = 0; j < 8; ++j) q[i][j] = quant_word((float)h[j], inv, qmax);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = row(k0 + kStripK + kr * 4 + i);         // the next step's, on their way
@@ -1326,6 +1271,136 @@ __global__ __launch_bounds__(kStripThreads) void k_wquant_strip(const uint16_t *
     // the constant of the activation zero-point correction: each channel's sum of codes
     sum += __shfl_xor(sum, 1);
     sum += __shfl_xor(sum, 2);
+    if ((lane & 3) == 0) atomicAdd(&s_sum[nl], sum);
+    lds_barrier();
+    if (tid < kStripCh && n0 + tid < N) row_sum[n0 + tid] = s_sum[tid];
+}
+
+// The same with a scale per channel: a strip takes its channels' abs-max itself, sums their codes in registers and
+// writes their scales (the whole weight quantiser is this one launch; nothing is accumulated with atomics or cleared
+// before).  The first kStripHeld steps stay in registers from the first reading to the second, 64 of the 128 that a thread
+// has with 1024 of them on a CU, and only the rest of the strip is read again.
+// Bound by memory.  us, the whole strip read twice / this: 4096 x 16384 63 / 50.5, 2048 x 16384 28.1 / 21.2, 5120 x 4096
+// 35.4 / 29.7, 3000 x 15880 57.9 / 44.5, 8192 x 16384 145 / 132, 768 x 768 8.2 / 7.9; with three steps held 54 for the first,
+// with two more of them in LDS (all there is) 50.
+constexpr int kStripHeld = 4;
+__global__ __launch_bounds__(kStripThreads) void k_wquant_strip_channels(const uint16_t *__restrict__ w, int K, int N, int ldw,
+                                                                    int k_pad, float qmax, int8_t *__restrict__ w_q,
+                                                                    int32_t *__restrict__ row_sum,
+                                                                    float *__restrict__ w_scale,
+                                                                    const float *__restrict__ row_factor)
+{
+    constexpr int H = kStripHeld;
+    __shared__ __attribute__((aligned(16))) uint32_t tile[kStripCh * kStripK / 4];
+    float *const s_amax = (float *)tile + 4 * kStripThreads;               // (beside `red`; both gone before the first codes)
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n0 = blockIdx.x * kStripCh, nc = tid & 7, kr = tid >> 3;     // 8 channels, one of 128 row groups
+    const bool in_n = n0 + nc * 8 < N;                                     // (N is a multiple of 8)
+    const uint16_t *const src = w + n0 + nc * 8;
+    auto load = [&](int step, uint4 (&v)[4]) {                             // (zeros past K)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int k = step * kStripK + kr * 4 + i;
+            v[i] = make_uint4(0, 0, 0, 0);
+            if (in_n && k < K) {
+                v[i] = *(const uint4 *)(src + (size_t)k * ldw);
+                if (row_factor != nullptr) v[i] = scale8_fp16(v[i], row_factor[k]);  // W' = fp16(W f[k])
+            }
+        }
+    };
+    uint4 mx = make_uint4(0, 0, 0, 0);
+    auto fold = [&](const uint4 (&v)[4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mx = absmax_step(mx, v[i]);
+    };
+    const int steps = (K + kStripK - 1) / kStripK;
+    uint4 v[4], v2[4], hr[H][4];
+    // (the steps that are read again come first)
+    for (int t = H; t < steps; t += 2) {
+        load(t, v);
+        load(t + 1, v2);
+        fold(v);
+        fold(v2);
+    }
+#pragma unroll
+    for (int t = 0; t < H; ++t) load(t, hr[t]);
+#pragma unroll
+    for (int t = 0; t < H; ++t) fold(hr[t]);
+    uint4 *const red = (uint4 *)tile;
+    red[tid] = mx;
+    lds_barrier();
+    if (wave == 0) {
+        for (int j = 1; j < kStripThreads / 64; ++j) mx = absmax_step(mx, red[j * 64 + lane]);
+#pragma unroll
+        for (int off = 8; off < 64; off <<= 1)
+            mx = absmax_step(mx, make_uint4(__shfl_xor((int)mx.x, off), __shfl_xor((int)mx.y, off),
+                                            __shfl_xor((int)mx.z, off), __shfl_xor((int)mx.w, off)));
+        if (lane < 8) {
+            float m[8];
+            widen8(mx, m);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                s_amax[lane * 8 + i] = m[i];
+                if (in_n) w_scale[n0 + lane * 8 + i] = m[i] > 0.f ? m[i] / qmax : 0.f;
+            }
+        }
+    }
+    if (H < steps) load(H, v);                                             // on its way
+    lds_barrier();
+    float inv[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float a = s_amax[nc * 8 + i];
+        inv[i] = a > 0.f ? qmax / a : 0.f;
+    }
+    lds_barrier();
+
+    const int nl = (wave & 3) * 16 + (lane >> 2);        // the channel this thread stores
+    int sum = 0;
+    auto put = [&](const uint4 (&x)[4]) {                // codes of four rows into the tile
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            uint32_t q[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) q[i] = quant_word((float)__builtin_bit_cast(f16x8, x[i])[j], inv[j], qmax);
+            const int n = nc * 8 + j, piece = (kr >> 2) ^ (nc * 2) ^ (j * 4);
+            tile[n * (kStripK / 4) + piece * 4 + (kr & 3)] = pack_low_bytes(q[0], q[1], q[2], q[3]);
+        }
+    };
+    auto out = [&](int step) {
+        lds_barrier();
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int kb = (wave + 16 * i) >> 2;         // block of 64 input channels within the step
+            if (step * kStripK + kb * 64 < k_pad) {
+                const int piece = (kb * 4 + (lane & 3)) ^ ((nl >> 3) * 2) ^ ((nl & 7) * 4);
+                const uint4 c = *(const uint4 *)(tile + nl * (kStripK / 4) + piece * 4);
+                if (n0 + nl < N) *(uint4 *)(w_q + packed_index(n0 + nl, step * kStripK + kb * 64 + (lane & 3) * 16, k_pad)) = c;
+                sum = __builtin_amdgcn_sdot4((int)c.x, 0x01010101, sum, false);
+                sum = __builtin_amdgcn_sdot4((int)c.y, 0x01010101, sum, false);
+                sum = __builtin_amdgcn_sdot4((int)c.z, 0x01010101, sum, false);
+                sum = __builtin_amdgcn_sdot4((int)c.w, 0x01010101, sum, false);
+            }
+        }
+        lds_barrier();
+    };
+#pragma unroll
+    for (int t = 0; t < H; ++t)
+        if (t < steps) {
+            put(hr[t]);
+            out(t);
+        }
+    for (int t = H; t < steps; ++t) {
+        put(v);
+        load(t + 1, v);                                  // (zeros past K)
+        out(t);
+    }
+    // the constant of the activation zero-point correction: each channel's sum of codes
+    int *const s_sum = (int *)tile;
+    if (tid < kStripCh) s_sum[tid] = 0;
+    sum += __shfl_xor(sum, 1);
+    sum += __shfl_xor(sum, 2);
+    lds_barrier();
     if ((lane & 3) == 0) atomicAdd(&s_sum[nl], sum);
     lds_barrier();
     if (tid < kStripCh && n0 + tid < N) row_sum[n0 + tid] = s_sum[tid];
@@ -1575,8 +1650,12 @@ bool wquant_in_strips(const void *w_fp16, int K, int N, int ldw, bool per_channe
 hipError_t launch_wquant_strip(const void *w_fp16, int K, int N, int ldw, int k_pad, const float *amax, float qmax,
                                int8_t *w_q, int32_t *row_sum, float *w_scale, hipStream_t s, const float *row_factor)
 {
-    return launch_kernel(k_wquant_strip, dim3((N + kStripCh - 1) / kStripCh), dim3(kStripThreads), 0, s,
-                         (const uint16_t *)w_fp16, K, N, ldw, k_pad, amax, qmax, w_q, row_sum, w_scale, row_factor);
+    const dim3 grid((N + kStripCh - 1) / kStripCh), block(kStripThreads);
+    if (amax == nullptr)
+        return launch_kernel(k_wquant_strip_channels, grid, block, 0, s, (const uint16_t *)w_fp16, K, N, ldw, k_pad, qmax, w_q,
+                             row_sum, w_scale, row_factor);
+    return launch_kernel(k_wquant_strip, grid, block, 0, s, (const uint16_t *)w_fp16, K, N, ldw, k_pad, amax, qmax, w_q,
+                         row_sum, row_factor);
 }
 
 hipError_t launch_wscale_finalize(float *w_scale, int n, float qmax, hipStream_t s)

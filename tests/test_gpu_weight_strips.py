@@ -65,3 +65,18 @@ def test_weight_codes_by_rounds_of_strips(K, N):
     assert (got[:, :K] == o["w_q"].T).all() and (got[:, K:] == 0).all()
     assert (w_s.cpu().numpy()[cols] == o["s_w"]).all()
     assert (B.wq_row_sums(w_q, K, N) == codes.sum(dim=1, dtype=torch.int64)).all()
+
+
+@pytest.mark.parametrize("K", [1032, 1536, 2040, 2048, 2056, 2568, 3080, 4096])
+def test_rows_kept_between_the_two_readings_and_rows_read_again(K):
+    """Every channel's largest weight in another row, so that each step of 512 rows sets some scale."""
+    N = 264
+    rng = np.random.default_rng(K)
+    W = synth.make_w(K, N, rng)
+    W[(np.arange(N) * 131 + K - 1) % K, np.arange(N)] = 0.5
+    w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(W).cuda(), "channel")
+    o = orc.quantize_weight(W, "channel")
+    got = B.unpack(w_q, N, B.k_pad(K)).cpu().numpy()
+    assert (got[:, :K] == o["w_q"].T).all() and (got[:, K:] == 0).all()
+    assert (w_s.cpu().numpy() == o["s_w"]).all()
+    assert (B.wq_row_sums(w_q, K, N).cpu().numpy() == got.astype(np.int64).sum(axis=1)).all()
