@@ -1606,18 +1606,18 @@ hipError_t launch_wquant_transpose(const void *w_fp16, int K, int N, int ldw, in
 }
 
 // Whether the weight quantiser works in strips of 64 output channels.  A strip streams K x 128 bytes
-// through one CU (~100 GB/s), with a scale per channel twice, the second time from the memory-side
-// cache.  us, 64 x 64 tiles / strips:
-//   per channel, saves four launches: 768 x 768 14.4 / 8.0, 5120 x 1280 40 / 27, 8192 x 64 51 / 40, 4096 x 16384 92 / 53.
+// through one CU (~100 GB/s), with a scale per channel what does not stay in registers twice, the second time from the
+// memory-side cache.  us, 64 x 64 tiles / strips:
+//   per channel, saves four launches: 768 x 768 14.4 / 7.9, 5120 x 1280 40 / 24, 4096 x 16384 92 / 51.
 //     Not where one strip has few channels (8192 x 8 34.3 / 37.7), or K is a fraction of the 512 rows of a step and
 //     there are many strips (64 x 50304 14.7 / 20.4).  Every CU holds one strip at a time, so a last round of few
 //     strips leaves the chip idle, and by K = 6144 that costs more than the launches (5120 x 17408 101 / 99, 6144 x
-//     17408 120 / 126, 8192 x 17408 156 / 194, 8192 x 22528 202 / 227; 5120 x 36864 203 / 210): not beyond K = 5120, or
-//     4096 from three rounds on, unless 5/6 of all rounds are full (8192 x 28672 262 / 257, 8192 x 49152 430 / 408, to
-//     K = 9216: 9216 x 40960 within 2 %; four rounds 6144 x 65536 even, 8192 x 65536 0.90 times as fast) or the last
+//     17408 134 / 136, 8192 x 17408 172 / 187): not beyond K = 5120, unless 2/3 of all rounds are full (8192 x 22528
+//     220 / 209, 8192 x 36864 340 / 321, 5120 x 36864 217 / 189, 6144 x 49984 334 / 280, 9216 x 22528 243 / 238, 9216 x
+//     32768 351 / 294; four rounds of strips all read twice: 8192 x 65536 0.90 times as fast) or the last
 //     one is a single strip, whose lines come several times as fast (8192 x 16448 170 / 153).  In one round the strips win
 //     with all CUs busy (16384 x 16384 1.10 times as fast, 28672 x 16384 1.05, 11264 x 16000 1.10), and with fewer while
-//     W stays near the cache's size (8704 x 15872 1.03, 12288 x 12288 0.98, 16384 x 12288 232 / 248).
+//     W stays near the cache's size (8704 x 15872 1.03, 12288 x 12288 187 / 172, 16384 x 12288 232 / 248).
 //   one scale per tensor, saves one launch (1.6 to 2.3 us on these calls, by how fast the host's launches come): to K =
 //     1024 (512 x 512 13.9 / 13.1, 768 x 2304 and 1024 x 2304 even, 1024 x 5120 15.8 / 15.0, 1024 x 16384 32.6 / 29.7),
 //     1280 with few channels (1280 x 256 11.6 / 12.1 or 14.3 / 12.7; 1280 x 1280 11.9 / 13.8, 2048 x 1280 13.7 / 16.7),
@@ -1626,9 +1626,9 @@ hipError_t launch_wquant_transpose(const void *w_fp16, int K, int N, int ldw, in
 //     strip (4096 x 32768 1.12 times as fast, 1024 x 32768 1.03, 4096 x 16448 1.06; 4096 x 28672 0.96, 4096 x 18432
 //     0.88, 8192 x 32768 0.97), or K is one step (512 x 18432 1.04, 256 x 24576 1.04).
 //   Rows of W off 128-byte lines: the pieces of a strip share lines with its neighbours', on other XCDs, which then
-//     fetch them as well, so W has to fit the cache the better the more rounds there are.  Strips' gain by K x N: one round
-//     6144 x 12296 1.06, 5120 x 15880 0.94 to 1.00, 6144 x 15880 0.97; two or three 3072 x 16392 1.08, 4096 x 16392 0.97,
-//     1600 x 32776 1.14, 2048 x 32776 0.96; four 1024 x 50264 0.95, 2048 x 50264 0.82.
+//     fetch them as well, so little may be read again.  Per channel: one round 5120 x 16376 106 / 85, 8192 x 12296 128 /
+//     110, 8192 x 15936 156 / 116; two or three 4096 x 16392 91 / 80, 4096 x 20008 109 / 98, 2048 x 32776 90 / 63; four
+//     1024 x 50264 75 / 56, 2048 x 50264 127 / 99, 3072 x 50264 182 / 161.
 bool wquant_in_strips(const void *w_fp16, int K, int N, int ldw, bool per_channel)
 {
     const size_t bytes = (size_t)K * N * 2;
@@ -1641,9 +1641,9 @@ bool wquant_in_strips(const void *w_fp16, int K, int N, int ldw, bool per_channe
         return rounds == 1 && strips >= 128 && K <= 8192;
     }
     if ((N < kStripCh && K > 4096) || (N > 512 * kStripCh && K < 256)) return false;
-    if (!whole_lines) return K <= 8192 && bytes <= ((size_t)(rounds == 1 ? 148 : rounds <= 3 ? 104 : 88) << 20);
-    if (rounds == 1) return K <= 8192 || strips >= 250 || (strips >= 192 && bytes <= ((size_t)272 << 20));
-    const bool full = strips - 256 * (rounds - 1) == 1 || (size_t)strips * 6 >= (size_t)rounds * 256 * 5;
+    if (!whole_lines) return K <= (rounds == 1 ? 8192 : rounds <= 3 ? 4096 : 3072) && rounds <= 4;
+    if (rounds == 1) return K <= 8192 || strips >= 250 || (strips >= 192 && bytes <= ((size_t)288 << 20));
+    const bool full = strips - 256 * (rounds - 1) == 1 || (size_t)strips * 3 >= (size_t)rounds * 256 * 2;
     return K <= (full ? (rounds <= 3 ? 9216 : 6144) : rounds == 2 ? 5120 : 4096);
 }
 
