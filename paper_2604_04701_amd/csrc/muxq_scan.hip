@@ -1628,7 +1628,8 @@ hipError_t launch_wquant_transpose(const void *w_fp16, int K, int N, int ldw, in
 //   Rows of W off 128-byte lines: the pieces of a strip share lines with its neighbours', on other XCDs, which then
 //     fetch them as well, so little may be read again.  Per channel: one round 5120 x 16376 106 / 85, 8192 x 12296 128 /
 //     110, 8192 x 15936 156 / 116; two or three 4096 x 16392 91 / 80, 4096 x 20008 109 / 98, 2048 x 32776 90 / 63; four
-//     1024 x 50264 75 / 56, 2048 x 50264 127 / 99, 3072 x 50264 182 / 161.
+//     1024 x 50264 75 / 56, 2048 x 50264 127 / 99, 3072 x 50264 182 / 161 (4096 x 40008 191 / 167); more 512 x 65544 58 / 38,
+//     600 x 80008 76 / 57, 1024 x 80008 110 / 81.
 bool wquant_in_strips(const void *w_fp16, int K, int N, int ldw, bool per_channel)
 {
     const size_t bytes = (size_t)K * N * 2;
@@ -1641,7 +1642,7 @@ bool wquant_in_strips(const void *w_fp16, int K, int N, int ldw, bool per_channe
         return rounds == 1 && strips >= 128 && K <= 8192;
     }
     if ((N < kStripCh && K > 4096) || (N > 512 * kStripCh && K < 256)) return false;
-    if (!whole_lines) return K <= (rounds == 1 ? 8192 : rounds <= 3 ? 4096 : 3072) && rounds <= 4;
+    if (!whole_lines) return rounds <= 4 ? K <= (rounds == 1 ? 8192 : rounds <= 3 ? 4096 : 3072) : bytes <= ((size_t)160 << 20);
     if (rounds == 1) return K <= 8192 || strips >= 250 || (strips >= 192 && bytes <= ((size_t)288 << 20));
     const bool full = strips - 256 * (rounds - 1) == 1 || (size_t)strips * 3 >= (size_t)rounds * 256 * 2;
     return K <= (full ? (rounds <= 3 ? 9216 : 6144) : rounds == 2 ? 5120 : 4096);
