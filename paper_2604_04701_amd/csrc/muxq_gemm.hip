@@ -446,9 +446,40 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
         return c;
     };
     Group cst = group(0);
+    // patch -> Y: 8 lanes cover the 128 bytes of one token, 8 tokens per instruction
+    const auto put = [&](int h, int fm) {
+        // (no branch at a store: lanes past N get an offset past the end)
+        const bool n_in = n_base + h * 64 + piece * 8 < a.N;
+        unsigned off[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) off[p] = n_in ? y_off[p] + h * 128 : 1u << 31;
+        const int rows = __builtin_amdgcn_readfirstlane(min(max(a.M - m_base - fm * 32, 0), 32));
+        const __amdgpu_buffer_rsrc_t r_y = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)(a.y + (size_t)(m_base + fm * 32) * a.ldy), 0, (int)((unsigned)rows * (unsigned)a.ldy * 2u), 0x00020000);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const int row = p * 8 + (lane >> 3);
+            const v4i v = *(const v4i *)(patch + row * ROW_BYTES + piece * 16);
+            if (EPI != kEpiLoads)
+                __builtin_amdgcn_raw_buffer_store_b128(v, r_y, off[p], 0, STREAM ? 2 : 0);
+            else if (n_in && row < rows)
+                store_y<STREAM>(a, m_base + fm * 32 + row, n_base + h * 64 + piece * 8, v);
+            if (GELU) {
+                const unsigned keep = n_in && row < rows ? ~0u : 0u;
+                const uint4 u = __builtin_bit_cast(uint4, v);
+                mx[h] = absmax_step(mx[h], make_uint4(u.x & keep, u.y & keep, u.z & keep, u.w & keep));
+            }
+        }
+    };
+    // Results that wait for the patch, in the registers of accumulators that are done with.  As a stream each half of the
+    // channels goes out before the next is worked out.  Through L2 all pieces of the rows go out one after the other, so
+    // that the other half of a line shared by two of them comes while L2 still has the first.  us a call, half by half /
+    // together: 11330 x 448 -> 14296 186 / 148, 13653 x 520 -> 10608 174 / 148, 4837 x 1600 -> 10168 113 / 104, 8811 x 776 ->
+    // 5264 72.5 / 71.0, 3001 x 1592 -> 4808 43.0 / 42.1.  (The forms with flags have no registers for that.)
+    constexpr bool TOGETHER = !STREAM && !epi_flags(EPI);
+    f16x4 held[FN / 2][FM][8];
 #pragma unroll
     for (int h = 0; h < FN / 2; ++h) {
-        f16x4 held[FM - 1][8];                     // the later tokens' results wait for the patch
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const Group nxt = h * 8 + e + 1 < FN * 4 ? group(h * 8 + e + 1) : cst;
@@ -468,42 +499,34 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
                     out[i] = (_Float16)y;
                     if (GELU) out[i] = (_Float16)gelu_tanh_f32((float)out[i]);
                 }
-                if (fm == 0) *(f16x4 *)(patch + fr * ROW_BYTES + (e * 8 + 4 * fh) * 2) = out;
-                else held[fm - 1][e] = out;
+                if (fm == 0 && (!TOGETHER || h == 0)) *(f16x4 *)(patch + fr * ROW_BYTES + (e * 8 + 4 * fh) * 2) = out;
+                else held[h][fm][e] = out;
             }
             cst = nxt;
             __builtin_amdgcn_sched_barrier(0);     // bounds the live temporaries (see scale_acc)
         }
-        // (no branch at a store: lanes past N get an offset past the end)
-        const bool n_in = n_base + h * 64 + piece * 8 < a.N;
-        unsigned off[4];
+        if (!TOGETHER) {
 #pragma unroll
-        for (int p = 0; p < 4; ++p) off[p] = n_in ? y_off[p] + h * 128 : 1u << 31;
+            for (int fm = 0; fm < FM; ++fm) {
+                if (fm > 0) {
 #pragma unroll
-        for (int fm = 0; fm < FM; ++fm) {
-            if (fm > 0) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) *(f16x4 *)(patch + fr * ROW_BYTES + (e * 8 + 4 * fh) * 2) = held[fm - 1][e];
-            }
-            const int rows = __builtin_amdgcn_readfirstlane(min(max(a.M - m_base - fm * 32, 0), 32));
-            const __amdgpu_buffer_rsrc_t r_y = __builtin_amdgcn_make_buffer_rsrc(
-                (void *)(a.y + (size_t)(m_base + fm * 32) * a.ldy), 0, (int)((unsigned)rows * (unsigned)a.ldy * 2u), 0x00020000);
-            // patch -> Y: 8 lanes cover the 128 bytes of one token, 8 tokens per instruction
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const int row = p * 8 + (lane >> 3);
-                const v4i v = *(const v4i *)(patch + row * ROW_BYTES + piece * 16);
-                if (EPI != kEpiLoads)
-                    __builtin_amdgcn_raw_buffer_store_b128(v, r_y, off[p], 0, STREAM ? 2 : 0);
-                else if (n_in && row < rows)
-                    store_y<STREAM>(a, m_base + fm * 32 + row, n_base + h * 64 + piece * 8, v);
-                if (GELU) {
-                    const unsigned keep = n_in && row < rows ? ~0u : 0u;
-                    const uint4 u = __builtin_bit_cast(uint4, v);
-                    mx[h] = absmax_step(mx[h], make_uint4(u.x & keep, u.y & keep, u.z & keep, u.w & keep));
+                    for (int e = 0; e < 8; ++e) *(f16x4 *)(patch + fr * ROW_BYTES + (e * 8 + 4 * fh) * 2) = held[h][fm][e];
                 }
+                put(h, fm);
             }
         }
+    }
+    if (TOGETHER) {
+#pragma unroll
+        for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+            for (int h = 0; h < FN / 2; ++h) {
+                if (fm + h > 0) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) *(f16x4 *)(patch + fr * ROW_BYTES + (e * 8 + 4 * fh) * 2) = held[h][fm][e];
+                }
+                put(h, fm);
+            }
     }
 
     if (EPI == kEpiLoads && a.dbg_acc != nullptr) {   // raw accumulators, debugging aid: plain per-lane stores

@@ -5,33 +5,42 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_common import B, check_case, check_mlp, check_own_scale, check_plain_y, orc, rows_every_block, sample_rows, synth
+from gpu_common import B, check_case, check_mlp, check_own_scale, check_plain_y, orc, rows_every_block, sample_rows, say, synth
 from paper_2604_04701_amd.synth import Case
 
 pytestmark = pytest.mark.gpu
 U = (20.0, 100.0)
-FORMS = {"128x128": (2100, 520, 1544), "256x256": (3077, 136, 4808), "128x256": (3400, 520, 6304)}
+# more tiles than workgroups are resident (512 of 128 x 128 and 128 x 256, 256 of 256 x 256), partial in both directions
+FORMS = {"128x128": (6607, 72, 2312), "256x256": (5222, 72, 4112), "128x256": (3400, 520, 6304)}
 
 
+@pytest.mark.parametrize("on_lines", [True, False])
 @pytest.mark.parametrize("bias_seed", [None, 7])
 @pytest.mark.parametrize("w_gran", ["tensor", "channel"])
 @pytest.mark.parametrize("x_gran", ["tensor", "token", "naive"])
 @pytest.mark.parametrize("form", FORMS)
-def test_every_combination_of_scales_and_bias(form, x_gran, w_gran, bias_seed):
-    """naive: the plain INT8 pipeline, which has no zero point."""
+def test_every_combination_of_scales_and_bias(form, x_gran, w_gran, bias_seed, on_lines):
+    """Rows of Y on 128-byte lines (stored as a stream) and off them (through L2, in another order); nothing past N.
+    naive: the plain INT8 pipeline, whose zero point is 0."""
     M, K, N = FORMS[form]
     rows = rows_every_block(M, 11)
-    case = Case("epilogue", M, K, N, 5, U, 900 + M)
-    if x_gran != "naive":
-        check_plain_y(case, rows=rows, w_gran=w_gran, bias_seed=bias_seed, x_gran=x_gran)
-        return
-    X, W, _ = synth.make_case(case)
+    X, W, _ = synth.make_case(Case("epilogue", M, K, N, 5, U, 900 + M))
     bias = None if bias_seed is None else np.random.default_rng(bias_seed).standard_normal(N).astype(np.float16)
+    bd = None if bias is None else torch.from_numpy(bias).cuda()
+    Xd = torch.from_numpy(X).cuda()
     w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(W).cuda(), w_gran)
-    Y = B.muxq_linear_naive_int8(torch.from_numpy(X).cuda(), w_q, w_s, N, w_gran,
-                                 bias=None if bias is None else torch.from_numpy(bias).cuda())
-    o = orc.linear(X, W, r_cap=0, w_gran=w_gran, bias16=bias, rows=rows)
-    assert (Y.cpu().numpy()[rows] == o["y16"]).all()
+    ldy = (N + 63) // 64 * 64 if on_lines else N + 8 if (N + 8) % 32 else N + 16
+    out = torch.full((M, ldy), 7.0, dtype=torch.float16, device="cuda")
+    say(f"[epilogue] {form} x={x_gran} w={w_gran} bias={bias_seed} ldy={ldy}")
+    if x_gran == "naive":
+        B.muxq_linear_naive_int8(Xd, w_q, w_s, N, w_gran, bias=bd, out=out[:, :N])
+        o = orc.linear(X, W, r_cap=0, w_gran=w_gran, bias16=bias, rows=rows)
+    else:
+        B.muxq_linear(Xd, w_q, w_s, N, w_gran, bias=bd, out=out[:, :N], x_gran=x_gran)
+        o = orc.linear(X, W, w_gran=w_gran, bias16=bias, rows=rows, x_gran=x_gran)
+    got = out.cpu().numpy()
+    assert (got[rows][:, :N] == o["y16"]).all()
+    assert (got[:, N:] == 7.0).all()
 
 
 @pytest.mark.parametrize("M,K,N", [(1500, 264, 2056), (3400, 520, 6304)])
