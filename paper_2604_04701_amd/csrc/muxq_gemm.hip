@@ -372,7 +372,7 @@ constexpr int epi_zero(int e) { return epi_flags(e) ? -1 : e >= kEpiPlainZ; }
 
 // The accumulators carry a zero-point term z * cn[n] (cn per channel, int32; z per launch or per token), which is
 // taken off in integers (one 24-bit multiply-add), so the result is the accumulator of Eq. 7 exactly; `sub_bias`
-// (see kAccBias) comes off as well, and is known to be zero with one zero point per launch.
+// (see kAccBias) comes off as well, and is known to be zero with one zero point per launch (0 among them: z_none).
 // GELU (compile time): the result goes through the tanh GELU, applied to the fp16 value the
 // layer would have stored, and `mx` (FN / 2 entries) collects, per lane, the running maxima of
 // the |fp16| values the lane stores (its 8 channels of each half, over its rows).
@@ -419,11 +419,15 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
         chan_ztok[lane] = zt;
     }
 
+    // One zero point for the launch and that is 0: the accumulators started at kAccBias, which comes off in the place of
+    // z * cn[n], as 1 * kAccBias.
+    const bool z_none = has_zc && !x_tok && z_launch == 0;
+    if (z_none) chan_zc[lane] = chan_zc[64 + lane] = kAccBias;
     int negz[FM];                                  // this lane's tokens
     float sxt[FM];
 #pragma unroll
     for (int fm = 0; fm < FM; ++fm) {
-        negz[fm] = !has_zc ? 0 : -(x_tok ? chan_ztok[fm * 32 + fr] : z_launch);
+        negz[fm] = !has_zc ? 0 : x_tok ? -chan_ztok[fm * 32 + fr] : z_none ? -1 : -z_launch;
         sxt[fm] = x_tok ? chan_tok[fm * 32 + fr] : sx;
     }
     // Y of the wave's rows of one fragment, as a buffer that ends with row M - 1: a store needs one 32-bit add, and
@@ -543,7 +547,7 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
                                acc[fn][fm][4 * g + 3]};
                     if (a.cn != nullptr)
                         raw -= *(const v4i *)(a.cn + n) * a.zero_point[a.x_per_token ? m : 0];
-                    raw -= sub_bias;
+                    raw -= z_none ? kAccBias : sub_bias;
                     *(v4i *)(a.dbg_acc + (size_t)m * a.N + n) = raw;
                 }
             }
@@ -675,7 +679,10 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
     // where the accumulators start (see kCnBias): what comes off with z * cn[n], or by itself (see kAccBias), and
     // what the Aux weighting has to take off
     const int sub_bias = has_zc && !x_tok ? 0 : kAccBias;
-    const int acc_bias = has_zc && !x_tok ? z_launch * a.cn_bias : kAccBias, acc_fix = ((1 << a.exp_shift) - 2) * acc_bias;
+    // (A zero point of 0, where the unlisted channels use the whole range, as without outliers: kAccBias all the same, which
+    // the epilogue takes off in the place of z * cn.  Started at 0 / so, us: 8192 x 4096 -> 16384 474 / 458, 16384 x 1280 ->
+    // 3840 112 / 109, naive 4096 x 4096 -> 4096 71.7 / 69.8.)
+    const int acc_bias = z_launch != 0 ? z_launch * a.cn_bias : kAccBias, acc_fix = ((1 << a.exp_shift) - 2) * acc_bias;
     const float rho = OWN == 1 ? aux_rho(a) : 0.f;
     // the tile's constants that come by DMA: weight scales (2 loads), bias, token scales, cn (2), z and rho per token
     constexpr bool CONSTS = EPI != kEpiLoads;
