@@ -369,6 +369,10 @@ constexpr int epi_bias(int e)
 }
 constexpr int epi_token(int e) { return epi_flags(e) ? -1 : e >= kEpiToken; }
 constexpr int epi_zero(int e) { return epi_flags(e) ? -1 : e >= kEpiPlainZ; }
+// Whether the accumulators of a launch with the zero point 0 start at kAccBias all the same.  Not in the 128 x 128 tiles: there
+// it gains 1 % without outliers (8192 x 1024 -> 1024 27.8 / 27.6 us), and the branch costs the other calls 1 to 2.5 %
+// (with outliers, a scale per channel: 1024 x 768 -> 3072 19.0 / 19.5, 8192 x 1024 -> 1024 30.1 / 30.4).
+constexpr bool z_offset(int fn) { return fn == 4; }
 
 // The accumulators carry a zero-point term z * cn[n] (cn per channel, int32; z per launch or per token), which is
 // taken off in integers (one 24-bit multiply-add), so the result is the accumulator of Eq. 7 exactly; `sub_bias`
@@ -421,7 +425,7 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
 
     // One zero point for the launch and that is 0: the accumulators started at kAccBias, which comes off in the place of
     // z * cn[n], as 1 * kAccBias.
-    const bool z_none = has_zc && !x_tok && z_launch == 0;
+    const bool z_none = z_offset(FN) && has_zc && !x_tok && z_launch == 0;
     if (z_none) chan_zc[lane] = chan_zc[64 + lane] = kAccBias;
     int negz[FM];                                  // this lane's tokens
     float sxt[FM];
@@ -682,7 +686,7 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
     // (A zero point of 0, where the unlisted channels use the whole range, as without outliers: kAccBias all the same, which
     // the epilogue takes off in the place of z * cn.  Started at 0 / so, us: 8192 x 4096 -> 16384 474 / 458, 16384 x 1280 ->
     // 3840 112 / 109, naive 4096 x 4096 -> 4096 71.7 / 69.8.)
-    const int acc_bias = z_launch != 0 ? z_launch * a.cn_bias : kAccBias, acc_fix = ((1 << a.exp_shift) - 2) * acc_bias;
+    const int acc_bias = has_zc && !x_tok && (z_launch != 0 || !z_offset(FN)) ? z_launch * a.cn_bias : kAccBias, acc_fix = ((1 << a.exp_shift) - 2) * acc_bias;
     const float rho = OWN == 1 ? aux_rho(a) : 0.f;
     // the tile's constants that come by DMA: weight scales (2 loads), bias, token scales, cn (2), z and rho per token
     constexpr bool CONSTS = EPI != kEpiLoads;
