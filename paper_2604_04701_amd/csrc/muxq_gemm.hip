@@ -504,6 +504,9 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
                     if (has_zc) t = __mul24(cst.z[i], negz[fm]) + t;
                     float y = sc * (float)(t - sub_bias);
                     if (BIAS != 0) y = y + (float)cst.b[i];   // + 0 without a bias: changes no finite value
+                    // The product is a binary32 value: without a bias and before the GELU the compiler folded it and the
+                    // conversion into one mixed-precision instruction with a single rounding.
+                    if (GELU && BIAS <= 0) asm volatile("" : "+v"(y));
                     out[i] = (_Float16)y;
                     if (GELU) out[i] = (_Float16)gelu_tanh_f32((float)out[i]);
                 }

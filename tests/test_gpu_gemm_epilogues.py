@@ -49,6 +49,30 @@ def test_gelu_with_every_kind_of_scales(w_gran, x_gran, M, K, N):
     check_mlp(M, K, N, 136, 910, w_gran=w_gran, x_gran=x_gran)
 
 
+@pytest.mark.parametrize("w_gran,x_gran", [("tensor", "tensor"), ("channel", "tensor"), ("tensor", "token"), ("channel", "token")])
+@pytest.mark.parametrize("form", FORMS)
+def test_gelu_without_a_bias(form, w_gran, x_gran):
+    """The first layer against the oracle, exact; the fused GELU against the stand-alone one on the fp16 values the
+    layer stores, bit for bit, and within one unit of the oracle's; its column maxima."""
+    M, K, N = FORMS[form]
+    rows = rows_every_block(M, 14)
+    X, W, _ = synth.make_case(Case("gelu", M, K, N, 5, U, 960 + M))
+    Xd = torch.from_numpy(X).cuda()
+    w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(W).cuda(), w_gran)
+    say(f"[gelu] {form} x={x_gran} w={w_gran}")
+    o = orc.linear(X, W, w_gran=w_gran, x_gran=x_gran, rows=rows)
+    Y = B.muxq_linear(Xd, w_q, w_s, N, w_gran, x_gran=x_gran)
+    assert (Y.cpu().numpy()[rows] == o["y16"]).all()
+    lay = B.workspace_layout(M, N, 8, 64)
+    ws, ws2 = B.alloc_workspace(M, N, 8, 64), B.alloc_workspace(M, N, 8, 64)
+    H, n_slabs = B.muxq_linear_gelu(Xd, w_q, w_s, N, w_gran, x_gran=x_gran, next_workspace=ws, next_layout=lay)
+    assert torch.equal(H.view(torch.int16), B.muxq_gelu_absmax(Y, ws2, lay).view(torch.int16))
+    slabs = ws[lay.absmax_partial:lay.absmax_partial + n_slabs * lay.k_pad * 2].view(torch.float16).view(n_slabs, -1)
+    assert torch.equal(slabs.amax(dim=0)[:N], H.abs().amax(dim=0))
+    got, want = H.cpu().numpy()[rows], orc.gelu_tanh(o["y16"])
+    assert np.abs(got.view(np.int16).astype(np.int32) - want.view(np.int16).astype(np.int32)).max() <= 1
+
+
 @pytest.mark.parametrize("M,K,N", [(8190, 2120, 1016), (3400, 520, 6304), (8300, 4104, 2312)])
 def test_128x256_tiles(M, K, N):
     """One tile per CU, ragged in both directions; several Aux steps; two tiles for some workgroups and K = 65 steps."""
