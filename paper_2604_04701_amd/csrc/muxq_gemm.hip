@@ -219,6 +219,20 @@ __device__ __forceinline__ float aux_rho(const GemmArgs &a)
     return sx > 0.f ? ((float)((1 << a.exp_shift) - 1) * sa) / sx : 0.f;
 }
 
+// Whether Y goes out as a stream.  Rows on 128-byte lines: a store instruction writes whole lines, and Y, which
+// is not read here again, stays out of the operands' way in L2 (16384 x 1280 -> 3840 90 us through L2, 87 us as a
+// stream).  Rows on 64-byte boundaries: whole transfers still, but half lines, which L2 would join.  That is worth
+// more while the memory-side cache takes Y in, and less once it does not, or while the L2s themselves hold it (768
+// input channels, us through L2 / as a stream: 1000 -> 20000 24.5 / 22.5, 2000 -> 20000 43 / 47, 12000 -> 20000
+// 250 / 202).  Other rows: the transfers at the ends of a piece are completed by the neighbouring piece, which only
+// happens in L2 (3001 -> 4808 19 / 27, 12000 -> 10000 111 / 145).
+__host__ __device__ __forceinline__ bool stream_rows(const GemmArgs &a)
+{
+    const uintptr_t start = (uintptr_t)a.y | (uintptr_t)a.ldy * 2;
+    const size_t mib = ((size_t)a.M * a.N * 2) >> 20;
+    return start % 128 == 0 || (start % 64 == 0 && (mib < 48 || mib >= 256));
+}
+
 // 16 bytes of Y.  STREAM: non-temporal (chosen by stream_rows).  Compile time: a branch at each store costs
 // 1 us per tile.
 template <bool STREAM>
@@ -345,16 +359,50 @@ __device__ __forceinline__ void epilogue(const GemmArgs &a, const v16i (&acc)[FN
 // (one kernel each and the reads ahead, us a call: 1024 x 768 -> 3072 19.9 -> 18.1, 8192 x 1024 -> 1024 30.5 -> 28.0, 3001 x
 // 1592 -> 4808 per vector 43.3 -> 41.6, 16384 x 1280 -> 3840 per vector 113.3 -> 108.4, 8192 x 4096 -> 16384 428 -> 422)
 enum Epi {
-    kEpiLoads,        // the wave loads its constants itself and also exports the raw accumulators when asked
-                      // (debugging; drains the memory queue once per tile), and takes any row stride of Y
+    kEpiAny,          // flags at run time; exports the raw accumulators when asked (debugging; drains the memory queue
+                      // once per tile) and takes any row stride of Y
     kEpiGeneral,      // flags at run time
-    kEpiPlain, kEpiBias, kEpiChan, kEpiChanBias,          // one activation scale, no zero point (the naive pipeline)
+    kEpiPlain, kEpiBias, kEpiChan, kEpiChanBias,          // one activation scale, no zero point (muxq_gemm_i8)
     kEpiPlainZ, kEpiBiasZ, kEpiChanZ, kEpiChanBiasZ,      // one activation scale, zero point
     kEpiToken, kEpiTokenBias,                             // scales per token, zero points per token
     kEpiVector, kEpiVectorBias,                           // the same with a scale per channel as well
     kEpis
 };
 constexpr int kChanFloats = 128 + 64 + 64 + 128 + 64 + 64;   // per-wave LDS for the tile's constants
+
+// kEpiAny: the rows m + p * 8 + lane / 8 of Y from channel n on.  A buffer for the 8 rows of each store, whose offsets reach
+// rows 2^28 elements apart; by address beyond.  (512 x 2048 -> 16384 with rows 2^25 elements apart: by address 36.2 us, so
+// 32.0.)
+constexpr int kBufferLdy = (1 << 28) - 64;
+__device__ __forceinline__ void put_any(const GemmArgs &a, const v4i (&v)[4], int m, int n, int lane)
+{
+    constexpr unsigned PAST = 0xfffffc00u;
+    static_assert((unsigned)kBufferLdy * 16u <= PAST, "the range check drops what is past the buffer");
+    const bool stream = stream_rows(a);
+    if (a.ldy <= kBufferLdy) {
+        const unsigned off = n < a.N ? (unsigned)(lane >> 3) * (unsigned)a.ldy * 2u + (unsigned)n * 2u : PAST;
+        const auto buffer = [&](int p) {
+            return __builtin_amdgcn_make_buffer_rsrc((void *)(a.y + (size_t)(m + p * 8) * a.ldy), 0,
+                                                     (int)((unsigned)min(max(a.M - m - p * 8, 0), 8) * (unsigned)a.ldy * 2u), 0x00020000);
+        };
+        if (stream) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) __builtin_amdgcn_raw_buffer_store_b128(v[p], buffer(p), off, 0, 2);
+        } else {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) __builtin_amdgcn_raw_buffer_store_b128(v[p], buffer(p), off, 0, 0);
+        }
+    } else {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const int row = m + p * 8 + (lane >> 3);
+            if (n < a.N && row < a.M) {
+                if (stream) store_y<true>(a, row, n, v[p]);
+                else store_y<false>(a, row, n, v[p]);
+            }
+        }
+    }
+}
 
 // -1: decided at run time from the arguments
 constexpr bool epi_flags(int e) { return e <= kEpiGeneral; }
@@ -389,7 +437,6 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
     constexpr int WCH = epi_chan(EPI), TOK = epi_token(EPI), BIAS = epi_bias(EPI), ZC = epi_zero(EPI);
     const bool w_chan = WCH < 0 ? a.w_per_channel != 0 : WCH != 0;
     const bool x_tok = TOK < 0 ? a.x_per_token != 0 : TOK != 0;
-    const bool has_bias = BIAS < 0 ? a.bias != nullptr : BIAS != 0;
     const bool has_zc = ZC < 0 ? a.cn != nullptr : ZC != 0;
     if (ZC == 1 && TOK == 0) sub_bias = 0;
     const float s_tensor = sx * sw0;
@@ -401,28 +448,6 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
     float *const chan_tok = chan + 128 + 64;
     int *const chan_zc = (int *)(chan + 256);      // cn of the wave's 128 channels
     int *const chan_ztok = (int *)(chan + 384);    // z of the wave's 64 tokens (per-token setting)
-    if (EPI == kEpiLoads) {                    // same raw layout as the loads of the first K step
-        const int n = n_base + 2 * lane;
-        float2 sw = make_float2(0.f, 0.f);
-        _Float16 b0 = (_Float16)0.f, b1 = (_Float16)0.f;
-        if (n < a.N) {                         // N % 8 == 0: a pair is in or out as a whole
-            if (a.w_per_channel) sw = *(const float2 *)(a.w_scale + n);
-            if (a.bias != nullptr) { b0 = a.bias[n]; b1 = a.bias[n + 1]; }
-        }
-        float sxm = 0.f;
-        if (a.x_per_token && m_base + lane < a.M) sxm = a.x_scale[m_base + lane];
-        *(float2 *)(chan + 2 * lane) = sw;
-        chan_bias[2 * lane] = b0;
-        chan_bias[2 * lane + 1] = b1;
-        chan_tok[lane] = sxm;
-        int z0 = 0, z1 = 0, zt = 0;
-        if (a.cn != nullptr && n < a.N) { z0 = a.cn[n]; z1 = a.cn[n + 1]; }
-        if (a.cn != nullptr && a.x_per_token && m_base + lane < a.M) zt = a.zero_point[m_base + lane];
-        chan_zc[2 * lane] = z0;
-        chan_zc[2 * lane + 1] = z1;
-        chan_ztok[lane] = zt;
-    }
-
     // One zero point for the launch and that is 0: the accumulators started at kAccBias, which comes off in the place of
     // z * cn[n], as 1 * kAccBias.
     const bool z_none = z_offset(FN) && has_zc && !x_tok && z_launch == 0;
@@ -448,11 +473,33 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
         c.w = make_float4(sw0, sw0, sw0, sw0);
         c.b = f16x4{0, 0, 0, 0};
         c.z = v4i{0, 0, 0, 0};
-        if (w_chan) c.w = *(const float4 *)(chan + at);
-        if (has_bias) c.b = *(const f16x4 *)(chan_bias + at);
-        if (has_zc) c.z = *(const v4i *)(chan_zc + at);
+        // (with flags: what the launch has not was loaded as zeros)
+        if (WCH < 0) {
+            const float4 w = *(const float4 *)(chan + at);
+            if (w_chan) c.w = w;
+        } else if (WCH != 0) c.w = *(const float4 *)(chan + at);
+        if (BIAS != 0) c.b = *(const f16x4 *)(chan_bias + at);
+        if (ZC != 0) c.z = *(const v4i *)(chan_zc + at);
         return c;
     };
+    // Raw accumulators, debugging aid: plain per-lane stores.  Before the results, which go into the accumulators' registers
+    // (behind them both were held, 38 to 102 registers spilled: 8192 x 2048 -> 8192 311 us, so 206).
+    if (EPI == kEpiAny && !GELU && a.dbg_acc != nullptr) {
+#pragma unroll
+        for (int e = 0; e < FN * 4; ++e) {
+            const int n = n_base + e * 8 + 4 * fh;
+            const v4i z = group(e).z;
+#pragma unroll
+            for (int fm = 0; fm < FM; ++fm) {
+                const int m = m_base + fm * 32 + fr;
+                v4i raw;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) raw[i] = __mul24(z[i], negz[fm]) + acc[e / 4][fm][4 * (e % 4) + i] - sub_bias;
+                if (n < a.N && m < a.M) *(v4i *)(a.dbg_acc + (size_t)m * a.N + n) = raw;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
     Group cst = group(0);
     // patch -> Y: 8 lanes cover the 128 bytes of one token, 8 tokens per instruction
     const auto put = [&](int h, int fm) {
@@ -464,20 +511,19 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
         const int rows = __builtin_amdgcn_readfirstlane(min(max(a.M - m_base - fm * 32, 0), 32));
         const __amdgpu_buffer_rsrc_t r_y = __builtin_amdgcn_make_buffer_rsrc(
             (void *)(a.y + (size_t)(m_base + fm * 32) * a.ldy), 0, (int)((unsigned)rows * (unsigned)a.ldy * 2u), 0x00020000);
+        v4i v[4];
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
             const int row = p * 8 + (lane >> 3);
-            const v4i v = *(const v4i *)(patch + row * ROW_BYTES + piece * 16);
-            if (EPI != kEpiLoads)
-                __builtin_amdgcn_raw_buffer_store_b128(v, r_y, off[p], 0, STREAM ? 2 : 0);
-            else if (n_in && row < rows)
-                store_y<STREAM>(a, m_base + fm * 32 + row, n_base + h * 64 + piece * 8, v);
+            v[p] = *(const v4i *)(patch + row * ROW_BYTES + piece * 16);
+            if (EPI != kEpiAny) __builtin_amdgcn_raw_buffer_store_b128(v[p], r_y, off[p], 0, STREAM ? 2 : 0);
             if (GELU) {
                 const unsigned keep = n_in && row < rows ? ~0u : 0u;
-                const uint4 u = __builtin_bit_cast(uint4, v);
+                const uint4 u = __builtin_bit_cast(uint4, v[p]);
                 mx[h] = absmax_step(mx[h], make_uint4(u.x & keep, u.y & keep, u.z & keep, u.w & keep));
             }
         }
+        if (EPI == kEpiAny) put_any(a, v, m_base + fm * 32, n_base + h * 64 + piece * 8, lane);
     };
     // Results that wait for the patch, in the registers of accumulators that are done with.  As a stream each half of the
     // channels goes out before the next is worked out.  Through L2 all pieces of the rows go out one after the other, so
@@ -501,12 +547,13 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
                     // Eq. 3: one binary32 product of the two scales, whichever granularity
                     const float sc = WCH == 0 && TOK == 0 ? s_tensor : sxt[fm] * wv[i];
                     int t = acc[fn][fm][4 * g + i];
-                    if (has_zc) t = __mul24(cst.z[i], negz[fm]) + t;
+                    if (ZC != 0) t = __mul24(cst.z[i], negz[fm]) + t;
                     float y = sc * (float)(t - sub_bias);
                     if (BIAS != 0) y = y + (float)cst.b[i];   // + 0 without a bias: changes no finite value
                     // The product is a binary32 value: without a bias and before the GELU the compiler folded it and the
-                    // conversion into one mixed-precision instruction with a single rounding.
-                    if (GELU && BIAS <= 0) asm volatile("" : "+v"(y));
+                    // conversion into one mixed-precision instruction with a single rounding.  (With flags it took the
+                    // conversions out of their groups and spilled 20 to 47 registers.)
+                    if (epi_flags(EPI) || (GELU && BIAS == 0)) asm volatile("" : "+v"(y));
                     out[i] = (_Float16)y;
                     if (GELU) out[i] = (_Float16)gelu_tanh_f32((float)out[i]);
                 }
@@ -537,26 +584,6 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
                     for (int e = 0; e < 8; ++e) *(f16x4 *)(patch + fr * ROW_BYTES + (e * 8 + 4 * fh) * 2) = held[h][fm][e];
                 }
                 put(h, fm);
-            }
-    }
-
-    if (EPI == kEpiLoads && a.dbg_acc != nullptr) {   // raw accumulators, debugging aid: plain per-lane stores
-#pragma unroll
-        for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int n = n_base + fn * 32 + 8 * g + 4 * fh;
-#pragma unroll
-                for (int fm = 0; fm < FM; ++fm) {
-                    const int m = m_base + fm * 32 + fr;
-                    if (n >= a.N || m >= a.M) continue;
-                    v4i raw = {acc[fn][fm][4 * g], acc[fn][fm][4 * g + 1], acc[fn][fm][4 * g + 2],
-                               acc[fn][fm][4 * g + 3]};
-                    if (a.cn != nullptr)
-                        raw -= *(const v4i *)(a.cn + n) * a.zero_point[a.x_per_token ? m : 0];
-                    raw -= z_none ? kAccBias : sub_bias;
-                    *(v4i *)(a.dbg_acc + (size_t)m * a.N + n) = raw;
-                }
             }
     }
 }
@@ -692,9 +719,8 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
     const int acc_bias = has_zc && !x_tok && (z_launch != 0 || !z_offset(FN)) ? z_launch * a.cn_bias : kAccBias, acc_fix = ((1 << a.exp_shift) - 2) * acc_bias;
     const float rho = OWN == 1 ? aux_rho(a) : 0.f;
     // the tile's constants that come by DMA: weight scales (2 loads), bias, token scales, cn (2), z and rho per token
-    constexpr bool CONSTS = EPI != kEpiLoads;
-    constexpr bool L_W = CONSTS && epi_chan(EPI) != 0, L_B = CONSTS && epi_bias(EPI) != 0, L_T = CONSTS && epi_token(EPI) != 0,
-                   L_Z = CONSTS && epi_zero(EPI) != 0, L_ZT = L_T && L_Z, L_RHO = CONSTS && OWN == 2;
+    constexpr bool L_W = epi_chan(EPI) != 0, L_B = epi_bias(EPI) != 0, L_T = epi_token(EPI) != 0, L_Z = epi_zero(EPI) != 0,
+                   L_ZT = L_T && L_Z, L_RHO = OWN == 2;
     constexpr int CONST_LOADS = 2 * L_W + L_B + L_T + 2 * L_Z + L_ZT + L_RHO;
 
     // ---- DMA side -------------------------------------------------------------
@@ -923,21 +949,12 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
             if (t == t_aux) {                                    // acc_aux -> c * acc_aux
                 if constexpr (OWN == 2) {
                     // one factor per token: staged with the tile's constants (issued with the
-                    // first K step, so everything older has to land first), or fetched here by
-                    // the form that loads its constants itself
+                    // first K step, so everything older has to land first)
                     float rho_t[FM];
-                    const float *rho_g = aux_rho_tok(a);
-                    if (!CONSTS) {
-#pragma unroll
-                        for (int fm = 0; fm < FM; ++fm)
-                            rho_t[fm] = rho_g[min(cur_tile.tile_m * TM + wave_m + fm * 32 + (lane & 31), a.M - 1)];
-                    }
                     __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds(0));
                     asm volatile("" ::: "memory");       // the reads below stay behind the wait
-                    if (CONSTS) {
 #pragma unroll
-                        for (int fm = 0; fm < FM; ++fm) rho_t[fm] = chan[448 + fm * 32 + (lane & 31)];
-                    }
+                    for (int fm = 0; fm < FM; ++fm) rho_t[fm] = chan[448 + fm * 32 + (lane & 31)];
                     scale_acc_rho_tok<FN, FM>(acc, rho_t, acc_bias);
                 } else if constexpr (OWN == 1) scale_acc_rho<FN, FM>(acc, rho, acc_bias);
                 else scale_acc<FN, FM>(acc, a.exp_shift, acc_fix);
@@ -995,8 +1012,8 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
         } else {
             epilogue_patch<FN, FM, PATCH_ROW, EPI, STREAM, false>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, z_launch, sub_bias, nullptr);
         }
-        // (a store is issued for a partial tile as well; only the store of the column maxima is not)
-        if (EPI != kEpiLoads && (!GELU || (full && a.slab_out != nullptr))) {
+        // (a buffer store is issued for a partial tile as well; a store by address or of the column maxima is not)
+        if ((EPI != kEpiAny || (full && a.dbg_acc == nullptr)) && (!GELU || (full && a.slab_out != nullptr))) {
             stores_pending = true;           // exactly STORES stores and no loads were issued
         } else {
             __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // unknown number of vector-memory operations: drain
@@ -1037,7 +1054,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_i8_persist_half(const GemmArgs 
 // 128 x 128 tiles, 4 waves of 64 x 64: for problems whose 256 x 256 tiles would leave the last, or the
 // only, round on the chip half empty.
 template <int STAGES, int EPI, int OWN, bool GELU, bool STREAM>
-__global__ __launch_bounds__(256) void k_gemm_i8_persist4(const GemmArgs a, const TileMap tm)
+__global__ __launch_bounds__(256, EPI == kEpiAny ? 2 : 1) void k_gemm_i8_persist4(const GemmArgs a, const TileMap tm)
 {
     gemm_persist_body<STAGES, 2, 2, 2, 2, EPI, OWN, GELU, STREAM>(a, tm);
 }
@@ -1540,18 +1557,19 @@ constexpr int kDeepSteps = 8;
 
 typedef void (*persist_kernel_t)(const GemmArgs, const TileMap);
 
-// The persistent kernels of one tile: what is fused or rescaled x what the epilogue applies x how Y is stored.
-// nullptr: not built, kEpiGeneral does it.
+// The persistent kernels of one tile: what is fused or rescaled x what the epilogue applies x how Y is stored (kEpiAny
+// decides that itself).  nullptr: not built.
 enum PersistKind { kKindUsual, kKindOwn, kKindOwnToken, kKindGelu, kKinds };
 template <int TILE, int EPI, int OWN, bool GELU>
 persist_kernel_t persist_kernel_of(bool stream)
 {
     constexpr int STAGES = 3;
+    constexpr bool BOTH = EPI != kEpiAny;
 #define MUXQ_FORM(STREAM_)                                                         \
     (TILE == kTile256   ? k_gemm_i8_persist8<STAGES, EPI, OWN, GELU, STREAM_>      \
      : TILE == kTile128 ? k_gemm_i8_persist4<STAGES, EPI, OWN, GELU, STREAM_>      \
                         : k_gemm_i8_persist_half<STAGES, EPI, OWN, GELU, STREAM_>)
-    return stream ? MUXQ_FORM(true) : MUXQ_FORM(false);
+    return stream ? MUXQ_FORM(BOTH) : MUXQ_FORM(false);
 #undef MUXQ_FORM
 }
 template <int TILE>
@@ -1560,7 +1578,7 @@ persist_kernel_t persist_kernel(int kind, int epi, bool stream)
 #define MUXQ_CASE(KIND_, EPI_, OWN_, GELU_) \
     case KIND_ * kEpis + EPI_: return persist_kernel_of<TILE, EPI_, OWN_, GELU_>(stream)
     switch (kind * kEpis + epi) {
-        MUXQ_CASE(kKindUsual, kEpiLoads, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiAny, 0, false);
         MUXQ_CASE(kKindUsual, kEpiGeneral, 0, false);
         MUXQ_CASE(kKindUsual, kEpiPlain, 0, false);
         MUXQ_CASE(kKindUsual, kEpiBias, 0, false);
@@ -1574,19 +1592,19 @@ persist_kernel_t persist_kernel(int kind, int epi, bool stream)
         MUXQ_CASE(kKindUsual, kEpiTokenBias, 0, false);
         MUXQ_CASE(kKindUsual, kEpiVector, 0, false);
         MUXQ_CASE(kKindUsual, kEpiVectorBias, 0, false);
-        MUXQ_CASE(kKindOwn, kEpiLoads, 1, false);
+        MUXQ_CASE(kKindOwn, kEpiAny, 1, false);
         MUXQ_CASE(kKindOwn, kEpiGeneral, 1, false);
         MUXQ_CASE(kKindOwn, kEpiPlainZ, 1, false);
         MUXQ_CASE(kKindOwn, kEpiBiasZ, 1, false);
         MUXQ_CASE(kKindOwn, kEpiChanZ, 1, false);
         MUXQ_CASE(kKindOwn, kEpiChanBiasZ, 1, false);
-        MUXQ_CASE(kKindOwnToken, kEpiLoads, 2, false);
+        MUXQ_CASE(kKindOwnToken, kEpiAny, 2, false);
         MUXQ_CASE(kKindOwnToken, kEpiGeneral, 2, false);
         MUXQ_CASE(kKindOwnToken, kEpiToken, 2, false);
         MUXQ_CASE(kKindOwnToken, kEpiTokenBias, 2, false);
         MUXQ_CASE(kKindOwnToken, kEpiVector, 2, false);
         MUXQ_CASE(kKindOwnToken, kEpiVectorBias, 2, false);
-        MUXQ_CASE(kKindGelu, kEpiLoads, 0, true);
+        MUXQ_CASE(kKindGelu, kEpiAny, 0, true);
         MUXQ_CASE(kKindGelu, kEpiGeneral, 0, true);
         MUXQ_CASE(kKindGelu, kEpiPlainZ, 0, true);
         MUXQ_CASE(kKindGelu, kEpiBiasZ, 0, true);
@@ -1598,34 +1616,19 @@ persist_kernel_t persist_kernel(int kind, int epi, bool stream)
 #undef MUXQ_CASE
 }
 
-// Whether Y goes out as a stream.  Rows on 128-byte lines: a store instruction writes whole lines, and Y, which
-// is not read here again, stays out of the operands' way in L2 (16384 x 1280 -> 3840 90 us through L2, 87 us as a
-// stream).  Rows on 64-byte boundaries: whole transfers still, but half lines, which L2 would join.  That is worth
-// more while the memory-side cache takes Y in, and less once it does not, or while the L2s themselves hold it (768
-// input channels, us through L2 / as a stream: 1000 -> 20000 24.5 / 22.5, 2000 -> 20000 43 / 47, 12000 -> 20000
-// 250 / 202).  Other rows: the transfers at the ends of a piece are completed by the neighbouring piece, which only
-// happens in L2 (3001 -> 4808 19 / 27, 12000 -> 10000 111 / 145).
-bool stream_rows(const GemmArgs &a)
-{
-    const uintptr_t start = (uintptr_t)a.y | (uintptr_t)a.ldy * 2;
-    const size_t mib = ((size_t)a.M * a.N * 2) >> 20;
-    return start % 128 == 0 || (start % 64 == 0 && (mib < 48 || mib >= 256));
-}
-
 template <int TILE>
 persist_kernel_t persist_kernel_for(const GemmArgs &a)
 {
     const int kind = a.gelu ? kKindGelu : !a.aux_own_scale ? kKindUsual : a.x_per_token ? kKindOwnToken : kKindOwn;
     const bool stream = stream_rows(a);
-    int epi = kEpiGeneral;
-    // rows of Y so far apart that 32 of them are beyond a buffer's 32-bit offsets are stored by address
-    if (a.dbg_acc != nullptr || a.ldy >= 1 << 25) epi = kEpiLoads;
-    else if (!a.x_per_token)
-        epi = (a.cn != nullptr ? kEpiPlainZ : kEpiPlain) + (a.w_per_channel ? 2 : 0) + (a.bias != nullptr ? 1 : 0);
-    else if (a.cn != nullptr)
-        epi = (a.w_per_channel ? kEpiVector : kEpiToken) + (a.bias != nullptr ? 1 : 0);
+    int epi = (a.x_per_token ? a.w_per_channel ? kEpiVector : kEpiToken
+                             : (a.cn != nullptr ? kEpiPlainZ : kEpiPlain) + (a.w_per_channel ? 2 : 0)) + (a.bias != nullptr ? 1 : 0);
+    // (32 rows of Y 2^25 elements apart are beyond the 32-bit offsets of the usual kernels' buffer.  Buffers of 8 rows in
+    // all kernels: 16384 x 1280 -> 3840 per vector 112.3 -> 113.5 us.)
+    if (a.dbg_acc != nullptr || a.ldy >= 1 << 25) epi = kEpiAny;
     const persist_kernel_t k = persist_kernel<TILE>(kind, epi, stream);
-    return k != nullptr ? k : persist_kernel<TILE>(kind, kEpiGeneral, stream);
+    // (the GELU without a bias: c_fc has one, so those are one kernel)
+    return k != nullptr || kind != kKindGelu ? k : persist_kernel<TILE>(kind, kEpiGeneral, stream);
 }
 
 template <int STAGES, int TILE>
@@ -1690,6 +1693,7 @@ hipError_t launch_persist(const GemmArgs &a, hipStream_t s)
     constexpr int wgs_per_cu = 160 * 1024 / lds_bytes;     // by LDS; registers allow at least as many
     static_assert(wgs_per_cu >= 1, "ring too deep");
     const persist_kernel_t kern = persist_kernel_for<TILE>(a);
+    if (kern == nullptr) return hipErrorInvalidDeviceFunction;
     int n_cu = 0;
     const hipError_t e = current_device_cus(n_cu);
     if (e != hipSuccess) return e;

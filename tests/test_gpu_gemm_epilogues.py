@@ -87,17 +87,31 @@ def test_aux_on_its_own_scale_with_every_kind_of_scales(w_gran, x_gran, bias_see
     check_own_scale(Case("epilogue_own", 1500, 264, 2056, 6, U, 920), w_gran=w_gran, x_gran=x_gran, bias_seed=bias_seed)
 
 
-@pytest.mark.parametrize("ldy", [(1 << 25) - 8, 1 << 25])
-def test_rows_of_y_far_apart(ldy):
-    """Row strides at the end of what a buffer's 32-bit offsets reach, and one beyond it."""
-    M, K, N = 129, 712, 16384
+FAR = {"128x128": (129, 712, 16384), "256x256": (200, 264, 65536), "128x256": (129, 2048, 32768)}
+
+
+@pytest.mark.parametrize("form,ldy", [("128x128", (1 << 25) - 8), ("128x128", 1 << 25), ("128x128", (1 << 28) - 64),
+                                      ("128x128", (1 << 28) - 56), ("256x256", (1 << 28) - 64), ("256x256", 1 << 28),
+                                      ("128x256", (1 << 28) - 64), ("128x256", 1 << 28)])
+def test_rows_of_y_far_apart(form, ldy):
+    """Row strides up to what a buffer's 32-bit offsets reach, and beyond it; 70 to 110 GB that are not touched in between.
+    The fused GELU against the same call with rows next to each other."""
+    M, K, N = FAR[form]
+    torch.cuda.empty_cache()
     rng = np.random.default_rng(ldy)
     X, _ = synth.make_x(M, K, 5, U, rng)
     W = synth.make_w(K, N, rng)
+    Xd = torch.from_numpy(X).cuda()
     out = torch.empty((M, ldy), dtype=torch.float16, device="cuda")
     out[:, N:N + 64] = 7.0
     w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(W).cuda())
-    B.muxq_linear(torch.from_numpy(X).cuda(), w_q, w_s, N, out=out[:, :N])
+    B.muxq_linear(Xd, w_q, w_s, N, out=out[:, :N])
     rows = sample_rows(M, 60, 3)
     assert (out[:, :N].cpu().numpy()[rows] == orc.linear(X, W, rows=rows)["y16"]).all()
     assert (out[:, N:N + 64] == 7.0).all()
+    if ldy > (1 << 28) - 64:
+        B.muxq_linear_gelu(Xd, w_q, w_s, N, out=out[:, :N])
+        assert torch.equal(out[:, :N], B.muxq_linear_gelu(Xd, w_q, w_s, N)[0])
+        assert (out[:, N:N + 64] == 7.0).all()
+    del out
+    torch.cuda.empty_cache()
