@@ -1579,7 +1579,6 @@ persist_kernel_t persist_kernel(int kind, int epi, bool stream)
     case KIND_ * kEpis + EPI_: return persist_kernel_of<TILE, EPI_, OWN_, GELU_>(stream)
     switch (kind * kEpis + epi) {
         MUXQ_CASE(kKindUsual, kEpiAny, 0, false);
-        MUXQ_CASE(kKindUsual, kEpiGeneral, 0, false);
         MUXQ_CASE(kKindUsual, kEpiPlain, 0, false);
         MUXQ_CASE(kKindUsual, kEpiBias, 0, false);
         MUXQ_CASE(kKindUsual, kEpiChan, 0, false);
@@ -1593,13 +1592,11 @@ persist_kernel_t persist_kernel(int kind, int epi, bool stream)
         MUXQ_CASE(kKindUsual, kEpiVector, 0, false);
         MUXQ_CASE(kKindUsual, kEpiVectorBias, 0, false);
         MUXQ_CASE(kKindOwn, kEpiAny, 1, false);
-        MUXQ_CASE(kKindOwn, kEpiGeneral, 1, false);
         MUXQ_CASE(kKindOwn, kEpiPlainZ, 1, false);
         MUXQ_CASE(kKindOwn, kEpiBiasZ, 1, false);
         MUXQ_CASE(kKindOwn, kEpiChanZ, 1, false);
         MUXQ_CASE(kKindOwn, kEpiChanBiasZ, 1, false);
         MUXQ_CASE(kKindOwnToken, kEpiAny, 2, false);
-        MUXQ_CASE(kKindOwnToken, kEpiGeneral, 2, false);
         MUXQ_CASE(kKindOwnToken, kEpiToken, 2, false);
         MUXQ_CASE(kKindOwnToken, kEpiTokenBias, 2, false);
         MUXQ_CASE(kKindOwnToken, kEpiVector, 2, false);
