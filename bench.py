@@ -263,15 +263,12 @@ def main():
                         r_cap=r_cap, out=Y, workspace=ws, wg_ticks=wg_ticks)
     torch.cuda.synchronize()
     n_used = int(B.ws_view(ws, lay, "n_outliers", M, N, r_cap)[0].item())
-    t256, t128 = -(-M // 256) * -(-N // 256), -(-M // 128) * -(-N // 128)
-    kernel = ("k_gemm_i8_persist8" if t256 >= 144 else
-              "k_gemm_i8_persist4" if lay.k_pad >= 2048 or (lay.k_pad >= 1024 and 128 <= t128 <= 384)
-              else "k_gemm_i8_small")
+    kernel = B.gemm_kernel(M, K, N)
     # how evenly the 8 XCDs finish (last call; workgroup i runs on XCD i % 8; ticks of 10 ns)
     xcd = None
     tk = wg_ticks.cpu().numpy().reshape(-1, 2)
     live = tk[:, 1] > 0
-    if kernel != "k_gemm_i8_small" and live.any():
+    if kernel.startswith("k_gemm_i8_persist") and live.any():
         t0 = tk[live, 0].min()
         on = lambda x: live & (np.arange(len(tk)) % 8 == x)
         xs = [x for x in range(8) if on(x).any()]

@@ -27,6 +27,10 @@ int muxq_linear_timed(const void *X_fp16, int M, int K, int ldx, const int8_t *w
                       void *workspace, size_t workspace_bytes, const muxq_act_opts *opts,
                       void *gemm_start, void *gemm_stop, int64_t *wg_ticks, void *stream);
 
+/* Name of the kernel that runs the GEMM of an M x K -> N layer ("" for shapes that are refused).  muxq_linear has one
+ * launch without it for few tokens; muxq_linear_timed and muxq_gemm_i8 always use it. */
+const char *muxq_gemm_kernel(int M, int K, int N);
+
 /* The issue rate of the INT8 MFMA instruction the GEMM uses (v_mfma_i32_32x32x32_i8) with
  * operands held in registers and nothing else running, on operand codes sampled from
  * a_codes / b_codes (device pointers, 16-byte aligned, n_bytes >= 16 each).  The matrix pipes

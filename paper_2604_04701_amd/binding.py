@@ -24,7 +24,7 @@ EXPORTS = ["muxq_version", "muxq_status_string", "muxq_k_pad", "muxq_wq_bytes",
            "muxq_noalloc_max_bytes", "muxq_linear_noalloc", "muxq_linear_gelu", "muxq_linear_gelu_slabs",
            "muxq_mlp", "muxq_mlp_workspace_bytes",
            "muxq_quantize_weight_smooth", "muxq_smooth_absmax",
-           "muxq_probe_mfma_rate", "muxq_static_bytes", "muxq_static_layout_of",
+           "muxq_probe_mfma_rate", "muxq_gemm_kernel", "muxq_static_bytes", "muxq_static_layout_of",
            "muxq_prepare_static", "muxq_linear_static", "muxq_gelu_absmax"]
 
 
@@ -128,6 +128,8 @@ def lib():
         L.muxq_quantize_weight_smooth.argtypes = [vp, i, i, i, i, i, vp, vp, vp, vp]
         L.muxq_smooth_absmax.restype = i
         L.muxq_smooth_absmax.argtypes = [vp, i, i, i, vp, vp, i, vp, vp]
+        L.muxq_gemm_kernel.restype = C.c_char_p
+        L.muxq_gemm_kernel.argtypes = [i, i, i]
         L.muxq_linear_gelu_slabs.restype = i
         L.muxq_linear_gelu_slabs.argtypes = [i, i, i]
         L.muxq_linear_gelu.restype = i
@@ -438,6 +440,11 @@ def muxq_linear_timed(X, w_q, w_scale, N, gemm_start, gemm_stop, w_gran="tensor"
                                    _p(workspace), workspace.numel(), C.byref(opts), gemm_start,
                                    gemm_stop, _p(wg_ticks), _stream()), "muxq_linear_timed")
     return out
+
+
+def gemm_kernel(M: int, K: int, N: int) -> str:
+    """Name of the kernel that runs the GEMM of an M x K -> N layer (include/muxq_measure.h)."""
+    return lib().muxq_gemm_kernel(M, K, N).decode()
 
 
 def wq_row_sums(w_q, K: int, N: int):

@@ -647,6 +647,11 @@ int muxq_linear_opts(const void *X, int M, int K, int ldx, const int8_t *w_q, co
                        opts && opts->aux_own_scale, opts ? opts->absmax_slabs : 0);
 }
 
+const char *muxq_gemm_kernel(int M, int K, int N)
+{
+    return check_dims(M, K, N) ? "" : muxq::gemm_kernel_name(M, N, kpad(K));
+}
+
 int muxq_linear_gelu_slabs(int M, int K, int N)
 {
     if (check_dims(M, K, N)) return 0;

@@ -1797,6 +1797,17 @@ int gemm_tile_rows(int M, int N, int k_pad)
     }
 }
 
+const char *gemm_kernel_name(int M, int N, int k_pad)
+{
+    switch (gemm_form(M, N, k_pad)) {
+    case kPersist256: return "k_gemm_i8_persist8";
+    case kPersist128: return "k_gemm_i8_persist4";
+    case kPersistHalf: return "k_gemm_i8_persist_half";
+    case kSmall64: return "k_gemm_i8_small";
+    default: return "k_gemm_i8_direct";
+    }
+}
+
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
 {
     switch (gemm_form(a.M, a.N, a.k_pad)) {

@@ -385,6 +385,7 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s);
 // Rows per output tile of the form launch_gemm picks for this problem, or 0 when it picks the
 // register-staged form (which does not write slab_out).
 int gemm_tile_rows(int M, int N, int k_pad);
+const char *gemm_kernel_name(int M, int N, int k_pad);
 
 // Per-device set-up of the GEMM kernels for the CURRENT device: the LDS attribute of the
 // persistent kernels and the CU count their grid is sized by.  Thread-safe, idempotent, and

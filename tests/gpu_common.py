@@ -170,11 +170,11 @@ def rows_every_block(M, seed, block=64):
     return sorted(rows)
 
 
-def check_own_scale(case: synth.Case, X=None, W=None, bias_seed=None, **over):
+def check_own_scale(case: synth.Case, X=None, W=None, bias_seed=None, rows=None, **over):
     """muxq_linear with Aux on a scale of its own against the oracle's aux_scale="own": scales and
     codes bit for bit; the accumulators equal acc_body + rne(rho * acc_aux) with
     rho = (2^e - 1) s_aux / s_x in binary32 (the library's stated recombination); Y within half a
-    unit of s_x s_w[n] plus rounding of the oracle's sum after dequantisation."""
+    unit of s_x s_w[n] plus rounding of the oracle's sum after dequantisation.  rows: the products on those only."""
     if X is None:
         X, W, _ = synth.make_case(case)
     kw = dict(w_gran=case.w_gran, threshold=case.threshold, e=case.exp, r_cap=case.r_cap)
@@ -186,7 +186,7 @@ def check_own_scale(case: synth.Case, X=None, W=None, bias_seed=None, **over):
     x_gran = kw.get("x_gran", "tensor")
     g = run_gpu(X, W, bias=bias, aux_scale="own", **kw)
     o = orc.linear(X, W, threshold=kw["threshold"], e=kw["e"], r_cap=kw["r_cap"], w_gran=kw["w_gran"],
-                   bias16=bias, aux_scale="own", x_gran=x_gran)
+                   bias16=bias, aux_scale="own", x_gran=x_gran, rows=rows)
     M, K, r, e = X.shape[0], X.shape[1], o["n_used"], kw["e"]
     assert g["n_outliers"].tolist() == [r, o["n_total"]]
     cfac = np.float32((1 << e) - 1)
@@ -208,10 +208,13 @@ def check_own_scale(case: synth.Case, X=None, W=None, bias_seed=None, **over):
         sxc, sac, rhoc = sx.astype(np.float64).reshape(-1, 1), sa.astype(np.float64).reshape(-1, 1), rho.reshape(-1, 1)
     assert (g["body_q"][:, :K] == o["body_q"]).all(), "body_q"
     assert (g["aux_q"][:, :r] == o["aux_q"]).all() and (g["aux_q"][:, r:] == 0).all(), "aux_q"
+    sel = slice(None) if rows is None else np.asarray(rows)
+    if x_gran == "token":
+        sxc, sac, rhoc = sxc[sel], sac[sel], rhoc[sel]
     want = o["acc_body"].astype(np.int64) + np.rint(rhoc * o["acc_aux"].astype(np.float32)).astype(np.int64)
-    assert (g["acc"] == want).all(), "accumulators after the rescale"
+    assert (g["acc"][sel] == want).all(), "accumulators after the rescale"
     sw = o["s_w"].astype(np.float64).reshape(1, -1)
-    yg = g["Y"].astype(np.float64)
+    yg = g["Y"][sel].astype(np.float64)
     # half a unit of s_x s_w[n] from rounding the Aux term to Body's grid; the fp16 rounding of
     # the output (2^-11 |y|); binary32 roundings of the two products on either side, which are
     # relative to the terms and not to their (possibly cancelling) sum

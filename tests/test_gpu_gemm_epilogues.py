@@ -12,6 +12,21 @@ pytestmark = pytest.mark.gpu
 U = (20.0, 100.0)
 # more tiles than workgroups are resident (512 of 128 x 128 and 128 x 256, 256 of 256 x 256), partial in both directions
 FORMS = {"128x128": (6607, 72, 2312), "256x256": (5222, 72, 4112), "128x256": (3400, 520, 6304)}
+FAR = {"128x128": (129, 712, 16384), "256x256": (200, 264, 65536), "128x256": (129, 2048, 32768)}
+KERNELS = {"128x128": "k_gemm_i8_persist4", "256x256": "k_gemm_i8_persist8", "128x256": "k_gemm_i8_persist_half"}
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_the_shapes_below_take_the_kernels_they_are_listed_for(form):
+    (M, K, N), (m, k, n) = FORMS[form], FAR[form]
+    assert B.gemm_kernel(M, K, N) == B.gemm_kernel(m, k, n) == KERNELS[form]
+    tn, tm = (int(x) for x in form.split("x"))
+    assert -(-N // tn) * -(-M // tm) > (256 if form == "256x256" else 512)
+
+
+def row_strides(N):
+    """On 128-byte lines, where Y goes out as a stream, and off 64 bytes, where it goes through L2."""
+    return (N + 63) // 64 * 64, N + 8 if (N + 8) % 32 else N + 16
 
 
 @pytest.mark.parametrize("on_lines", [True, False])
@@ -29,7 +44,7 @@ def test_every_combination_of_scales_and_bias(form, x_gran, w_gran, bias_seed, o
     bd = None if bias is None else torch.from_numpy(bias).cuda()
     Xd = torch.from_numpy(X).cuda()
     w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(W).cuda(), w_gran)
-    ldy = (N + 63) // 64 * 64 if on_lines else N + 8 if (N + 8) % 32 else N + 16
+    ldy = row_strides(N)[0 if on_lines else 1]
     out = torch.full((M, ldy), 7.0, dtype=torch.float16, device="cuda")
     say(f"[epilogue] {form} x={x_gran} w={w_gran} bias={bias_seed} ldy={ldy}")
     if x_gran == "naive":
@@ -41,6 +56,45 @@ def test_every_combination_of_scales_and_bias(form, x_gran, w_gran, bias_seed, o
     got = out.cpu().numpy()
     assert (got[rows][:, :N] == o["y16"]).all()
     assert (got[:, N:] == 7.0).all()
+
+
+@pytest.mark.parametrize("on_lines", [True, False])
+@pytest.mark.parametrize("bias_seed", [None, 9])
+@pytest.mark.parametrize("w_gran", ["tensor", "channel"])
+@pytest.mark.parametrize("form", FORMS)
+def test_gemm_on_codes_without_a_zero_point(form, w_gran, bias_seed, on_lines):
+    """muxq_gemm_i8 on codes of the full range, with Aux steps and without: Y is the product of the codes, exact."""
+    M, K, N = FORMS[form]
+    rng = np.random.default_rng(M + N)
+    rows = np.array(rows_every_block(M, 13))
+    kp = B.k_pad(K)
+    a = rng.integers(-127, 128, (M, kp), dtype=np.int8)
+    aux = rng.integers(-127, 128, (M, 64), dtype=np.int8)
+    w_aux = rng.integers(-127, 128, (N, 64), dtype=np.int8)
+    a[:, K:] = 0
+    aux[:, 5:] = 0
+    w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(synth.make_w(K, N, rng)).cuda(), w_gran)
+    wn = B.unpack(w_q, N, kp).cpu().numpy()
+    bias = None if bias_seed is None else np.random.default_rng(bias_seed).standard_normal(N).astype(np.float16)
+    sx = np.float32(0.013)
+    dev = lambda t: torch.from_numpy(t).cuda()
+    ldy = row_strides(N)[0 if on_lines else 1]
+    say(f"[gemm] {form} w={w_gran} bias={bias_seed} ldy={ldy}")
+    for with_aux in (False, True):
+        out = torch.full((M, ldy), 7.0, dtype=torch.float16, device="cuda")
+        extra = dict(aux_q=B.pack(dev(aux)), w_aux=B.pack(dev(w_aux)), r_cap=64, exp=3,
+                     n_outliers=torch.tensor([5, 5], dtype=torch.int32, device="cuda")) if with_aux else {}
+        B.muxq_gemm_i8(B.pack(dev(a)), M, K, w_q, N, torch.tensor([sx, 1 / sx], device="cuda"), w_s, w_gran,
+                       bias=None if bias is None else dev(bias), out=out[:, :N], **extra)
+        # whole numbers below 2^53: exact in binary64
+        acc = a[rows].astype(np.float64) @ wn.T.astype(np.float64)
+        if with_aux:
+            acc += 7.0 * (aux[rows].astype(np.float64) @ w_aux.T.astype(np.float64))
+        y = (sx * w_s.cpu().numpy()) * acc.astype(np.float32)
+        want = (y if bias is None else y + bias.astype(np.float32)).astype(np.float16)
+        got = out.cpu().numpy()
+        assert (got[rows][:, :N] == want).all()
+        assert (got[:, N:] == 7.0).all()
 
 
 @pytest.mark.parametrize("M,K,N", [(1500, 264, 2056), (3400, 520, 6304)])
@@ -83,11 +137,20 @@ def test_128x256_tiles(M, K, N):
 
 @pytest.mark.parametrize("w_gran,x_gran", [("tensor", "tensor"), ("channel", "tensor"), ("tensor", "token"), ("channel", "token")])
 @pytest.mark.parametrize("bias_seed", [None, 8])
-def test_aux_on_its_own_scale_with_every_kind_of_scales(w_gran, x_gran, bias_seed):
-    check_own_scale(Case("epilogue_own", 1500, 264, 2056, 6, U, 920), w_gran=w_gran, x_gran=x_gran, bias_seed=bias_seed)
-
-
-FAR = {"128x128": (129, 712, 16384), "256x256": (200, 264, 65536), "128x256": (129, 2048, 32768)}
+@pytest.mark.parametrize("form", FORMS)
+def test_aux_on_its_own_scale_with_every_kind_of_scales(form, w_gran, x_gran, bias_seed):
+    """With the accumulators exported (a kernel of its own) against the oracle; without, as a program calls it, the same Y."""
+    M, K, N = FORMS[form]
+    case = Case("epilogue_own", M, K, N, 6, U, 920 + M)
+    g, _ = check_own_scale(case, rows=rows_every_block(M, 15), w_gran=w_gran, x_gran=x_gran, bias_seed=bias_seed)
+    X, W, _ = synth.make_case(case)
+    bias = None if bias_seed is None else torch.from_numpy(np.random.default_rng(bias_seed).standard_normal(N).astype(np.float16)).cuda()
+    w_q, w_s = B.muxq_quantize_weight(torch.from_numpy(W).cuda(), w_gran)
+    for ldy in row_strides(N):
+        out = torch.full((M, ldy), 7.0, dtype=torch.float16, device="cuda")
+        B.muxq_linear(torch.from_numpy(X).cuda(), w_q, w_s, N, w_gran, bias=bias, out=out[:, :N], x_gran=x_gran, aux_scale="own")
+        got = out.cpu().numpy()
+        assert (got[:, :N] == g["Y"]).all() and (got[:, N:] == 7.0).all()
 
 
 @pytest.mark.parametrize("form,ldy", [("128x128", (1 << 25) - 8), ("128x128", 1 << 25), ("128x128", (1 << 28) - 64),
