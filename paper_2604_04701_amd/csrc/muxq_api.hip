@@ -358,7 +358,7 @@ const char *muxq_status_string(int status)
 
 int muxq_init(void)
 {
-    MUXQ_TRY(muxq::gemm_prepare_device());
+    MUXQ_TRY(muxq::gemm_prepare_all());
     void *p = nullptr;
     MUXQ_TRY(noalloc_scratch_ptr(&p));
     return MUXQ_OK;

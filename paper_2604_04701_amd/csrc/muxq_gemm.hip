@@ -63,6 +63,13 @@
 #include <atomic>
 #include <mutex>
 
+// Compiled four times, as device binaries that are loaded when the first of their kernels is used: this file with the usual
+// kernels, and muxq_gemm_own.hip, _gelu.hip and _codes.hip, which include it, with those of part_of.  (All in one binary
+// loading the library took 2.9 ms and a program's first call 10 ms; so 1.0 and 3.2 ms, as with 16 kernels in all.)
+#ifndef MUXQ_GEMM_PART
+#define MUXQ_GEMM_PART 0
+#endif
+
 namespace muxq {
 namespace {
 
@@ -1059,6 +1066,8 @@ __global__ __launch_bounds__(256, EPI == kEpiAny ? 2 : 1) void k_gemm_i8_persist
     gemm_persist_body<STAGES, 2, 2, 2, 2, EPI, OWN, GELU, STREAM>(a, tm);
 }
 
+#if MUXQ_GEMM_PART == 0
+
 // --------------------------------------------------------------------------
 // Small tiles (64 x 64), 4 waves, register staging.
 // --------------------------------------------------------------------------
@@ -1539,6 +1548,8 @@ TileMap make_tile_map(const GemmArgs &a, int TN, int TM, int &grid, bool persist
     return tm;
 }
 
+#endif  // MUXQ_GEMM_PART == 0
+
 // LDS bytes of a persistent kernel: the operand ring, the waves' epilogue patches and constants.
 enum PersistTileForm { kTile256, kTile128, kTileHalf };
 constexpr int tile_n_of(int t) { return t == kTile256 ? 256 : 128; }
@@ -1550,10 +1561,6 @@ constexpr int persist_lds_bytes()
     return STAGES * (tile_n_of(TILE) + tile_m_of(TILE)) * BK +
            waves_of(TILE) * ((TILE == kTileHalf ? 0 : 32 * (2 * 64 + 16)) + kChanFloats * 4);
 }
-
-// K steps whose loads a workgroup of k_gemm_i8_small_deep issues together (64 staging registers,
-// 64 KiB of LDS).
-constexpr int kDeepSteps = 8;
 
 typedef void (*persist_kernel_t)(const GemmArgs, const TileMap);
 
@@ -1572,17 +1579,22 @@ persist_kernel_t persist_kernel_of(bool stream)
     return stream ? MUXQ_FORM(BOTH) : MUXQ_FORM(false);
 #undef MUXQ_FORM
 }
-template <int TILE>
-persist_kernel_t persist_kernel(int kind, int epi, bool stream)
+// Which binary a kernel is in: 1 own scales of Aux, 2 the fused GELU, 3 what a layer has no use for in its calls (the
+// accumulator export, far rows, muxq_gemm_i8 on its own).
+constexpr int part_of(int kind, int epi)
 {
-#define MUXQ_CASE(KIND_, EPI_, OWN_, GELU_) \
+    return kind == kKindOwn || kind == kKindOwnToken ? 1 : kind == kKindGelu ? 2 : epi == kEpiAny || (epi >= kEpiPlain && epi <= kEpiChanBias) ? 3 : 0;
+}
+
+// The kernels of this binary.
+template <int TILE>
+persist_kernel_t persist_kernel_here(int kind, int epi, bool stream)
+{
+#define MUXQ_CASE(KIND_, EPI_, OWN_, GELU_)                                                        \
+    static_assert(part_of(KIND_, EPI_) == MUXQ_GEMM_PART, "in another binary");                    \
     case KIND_ * kEpis + EPI_: return persist_kernel_of<TILE, EPI_, OWN_, GELU_>(stream)
     switch (kind * kEpis + epi) {
-        MUXQ_CASE(kKindUsual, kEpiAny, 0, false);
-        MUXQ_CASE(kKindUsual, kEpiPlain, 0, false);
-        MUXQ_CASE(kKindUsual, kEpiBias, 0, false);
-        MUXQ_CASE(kKindUsual, kEpiChan, 0, false);
-        MUXQ_CASE(kKindUsual, kEpiChanBias, 0, false);
+#if MUXQ_GEMM_PART == 0
         MUXQ_CASE(kKindUsual, kEpiPlainZ, 0, false);
         MUXQ_CASE(kKindUsual, kEpiBiasZ, 0, false);
         MUXQ_CASE(kKindUsual, kEpiChanZ, 0, false);
@@ -1591,6 +1603,7 @@ persist_kernel_t persist_kernel(int kind, int epi, bool stream)
         MUXQ_CASE(kKindUsual, kEpiTokenBias, 0, false);
         MUXQ_CASE(kKindUsual, kEpiVector, 0, false);
         MUXQ_CASE(kKindUsual, kEpiVectorBias, 0, false);
+#elif MUXQ_GEMM_PART == 1
         MUXQ_CASE(kKindOwn, kEpiAny, 1, false);
         MUXQ_CASE(kKindOwn, kEpiPlainZ, 1, false);
         MUXQ_CASE(kKindOwn, kEpiBiasZ, 1, false);
@@ -1601,6 +1614,7 @@ persist_kernel_t persist_kernel(int kind, int epi, bool stream)
         MUXQ_CASE(kKindOwnToken, kEpiTokenBias, 2, false);
         MUXQ_CASE(kKindOwnToken, kEpiVector, 2, false);
         MUXQ_CASE(kKindOwnToken, kEpiVectorBias, 2, false);
+#elif MUXQ_GEMM_PART == 2
         MUXQ_CASE(kKindGelu, kEpiAny, 0, true);
         MUXQ_CASE(kKindGelu, kEpiGeneral, 0, true);
         MUXQ_CASE(kKindGelu, kEpiPlainZ, 0, true);
@@ -1608,52 +1622,87 @@ persist_kernel_t persist_kernel(int kind, int epi, bool stream)
         MUXQ_CASE(kKindGelu, kEpiChanBiasZ, 0, true);
         MUXQ_CASE(kKindGelu, kEpiTokenBias, 0, true);
         MUXQ_CASE(kKindGelu, kEpiVectorBias, 0, true);
+#else
+        MUXQ_CASE(kKindUsual, kEpiAny, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiPlain, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiBias, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiChan, 0, false);
+        MUXQ_CASE(kKindUsual, kEpiChanBias, 0, false);
+#endif
     default: return nullptr;
     }
 #undef MUXQ_CASE
 }
 
-template <int TILE>
-persist_kernel_t persist_kernel_for(const GemmArgs &a)
+}  // namespace
+
+template <int PART> const void *persist_kernel_of_part(int tile, int kind, int epi, bool stream);
+template <> const void *persist_kernel_of_part<MUXQ_GEMM_PART>(int tile, int kind, int epi, bool stream)
 {
-    const int kind = a.gelu ? kKindGelu : !a.aux_own_scale ? kKindUsual : a.x_per_token ? kKindOwnToken : kKindOwn;
-    const bool stream = stream_rows(a);
-    int epi = (a.x_per_token ? a.w_per_channel ? kEpiVector : kEpiToken
-                             : (a.cn != nullptr ? kEpiPlainZ : kEpiPlain) + (a.w_per_channel ? 2 : 0)) + (a.bias != nullptr ? 1 : 0);
-    // (32 rows of Y 2^25 elements apart are beyond the 32-bit offsets of the usual kernels' buffer.  Buffers of 8 rows in
-    // all kernels: 16384 x 1280 -> 3840 per vector 112.3 -> 113.5 us.)
-    if (a.dbg_acc != nullptr || a.ldy >= 1 << 25) epi = kEpiAny;
-    const persist_kernel_t k = persist_kernel<TILE>(kind, epi, stream);
-    // (the GELU without a bias: c_fc has one, so those are one kernel)
-    return k != nullptr || kind != kKindGelu ? k : persist_kernel<TILE>(kind, kEpiGeneral, stream);
+    return (const void *)(tile == kTile256   ? persist_kernel_here<kTile256>(kind, epi, stream)
+                          : tile == kTile128 ? persist_kernel_here<kTile128>(kind, epi, stream)
+                                             : persist_kernel_here<kTileHalf>(kind, epi, stream));
 }
 
-template <int STAGES, int TILE>
-hipError_t persist_lds_attributes()
+#if MUXQ_GEMM_PART == 0
+
+template <> const void *persist_kernel_of_part<1>(int tile, int kind, int epi, bool stream);
+template <> const void *persist_kernel_of_part<2>(int tile, int kind, int epi, bool stream);
+template <> const void *persist_kernel_of_part<3>(int tile, int kind, int epi, bool stream);
+
+namespace {
+
+persist_kernel_t persist_kernel(int tile, int kind, int epi, bool stream)
 {
-    for (int i = 0; i < kKinds * kEpis * 2; ++i) {
-        const persist_kernel_t k = persist_kernel<TILE>(i / 2 / kEpis, i / 2 % kEpis, i % 2 != 0);
-        if (k == nullptr) continue;
-        const hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 persist_lds_bytes<STAGES, TILE>());
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    const int part = part_of(kind, epi);
+    return (persist_kernel_t)(part == 1   ? persist_kernel_of_part<1>(tile, kind, epi, stream)
+                              : part == 2 ? persist_kernel_of_part<2>(tile, kind, epi, stream)
+                              : part == 3 ? persist_kernel_of_part<3>(tile, kind, epi, stream)
+                                          : persist_kernel_of_part<0>(tile, kind, epi, stream));
 }
+
+// K steps whose loads a workgroup of k_gemm_i8_small_deep issues together (64 staging registers,
+// 64 KiB of LDS).
+constexpr int kDeepSteps = 8;
 
 // What the launcher needs to know about a device, found once per device (gemm_prepare_device).
 constexpr int kMaxDevices = 64;
 std::atomic<int> g_device_cus[kMaxDevices];      // 0 = not prepared yet
 std::mutex g_prepare_mutex;
 
+// The persistent kernels take more LDS than a kernel may without asking, so each needs an attribute set on each device, which
+// loads its binary: for a kernel's first launch, and in muxq_init for all (first launches under capture).
+std::atomic<unsigned char> g_lds_set[kMaxDevices][3][kKinds * kEpis * 2];
+
+template <int STAGES, int TILE>
+hipError_t set_persist_lds(int dev, int kind, int epi, bool stream, persist_kernel_t k)
+{
+    std::atomic<unsigned char> &set = g_lds_set[dev][TILE][(kind * kEpis + epi) * 2 + (stream ? 1 : 0)];
+    if (set.load(std::memory_order_acquire) != 0) return hipSuccess;
+    std::lock_guard<std::mutex> lock(g_prepare_mutex);
+    const hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             persist_lds_bytes<STAGES, TILE>());
+    if (e == hipSuccess) set.store(1, std::memory_order_release);
+    return e;
+}
+
+template <int STAGES, int TILE>
+hipError_t set_all_persist_lds(int dev)
+{
+    for (int i = 0; i < kKinds * kEpis * 2; ++i) {
+        const int kind = i / 2 / kEpis, epi = i / 2 % kEpis;
+        const persist_kernel_t k = persist_kernel(TILE, kind, epi, i % 2 != 0);
+        const hipError_t e = k == nullptr ? hipSuccess : set_persist_lds<STAGES, TILE>(dev, kind, epi, i % 2 != 0, k);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t prepare_current_device(int dev)
 {
     std::lock_guard<std::mutex> lock(g_prepare_mutex);
     if (g_device_cus[dev].load(std::memory_order_acquire) != 0) return hipSuccess;
     hipError_t e;
-    if ((e = persist_lds_attributes<3, kTile256>()) != hipSuccess) return e;
-    if ((e = persist_lds_attributes<3, kTile128>()) != hipSuccess) return e;
-    if ((e = persist_lds_attributes<3, kTileHalf>()) != hipSuccess) return e;
     e = hipFuncSetAttribute((const void *)k_gemm_i8_small_deep<kDeepSteps>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, kDeepSteps * 128 * BK);
     if (e != hipSuccess) return e;
@@ -1667,9 +1716,9 @@ hipError_t prepare_current_device(int dev)
 }
 
 // CU count (rounded down to a multiple of 8) of the current device, preparing it on first use.
-hipError_t current_device_cus(int &n_cu)
+hipError_t current_device_cus(int &n_cu, int &dev)
 {
-    int dev = 0;
+    dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
@@ -1683,17 +1732,25 @@ hipError_t current_device_cus(int &n_cu)
 template <int STAGES, int TILE>
 hipError_t launch_persist(const GemmArgs &a, hipStream_t s)
 {
-    static_assert(STAGES == 3, "gemm_prepare_device sets the LDS attribute of the 3-stage forms");
     int total;
     const TileMap tm = make_tile_map(a, tile_n_of(TILE), tile_m_of(TILE), total, true, TILE == kTile256 ? 32 : 64);
     constexpr int lds_bytes = persist_lds_bytes<STAGES, TILE>();
     constexpr int wgs_per_cu = 160 * 1024 / lds_bytes;     // by LDS; registers allow at least as many
     static_assert(wgs_per_cu >= 1, "ring too deep");
-    const persist_kernel_t kern = persist_kernel_for<TILE>(a);
+    const int kind = a.gelu ? kKindGelu : !a.aux_own_scale ? kKindUsual : a.x_per_token ? kKindOwnToken : kKindOwn;
+    const bool stream = stream_rows(a);
+    int epi = (a.x_per_token ? a.w_per_channel ? kEpiVector : kEpiToken
+                             : (a.cn != nullptr ? kEpiPlainZ : kEpiPlain) + (a.w_per_channel ? 2 : 0)) + (a.bias != nullptr ? 1 : 0);
+    // (32 rows of Y 2^25 elements apart are beyond the 32-bit offsets of the usual kernels' buffer.  Buffers of 8 rows in
+    // all kernels: 16384 x 1280 -> 3840 per vector 112.3 -> 113.5 us.)
+    if (a.dbg_acc != nullptr || a.ldy >= 1 << 25) epi = kEpiAny;
+    persist_kernel_t kern = persist_kernel(TILE, kind, epi, stream);
+    // (the GELU without a bias: c_fc has one, so those are one kernel)
+    if (kern == nullptr && kind == kKindGelu) kern = persist_kernel(TILE, kind, epi = kEpiGeneral, stream);
     if (kern == nullptr) return hipErrorInvalidDeviceFunction;
-    int n_cu = 0;
-    const hipError_t e = current_device_cus(n_cu);
-    if (e != hipSuccess) return e;
+    int n_cu = 0, dev = 0;
+    hipError_t e = current_device_cus(n_cu, dev);
+    if (e != hipSuccess || (e = set_persist_lds<STAGES, TILE>(dev, kind, epi, stream, kern)) != hipSuccess) return e;
     const int grid = total < n_cu * wgs_per_cu ? total : n_cu * wgs_per_cu;
     return launch_kernel(kern, dim3(grid), dim3(waves_of(TILE) * 64), lds_bytes, s, a, tm);
 }
@@ -1702,8 +1759,8 @@ hipError_t launch_small(const GemmArgs &a, hipStream_t s)
 {
     int grid;
     const TileMap tm = make_tile_map(a, 64, 64, grid);
-    int n_cu = 0;                             // (prepares the device on first use: LDS attribute)
-    const hipError_t e = current_device_cus(n_cu);
+    int n_cu = 0, dev = 0;                    // (prepares the device on first use: LDS attribute)
+    const hipError_t e = current_device_cus(n_cu, dev);
     if (e != hipSuccess) return e;
     if ((long)tm.tiles_m * tm.tiles_n <= n_cu)
         return launch_kernel(k_gemm_i8_small_deep<kDeepSteps>, dim3(grid), dim3(256),
@@ -1723,8 +1780,18 @@ hipError_t launch_direct(const GemmArgs &a, hipStream_t s)
 
 hipError_t gemm_prepare_device()
 {
-    int n_cu = 0;
-    return current_device_cus(n_cu);
+    int n_cu = 0, dev = 0;
+    return current_device_cus(n_cu, dev);
+}
+
+hipError_t gemm_prepare_all()
+{
+    int n_cu = 0, dev = 0;
+    hipError_t e = current_device_cus(n_cu, dev);
+    if (e == hipSuccess) e = set_all_persist_lds<3, kTile256>(dev);
+    if (e == hipSuccess) e = set_all_persist_lds<3, kTile128>(dev);
+    if (e == hipSuccess) e = set_all_persist_lds<3, kTileHalf>(dev);
+    return e;
 }
 
 enum GemmForm {
@@ -1822,5 +1889,7 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
     default: return launch_small(a, s);
     }
 }
+
+#endif  // MUXQ_GEMM_PART == 0
 
 }  // namespace muxq

@@ -387,10 +387,12 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s);
 int gemm_tile_rows(int M, int N, int k_pad);
 const char *gemm_kernel_name(int M, int N, int k_pad);
 
-// Per-device set-up of the GEMM kernels for the CURRENT device: the LDS attribute of the
-// persistent kernels and the CU count their grid is sized by.  Thread-safe, idempotent, and
-// NOT capturable into a graph (it queries the device and sets function attributes).
-// launch_gemm calls it itself when the current device has not been prepared yet.
+// Per-device set-up of the GEMM kernels for the CURRENT device: the CU count the persistent kernels' grid is
+// sized by, the LDS attributes of the small and few-token kernels.  Thread-safe, idempotent, and
+// NOT to be called under capture (it queries the device and sets function attributes).
+// launch_gemm calls it itself when the current device has not been prepared yet, and sets the LDS attribute of a
+// persistent kernel before that kernel's first launch.
 hipError_t gemm_prepare_device();
+hipError_t gemm_prepare_all();        // the same and every kernel's binary and LDS attribute
 
 }  // namespace muxq

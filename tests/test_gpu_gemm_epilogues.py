@@ -1,6 +1,10 @@
 """The epilogues of the persistent GEMM, one kernel for each combination of scales, bias, zero point, GELU and way
 of storing Y, on partial tiles in both directions and several tiles per workgroup.  Y against the CPU oracle, exact
 (the order of binary32 operations is the same on both sides)."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -178,3 +182,39 @@ def test_rows_of_y_far_apart(form, ldy):
         assert (out[:, N:N + 64] == 7.0).all()
     del out
     torch.cuda.empty_cache()
+
+
+FIRST_LAUNCH = """
+import sys, torch
+from paper_2604_04701_amd import binding as B
+if sys.argv[1] == "init":
+    B.muxq_init()
+M, K, N = 2048, 1024, 4096
+X = torch.randn(M, K, device="cuda").half()
+X[:, :5] *= 50
+w_q, w_s = B.muxq_quantize_weight((0.02 * torch.randn(K, N, device="cuda")).half())
+kinds = [lambda **kw: B.muxq_linear(X, w_q, w_s, N, **kw), lambda **kw: B.muxq_linear(X, w_q, w_s, N, aux_scale="own", **kw),
+         lambda **kw: B.muxq_linear_gelu(X, w_q, w_s, N, **kw)[0]]
+for kind in kinds:
+    out, ws = torch.empty(M, N, dtype=torch.float16, device="cuda"), B.alloc_workspace(M, K, N, 64)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        kind(out=out, workspace=ws)
+    for _ in range(3):
+        X.copy_(torch.randn(M, K, device="cuda").half())
+        graph.replay()
+        torch.cuda.synchronize()
+        got = out.clone()
+        assert torch.equal(got, kind())
+        torch.cuda.synchronize()
+print("captured", flush=True)
+"""
+
+
+@pytest.mark.parametrize("init", ["init", "plain"])
+def test_first_launch_of_each_kind_under_capture(init):
+    """A process whose first launch of a kernel, which loads its binary and sets its attribute, is captured into a graph."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", FIRST_LAUNCH, init], capture_output=True, text=True, timeout=100, cwd=root)
+    assert r.returncode == 0 and "captured" in r.stdout, r.stderr[-2000:]
