@@ -1611,13 +1611,16 @@ hipError_t launch_wquant_transpose(const void *w_fp16, int K, int N, int ldw, in
 //   per channel, saves four launches: 768 x 768 14.4 / 7.9, 5120 x 1280 40 / 24, 4096 x 16384 92 / 51.
 //     Not where one strip has few channels (8192 x 8 34.3 / 37.7), or K is a fraction of the 512 rows of a step and
 //     there are many strips (64 x 50304 14.7 / 20.4).  Every CU holds one strip at a time, so a last round of few
-//     strips leaves the chip idle, and by K = 6144 that costs more than the launches (5120 x 17408 101 / 99, 6144 x
-//     17408 134 / 136, 8192 x 17408 172 / 187): not beyond K = 5120, unless 2/3 of all rounds are full (8192 x 22528
-//     220 / 209, 8192 x 36864 340 / 321, 5120 x 36864 217 / 189, 6144 x 49984 334 / 280, 9216 x 22528 243 / 238, 9216 x
-//     32768 351 / 294; four rounds of strips all read twice: 8192 x 65536 0.90 times as fast) or the last
-//     one is a single strip, whose lines come several times as fast (8192 x 16448 170 / 153).  In one round the strips win
-//     with all CUs busy (16384 x 16384 1.10 times as fast, 28672 x 16384 1.05, 11264 x 16000 1.10), and with fewer while
-//     W stays near the cache's size (8704 x 15872 1.03, 12288 x 12288 187 / 172, 16384 x 12288 232 / 248).
+//     strips leaves the chip idle, and with two rounds that costs more than the launches by K = 6144 (5120 x 17408 101 /
+//     99, 6144 x 17408 134 / 136, 8192 x 17408 172 / 187): not beyond K = 5120, unless 2/3 of the two are full (8192 x
+//     22528 220 / 209, 9216 x 22528 243 / 238) or the last one is a single strip, whose lines come several times as
+//     fast (8192 x 16448 170 / 153).  Three rounds are as well used by any last one: to K = 9216 (514 strips 4608 x 32896
+//     204 / 139 and 9216 x 32896 368 / 318, 6144 x 33280 233 / 224, 8192 x 36864 340 / 321, 9216 x 32768 351 / 294); more
+//     to 6144 (6144 x 49280 331 / 274, 6144 x 57344 367 / 322, 5632 x 65600 349 / 309; all read twice 8192 x 65536 0.90
+//     times as fast).  In one round the strips win with all CUs busy (16384 x 16384 1.10 times as fast, 28672 x 16384 550 /
+//     500, 11264 x 16000 214 / 174), with three quarters of them to K = 24576 (12288 x 12288 187 / 171, 16384 x 12288 245 /
+//     232, 24576 x 12288 359 / 348, 24576 x 15616 425 / 374; 32768 x 12288 451 / 456), with fewer to 8192 (9216 x 8192 101 /
+//     91, 12288 x 8192 126 / 131, 16384 x 6144 132 / 164).
 //   one scale per tensor, saves one launch (1.6 to 2.3 us on these calls, by how fast the host's launches come): to K =
 //     1024 (512 x 512 13.9 / 13.1, 768 x 2304 and 1024 x 2304 even, 1024 x 5120 15.8 / 15.0, 1024 x 16384 32.6 / 29.7),
 //     1280 with few channels (1280 x 256 11.6 / 12.1 or 14.3 / 12.7; 1280 x 1280 11.9 / 13.8, 2048 x 1280 13.7 / 16.7),
@@ -1643,9 +1646,9 @@ bool wquant_in_strips(const void *w_fp16, int K, int N, int ldw, bool per_channe
     }
     if ((N < kStripCh && K > 4096) || (N > 512 * kStripCh && K < 256)) return false;
     if (!whole_lines) return rounds <= 4 ? K <= (rounds == 1 ? 8192 : rounds <= 3 ? 4096 : 3072) : bytes <= ((size_t)160 << 20);
-    if (rounds == 1) return K <= 8192 || strips >= 250 || (strips >= 192 && bytes <= ((size_t)288 << 20));
-    const bool full = strips - 256 * (rounds - 1) == 1 || (size_t)strips * 3 >= (size_t)rounds * 256 * 2;
-    return K <= (full ? (rounds <= 3 ? 9216 : 6144) : rounds == 2 ? 5120 : 4096);
+    if (rounds == 1) return strips >= 250 || K <= (strips >= 192 ? 24576 : 8192);
+    if (rounds == 2) return K <= (strips == 257 || strips * 3 >= 512 * 2 ? 9216 : 5120);
+    return K <= (rounds == 3 ? 9216 : 6144);
 }
 
 hipError_t launch_wquant_strip(const void *w_fp16, int K, int N, int ldw, int k_pad, const float *amax, float qmax,

@@ -51,7 +51,7 @@ def test_weight_codes_on_both_sides_of_the_line(K, N, ldw, gran):
 
 
 @pytest.mark.parametrize("K,N", [(5128, 16448), (5128, 16512), (8200, 15936), (8200, 16000), (4104, 33024),
-                                 (9224, 16448), (5120, 12296), (3072, 18440)])
+                                 (9224, 16448), (5120, 12296), (3072, 18440), (12296, 12416), (24584, 12288)])
 def test_weight_codes_by_rounds_of_strips(K, N):
     """Strips in one round and in several, the last one short, a single strip or full, rows on and off 128-byte lines, and
     the separate launches beside them (the channels are independent: the oracle takes some of each strip, all of the last)."""
