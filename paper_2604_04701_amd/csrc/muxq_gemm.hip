@@ -1837,15 +1837,21 @@ static GemmForm gemm_form(int M, int N, int k_pad)
     // computes one tile under the other's epilogue, but fetches half as much again per K step: by the sweep (in K steps) 1.15
     // steps + 4 against steps + 7, and a last round of at most 256 tiles, one to a CU, is 0.62 of a full one.  us, 256 x 256 /
     // 128 x 256: 8192 x 1024 -> 4096 55.3 / 53.5, 5239 x 1728 -> 7224 122 / 108, 10796 x 1480 -> 3664 with GELU 123 / 110,
-    // 16384 x 1280 -> 3840 111 / 117, 8192 x 4096 -> 16384 434 / 480 (K below 512 was not in the sweep).
+    // 16384 x 1280 -> 3840 111 / 117, 8192 x 4096 -> 16384 434 / 480 (K below 512 was not in the sweep).  Of 80 more shapes the
+    // rule is within 2.5 % of the best form for all but: rows of Y off 128-byte lines and Y of 100 MiB or more, where the
+    // narrower tile shares more lines with other workgroups (14061 x 752 -> 12600 207 / 228, 5043 x 720 -> 11256 83 / 88, 7624 x
+    // 944 -> 15504 162 / 170, but 6589 x 568 -> 14432 1.06 times as fast), one round half full (749 x 952 -> 11104 25.0 /
+    // 25.9, 5066 x 712 -> 2352 32.8 / 33.4, 6650 x 688 -> 2200 37.1 / 38.0), and 3399 x 536 -> 12024 (128 x 128 49.4 / 53.2).
     // Against 128 x 128 it reads a quarter less through LDS, which pays with a long K: a round 0.415 steps - 0.3 (16384 x 5120
     // -> 1280 203 / 191, 4352 x 5120 -> 4680 142 / 132, 16059 x 1432 -> 2152 107 / 102), and in two nearly full rounds
     // from K = 2048 on (8192 x 4096 -> 1024 80.3 / 76.5; 8192 x 1024 -> 1024 31.2 / 31.9; with 384 tiles even, with 270 7 %
-    // slower).
+    // slower), if that is one tile for each CU: where M leaves half a row of tiles empty it can be more, and then one CU works
+    // on two (1040 x 2072 -> 6968, 275 tiles, 32.3 / 39.2; 1642 x 5024 -> 4744, 266, 59.4 / 73.7).  By 27 shapes with K from
+    // 2048 to 5120: to 256 tiles 0.99 to 1.05 times as fast, from 258 to 275 tiles 0.78 to 0.85.
     const long t_half = tiles(128, 256), last = t_half % 512, steps = k_pad / 64 + 1;
     const long half = (100 * (t_half / 512) + (last == 0 ? 0 : last <= 256 ? 62 : 100)) * (115 * steps + 400) / 100;
     if (square128) {
-        if (rounds128 == 2 ? k_pad >= 2048 && t128 > 448
+        if (rounds128 == 2 ? k_pad >= 2048 && t128 > 448 && t_half <= 256
                            : rounds128 >= 5 && k_pad >= 1024 && 10 * half < rounds128 * (415 * steps - 300)) return kPersistHalf;
         return kPersist128;
     }

@@ -226,3 +226,13 @@ def test_noalloc_entry_point_refuses_oversize_before_touching_the_gpu():
     st = L.muxq_linear_noalloc(FAKE, 8192, 4096, 4096, FAKE, FAKE, 0, 16384, None, 6.0, 2, 64, FAKE, 16384, None)
     assert st == 5                                           # MUXQ_ERR_WORKSPACE
     assert L.muxq_linear_noalloc(FAKE, 128, 772, 772, FAKE, FAKE, 0, 768, None, 6.0, 2, 64, FAKE, 768, None) == 2
+
+
+def test_gemm_kernels_by_size():
+    """Two nearly full rounds of 128 x 128 tiles with a long K: 128 x 256 tiles if they are one for each of the 256 CUs,
+    not where a ragged M makes them more."""
+    assert B.gemm_kernel(8192, 4096, 1024) == B.gemm_kernel(4209, 3000, 1728) == "k_gemm_i8_persist_half"
+    for M, K, N in ((1040, 2072, 6968), (1642, 5024, 4744), (1402, 2560, 5456), (2850, 5120, 2696)):
+        assert B.gemm_kernel(M, K, N) == "k_gemm_i8_persist4"
+        assert B.lib().muxq_linear_gelu_slabs(M, K, N) == (M + 127) // 128
+    assert B.gemm_kernel(0, 64, 64) == B.gemm_kernel(64, 64, 9) == ""
