@@ -27,7 +27,8 @@ int muxq_linear_timed(const void *X_fp16, int M, int K, int ldx, const int8_t *w
                       void *workspace, size_t workspace_bytes, const muxq_act_opts *opts,
                       void *gemm_start, void *gemm_stop, int64_t *wg_ticks, void *stream);
 
-/* Name of the kernel that runs the GEMM of an M x K -> N layer ("" for shapes that are refused).  muxq_linear has one
+/* Name of the kernel that runs the GEMM of an M x K -> N layer whose rows of Y are on 64-byte boundaries ("" for
+ * shapes that are refused).  muxq_linear has one
  * launch without it for few tokens; muxq_linear_timed and muxq_gemm_i8 always use it. */
 const char *muxq_gemm_kernel(int M, int K, int N);
 

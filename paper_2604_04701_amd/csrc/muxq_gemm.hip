@@ -1809,7 +1809,9 @@ enum GemmForm {
 //   1024 x 4096 -> 1024  64x64 12.3,  32x64 14.7,  persistent 128 22.5
 //   512 x 1024 -> 3072   persistent 128 10.4,  small 10.8,  32x32 13.0,  64x64 15.7
 //   1024 x 320 -> 1000   small 6.2,  64x64 8.2,  persistent 128 8.9
-static GemmForm gemm_form(int M, int N, int k_pad)
+//
+// off_lines: rows of Y off 64-byte boundaries, no GELU (it matters for the tiles of 256 tokens alone, whose slabs are the same)
+static GemmForm gemm_form(int M, int N, int k_pad, bool off_lines = false)
 {
     const auto tiles = [&](int tn, int tm) { return (long)((N + tn - 1) / tn) * ((M + tm - 1) / tm); };
     const long t64 = tiles(64, 64), t128 = tiles(128, 128), t256 = tiles(256, 256);
@@ -1837,11 +1839,12 @@ static GemmForm gemm_form(int M, int N, int k_pad)
     // computes one tile under the other's epilogue, but fetches half as much again per K step: by the sweep (in K steps) 1.15
     // steps + 4 against steps + 7, and a last round of at most 256 tiles, one to a CU, is 0.62 of a full one.  us, 256 x 256 /
     // 128 x 256: 8192 x 1024 -> 4096 55.3 / 53.5, 5239 x 1728 -> 7224 122 / 108, 10796 x 1480 -> 3664 with GELU 123 / 110,
-    // 16384 x 1280 -> 3840 111 / 117, 8192 x 4096 -> 16384 434 / 480 (K below 512 was not in the sweep).  Of 80 more shapes the
-    // rule is within 2.5 % of the best form for all but: rows of Y off 128-byte lines and Y of 100 MiB or more, where the
-    // narrower tile shares more lines with other workgroups (14061 x 752 -> 12600 207 / 228, 5043 x 720 -> 11256 83 / 88, 7624 x
-    // 944 -> 15504 162 / 170, but 6589 x 568 -> 14432 1.06 times as fast), one round half full (749 x 952 -> 11104 25.0 /
-    // 25.9, 5066 x 712 -> 2352 32.8 / 33.4, 6650 x 688 -> 2200 37.1 / 38.0), and 3399 x 536 -> 12024 (128 x 128 49.4 / 53.2).
+    // 16384 x 1280 -> 3840 111 / 117, 8192 x 4096 -> 16384 434 / 480 (K below 512 was not in the sweep).  Where
+    // the rows of Y are off 64-byte boundaries the narrower tile shares more lines with other workgroups, and with 100 MiB of
+    // Y or more that is counted as 1.1 (14061 x 752 -> 12600 207 / 228, 6569 x 912 -> 14704 121 / 133, 13653 x 520 -> 10608 142 /
+    // 155; the line is not sharp: 15259 x 1856 -> 4464 169 / 164, 11828 x 584 -> 8744 131 / 130; with the GELU, or on 64 bytes, 6589 x
+    // 568 -> 14432, 128 x 256 is 4 to 9 % the faster).  Of 80 more shapes the rule is then within 2.5 % of the best
+    // form for all but one round half full (749 x 952 -> 11104 25.0 / 25.9) and 3399 x 536 -> 12024 (128 x 128 49.4 / 53.2).
     // Against 128 x 128 it reads a quarter less through LDS, which pays with a long K: a round 0.415 steps - 0.3 (16384 x 5120
     // -> 1280 203 / 191, 4352 x 5120 -> 4680 142 / 132, 16059 x 1432 -> 2152 107 / 102), and in two nearly full rounds
     // from K = 2048 on (8192 x 4096 -> 1024 80.3 / 76.5; 8192 x 1024 -> 1024 31.2 / 31.9; with 384 tiles even, with 270 7 %
@@ -1855,7 +1858,8 @@ static GemmForm gemm_form(int M, int N, int k_pad)
                            : rounds128 >= 5 && k_pad >= 1024 && 10 * half < rounds128 * (415 * steps - 300)) return kPersistHalf;
         return kPersist128;
     }
-    return k_pad >= 512 && half < rounds256 * 100 * (steps + 7) ? kPersistHalf : kPersist256;
+    const bool wide = off_lines && (size_t)M * N * 2 >= (size_t)100 << 20;
+    return k_pad >= 512 && (wide ? half * 11 / 10 : half) < rounds256 * 100 * (steps + 7) ? kPersistHalf : kPersist256;
 }
 
 int gemm_tile_rows(int M, int N, int k_pad)
@@ -1883,7 +1887,8 @@ const char *gemm_kernel_name(int M, int N, int k_pad)
 
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
 {
-    switch (gemm_form(a.M, a.N, a.k_pad)) {
+    const bool off_lines = !a.gelu && (((uintptr_t)a.y | (uintptr_t)a.ldy * 2) % 64) != 0;
+    switch (gemm_form(a.M, a.N, a.k_pad, off_lines)) {
     case kPersist256: return launch_persist<3, kTile256>(a, s);
     case kPersist128: return launch_persist<3, kTile128>(a, s);
     case kPersistHalf: return launch_persist<3, kTileHalf>(a, s);
