@@ -822,7 +822,7 @@ def test_mlp_gelu_fused_into_the_first_gemm(shape, tile_rows, w_gran, x_gran):
 
 def test_mlp_full_size_gpt2_medium():
     n = check_mlp(8192, 1024, 4096, 1024, seed=3100)       # configuration 3: c_fc, GELU, c_proj
-    assert n == 32                                         # one slab per row of 256 x 256 tiles
+    assert n == 32                                         # one slab per row of 128 x 256 tiles
     # more than 64 rows of tiles: the maxima come from a pass over H, at that pass's slab count
     assert 1 <= B.lib().muxq_linear_gelu_slabs(32768, 1024, 4096) <= 64
 
