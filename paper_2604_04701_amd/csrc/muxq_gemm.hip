@@ -537,8 +537,10 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
     // channels goes out before the next is worked out.  Through L2 all pieces of the rows go out one after the other, so
     // that the other half of a line shared by two of them comes while L2 still has the first.  us a call, half by half /
     // together: 11330 x 448 -> 14296 186 / 148, 13653 x 520 -> 10608 174 / 148, 4837 x 1600 -> 10168 113 / 104, 8811 x 776 ->
-    // 5264 72.5 / 71.0, 3001 x 1592 -> 4808 43.0 / 42.1.  (The forms with flags have no registers for that.)
-    constexpr bool TOGETHER = !STREAM && !epi_flags(EPI);
+    // 5264 72.5 / 71.0, 3001 x 1592 -> 4808 43.0 / 42.1.  (The forms with flags have no registers for that;
+    // with the GELU, whose work per output is twice as much, the stores are better spread: 11608 x 760 -> 5368 105.0 / 108.9,
+    // 3333 x 200 -> 4104 29.2 / 30.2, 5239 x 1728 -> 7224 100.3 / 98.4.)
+    constexpr bool TOGETHER = !STREAM && !epi_flags(EPI) && !GELU;
     f16x4 held[FN / 2][FM][8];
 #pragma unroll
     for (int h = 0; h < FN / 2; ++h) {
