@@ -139,7 +139,7 @@ const char *muxq_status_string(int status);
  * count their grids are sized by, the address of the library's static scratch array.
  * Thread-safe and idempotent; queries the device, so it must NOT be called while a stream is
  * being captured into a graph.  Optional otherwise: the first call of an entry point on a
- * device does the same work itself, for the kernels that it launches (about 3 ms where this is 15,
+ * device does the same work itself, for the kernels that it launches (about 4 ms where this is 16,
  * which loads all of them) -- call muxq_init() once per device beforehand when
  * first calls would be made under capture.  Returns MUXQ_OK or MUXQ_ERR_HIP. */
 int muxq_init(void);

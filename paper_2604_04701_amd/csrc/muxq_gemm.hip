@@ -65,7 +65,7 @@
 
 // Compiled four times, as device binaries that are loaded when the first of their kernels is used: this file with the usual
 // kernels, and muxq_gemm_own.hip, _gelu.hip and _codes.hip, which include it, with those of part_of.  (All in one binary
-// loading the library took 2.9 ms and a program's first call 10 ms; so 1.0 and 3.2 ms, as with 16 kernels in all.)
+// loading the library took 2.9 ms and a program's first call 10 ms, with 200 kernels; so 1.1 and 3.7 ms, with 210.)
 #ifndef MUXQ_GEMM_PART
 #define MUXQ_GEMM_PART 0
 #endif
@@ -239,6 +239,15 @@ __host__ __device__ __forceinline__ bool stream_rows(const GemmArgs &a)
     const size_t mib = ((size_t)a.M * a.N * 2) >> 20;
     return start % 128 == 0 || (start % 64 == 0 && (mib < 48 || mib >= 256));
 }
+
+// How a persistent kernel stores Y: through L2 or as a stream half of a wave's channels at a time, or through L2 with
+// all pieces of a row one after the other, so that L2 still has a line that two of them share when the second comes.  The last
+// pays where Y is more than the L2s hold, 32 MiB (us a call, by halves / together: 11330 x 448 -> 14296 186 / 148, 13653 x 520 ->
+// 10608 174 / 148, 4837 x 1600 -> 10168 113 / 104, 8811 x 776 -> 5264 72.5 / 71.0); below, the first stores come too late
+// (11873 x 312 -> 680 30.3 / 31.3, 14185 x 120 -> 520 23.7 / 24.1, but 3001 x 1592 -> 4808 43.0 / 42.1).  Not in the 128 x 128
+// tiles, whose waves have one piece of a row, nor with the GELU, whose work per output is twice as much (11608 x 760 -> 5368 105.0 /
+// 108.9, 5239 x 1728 -> 7224 100.3 / 98.4).
+enum Store { kStoreL2, kStoreStream, kStoreTogether, kStores };
 
 // 16 bytes of Y.  STREAM: non-temporal (chosen by stream_rows).  Compile time: a branch at each store costs
 // 1 us per tile.
@@ -436,7 +445,7 @@ constexpr bool z_offset(int fn) { return fn == 4; }
 // GELU (compile time): the result goes through the tanh GELU, applied to the fp16 value the
 // layer would have stored, and `mx` (FN / 2 entries) collects, per lane, the running maxima of
 // the |fp16| values the lane stores (its 8 channels of each half, over its rows).
-template <int FN, int FM, int ROW_BYTES, int EPI, bool STREAM, bool GELU>
+template <int FN, int FM, int ROW_BYTES, int EPI, int STORE, bool GELU>
 __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&acc)[FN][FM],
                                                int m_base, int n_base, int lane,
                                                unsigned char *patch, float *chan, float sx,
@@ -524,7 +533,7 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
         for (int p = 0; p < 4; ++p) {
             const int row = p * 8 + (lane >> 3);
             v[p] = *(const v4i *)(patch + row * ROW_BYTES + piece * 16);
-            if (EPI != kEpiAny) __builtin_amdgcn_raw_buffer_store_b128(v[p], r_y, off[p], 0, STREAM ? 2 : 0);
+            if (EPI != kEpiAny) __builtin_amdgcn_raw_buffer_store_b128(v[p], r_y, off[p], 0, STORE == kStoreStream ? 2 : 0);
             if (GELU) {
                 const unsigned keep = n_in && row < rows ? ~0u : 0u;
                 const uint4 u = __builtin_bit_cast(uint4, v[p]);
@@ -533,14 +542,9 @@ __device__ __forceinline__ void epilogue_patch(const GemmArgs &a, const v16i (&a
         }
         if (EPI == kEpiAny) put_any(a, v, m_base + fm * 32, n_base + h * 64 + piece * 8, lane);
     };
-    // Results that wait for the patch, in the registers of accumulators that are done with.  As a stream each half of the
-    // channels goes out before the next is worked out.  Through L2 all pieces of the rows go out one after the other, so
-    // that the other half of a line shared by two of them comes while L2 still has the first.  us a call, half by half /
-    // together: 11330 x 448 -> 14296 186 / 148, 13653 x 520 -> 10608 174 / 148, 4837 x 1600 -> 10168 113 / 104, 8811 x 776 ->
-    // 5264 72.5 / 71.0, 3001 x 1592 -> 4808 43.0 / 42.1.  (The forms with flags have no registers for that;
-    // with the GELU, whose work per output is twice as much, the stores are better spread: 11608 x 760 -> 5368 105.0 / 108.9,
-    // 3333 x 200 -> 4104 29.2 / 30.2, 5239 x 1728 -> 7224 100.3 / 98.4.)
-    constexpr bool TOGETHER = !STREAM && !epi_flags(EPI) && !GELU;
+    // Results that wait for the patch, in the registers of accumulators that are done with: kStoreTogether those of all
+    // pieces, which then go out one after the other, else those of half of the channels.
+    constexpr bool TOGETHER = STORE == kStoreTogether;
     f16x4 held[FN / 2][FM][8];
 #pragma unroll
     for (int h = 0; h < FN / 2; ++h) {
@@ -673,7 +677,7 @@ __device__ __forceinline__ PersistTile tile_at(const TileMap &map, int j, int st
 // accumulators (nor the per-launch form the per-token factors: 109 spilled registers in one kernel).
 // GELU (compile time): the fused-activation form (GemmArgs::gelu): every epilogue applies the
 // GELU and, with slab_out, the workgroup leaves the column maxima of its tile of Y.
-template <int STAGES, int WN, int WM, int FN, int FM, int EPI, int OWN, bool GELU, bool STREAM>
+template <int STAGES, int WN, int WM, int FN, int FM, int EPI, int OWN, bool GELU, int STORE>
 __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileMap &tm)
 {
     constexpr int NWAVES = WN * WM, TN = WN * FN * 32, TM = WM * FM * 32, SWZ = 1;
@@ -983,7 +987,7 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
             uint4 mxh[FN / 2];
 #pragma unroll
             for (int h = 0; h < FN / 2; ++h) mxh[h] = make_uint4(0, 0, 0, 0);
-            epilogue_patch<FN, FM, PATCH_ROW, EPI, STREAM, true>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, z_launch, sub_bias, mxh);
+            epilogue_patch<FN, FM, PATCH_ROW, EPI, STORE, true>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, z_launch, sub_bias, mxh);
             if (a.slab_out != nullptr) {
                 // A lane holds the maxima of its 8 channels of each half over the rows it stored;
                 // the 8 lane groups of a wave hold different rows: fold them through the wave's
@@ -1020,7 +1024,7 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
                 }
             }
         } else {
-            epilogue_patch<FN, FM, PATCH_ROW, EPI, STREAM, false>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, z_launch, sub_bias, nullptr);
+            epilogue_patch<FN, FM, PATCH_ROW, EPI, STORE, false>(a, acc, m_base, n_base, lane, patch, chan, sx, sw0, z_launch, sub_bias, nullptr);
         }
         // (a buffer store is issued for a partial tile as well; a store by address or of the column maxima is not)
         if ((EPI != kEpiAny || (full && a.dbg_acc == nullptr)) && (!GELU || (full && a.slab_out != nullptr))) {
@@ -1046,27 +1050,27 @@ __device__ __forceinline__ void gemm_persist_body(const GemmArgs &a, const TileM
 #undef MUXQ_CONST_LOAD
 }
 
-template <int STAGES, int EPI, int OWN, bool GELU, bool STREAM>
+template <int STAGES, int EPI, int OWN, bool GELU, int STORE>
 __global__ __launch_bounds__(512) void k_gemm_i8_persist8(const GemmArgs a, const TileMap tm)
 {
-    gemm_persist_body<STAGES, 2, 4, 4, 2, EPI, OWN, GELU, STREAM>(a, tm);
+    gemm_persist_body<STAGES, 2, 4, 4, 2, EPI, OWN, GELU, STORE>(a, tm);
 }
 
 // 128 (n) x 256 (m) tiles, 4 waves of 128 x 64, two workgroups per CU.  The epilogue's patches lie in the ring, in the
 // stage that was computed last: every wave's in the part that it will load itself, so that its own loads follow its own
 // stores to Y, and no wave still reads operands there (the barrier of the tile's last step came after the last read).
-template <int STAGES, int EPI, int OWN, bool GELU, bool STREAM>
+template <int STAGES, int EPI, int OWN, bool GELU, int STORE>
 __global__ __launch_bounds__(256, 2) void k_gemm_i8_persist_half(const GemmArgs a, const TileMap tm)
 {
-    gemm_persist_body<STAGES, 1, 4, 4, 2, EPI, OWN, GELU, STREAM>(a, tm);
+    gemm_persist_body<STAGES, 1, 4, 4, 2, EPI, OWN, GELU, STORE>(a, tm);
 }
 
 // 128 x 128 tiles, 4 waves of 64 x 64: for problems whose 256 x 256 tiles would leave the last, or the
 // only, round on the chip half empty.
-template <int STAGES, int EPI, int OWN, bool GELU, bool STREAM>
+template <int STAGES, int EPI, int OWN, bool GELU, int STORE>
 __global__ __launch_bounds__(256, EPI == kEpiAny ? 2 : 1) void k_gemm_i8_persist4(const GemmArgs a, const TileMap tm)
 {
-    gemm_persist_body<STAGES, 2, 2, 2, 2, EPI, OWN, GELU, STREAM>(a, tm);
+    gemm_persist_body<STAGES, 2, 2, 2, 2, EPI, OWN, GELU, STORE>(a, tm);
 }
 
 #if MUXQ_GEMM_PART == 0
@@ -1571,15 +1575,17 @@ typedef void (*persist_kernel_t)(const GemmArgs, const TileMap);
 // decides that itself).  nullptr: not built.
 enum PersistKind { kKindUsual, kKindOwn, kKindOwnToken, kKindGelu, kKinds };
 template <int TILE, int EPI, int OWN, bool GELU>
-persist_kernel_t persist_kernel_of(bool stream)
+persist_kernel_t persist_kernel_of(int store)
 {
     constexpr int STAGES = 3;
-    constexpr bool BOTH = EPI != kEpiAny;
-#define MUXQ_FORM(STREAM_)                                                         \
-    (TILE == kTile256   ? k_gemm_i8_persist8<STAGES, EPI, OWN, GELU, STREAM_>      \
-     : TILE == kTile128 ? k_gemm_i8_persist4<STAGES, EPI, OWN, GELU, STREAM_>      \
-                        : k_gemm_i8_persist_half<STAGES, EPI, OWN, GELU, STREAM_>)
-    return stream ? MUXQ_FORM(BOTH) : MUXQ_FORM(false);
+    // (a form that is not built stands for the plain one)
+    constexpr int AS_STREAM = EPI == kEpiAny ? kStoreL2 : kStoreStream;
+    constexpr int AS_TOGETHER = epi_flags(EPI) || GELU || TILE == kTile128 ? kStoreL2 : kStoreTogether;
+#define MUXQ_FORM(STORE_)                                                         \
+    (TILE == kTile256   ? k_gemm_i8_persist8<STAGES, EPI, OWN, GELU, STORE_>      \
+     : TILE == kTile128 ? k_gemm_i8_persist4<STAGES, EPI, OWN, GELU, STORE_>      \
+                        : k_gemm_i8_persist_half<STAGES, EPI, OWN, GELU, STORE_>)
+    return store == kStoreStream ? MUXQ_FORM(AS_STREAM) : store == kStoreTogether ? MUXQ_FORM(AS_TOGETHER) : MUXQ_FORM(kStoreL2);
 #undef MUXQ_FORM
 }
 // Which binary a kernel is in: 1 own scales of Aux, 2 the fused GELU, 3 what a layer has no use for in its calls (the
@@ -1591,11 +1597,11 @@ constexpr int part_of(int kind, int epi)
 
 // The kernels of this binary.
 template <int TILE>
-persist_kernel_t persist_kernel_here(int kind, int epi, bool stream)
+persist_kernel_t persist_kernel_here(int kind, int epi, int store)
 {
 #define MUXQ_CASE(KIND_, EPI_, OWN_, GELU_)                                                        \
     static_assert(part_of(KIND_, EPI_) == MUXQ_GEMM_PART, "in another binary");                    \
-    case KIND_ * kEpis + EPI_: return persist_kernel_of<TILE, EPI_, OWN_, GELU_>(stream)
+    case KIND_ * kEpis + EPI_: return persist_kernel_of<TILE, EPI_, OWN_, GELU_>(store)
     switch (kind * kEpis + epi) {
 #if MUXQ_GEMM_PART == 0
         MUXQ_CASE(kKindUsual, kEpiPlainZ, 0, false);
@@ -1639,29 +1645,29 @@ persist_kernel_t persist_kernel_here(int kind, int epi, bool stream)
 
 }  // namespace
 
-template <int PART> const void *persist_kernel_of_part(int tile, int kind, int epi, bool stream);
-template <> const void *persist_kernel_of_part<MUXQ_GEMM_PART>(int tile, int kind, int epi, bool stream)
+template <int PART> const void *persist_kernel_of_part(int tile, int kind, int epi, int store);
+template <> const void *persist_kernel_of_part<MUXQ_GEMM_PART>(int tile, int kind, int epi, int store)
 {
-    return (const void *)(tile == kTile256   ? persist_kernel_here<kTile256>(kind, epi, stream)
-                          : tile == kTile128 ? persist_kernel_here<kTile128>(kind, epi, stream)
-                                             : persist_kernel_here<kTileHalf>(kind, epi, stream));
+    return (const void *)(tile == kTile256   ? persist_kernel_here<kTile256>(kind, epi, store)
+                          : tile == kTile128 ? persist_kernel_here<kTile128>(kind, epi, store)
+                                             : persist_kernel_here<kTileHalf>(kind, epi, store));
 }
 
 #if MUXQ_GEMM_PART == 0
 
-template <> const void *persist_kernel_of_part<1>(int tile, int kind, int epi, bool stream);
-template <> const void *persist_kernel_of_part<2>(int tile, int kind, int epi, bool stream);
-template <> const void *persist_kernel_of_part<3>(int tile, int kind, int epi, bool stream);
+template <> const void *persist_kernel_of_part<1>(int tile, int kind, int epi, int store);
+template <> const void *persist_kernel_of_part<2>(int tile, int kind, int epi, int store);
+template <> const void *persist_kernel_of_part<3>(int tile, int kind, int epi, int store);
 
 namespace {
 
-persist_kernel_t persist_kernel(int tile, int kind, int epi, bool stream)
+persist_kernel_t persist_kernel(int tile, int kind, int epi, int store)
 {
     const int part = part_of(kind, epi);
-    return (persist_kernel_t)(part == 1   ? persist_kernel_of_part<1>(tile, kind, epi, stream)
-                              : part == 2 ? persist_kernel_of_part<2>(tile, kind, epi, stream)
-                              : part == 3 ? persist_kernel_of_part<3>(tile, kind, epi, stream)
-                                          : persist_kernel_of_part<0>(tile, kind, epi, stream));
+    return (persist_kernel_t)(part == 1   ? persist_kernel_of_part<1>(tile, kind, epi, store)
+                              : part == 2 ? persist_kernel_of_part<2>(tile, kind, epi, store)
+                              : part == 3 ? persist_kernel_of_part<3>(tile, kind, epi, store)
+                                          : persist_kernel_of_part<0>(tile, kind, epi, store));
 }
 
 // K steps whose loads a workgroup of k_gemm_i8_small_deep issues together (64 staging registers,
@@ -1675,12 +1681,12 @@ std::mutex g_prepare_mutex;
 
 // The persistent kernels take more LDS than a kernel may without asking, so each needs an attribute set on each device, which
 // loads its binary: for a kernel's first launch, and in muxq_init for all (first launches under capture).
-std::atomic<unsigned char> g_lds_set[kMaxDevices][3][kKinds * kEpis * 2];
+std::atomic<unsigned char> g_lds_set[kMaxDevices][3][kKinds * kEpis * kStores];
 
 template <int STAGES, int TILE>
-hipError_t set_persist_lds(int dev, int kind, int epi, bool stream, persist_kernel_t k)
+hipError_t set_persist_lds(int dev, int kind, int epi, int store, persist_kernel_t k)
 {
-    std::atomic<unsigned char> &set = g_lds_set[dev][TILE][(kind * kEpis + epi) * 2 + (stream ? 1 : 0)];
+    std::atomic<unsigned char> &set = g_lds_set[dev][TILE][(kind * kEpis + epi) * kStores + store];
     if (set.load(std::memory_order_acquire) != 0) return hipSuccess;
     std::lock_guard<std::mutex> lock(g_prepare_mutex);
     const hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1692,10 +1698,10 @@ hipError_t set_persist_lds(int dev, int kind, int epi, bool stream, persist_kern
 template <int STAGES, int TILE>
 hipError_t set_all_persist_lds(int dev)
 {
-    for (int i = 0; i < kKinds * kEpis * 2; ++i) {
-        const int kind = i / 2 / kEpis, epi = i / 2 % kEpis;
-        const persist_kernel_t k = persist_kernel(TILE, kind, epi, i % 2 != 0);
-        const hipError_t e = k == nullptr ? hipSuccess : set_persist_lds<STAGES, TILE>(dev, kind, epi, i % 2 != 0, k);
+    for (int i = 0; i < kKinds * kEpis * kStores; ++i) {
+        const int kind = i / kStores / kEpis, epi = i / kStores % kEpis, store = i % kStores;
+        const persist_kernel_t k = persist_kernel(TILE, kind, epi, store);
+        const hipError_t e = k == nullptr ? hipSuccess : set_persist_lds<STAGES, TILE>(dev, kind, epi, store, k);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -1741,19 +1747,19 @@ hipError_t launch_persist(const GemmArgs &a, hipStream_t s)
     constexpr int wgs_per_cu = 160 * 1024 / lds_bytes;     // by LDS; registers allow at least as many
     static_assert(wgs_per_cu >= 1, "ring too deep");
     const int kind = a.gelu ? kKindGelu : !a.aux_own_scale ? kKindUsual : a.x_per_token ? kKindOwnToken : kKindOwn;
-    const bool stream = stream_rows(a);
+    const int store = stream_rows(a) ? kStoreStream : (size_t)a.M * a.N * 2 > (size_t)32 << 20 ? kStoreTogether : kStoreL2;
     int epi = (a.x_per_token ? a.w_per_channel ? kEpiVector : kEpiToken
                              : (a.cn != nullptr ? kEpiPlainZ : kEpiPlain) + (a.w_per_channel ? 2 : 0)) + (a.bias != nullptr ? 1 : 0);
     // (32 rows of Y 2^25 elements apart are beyond the 32-bit offsets of the usual kernels' buffer.  Buffers of 8 rows in
     // all kernels: 16384 x 1280 -> 3840 per vector 112.3 -> 113.5 us.)
     if (a.dbg_acc != nullptr || a.ldy >= 1 << 25) epi = kEpiAny;
-    persist_kernel_t kern = persist_kernel(TILE, kind, epi, stream);
+    persist_kernel_t kern = persist_kernel(TILE, kind, epi, store);
     // (the GELU without a bias: c_fc has one, so those are one kernel)
-    if (kern == nullptr && kind == kKindGelu) kern = persist_kernel(TILE, kind, epi = kEpiGeneral, stream);
+    if (kern == nullptr && kind == kKindGelu) kern = persist_kernel(TILE, kind, epi = kEpiGeneral, store);
     if (kern == nullptr) return hipErrorInvalidDeviceFunction;
     int n_cu = 0, dev = 0;
     hipError_t e = current_device_cus(n_cu, dev);
-    if (e != hipSuccess || (e = set_persist_lds<STAGES, TILE>(dev, kind, epi, stream, kern)) != hipSuccess) return e;
+    if (e != hipSuccess || (e = set_persist_lds<STAGES, TILE>(dev, kind, epi, store, kern)) != hipSuccess) return e;
     const int grid = total < n_cu * wgs_per_cu ? total : n_cu * wgs_per_cu;
     return launch_kernel(kern, dim3(grid), dim3(waves_of(TILE) * 64), lds_bytes, s, a, tm);
 }
