@@ -84,40 +84,61 @@ struct ActShared {
     uint16_t slot[kActMaxK];             // list position of each listed channel
     int idx[kActMaxCap];                 // the list
     uint8_t mask[kActThreads];           // per chunk of 8 channels: which are listed
-    __attribute__((aligned(16))) int tot[kActWaves];
-    __attribute__((aligned(16))) uint32_t max[kActWaves];
+    int tot[kActWaves];
+    uint32_t max[kActWaves];
     float amax;                          // given list only
+    float sx, inv;                       // one scale per call
+    int z;
 };
 
-// Fold, selection and list for the whole workgroup.  want_max: false where neither the candidates (a
-// list fixed offline) nor the scale (one per token) need the column maxima.
-// load_x (want_max): requests the workgroup's first rows of X, behind the first slabs: loads come back in the order
-// they were issued, and the fold would wait for X as well (8192 x 1024 -> 1024 27.7 -> 27.1 us a call).
-template <typename LoadX>
-__device__ __forceinline__ Selected act_select(const ActArgs &a, ActShared &sh, bool want_max, bool want_scale, uint4 &mx,
-                                               LoadX &&load_x)
+// This thread's part of the fold, of N slabs p, p + P, ... at most.  The loads of N slabs are all
+// requested at once, and the workgroup's first rows of X behind them (load_x): loads come back in the order they
+// were issued, and the fold would wait for X as well.  (Past the end the last slab again: a branch per load would
+// serialise the loads.  N fits the slabs there are, because what 16 waves read twice counts: always eight of them, 0.2-0.4 us.)
+template <int N, typename LoadX>
+__device__ __forceinline__ uint4 fold_slabs(const ActArgs &a, int c, int p, int P, bool on, LoadX &&load_x)
 {
-    const int tid = threadIdx.x, C = a.K / 8, CA = a.k_pad / 8;
+    const uint16_t *const src = a.slabs + (size_t)c * 8;
+    uint4 q[N], mx = make_uint4(0, 0, 0, 0);
+    if (on)
+#pragma unroll
+        for (int j = 0; j < N; ++j) q[j] = *(const uint4 *)(src + (size_t)min(p + j * P, a.n_slabs - 1) * a.slab_ld);
+    __builtin_amdgcn_sched_barrier(0);
+    load_x();
+    __builtin_amdgcn_sched_barrier(0);
+    if (on)
+#pragma unroll
+        for (int j = 0; j < N; ++j) mx = absmax_step(mx, q[j]);
+    return mx;
+}
+
+// Fold, selection and list for the whole workgroup.  WANT_MAX: false where neither the candidates (a
+// list fixed offline) nor the scale (one per token) need the column maxima.
+// load_x (WANT_MAX): requests the workgroup's first rows of X.
+// WANT_SCALE: the scale of the call is left in `sh`.
+template <bool WANT_MAX, bool WANT_SCALE, typename LoadX>
+__device__ __forceinline__ Selected act_select(const ActArgs &a, ActShared &sh, float shrink, uint4 &mx, LoadX &&load_x)
+{
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), C = a.K / 8, CA = a.k_pad / 8;
+    const int n_seg = (CA + 63) / 64;                    // waves that hold chunks in the selection
+    const bool holds = wave < n_seg;
     mx = make_uint4(0, 0, 0, 0);
-    if (want_max) {
+    if (WANT_MAX) {
         const int P = quotient(kActThreads, a.by_chunks), p = quotient(tid, a.by_chunks), c = tid - p * CA;
         const bool on = p < P && c < C && p < a.n_slabs;
-        const uint16_t *const src = a.slabs + (size_t)c * 8;
-        uint4 q[8];
-        // (past the end the last slab again: a branch per load would serialise the loads)
-        auto request = [&](int sl) {
+        if (a.n_slabs <= P) {
+            mx = fold_slabs<1>(a, c, p, P, on, load_x);
+        } else if (a.n_slabs <= 2 * P) {
+            mx = fold_slabs<2>(a, c, p, P, on, load_x);
+        } else if (a.n_slabs <= 4 * P) {
+            mx = fold_slabs<4>(a, c, p, P, on, load_x);
+        } else {
+            mx = fold_slabs<8>(a, c, p, P, on, load_x);
+            for (int sl = p + 8 * P; on && sl < a.n_slabs; sl += 8 * P) {
+                uint4 q[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) q[j] = *(const uint4 *)(src + (size_t)min(sl + j * P, a.n_slabs - 1) * a.slab_ld);
-        };
-        if (on) request(p);
-        __builtin_amdgcn_sched_barrier(0);
-        load_x();
-        __builtin_amdgcn_sched_barrier(0);
-        if (on) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) mx = absmax_step(mx, q[j]);
-            for (int sl = p + 8 * P; sl < a.n_slabs; sl += 8 * P) {
-                request(sl);
+                for (int j = 0; j < 8; ++j)
+                    q[j] = *(const uint4 *)(a.slabs + (size_t)c * 8 + (size_t)min(sl + j * P, a.n_slabs - 1) * a.slab_ld);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) mx = absmax_step(mx, q[j]);
             }
@@ -125,29 +146,48 @@ __device__ __forceinline__ Selected act_select(const ActArgs &a, ActShared &sh, 
         if (P > 1) {
             sh.part[tid] = mx;
             lds_barrier();
-            mx = make_uint4(0, 0, 0, 0);
-            if (tid < CA)
-                for (int g = 0; g < min(P, a.n_slabs); ++g) mx = absmax_step(mx, sh.part[g * CA + tid]);
+            if (holds) {
+                const int G = min(P, a.n_slabs), at = min(tid, CA - 1);
+                mx = make_uint4(0, 0, 0, 0);
+                for (int g = 0; g < G; g += 4) {         // (past the end the last part again)
+                    uint4 q[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) q[j] = sh.part[min(g + j, G - 1) * CA + at];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) mx = absmax_step(mx, q[j]);
+                }
+                if (tid >= CA) mx = make_uint4(0, 0, 0, 0);
+            }
         }
     }
     uint32_t cand = 0;
-    if (tid < C) {
-        if (a.static_mask != nullptr) {
-            cand = a.static_mask[tid];
-        } else {
-            float v[8];
-            widen8(mx, v);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) cand |= (v[i] > a.threshold ? 1u : 0u) << i;
+    if (holds) {
+        if (a.static_mask != nullptr)
+            cand = tid < C ? a.static_mask[tid] : 0u;
+        else if (WANT_MAX) {
+            cand = chunk_candidates(mx, a.threshold, a.cut);
+            if (tid >= C) cand = 0;
         }
     }
-    const Selected r = select_channels<kActWaves>(mx, cand, true, tid >> 6, a.r_cap, want_scale, sh.tot, sh.max);
-    if (tid < CA) sh.mask[tid] = (uint8_t)r.listed;
-    int rank = r.first;
-    for (uint32_t mm = r.listed; mm != 0; mm &= mm - 1, ++rank) {
-        const int k = tid * 8 + __builtin_ctz(mm);
-        sh.slot[k] = (uint16_t)rank;
-        sh.idx[rank] = k;
+    const Selected r = select_channels<kActWaves>(mx, cand, holds, wave, n_seg, a.r_cap, WANT_SCALE, sh.tot, sh.max);
+    if (holds) {
+        if (tid < CA) sh.mask[tid] = (uint8_t)r.listed;
+        int rank = r.first;
+        for (uint32_t mm = r.listed; mm != 0; mm &= mm - 1, ++rank) {
+            const int k = tid * 8 + __builtin_ctz(mm);
+            sh.slot[k] = (uint16_t)rank;
+            sh.idx[rank] = k;
+        }
+    }
+    if (WANT_SCALE && wave == kActWaves - 1) {           // (as a rule a wave without chunks)
+        float sx, inv;
+        int z;
+        call_scale(r.maxima, shrink, a.qmax, sx, inv, z);
+        if (tid == kActThreads - 1) {
+            sh.sx = sx;
+            sh.inv = inv;
+            sh.z = z;
+        }
     }
     lds_barrier();
     return r;
@@ -294,9 +334,11 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_select(const ActArgs a
         }
     } else {
         uint4 mx;
-        const Selected sel = act_select(a, sh, true, true, mx, [&] { load(row); });
+        const Selected sel = act_select<true, true>(a, sh, shrink, mx, [&] { load(row); });
         used = sel.used;
-        call_scale(sel.maxima, shrink, a.qmax, sx, inv, z);
+        sx = sh.sx;
+        inv = sh.inv;
+        z = sh.z;
         if (blockIdx.x == 0) {
             store_selection(sel, mx, tid, C, CA, true, a.r_cap, true, inv, shrink, a.col_absmax, a.col_scale, a.col_slot,
                             a.col_mask, a.idx, a.n_outliers);
@@ -381,13 +423,12 @@ __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
     // (P rows of every workgroup in turn: see k_quantize_select)
     const int stride = (int)gridDim.x * P;
     int row = (int)blockIdx.x * P + p;
-    constexpr bool want_max = !STATIC;
     if (STATIC) load(row, raw);
 
     const float shrink = __uint_as_float((uint32_t)(127 - a.exp) << 23);  // 2^-exp
     uint4 mx;
-    const Selected sel = act_select(a, sh, want_max, false, mx, [&] { load(row, raw); });
-    if (blockIdx.x == 0 && want_max)
+    const Selected sel = act_select<!STATIC, false>(a, sh, shrink, mx, [&] { load(row, raw); });
+    if (blockIdx.x == 0 && !STATIC)
         store_selection(sel, mx, tid, C, CA, true, a.r_cap, false, 0.f, shrink, a.col_absmax, a.col_scale, a.col_slot,
                         a.col_mask, a.idx, a.n_outliers);
     const int used = __builtin_amdgcn_readfirstlane(sel.used);       // (the same in every lane)
@@ -485,6 +526,7 @@ hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool give
 {
     ActArgs a = args;
     a.by_chunks = divisor(a.k_pad / 8);
+    a.cut = magnitude_cut(a.threshold);
     // pieces of a row: of 64 chunks, or with one scale per row of as many as a wave keeps in registers
     a.pieces = !per_token ? (a.k_pad / 8 + 63) / 64 : a.k_pad <= 1024 ? 1 : (a.k_pad + 2047) / 2048;
     a.by_pieces = divisor(a.pieces);

@@ -45,6 +45,7 @@ struct FewPlan {
     int div;                 // wave / pieces == wave * div >> 16
     int share_parts, share_len;          // codes for the caller: a row in so many parts of so many 16-byte units
     int codes, aux, waux, red, idx, part, total;     // LDS offsets (X itself at 0)
+    int cut;                 // the threshold, see chunk_candidates
 };
 
 FewPlan few_plan(int M, int K, int k_pad, int r_cap, int grid)
@@ -93,6 +94,7 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
     __shared__ uint32_t s_row[kFewMaxM * kFewWaves];     // per token: the maxima of a row's pieces
     __shared__ float s_sx[kFewMaxM], s_inv[kFewMaxM];
     __shared__ int s_z[kFewMaxM];
+    __shared__ uint32_t s_pick[kFewMaxK / 8];            // per chunk: which channels are listed, rank of the first << 8
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int M = a.M, K = a.K, k_pad = a.k_pad, N = a.N, r_cap = a.r_cap;
@@ -174,34 +176,35 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
             uint4 *const part = (uint4 *)(lds + L.part);
             part[tid] = mx;
             lds_barrier();
-            const int groups = min(P, M);
-            mx = part[seg * 64 + lane];
-            for (int g = 1; g < groups; ++g) mx = absmax_step(mx, part[(g * S + seg) * 64 + lane]);
-            if (p >= P) mx = make_uint4(0, 0, 0, 0);
-            lds_barrier();
+            if (p == 0)
+                for (int g = 1; g < min(P, M); ++g) mx = absmax_step(mx, part[(g * S + seg) * 64 + lane]);
         }
     }
+
+    // ---- selection (Sec. III-C) with the capacity rule ----
+    const float shrink = __uint_as_float((uint32_t)(127 - a.exp) << 23);  // 2^-exp
+    // (in the waves of the first row group; the others take the lists over)
+    const bool holds = p == 0;
+    if (holds && !is_static) {
+        listed = chunk_candidates(mx, a.threshold, L.cut);
+        if (!in_c) listed = 0;
+    }
+    const Selected sel = select_channels<kFewWaves>(mx, listed, holds, seg, S, r_cap, !TOKEN, s_tot, s_max);
+    const int used = sel.used;
+    const uint32_t call_max = sel.maxima;
+    // (the parts of the maxima, which may lie here, were read before the barriers of the selection)
     for (int i = tid * 4; i < M * r_cap; i += kFewThreads * 4) *(uint32_t *)(aux + i) = 0u;
     for (int i = tid * 4; i < 16 * r_cap; i += kFewThreads * 4) *(uint32_t *)(waux + i) = 0u;
     for (int i = tid; i < n_mb * 256; i += kFewThreads) red[i] = 0;
-
-    // ---- selection (Sec. III-C) with the capacity rule; every row group does it for its chunks ----
-    const float shrink = __uint_as_float((uint32_t)(127 - a.exp) << 23);  // 2^-exp
-    if (in_c && !is_static) {
-        float v[8];
-        widen8(mx, v);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) listed |= (v[i] > a.threshold ? 1u : 0u) << i;
+    if (holds) {
+        int rank = sel.first;
+        for (uint32_t mm = sel.listed; mm != 0; mm &= mm - 1, ++rank) idx_lds[rank] = c * 8 + __builtin_ctz(mm);
+        s_pick[c] = sel.listed | (uint32_t)sel.first << 8;
     }
-    const Selected sel = select_channels<kFewWaves>(mx, listed, p == 0, seg, r_cap, !TOKEN, s_tot, s_max);
-    listed = sel.listed;
-    const int first = sel.first, used = sel.used;
-    const uint32_t call_max = sel.maxima;
-    if (p == 0) {
-        int rank = first;
-        for (uint32_t mm = listed; mm != 0; mm &= mm - 1, ++rank) idx_lds[rank] = c * 8 + __builtin_ctz(mm);
-    }
-    if (!TOKEN) lds_barrier();
+    lds_barrier();
+    const uint32_t pick = p < P ? s_pick[c] : 0u;
+    listed = pick & 0xffu;
+    const int first = (int)(pick >> 8);
 
     float inv = 0.f, sx_call = 0.f;
     int z = 0;
@@ -472,7 +475,8 @@ hipError_t launch_linear_few(const FewArgs &a, hipStream_t s)
     if (e != hipSuccess) return e;
     // every workgroup repeats the activation side: no more of them than are resident at once
     const int nblk = (a.N + 15) / 16, grid = nblk < 256 ? nblk : 256;
-    const FewPlan plan = few_plan(a.M, a.K, a.k_pad, a.r_cap, grid);
+    FewPlan plan = few_plan(a.M, a.K, a.k_pad, a.r_cap, grid);
+    plan.cut = magnitude_cut(a.threshold);
     return launch_kernel(few_kernel((a.M + 15) / 16, a.x_per_token != 0), dim3(grid), dim3(kFewThreads), plan.total, s,
                          a, plan);
 }

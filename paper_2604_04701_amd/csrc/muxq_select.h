@@ -106,7 +106,19 @@ __device__ __forceinline__ uint32_t wave_row_maxima(const uint4 (&raw)[NC], uint
     return wave_max_u16x2_to_lane63(m);
 }
 
-// What select_channels returns for this thread's chunk and for the call.
+// Whether a lane of the wave has a NaN among its magnitudes.
+__device__ __forceinline__ bool wave_has_nan(uint4 mx)
+{
+    const muxq_u16x2 inf = {0x7c00, 0x7c00};
+    const uint32_t d[4] = {mx.x, mx.y, mx.z, mx.w};
+    uint32_t over = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        over |= __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(muxq_u16x2, d[i]), inf));
+    return __ballot(over != 0) != 0;
+}
+
+// What select_channels returns: for this thread's chunk (in the waves that hold chunks), and for the call.
 struct Selected {
     uint32_t listed;     // bit i: channel i of the chunk is listed
     int first;           // rank of the chunk's first candidate
@@ -114,51 +126,104 @@ struct Selected {
     uint32_t maxima;     // chunk_maxima over all channels (want_max)
 };
 
-// Sec. III-C with the capacity rule: the r_cap lowest candidates are listed.  All NW waves of the
-// workgroup call it; a thread brings the column maxima `mx` of its chunk and its candidates, one
-// bit per channel.  Chunks are numbered 64 seg + lane; waves with `counted` false hold copies of chunks
-// that others bring.  Two barriers at least; the caller's LDS writes before are visible after.
+// The channels of a chunk whose column maxima are over the threshold, one bit each.  `cut` is the
+// threshold as the bits of the largest fp16 magnitude that is not over it (magnitude_cut), so that
+// two channels are compared in one instruction; a NaN is never over it.  (All lanes of a wave call.)
+__device__ __forceinline__ uint32_t chunk_candidates(uint4 mx, float threshold, int cut)
+{
+    if (cut < 0 || wave_has_nan(mx)) {                   // (a negative threshold: every number is over it)
+        float v[8];
+        widen8(mx, v);
+        uint32_t cand = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) cand |= (v[i] > threshold ? 1u : 0u) << i;
+        return cand;
+    }
+    const muxq_u16x2 cut2 = {(unsigned short)cut, (unsigned short)cut}, one = {1, 1};
+    const uint32_t d[4] = {mx.x, mx.y, mx.z, mx.w};
+    uint32_t m = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const muxq_u16x2 over = __builtin_elementwise_sub_sat(__builtin_bit_cast(muxq_u16x2, d[i]), cut2);
+        m |= __builtin_bit_cast(uint32_t, __builtin_elementwise_min(over, one)) << (2 * i);
+    }
+    return (m | m >> 15) & 0xffu;
+}
+inline int magnitude_cut(float threshold)
+{
+    if (!(threshold >= 0.f)) return -1;
+    int lo = 0, hi = 0x7c00;                             // +0 is not over it; bits of fp16 order like the values
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        const float v = mid == 0x7c00 ? __builtin_inff()
+                      : mid < 0x400 ? __builtin_ldexpf((float)mid, -24)
+                                    : __builtin_ldexpf((float)(0x400 | (mid & 0x3ff)), (mid >> 10) - 25);
+        if (v <= threshold) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// Sec. III-C with the capacity rule: the r_cap lowest candidates are listed.  The first `n_seg` pieces
+// of 64 chunks are in one wave each; a thread of those (`holds`, the same in a wave) brings the column maxima `mx`
+// (magnitudes) of chunk 64 seg + lane and its candidates.  All NW waves of the workgroup call; two
+// barriers at least; the caller's LDS writes before are visible after.
+// A chain of latencies that every workgroup walks: 16 waves that all work out everything are bound by
+// their instructions (four waves on a SIMD), so only the waves that hold chunks do, and what all need of the waves' results
+// is read by 16 lanes side by side (8192 x 1024, from the column maxima to the list 1.5 -> 0.9 us).
 template <int NW>
-__device__ __forceinline__ Selected select_channels(uint4 mx, uint32_t cand, bool counted, int seg, int r_cap,
+__device__ __forceinline__ Selected select_channels(uint4 mx, uint32_t cand, bool holds, int seg, int n_seg, int r_cap,
                                                     bool want_max, int *s_tot, uint32_t *s_max)
 {
-    static_assert(NW % 4 == 0, "read four at a time");
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    static_assert(NW == 16, "a row of 16 lanes reads the waves' results");
+    const int lane = threadIdx.x & 63;
     Selected r;
-    const int cnt = __builtin_popcount(cand);
-    const int incl = wave_inclusive_sum(cnt);
-    uint32_t top = want_max ? wave_max_u16x2_to_lane63(chunk_maxima(drop_nan(mx), cand)) : 0u;
-    if (lane == 63) {
-        s_tot[wave] = counted ? incl : 0;
-        s_max[wave] = counted ? top : 0u;
+    r.listed = cand;
+    int incl = 0;
+    if (holds) {
+        incl = wave_inclusive_sum(__builtin_popcount(cand));
+        uint32_t top = 0;
+        if (want_max) {
+            if (wave_has_nan(mx)) mx = drop_nan(mx);
+            top = wave_max_u16x2_to_lane63(chunk_maxima(mx, cand));
+        }
+        if (lane == 63) {
+            s_tot[seg] = incl;
+            s_max[seg] = top;
+        }
     }
     lds_barrier();
-    r.listed = cand;
-    r.first = incl - cnt;
-    r.found = 0;
-    r.maxima = 0;
-#pragma unroll
-    for (int i = 0; i < NW; i += 4) {
-        const int4 t = *(const int4 *)(s_tot + i);
-        const uint4 m = *(const uint4 *)(s_max + i);
-        r.first += (i < seg ? t.x : 0) + (i + 1 < seg ? t.y : 0) + (i + 2 < seg ? t.z : 0) + (i + 3 < seg ? t.w : 0);
-        r.found += t.x + t.y + t.z + t.w;
-        r.maxima = pk_max_u16(r.maxima, pk_max_u16(pk_max_u16(m.x, m.y), pk_max_u16(m.z, m.w)));
+    const bool in = (lane & 15) < n_seg;
+    uint32_t tot = in ? (uint32_t)s_tot[lane & 15] : 0u, m = in ? s_max[lane & 15] : 0u;
+    tot += dpp_zero<0x111>(tot);                         // row_shr 1, 2, 4, 8: sums over a row of 16 lanes
+    tot += dpp_zero<0x112>(tot);
+    tot += dpp_zero<0x114>(tot);
+    tot += dpp_zero<0x118>(tot);
+    if (want_max) {
+        m = pk_max_u16(m, dpp_zero<0x111>(m));
+        m = pk_max_u16(m, dpp_zero<0x112>(m));
+        m = pk_max_u16(m, dpp_zero<0x114>(m));
+        m = pk_max_u16(m, dpp_zero<0x118>(m));
     }
+    r.found = __builtin_amdgcn_readlane((int)tot, 15);
+    r.maxima = (uint32_t)__builtin_amdgcn_readlane((int)m, 15);
+    r.first = incl - __builtin_popcount(cand) + (seg > 0 ? __builtin_amdgcn_readlane((int)tot, max(seg, 1) - 1) : 0);
     r.used = min(r.found, r_cap);
     if (r.found > r_cap) {
-        uint32_t kept = 0;
-        int rank = r.first;
-        for (uint32_t mm = cand; mm != 0; mm &= mm - 1, ++rank)
-            if (rank < r_cap) kept |= mm & (0u - mm);
-        r.listed = kept;
+        if (holds) {
+            uint32_t kept = 0;
+            int rank = r.first;
+            for (uint32_t mm = cand; mm != 0; mm &= mm - 1, ++rank)
+                if (rank < r_cap) kept |= mm & (0u - mm);
+            r.listed = kept;
+        }
         if (want_max) {
-            top = wave_max_u16x2_to_lane63(chunk_maxima(drop_nan(mx), kept));
+            const uint32_t top = holds ? wave_max_u16x2_to_lane63(chunk_maxima(mx, r.listed)) : 0u;
             lds_barrier();                               // s_max is consumed
-            if (lane == 63) s_max[wave] = counted ? top : 0u;
+            if (holds && lane == 63) s_max[seg] = top;
             lds_barrier();
             r.maxima = 0;
-            for (int i = 0; i < NW; ++i) r.maxima = pk_max_u16(r.maxima, s_max[i]);
+            for (int i = 0; i < n_seg; ++i) r.maxima = pk_max_u16(r.maxima, s_max[i]);
         }
     }
     return r;

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import test_gpu_parity as T
-from gpu_common import B, check_case, check_plain_y, orc, sample_rows, synth
+from gpu_common import B, check_case, check_plain_y, compare, orc, run_gpu, sample_rows, synth
 from paper_2604_04701_amd.synth import Case
 
 pytestmark = pytest.mark.gpu
@@ -28,6 +28,19 @@ def test_select_and_quantise_all_stages(shape, x_gran):
 @pytest.mark.parametrize("r_cap,r", [(0, 5), (64, 0), (64, 64), (64, 90), (128, 100), (256, 200)])
 def test_select_and_quantise_capacity(r_cap, r, x_gran):
     check_case(Case("act_cap", 333, 712, 136, r, U, 940 + r), r_cap=r_cap, e=3, x_gran=x_gran)
+
+
+@pytest.mark.parametrize("threshold", [-1.0, 0.0, 2.0 ** -25, 2.0 ** -24, 3.5e-5, 6.0, 6.001, 65504.0, float("inf")])
+@pytest.mark.parametrize("M", [3, 300])
+def test_thresholds(M, threshold):
+    """The threshold is any binary32 value, also between two fp16 values, below the smallest or above the largest
+    one (the kernels compare fp16 magnitudes with the largest one that is not over it)."""
+    X, W, _ = synth.make_case(Case("act_thr", M, 200, 72, 4, U, 980))
+    X[:, :8] = 0
+    X[0, 1:8] = [2.0 ** -24, 2.0 ** -23, 3.4e-5, 3.6e-5, 6.0, 6.0039, 65504.0]
+    X[M - 1, 8:10] = [-6.0, -6.0039]
+    kw = dict(threshold=threshold, r_cap=256)
+    compare(run_gpu(X, W, **kw), orc.linear(X, W, **kw), 200, 72, 256)
 
 
 @pytest.mark.parametrize("x_gran", ["tensor", "token"])
