@@ -269,12 +269,34 @@ __device__ __forceinline__ void quantize_chunk(const ActArgs &a, const ActShared
     *(uint2 *)(a.body_q + packed_index(row, c * 8, a.k_pad)) = packed;
 }
 
-// One activation scale for the call.  A wave owns a piece of 64 chunks of a row, a thread one chunk
-// (its mask and every address but the row's part, which is scalar, are fixed: the work per code is the
-// quantisation itself, 3 vector instructions and a share of the packing), and takes it in row after row, up to U rows in flight.  All
-// workgroups walk X together: what is in flight at one time is one contiguous piece of memory.  (A
-// range of rows for each workgroup puts all of them on the same few memory channels where a range
-// is a multiple of a large power of two: 16384 x 5120 from HBM 65 us instead of 45 us.)
+// Aux columns past the list, zeroed for an equal share of the rows: four codes to a store.
+__device__ __forceinline__ void zero_aux_rest(const ActArgs &a, int used)
+{
+    const int per = (a.M + (int)gridDim.x - 1) / (int)gridDim.x, r1 = min(a.M, ((int)blockIdx.x + 1) * per);
+    for (int r = (int)blockIdx.x * per + ((int)threadIdx.x >> 4); r < r1; r += kActThreads / 16)
+        for (int j = ((int)threadIdx.x & 15) * 4; j < a.r_cap; j += 64) {
+            int8_t *const dst = a.aux_q + packed_index(r, j, a.r_cap);
+            if (j >= used)
+                *(uint32_t *)dst = 0u;
+            else
+                for (int i = max(used - j, 0); i < 4; ++i) dst[i] = 0;
+        }
+}
+
+// One activation scale for the call.  The unit of work is 8 rows x 64 channels: 16 bytes of X a lane, and half a block of
+// the packed codes, 512 contiguous bytes, which go out as whole lines.  A wave keeps to one column of blocks, so its
+// lanes' channels, masks and all of an address but one scalar are fixed, and the work per code is the
+// quantisation itself, 3 vector instructions and a share of the packing; it takes every `groups`-th block of 8 rows, up to U
+// of them in flight, a request behind each one that is worked on.  All workgroups walk X together: what is in flight at one
+// time is one contiguous piece of memory.  (A range of rows for each workgroup puts all of them on the same few memory
+// channels where a range is a multiple of a large power of two: 16384 x 5120 from HBM 65 us instead of 45 us.)
+// Few codes (up to 10 MB) are stored at agent scope, which writes them through: stored as usual they all are dirty in the
+// L2s when the kernel ends, and wait to be written back then.  With more of them the L2s write while the kernel
+// runs anyway, and do it better by themselves (us a call, through / as usual: 9000 x 520 -> 1000 28.8 / 29.3, 8192 x 1024 -> 1024
+// 28.3 / 28.4, 6000 x 2048 -> 1024 35.1 / 34.9, 8192 x 4096 -> 4096 139.6 / 137.2, 20000 x 4096 -> 512 130.9 / 126.6).
+// Against rows of 64 chunks to a wave, four rows requested at a time (64-byte pieces of the codes): 8192 x 1024 11.8 -> 9.4 us, 8192
+// x 4096 30.2 -> 24 us (100 MB, 4.2 TB/s with the selection in it), a call of 9000 x 520 -> 1000 38.4 -> 28.8 us.  U = 2; 3, 4, 6
+// and 8 are up to 2 % slower.
 // GIVEN: the list and the column maxima are the caller's (muxq_build_aux): any list of channels, each
 // named once, and any binary32 maxima.
 template <bool GIVEN>
@@ -282,23 +304,22 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_select(const ActArgs a
 {
     __shared__ ActShared sh;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int C = a.K / 8, CA = a.k_pad / 8;
-    constexpr int U = 4;
-    const int S = a.pieces, P = a.groups, p = quotient(wave, a.by_pieces), seg = wave - p * S;
-    const int c = seg * 64 + lane;
-    const bool in_c = c < C && p < P;
-    const int deep = a.deep;                         // rows in flight, at most U
-    const int stride = (int)gridDim.x * P * deep;
-    int row = p < P ? (int)blockIdx.x * P * deep + p : a.M;    // (waves without a piece: no row)
+    const int C = a.K / 8, CA = a.k_pad / 8, CB = a.k_pad / 64;
+    constexpr int U = 2;
+    const int G = a.groups, g = (int)blockIdx.x * a.waves + wave, rg = quotient(g, a.by_pieces), cb = g - rg * CB;
+    const int nb = (a.M + 7) >> 3;
+    int rb = wave < a.waves && rg < G ? rg : nb;         // block of 8 rows (waves without one: past the end)
+    const int c = cb * 8 + (lane & 7), lr = lane >> 3;
+    const bool in_c = c < C;
+    const uint16_t *const xc = a.x + min(c, C - 1) * 8;  // (lanes of the K padding read the last channels)
     uint4 raw[U];
-    auto load = [&](int r) {
+    auto load = [&](int b) { return *(const uint4 *)(xc + (size_t)min(b * 8 + lr, a.M - 1) * a.ldx); };
+    auto load_first = [&] {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            raw[u] = make_uint4(0, 0, 0, 0);
-            if (u < deep && r + u * P < a.M && in_c) raw[u] = *(const uint4 *)(a.x + (size_t)(r + u * P) * a.ldx + c * 8);
-        }
+        for (int u = 0; u < U; ++u)
+            if (rb + u * G < nb) raw[u] = load(rb + u * G);
     };
-    if (GIVEN) load(row);
+    if (GIVEN) load_first();
 
     const float shrink = __uint_as_float((uint32_t)(127 - a.exp) << 23);  // 2^-exp
     float sx, inv;
@@ -334,7 +355,7 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_select(const ActArgs a
         }
     } else {
         uint4 mx;
-        const Selected sel = act_select<true, true>(a, sh, shrink, mx, [&] { load(row); });
+        const Selected sel = act_select<true, true>(a, sh, shrink, mx, load_first);
         used = sel.used;
         sx = sh.sx;
         inv = sh.inv;
@@ -349,18 +370,15 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_select(const ActArgs a
             }
         }
     }
-    const ActGather g = gather_request(a, sh, blockIdx.x * 64 + (tid >> 4), used);
+    const ActGather g_aux = gather_request(a, sh, blockIdx.x * 64 + (tid >> 4), used);
 
-    // Aux columns past the list, in equal shares of the rows
-    if (used < a.r_cap) {
-        const int per = (a.M + (int)gridDim.x - 1) / (int)gridDim.x, r1 = min(a.M, ((int)blockIdx.x + 1) * per);
-        for (int r = blockIdx.x * per + (tid >> 6); r < r1; r += kActWaves)
-            for (int j = used + (tid & 63); j < a.r_cap; j += 64) a.aux_q[packed_index(r, j, a.r_cap)] = 0;
-    }
     const float inv_listed = inv * shrink, magic = 12582912.0f + (float)z;
-    const uint32_t mask = in_c ? sh.mask[c] : 0u;
+    const uint32_t mask = rb < nb && in_c ? sh.mask[c] : 0u;
+    const bool wave_listed = __ballot(mask != 0) != 0;
+    const uint32_t keep = in_c ? ~0u : 0u;               // K padding of Body: zeros
+    const bool through = (size_t)a.M * a.k_pad <= (size_t)10 << 20;
     // the multiplier and the rounding constant of each of the thread's channels, once: where the list is
-    // full its entries are the lowest channels (the capacity rule), all in the first pieces, and codes put
+    // full its entries are the lowest channels (the capacity rule), all in the first columns, and codes put
     // right one by one made those waves the last (64 of 4096 channels: 34 us against 27 us)
     float mul[8], mag[8];
 #pragma unroll
@@ -369,32 +387,36 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_select(const ActArgs a
         mul[i] = l ? inv_listed : inv;
         mag[i] = l ? 12582912.0f : magic;
     }
-    for (; row < a.M; row += stride) {
+    while (rb < nb) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int r = row + u * P;
-            if (u >= deep || r >= a.M) break;
-            if (in_c && GIVEN) {                     // (from HBM the shorter register list is 4 % faster)
-                quantize_chunk(a, sh, r, c, raw[u], mask, inv, inv_listed, magic);
-            } else if (in_c) {
-                const f16x8 h = __builtin_bit_cast(f16x8, raw[u]);
-                uint32_t q[8];
+            if (rb >= nb) break;
+            const f16x8 h = __builtin_bit_cast(f16x8, raw[u]);
+            if (rb + U * G < nb) raw[u] = load(rb + U * G);
+            uint32_t q[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) q[i] = quant_word((float)h[i], mul[i], a.qmax, mag[i]);
-                const uint2 packed = make_uint2(pack_low_bytes(q[0], q[1], q[2], q[3]), pack_low_bytes(q[4], q[5], q[6], q[7]));
-                *(uint2 *)(a.body_q + packed_index(r, c * 8, a.k_pad)) = packed;
-                for (uint32_t mm = mask; mm != 0; mm &= mm - 1) {          // Aux (Eq. 5)
-                    const int i = __builtin_ctz(mm);
-                    a.aux_q[packed_index(r, sh.slot[c * 8 + i], a.r_cap)] =
-                        (int8_t)((i < 4 ? packed.x : packed.y) >> ((i & 3) * 8));
-                }
-            } else if (c < CA) {                     // K padding of Body
-                *(uint2 *)(a.body_q + packed_index(r, c * 8, a.k_pad)) = make_uint2(0, 0);
+            for (int i = 0; i < 8; ++i) q[i] = quant_word((float)h[i], mul[i], a.qmax, mag[i]);
+            const uint2 packed = make_uint2(pack_low_bytes(q[0], q[1], q[2], q[3]) & keep, pack_low_bytes(q[4], q[5], q[6], q[7]) & keep);
+            const int r = rb * 8 + lr;
+            if (r < a.M) {
+                int8_t *const dst = a.body_q + ((size_t)(rb >> 1) * CB + cb) * 1024 + (rb & 1) * 512;      // = packed_index(8 rb, 64 cb)
+                if (through)
+                    __hip_atomic_store((unsigned long long *)(dst + lane * 8), __builtin_bit_cast(unsigned long long, packed),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                else
+                    *(uint2 *)(dst + lane * 8) = packed;
+                if (wave_listed)
+                    for (uint32_t mm = mask; mm != 0; mm &= mm - 1) {          // Aux (Eq. 5)
+                        const int i = __builtin_ctz(mm);
+                        a.aux_q[packed_index(r, sh.slot[c * 8 + i], a.r_cap)] =
+                            (int8_t)((i < 4 ? packed.x : packed.y) >> ((i & 3) * 8));
+                    }
             }
+            rb += G;
         }
-        load(row + stride);
     }
-    gather_rest(a, sh, used, g);
+    zero_aux_rest(a, used);
+    gather_rest(a, sh, used, g_aux);
 }
 
 // One activation scale per row.  A row is `pieces` pieces of 64 NC chunks; a wave takes a piece, a lane
@@ -527,15 +549,25 @@ hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool give
     ActArgs a = args;
     a.by_chunks = divisor(a.k_pad / 8);
     a.cut = magnitude_cut(a.threshold);
-    // pieces of a row: of 64 chunks, or with one scale per row of as many as a wave keeps in registers
-    a.pieces = !per_token ? (a.k_pad / 8 + 63) / 64 : a.k_pad <= 1024 ? 1 : (a.k_pad + 2047) / 2048;
-    a.by_pieces = divisor(a.pieces);
     // every workgroup selects for itself, so no more of them than are resident at once, but enough for
     // a share of the weight side each (64 output channels)
-    a.groups = min(kActWaves / a.pieces, (a.M + 255) / 256);       // rows of a workgroup at a time
-    a.deep = per_token ? 1 : max(1, min(4, a.M / (256 * a.groups)));
-    const int rows = a.groups * a.deep;
-    const int grid = min(max((a.M + rows - 1) / rows, a.cn != nullptr ? (a.N + 63) / 64 : 1), 256);
+    const int most = 256, weight_side = a.cn != nullptr ? (a.N + 63) / 64 : 1;
+    int grid;
+    if (!per_token) {
+        // columns of 64 channels, and as many waves as there are blocks of 8 rows in them
+        const int columns = a.k_pad / 64, blocks = (a.M + 7) / 8;
+        const long long units = (long long)columns * blocks;
+        a.by_pieces = divisor(columns);
+        a.waves = (int)min((long long)kActWaves, (units + most - 1) / most);
+        grid = (int)min((long long)most, max((units + a.waves - 1) / a.waves, (long long)weight_side));
+        a.groups = min(grid * a.waves / columns, blocks);
+    } else {
+        // pieces of a row, of as many chunks as a wave keeps in registers; rows of a workgroup at a time
+        a.pieces = a.k_pad <= 1024 ? 1 : (a.k_pad + 2047) / 2048;
+        a.by_pieces = divisor(a.pieces);
+        a.groups = min(kActWaves / a.pieces, (a.M + 255) / 256);
+        grid = min(max((a.M + a.groups - 1) / a.groups, weight_side), most);
+    }
     void (*kern)(const ActArgs);
     if (!per_token)
         kern = given ? k_quantize_select<true> : k_quantize_select<false>;
