@@ -132,6 +132,8 @@ __device__ __forceinline__ Selected act_select(const ActArgs &a, ActShared &sh, 
             mx = fold_slabs<2>(a, c, p, P, on, load_x);
         } else if (a.n_slabs <= 4 * P) {
             mx = fold_slabs<4>(a, c, p, P, on, load_x);
+        } else if (a.n_slabs <= 5 * P) {
+            mx = fold_slabs<5>(a, c, p, P, on, load_x);
         } else {
             mx = fold_slabs<8>(a, c, p, P, on, load_x);
             for (int sl = p + 8 * P; on && sl < a.n_slabs; sl += 8 * P) {
@@ -245,28 +247,10 @@ __device__ __forceinline__ void gather_rest(const ActArgs &a, const ActShared &s
     }
 }
 
-// Codes of one chunk of 8 channels of a row: Body (Eq. 1, 4; unlisted channels as code + z, which
-// rides on `magic`), and the Aux codes of the channels in `mask` (Eq. 5).
-__device__ __forceinline__ void quantize_chunk(const ActArgs &a, const ActShared &sh, int row, int c, uint4 raw, uint32_t mask,
-                                               float inv, float inv_listed, float magic)
+// 8 codes, stored at agent scope: written through, where a usual store leaves them dirty in L2 until the kernel ends.
+__device__ __forceinline__ void store_through(int8_t *dst, uint2 codes)
 {
-    const f16x8 h = __builtin_bit_cast(f16x8, raw);
-    uint32_t q[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) q[i] = quant_word((float)h[i], inv, a.qmax, magic);
-    uint2 packed = make_uint2(pack_low_bytes(q[0], q[1], q[2], q[3]), pack_low_bytes(q[4], q[5], q[6], q[7]));
-    for (uint32_t mm = mask; mm != 0; mm &= mm - 1) {              // few lanes: listed channels again, shrunk, no z
-        const int i = __builtin_ctz(mm), d = i >> 1;
-        const uint32_t word = d == 0 ? raw.x : d == 1 ? raw.y : d == 2 ? raw.z : raw.w;
-        const float xi = (float)__builtin_bit_cast(_Float16, (unsigned short)(word >> ((i & 1) * 16)));
-        const uint32_t code = quant_word(xi, inv_listed, a.qmax) & 0xffu, sh8 = (uint32_t)(i & 3) * 8u;
-        if (i < 4)
-            packed.x = (packed.x & ~(0xffu << sh8)) | (code << sh8);
-        else
-            packed.y = (packed.y & ~(0xffu << sh8)) | (code << sh8);
-        a.aux_q[packed_index(row, sh.slot[c * 8 + i], a.r_cap)] = (int8_t)code;
-    }
-    *(uint2 *)(a.body_q + packed_index(row, c * 8, a.k_pad)) = packed;
+    __hip_atomic_store((unsigned long long *)dst, __builtin_bit_cast(unsigned long long, codes), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Aux columns past the list, zeroed for an equal share of the rows: four codes to a store.
@@ -290,9 +274,8 @@ __device__ __forceinline__ void zero_aux_rest(const ActArgs &a, int used)
 // of them in flight, a request behind each one that is worked on.  All workgroups walk X together: what is in flight at one
 // time is one contiguous piece of memory.  (A range of rows for each workgroup puts all of them on the same few memory
 // channels where a range is a multiple of a large power of two: 16384 x 5120 from HBM 65 us instead of 45 us.)
-// Few codes (up to 10 MB) are stored at agent scope, which writes them through: stored as usual they all are dirty in the
-// L2s when the kernel ends, and wait to be written back then.  With more of them the L2s write while the kernel
-// runs anyway, and do it better by themselves (us a call, through / as usual: 9000 x 520 -> 1000 28.8 / 29.3, 8192 x 1024 -> 1024
+// Few codes (up to 10 MB) are written through: stored as usual they all are dirty in the L2s when the kernel ends, and
+// wait to be written back then.  With more of them the L2s write while the kernel runs anyway, and do it better by themselves (us a call, through / as usual: 9000 x 520 -> 1000 28.8 / 29.3, 8192 x 1024 -> 1024
 // 28.3 / 28.4, 6000 x 2048 -> 1024 35.1 / 34.9, 8192 x 4096 -> 4096 139.6 / 137.2, 20000 x 4096 -> 512 130.9 / 126.6).
 // Against rows of 64 chunks to a wave, four rows requested at a time (64-byte pieces of the codes): 8192 x 1024 11.8 -> 9.4 us, 8192
 // x 4096 30.2 -> 24 us (100 MB, 4.2 TB/s with the selection in it), a call of 9000 x 520 -> 1000 38.4 -> 28.8 us.  U = 2; 3, 4, 6
@@ -401,8 +384,7 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_select(const ActArgs a
             if (r < a.M) {
                 int8_t *const dst = a.body_q + ((size_t)(rb >> 1) * CB + cb) * 1024 + (rb & 1) * 512;      // = packed_index(8 rb, 64 cb)
                 if (through)
-                    __hip_atomic_store((unsigned long long *)(dst + lane * 8), __builtin_bit_cast(unsigned long long, packed),
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    store_through(dst + lane * 8, packed);
                 else
                     *(uint2 *)(dst + lane * 8) = packed;
                 if (wave_listed)
@@ -419,85 +401,158 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_select(const ActArgs a
     gather_rest(a, sh, used, g_aux);
 }
 
-// One activation scale per row.  A row is `pieces` pieces of 64 NC chunks; a wave takes a piece, a lane
-// the chunks lane, lane + 64, ... of it, in registers from the row's maximum to the codes; the next
-// rows are on their way meanwhile.  The pieces' maxima meet in LDS (one barrier per step of all rows
-// in flight; the two halves of `s_piece` take turns).
+// One activation scale per row.  A wave takes 64 / LANES rows x NB pieces of LANES chunks, 16 bytes of each piece a lane, in
+// registers from the rows' maxima to the codes: with 16 lanes to a row, what is worked out for a row (its maximum over the lanes, the
+// scale, two divisions) is worked out for 4 rows at once, and the codes go out as 256 contiguous bytes.  The next rows are
+// requested piece by piece as these are worked on.  Rows longer than that are in `pieces` waves, whose maxima meet in LDS (one
+// barrier per step; the two halves of `s_piece` take turns).  Against single rows of up to 4 x 64 chunks a wave: 16384 x 1280
+// 24.8 -> 21.8 us (63 MB, with the selection in it), a call of 60000 x 1280 -> 512 138 -> 122 us.  The codes are written through: a call
+// of 8192 x 4096 -> 1024 72.2 -> 71.4 us, 6000 x 2048 -> 768 38.4 -> 37.8.
+// A kernel starts with a cold instruction cache, and what is unrolled NB times is kept short (1 KB of code takes about 0.12 us
+// to fetch: 10 pieces with everything unrolled was 2 us slower than 4 on 1024 x 768): the column masks of the maxima come from LDS, and pieces with a listed channel or K padding are put aside, in LDS,
+// for a rolled loop.
 // STATIC: the list was fixed offline (a kernel of its own: nothing waits for slabs, and the rows are requested first).
-template <int NC, bool STATIC>
+template <int NB, int LANES, bool STATIC>
 __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
 {
+    constexpr int R = 64 / LANES;
+    static_assert(NB * LANES <= 128, "what is put aside fits LDS");
     __shared__ ActShared sh;
-    __shared__ uint32_t s_piece[2][kActWaves];
+    __shared__ __attribute__((aligned(16))) uint32_t s_piece[2][kActWaves * 4 * R];
+    __shared__ uint4 s_aside[kActWaves][NB][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int C = a.K / 8, CA = a.k_pad / 8;
-    const int S = a.pieces, P = a.groups, p = quotient(wave, a.by_pieces), seg = wave - p * S;
-    const int c0 = seg * 64 * NC + lane;
-    uint4 raw[NC];
-    auto load = [&](int row, uint4 (&v)[NC]) {
-        const uint16_t *src = a.x + (size_t)row * a.ldx + c0 * 8;
+    const int S = a.pieces, S4 = (S + 3) & ~3, P = a.groups, p = quotient(wave, a.by_pieces), seg = wave - p * S;
+    const int c0 = seg * NB * LANES + lane % LANES, lr = lane / LANES, n_rb = (a.M + R - 1) / R;
+    uint4 raw[NB];
+    auto chunk = [&](int j) { return min(c0 + j * LANES, C - 1); };          // (past the end the last chunk again)
+    auto row_of = [&](int rb) { return a.x + (size_t)min(rb * R + lr, a.M - 1) * a.ldx; };
+    auto load = [&](const uint16_t *row, int j) { return *(const uint4 *)(row + chunk(j) * 8); };
+    const int stride = (int)gridDim.x * P;
+    int rb = (int)blockIdx.x * P + p;
+    auto load_first = [&] {
+        if (p < P && rb < n_rb) {
+            const uint16_t *const row = row_of(rb);
 #pragma unroll
-        for (int i = 0; i < NC; ++i) {
-            v[i] = make_uint4(0, 0, 0, 0);
-            if (row < a.M && p < P && c0 + 64 * i < C) v[i] = *(const uint4 *)(src + 512 * i);
+            for (int j = 0; j < NB; ++j) raw[j] = load(row, j);
         }
     };
-    // (P rows of every workgroup in turn: see k_quantize_select)
-    const int stride = (int)gridDim.x * P;
-    int row = (int)blockIdx.x * P + p;
-    if (STATIC) load(row, raw);
+    if (STATIC) load_first();
+    if (tid < 2 * kActWaves * 4 * R) (&s_piece[0][0])[tid] = 0;
 
     const float shrink = __uint_as_float((uint32_t)(127 - a.exp) << 23);  // 2^-exp
     uint4 mx;
-    const Selected sel = act_select<!STATIC, false>(a, sh, shrink, mx, [&] { load(row, raw); });
+    const Selected sel = act_select<!STATIC, false>(a, sh, shrink, mx, load_first);
     if (blockIdx.x == 0 && !STATIC)
         store_selection(sel, mx, tid, C, CA, true, a.r_cap, false, 0.f, shrink, a.col_absmax, a.col_scale, a.col_slot,
                         a.col_mask, a.idx, a.n_outliers);
     const int used = __builtin_amdgcn_readfirstlane(sel.used);       // (the same in every lane)
     const ActGather g = gather_request(a, sh, blockIdx.x * 64 + (tid >> 4), used);
-    uint32_t mk = 0;                                 // this lane's chunk masks, one to a byte
-    static_assert(NC <= 4, "four masks to a word");
+    // magnitudes of the unlisted channels of each chunk (the parts of the fold have been read)
+    uint4 *const s_unlisted = sh.part;
+    if (tid < C) {
+        const uint32_t m = sh.mask[tid];
+        uint32_t d[4];
 #pragma unroll
-    for (int i = 0; i < NC; ++i)
-        if (c0 + 64 * i < C) mk |= (uint32_t)sh.mask[c0 + 64 * i] << (8 * i);
+        for (int i = 0; i < 4; ++i) d[i] = (m >> (2 * i) & 1u ? 0u : 0x7fffu) | (m >> (2 * i + 1) & 1u ? 0u : 0x7fff0000u);
+        s_unlisted[tid] = make_uint4(d[0], d[1], d[2], d[3]);
+    }
+    uint32_t aside = 0;                                  // which pieces are not all unlisted channels
+#pragma unroll 1
+    for (int j = 0; j < NB; ++j) {
+        const int c = c0 + j * LANES;
+        if (__ballot(c >= C || sh.mask[min(c, C - 1)] != 0) != 0) aside |= 1u << j;
+    }
+    aside = __builtin_amdgcn_readfirstlane(aside);
+    lds_barrier();
 
     // (the same number of steps for all waves: they meet at the barrier)
-    for (int step = 0, r0 = (int)blockIdx.x * P; r0 < a.M; ++step, r0 += stride, row += stride) {
-        uint4 nx[NC];
-        load(row + stride, nx);
-        uint32_t m = wave_row_maxima(raw, mk);
+    for (int step = 0, r0 = (int)blockIdx.x * P; r0 < n_rb; ++step, r0 += stride, rb += stride) {
+        const bool on = p < P && rb < n_rb;
+        uint32_t m = 0;
+        if (on) {
+            // listed and unlisted apart, two halves to a word
+            uint32_t nm = 0, lm = 0;
+            auto take = [&](const uint4 &v, const uint4 &k) {
+                nm = pk_max_u16(pk_max_u16(pk_max_u16(nm, v.x & k.x), pk_max_u16(v.y & k.y, v.z & k.z)), v.w & k.w);
+                lm = pk_max_u16(pk_max_u16(pk_max_u16(lm, v.x & ~k.x & 0x7fff7fffu), pk_max_u16(v.y & ~k.y & 0x7fff7fffu, v.z & ~k.z & 0x7fff7fffu)),
+                                v.w & ~k.w & 0x7fff7fffu);
+            };
+            auto both = [&] { return max(nm & 0xffffu, nm >> 16) | max(lm & 0xffffu, lm >> 16) << 16; };
+#pragma unroll
+            for (int j = 0; j < NB; ++j) take(raw[j], s_unlisted[chunk(j)]);
+            m = lanes_max_u16x2<LANES>(both());
+            // (a NaN wins the integer comparison, so it shows; the maxima are taken again without it)
+            if (__ballot((m & 0xffffu) > 0x7c00u || (m >> 16) > 0x7c00u) != 0) {
+                const uint16_t *const row = row_of(rb);
+                nm = lm = 0;
+#pragma unroll 1
+                for (int j = 0; j < NB; ++j) take(drop_nan(load(row, j)), s_unlisted[chunk(j)]);
+                m = lanes_max_u16x2<LANES>(both());
+            }
+        }
         if (S > 1) {
-            if (lane == 63) s_piece[step & 1][wave] = m;
+            if (on && lane % LANES == 0) s_piece[step & 1][(p * R + lr) * S4 + seg] = m;
             lds_barrier();
-            m = 0;
-            for (int i = 0; i < S; ++i) m = pk_max_u16(m, s_piece[step & 1][min(p, P - 1) * S + i]);
-        } else {
-            m = (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+            if (on)
+                for (int i = 0; i < S; i += 4) {
+                    const uint4 o = *(const uint4 *)&s_piece[step & 1][(p * R + lr) * S4 + i];
+                    m = pk_max_u16(m, pk_max_u16(pk_max_u16(o.x, o.y), pk_max_u16(o.z, o.w)));
+                }
         }
-        if (p < P && row < a.M) {
-            float sx, inv;
-            int z;
-            call_scale(m, shrink, a.qmax, sx, inv, z);
-            if (lane == 0 && seg == 0) {
-                a.x_scale[row] = sx;
-                a.x_scale[a.M + row] = inv;
-                ((int32_t *)a.x_scale)[2 * (size_t)a.M + row] = z;
-            }
-            const float inv_listed = inv * shrink, magic = 12582912.0f + (float)z;
-#pragma unroll
-            for (int i = 0; i < NC; ++i) {
-                const int c = c0 + 64 * i;
-                if (c < C)
-                    quantize_chunk(a, sh, row, c, raw[i], (mk >> (8 * i)) & 0xffu, inv, inv_listed, magic);
-                else if (c < CA)                     // K padding of Body
-                    *(uint2 *)(a.body_q + packed_index(row, c * 8, a.k_pad)) = make_uint2(0, 0);
-            }
-            if (seg == S - 1)
-                for (int j = used + lane; j < a.r_cap; j += 64) a.aux_q[packed_index(row, j, a.r_cap)] = 0;
+        if (!on) continue;
+        const int row = rb * R + lr;
+        float sx, inv;
+        int z;
+        call_scale(m, shrink, a.qmax, sx, inv, z);
+        if (seg == 0 && lane % LANES == 0 && row < a.M) {
+            a.x_scale[row] = sx;
+            a.x_scale[a.M + row] = inv;
+            ((int32_t *)a.x_scale)[2 * (size_t)a.M + row] = z;
         }
+        const float inv_listed = inv * shrink, magic = 12582912.0f + (float)z;
+        const bool more = rb + stride < n_rb;
+        const uint16_t *const next = row_of(rb + stride);
+        int8_t *const dst = a.body_q + packed_index(row, c0 * 8, a.k_pad);
+        constexpr int PIECE = LANES / 8 * 1024;          // bytes of packed codes from piece to piece
 #pragma unroll
-        for (int i = 0; i < NC; ++i) raw[i] = nx[i];
+        for (int j = 0; j < NB; ++j) {
+            const uint4 v = raw[j];
+            if (more) raw[j] = load(next, j);
+            if ((aside >> j & 1u) != 0) {
+                s_aside[wave][j][lane] = v;
+            } else {
+                const f16x8 h = __builtin_bit_cast(f16x8, v);
+                uint32_t q[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) q[i] = quant_word((float)h[i], inv, a.qmax, magic);
+                const uint2 packed = make_uint2(pack_low_bytes(q[0], q[1], q[2], q[3]), pack_low_bytes(q[4], q[5], q[6], q[7]));
+                if (row < a.M) store_through(dst + j * PIECE, packed);
+            }
+        }
+#pragma unroll 1
+        for (uint32_t rest = aside; rest != 0; rest &= rest - 1) {
+            const int j = __builtin_ctz(rest), c = c0 + j * LANES;
+            const f16x8 h = __builtin_bit_cast(f16x8, s_aside[wave][j][lane]);
+            const uint32_t mask = c < C ? (uint32_t)sh.mask[c] : 0u;
+            uint32_t q[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {                // listed channels: shrunk, no z
+                const bool l = ((mask >> i) & 1u) != 0;
+                q[i] = quant_word((float)h[i], l ? inv_listed : inv, a.qmax, l ? 12582912.0f : magic);
+            }
+            uint2 packed = make_uint2(pack_low_bytes(q[0], q[1], q[2], q[3]), pack_low_bytes(q[4], q[5], q[6], q[7]));
+            if (c >= C) packed = make_uint2(0, 0);       // K padding of Body
+            if (row < a.M && c < CA) {
+                store_through(dst + j * PIECE, packed);
+                for (uint32_t mm = mask; mm != 0; mm &= mm - 1) {      // Aux (Eq. 5)
+                    const int i = __builtin_ctz(mm);
+                    a.aux_q[packed_index(row, sh.slot[c * 8 + i], a.r_cap)] = (int8_t)((i < 4 ? packed.x : packed.y) >> ((i & 3) * 8));
+                }
+            }
+        }
     }
+    zero_aux_rest(a, used);
     gather_rest(a, sh, used, g);
 }
 
@@ -544,6 +599,32 @@ hipError_t launch_fold_slabs(uint16_t *partial, int n_slabs, int k_pad, hipStrea
     return launch_kernel(k_fold_slabs, dim3((k_pad / 8 + 63) / 64), dim3(256), 0, s, partial, n_slabs, k_pad);
 }
 
+// The form of k_rows_select: single rows in pieces of 2 x 64 chunks, or 4 rows in pieces of 4 or 5 x 16.  Each is bound by its
+// vector instructions, about 60 for a piece of 64 lanes x 16 bytes and 200 for what is worked out once per row, times the waves on a SIMD
+// and the steps, and the least of the three estimates is the fastest or within 1 % of it (19 shapes, 24 x 5120 to 60000 x 1280).
+// us a call, single rows / 4 rows x 4 / 4 rows x 5: 512 x 4096 -> 1024 21.8 / 22.4 / 22.7, 2000 x 1280 -> 1280 23.6 / 22.8 / 23.0, 8192 x 4096
+// -> 1024 81.1 / 73.7 / 74.6, 9000 x 520 -> 1000 37.0 / 36.0 / 32.3, 60000 x 1280 -> 512 168 / 125 / 124.
+// Returns the groups of rows; pieces: waves to a group, at_once: groups of a workgroup at a time.
+int row_form(int M, int k_pad, int &form, int &pieces, int &at_once)
+{
+    static const struct { int pieces, lanes; } kForms[3] = {{2, 64}, {4, 16}, {5, 16}};
+    int groups = 0;
+    long long best = -1;
+    for (int f = 0; f < 3; ++f) {
+        const int rows = 64 / kForms[f].lanes, n = (M + rows - 1) / rows;
+        const int S = (k_pad / 8 + kForms[f].pieces * kForms[f].lanes - 1) / (kForms[f].pieces * kForms[f].lanes);
+        const int P = min(kActWaves / S, (n + 255) / 256);
+        const long long cost = (long long)((n + 256 * P - 1) / (256 * P)) * ((P * S + 3) / 4) * (60 * kForms[f].pieces + 200);
+        if (best >= 0 && cost >= best) continue;
+        best = cost;
+        form = f;
+        groups = n;
+        pieces = S;
+        at_once = P;
+    }
+    return groups;
+}
+
 hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool given, hipStream_t s)
 {
     ActArgs a = args;
@@ -552,7 +633,7 @@ hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool give
     // every workgroup selects for itself, so no more of them than are resident at once, but enough for
     // a share of the weight side each (64 output channels)
     const int most = 256, weight_side = a.cn != nullptr ? (a.N + 63) / 64 : 1;
-    int grid;
+    int grid, form = 0;
     if (!per_token) {
         // columns of 64 channels, and as many waves as there are blocks of 8 rows in them
         const int columns = a.k_pad / 64, blocks = (a.M + 7) / 8;
@@ -562,18 +643,20 @@ hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool give
         grid = (int)min((long long)most, max((units + a.waves - 1) / a.waves, (long long)weight_side));
         a.groups = min(grid * a.waves / columns, blocks);
     } else {
-        // pieces of a row, of as many chunks as a wave keeps in registers; rows of a workgroup at a time
-        a.pieces = a.k_pad <= 1024 ? 1 : (a.k_pad + 2047) / 2048;
+        const int groups = row_form(a.M, a.k_pad, form, a.pieces, a.groups);
         a.by_pieces = divisor(a.pieces);
-        a.groups = min(kActWaves / a.pieces, (a.M + 255) / 256);
-        grid = min(max((a.M + a.groups - 1) / a.groups, weight_side), most);
+        grid = min(max((groups + a.groups - 1) / a.groups, weight_side), most);
     }
     void (*kern)(const ActArgs);
+    const bool is_static = a.static_mask != nullptr;
     if (!per_token)
         kern = given ? k_quantize_select<true> : k_quantize_select<false>;
+    else if (form == 0)
+        kern = is_static ? k_rows_select<2, 64, true> : k_rows_select<2, 64, false>;
+    else if (form == 1)
+        kern = is_static ? k_rows_select<4, 16, true> : k_rows_select<4, 16, false>;
     else
-        kern = a.k_pad <= 1024 ? (a.static_mask != nullptr ? k_rows_select<2, true> : k_rows_select<2, false>)
-                               : (a.static_mask != nullptr ? k_rows_select<4, true> : k_rows_select<4, false>);
+        kern = is_static ? k_rows_select<5, 16, true> : k_rows_select<5, 16, false>;
     return launch_kernel(kern, dim3(grid), dim3(kActThreads), 0, s, a);
 }
 

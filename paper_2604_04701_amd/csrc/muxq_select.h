@@ -60,6 +60,16 @@ __device__ __forceinline__ uint32_t wave_max_u16x2_to_lane63(uint32_t v)
     v = pk_max_u16(v, dpp_zero<0x142, 0xa>(v));              // lane 15 of a row to the next one
     return pk_max_u16(v, dpp_zero<0x143, 0xc>(v));           // lane 31 to the upper half
 }
+// ... over each LANES (16 or 64) neighbouring lanes, in all of them.
+template <int LANES>
+__device__ __forceinline__ uint32_t lanes_max_u16x2(uint32_t v)
+{
+    if (LANES == 64) return (uint32_t)__builtin_amdgcn_readlane((int)wave_max_u16x2_to_lane63(v), 63);
+    v = pk_max_u16(v, dpp_zero<0x121>(v));                   // rotations of a row of 16 by 1, 2, 4, 8
+    v = pk_max_u16(v, dpp_zero<0x122>(v));
+    v = pk_max_u16(v, dpp_zero<0x124>(v));
+    return pk_max_u16(v, dpp_zero<0x128>(v));
+}
 __device__ __forceinline__ int wave_inclusive_sum(int x)
 {
     uint32_t v = (uint32_t)x;

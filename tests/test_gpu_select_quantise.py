@@ -43,6 +43,43 @@ def test_thresholds(M, threshold):
     compare(run_gpu(X, W, **kw), orc.linear(X, W, **kw), 200, 72, 256)
 
 
+# one scale per row: single rows (2 x 64 chunks to a wave), and 4 rows at a time in pieces of 4 and of 5 x 16 chunks, each with one
+# wave to the rows and with several, whole pieces and K padding, M off the groups of 4
+ROW_SHAPES = [(40, 1024, 24), (70, 3080, 24), (255, 8192, 24), (8195, 512, 24), (6001, 1032, 24), (2003, 5120, 24), (5002, 640, 24),
+              (9001, 600, 24), (12001, 1280, 24), (9999, 8, 24)]
+
+
+@pytest.mark.parametrize("shape", ROW_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_rows_of_each_form(shape):
+    M, K, N = shape
+    check_case(Case("act_rows", M, K, N, min(9, K // 8), U, 990), x_gran="token")
+    case = Case("act_rows_static", M, K, N, min(5, K // 8), U, 991)
+    if M * K < 4_000_000:
+        T._check_static(case, [int(k) for k in synth.make_case(case)[2]], "token", "channel", with_bias=True)
+
+
+@pytest.mark.parametrize("M,K", [(40, 1024), (6001, 520), (9001, 600)])
+def test_rows_with_nan_and_infinity(M, K):
+    """A NaN sets no scale (and hides its channel from the list), an infinity makes its row's scale infinite; the codes
+    and scales of all other rows are those of the list that results, by the formulas in binary32."""
+    X, W, ch = synth.make_case(Case("act_nan", M, K, 24, 3, U, 992))
+    hit = [(5, (int(ch[0]) + 1) % K, np.nan), (9, (int(ch[1]) + 1) % K, np.inf), (M - 1, int(ch[2]), np.nan)]
+    for r, k, v in hit:
+        X[r, k] = v
+    got = run_gpu(X, W, x_gran="token", finite=False)
+    lst = got["outlier_idx"][:got["n_outliers"][0]]
+    assert lst.tolist() == sorted([int(ch[0]), int(ch[1]), hit[1][1]])
+    mult = np.ones(K, np.float32)
+    mult[lst] = 0.25
+    amax = np.nanmax(np.abs(X.astype(np.float32)) * mult, axis=1)
+    s_x, inv = amax / np.float32(127), np.float32(127) / amax
+    assert (got["x_scale"][0] == s_x).all() and (got["x_scale"][1] == inv).all()
+    rows = np.ones(M, bool)
+    rows[[5, 9, M - 1]] = False
+    want = np.clip(np.rint(X[rows].astype(np.float32) * (inv[rows, None] * mult)), -127, 127)
+    assert (got["body_q"][rows][:, :K] == want).all() and (got["aux_q"][rows][:, :len(lst)] == want[:, lst]).all()
+
+
 @pytest.mark.parametrize("x_gran", ["tensor", "token"])
 def test_select_and_quantise_static_lists(x_gran):
     for M, K, N in ((70, 2056, 72), (900, 264, 264)):
