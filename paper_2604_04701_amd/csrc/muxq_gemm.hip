@@ -1349,6 +1349,11 @@ __global__ __launch_bounds__(256) void k_gemm_i8_small_deep(const GemmArgs a, co
 // 32x32x32 rate, do not matter.
 // The Aux K steps all belong to the last wave (which has the fewest Body steps), come first there
 // and are weighted before its Body steps, as in the other forms.
+// What counts beside the bytes is that no request waits for anything and nothing waits for a request it does not use: the first
+// Aux step and the epilogue's constants, token scales and zero points are requested with the first Body steps, without
+// branches.  (Before, a wave waited for all its first loads for the sake of a constant, the last wave was 2.6 us behind the others
+// with Aux, every DEPTH steps all loads were waited for, and the end began with two loads: 512 x 4096 -> 1024 11.4 -> 9.2 us,
+// 24 x 5120 -> 1280 6.9 -> 5.4, 1024 x 4096 -> 1024 15.4 -> 12.)
 // --------------------------------------------------------------------------
 template <int TNB, int TMB, int DEPTH, int W>
 __global__ __launch_bounds__(W * 64) void k_gemm_i8_direct(const GemmArgs a, const TileMap tm)
@@ -1377,6 +1382,21 @@ __global__ __launch_bounds__(W * 64) void k_gemm_i8_direct(const GemmArgs a, con
 #pragma unroll
         for (int j = 0; j < TMB; ++j) acc[i][j] = v4i{0, 0, 0, 0};
 
+    // The last wave's first Aux step, requested before anything else: its Body steps wait for it.  (Read whether or not there
+    // are listed channels; the count comes at the same time.)
+    const int aux_row_bytes = a.r_cap / BK * 1024;             // bytes of 16 packed Aux rows
+    const bool aux_wave = wave == W - 1 && a.n_outliers != nullptr && a.r_cap > 0;
+    typedef const __attribute__((address_space(4))) int32_t *scalar_ptr_t;       // (a scalar load: nothing queues behind it)
+    const int32_t n_listed = *(scalar_ptr_t)(uintptr_t)(aux_wave ? (const void *)a.n_outliers : (const void *)a.x_scale);
+    // (The other waves read 16 bytes of the weights: behind a branch the values were copied, and the copy waited for.)
+    v4i wa[TNB], xa[TMB];
+    const int8_t *const wa_src = aux_wave ? a.w_aux : a.w_q, *const xa_src = aux_wave ? a.aux_q : a.w_q;
+    const int aux_off = aux_wave ? lane_off : 0, aux_rows = aux_wave ? aux_row_bytes : 0;
+#pragma unroll
+    for (int i = 0; i < TNB; ++i) wa[i] = *(const v4i *)(wa_src + (size_t)bn[i] * aux_rows + aux_off);
+#pragma unroll
+    for (int i = 0; i < TMB; ++i) xa[i] = *(const v4i *)(xa_src + (size_t)bm[i] * aux_rows + aux_off);
+
     v4i wf[DEPTH][TNB], xf[DEPTH][TMB];
     const int8_t *wp[TNB], *xp[TMB];
 #pragma unroll
@@ -1396,68 +1416,104 @@ __global__ __launch_bounds__(W * 64) void k_gemm_i8_direct(const GemmArgs a, con
         for (int d = 0; d < DEPTH; ++d) load(d, d);
     }
 
-    // epilogue constants: a thread finishes 4 channels (n quad nq) of the tokens m0, m0 + MSTEP, ...
-    constexpr int MSTEP = W * 64 / NQ;
+    // Epilogue constants: a thread finishes 4 channels (n quad nq) of the tokens m0, m0 + MSTEP, ...  Requested behind the
+    // first K steps and not touched before the end: no branches, what there is not is read from another place.
+    constexpr int MSTEP = W * 64 / NQ, MT = (TMB * 16 + MSTEP - 1) / MSTEP;
     const int nq = tid % NQ, m0 = tid / NQ;
     const int n = tile_n * TNB * 16 + nq * 4;
     const bool n_in = n < a.N;                            // N % 8 == 0: a run of 4 is in or out as a whole
-    float4 sw = make_float4(0.f, 0.f, 0.f, 0.f);
-    f16x4 bias = {0, 0, 0, 0};
-    v4i cn = {0, 0, 0, 0};
-    if (n_in) {
-        const int st = a.w_per_channel ? 1 : 0, ns = a.w_per_channel ? n : 0;
-        sw = make_float4(a.w_scale[ns], a.w_scale[ns + st], a.w_scale[ns + 2 * st], a.w_scale[ns + 3 * st]);
-        if (a.bias != nullptr) {
+    const int nc = min(n, a.N - 4), w_at = a.w_per_channel ? nc : 0, w_step = a.w_per_channel ? 1 : 0;
+    const unsigned short *const bias_src = a.bias != nullptr ? (const unsigned short *)a.bias : (const unsigned short *)a.w_scale;
+    const int b_at = a.bias != nullptr ? nc : 0, b_step = a.bias != nullptr ? 1 : 0;
+    float swv[4];
+    unsigned short bias[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) bias[i] = a.bias[n + i];
-        }
-        if (a.cn != nullptr) cn = *(const v4i *)(a.cn + n) - a.cn_bias;
+    for (int i = 0; i < 4; ++i) {
+        swv[i] = a.w_scale[w_at + i * w_step];
+        bias[i] = bias_src[b_at + i * b_step];
     }
+    const v4i cn_raw = *(const v4i *)(a.cn != nullptr ? (const void *)(a.cn + nc) : (const void *)a.w_q);
+    const int32_t *const z_src = a.cn != nullptr ? a.zero_point : (const int32_t *)a.x_scale;
+    float sxv[MT];
+    int zv[MT];
+#pragma unroll
+    for (int k = 0; k < MT; ++k) {
+        const int tok = a.x_per_token ? min(tile_m * TMB * 16 + m0 + k * MSTEP, a.M - 1) : 0;
+        sxv[k] = a.x_scale[tok];
+        zv[k] = z_src[tok];
+    }
+    __builtin_amdgcn_sched_barrier(0);
     if (tid < TNB * 16) s_colmax[tid] = 0;
 
-    if (wave == W - 1) {
-        const int t_aux = aux_tiles(a), r_tiles = a.r_cap / BK;
-        for (int t = 0; t < t_aux; ++t) {
-            v4i wa[TNB], xa[TMB];
-#pragma unroll
-            for (int i = 0; i < TNB; ++i) wa[i] = *(const v4i *)(a.w_aux + ((size_t)bn[i] * r_tiles + t) * 1024 + lane_off);
-#pragma unroll
-            for (int i = 0; i < TMB; ++i) xa[i] = *(const v4i *)(a.aux_q + ((size_t)bm[i] * r_tiles + t) * 1024 + lane_off);
+    if (aux_wave) {
+        const int t_aux = (max(0, min(n_listed, a.r_cap)) + BK - 1) / BK;
+        // (the first step by itself: in one loop with the others it would wait for the Body loads too)
+        if (t_aux > 0) {
 #pragma unroll
             for (int i = 0; i < TNB; ++i)
 #pragma unroll
                 for (int j = 0; j < TMB; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa[i], xa[j], acc[i][j], 0, 0, 0);
         }
-        if (t_aux > 0) {                                  // acc_aux -> (2^e - 1) acc_aux, or onto Body's scale
-            const float rho = aux_rho(a);
+        for (int t = 1; t < t_aux; ++t) {
+            v4i wn[TNB], xn[TMB];
 #pragma unroll
-            for (int j = 0; j < TMB; ++j) {
-                float r = rho;
-                if (a.aux_own_scale && a.x_per_token)
-                    r = aux_rho_tok(a)[min((tile_m * TMB + j) * 16 + (lane & 15), a.M - 1)];
+            for (int i = 0; i < TNB; ++i) wn[i] = *(const v4i *)(a.w_aux + (size_t)bn[i] * aux_row_bytes + t * 1024 + lane_off);
 #pragma unroll
-                for (int i = 0; i < TNB; ++i)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        acc[i][j][v] = a.aux_own_scale
-                                           ? (int)__builtin_rintf(r * (float)acc[i][j][v])
-                                           : (int)(((unsigned)acc[i][j][v] << a.exp_shift) - (unsigned)acc[i][j][v]);
-            }
-        }
-    }
-    for (int t = 0; t < nk; t += DEPTH) {
-#pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            if (t + d >= nk) break;
+            for (int i = 0; i < TMB; ++i) xn[i] = *(const v4i *)(a.aux_q + (size_t)bm[i] * aux_row_bytes + t * 1024 + lane_off);
 #pragma unroll
             for (int i = 0; i < TNB; ++i)
 #pragma unroll
                 for (int j = 0; j < TMB; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[d][i], xf[d][j], acc[i][j], 0, 0, 0);
-            if (t + d + DEPTH < nk) load(d, t + d + DEPTH);
+                    acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wn[i], xn[j], acc[i][j], 0, 0, 0);
+        }
+        if (t_aux > 0 && !a.aux_own_scale) {              // acc_aux -> (2^e - 1) acc_aux
+#pragma unroll
+            for (int i = 0; i < TNB; ++i)
+#pragma unroll
+                for (int j = 0; j < TMB; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        acc[i][j][v] = (int)(((unsigned)acc[i][j][v] << a.exp_shift) - (unsigned)acc[i][j][v]);
+        } else if (t_aux > 0) {                           // ... or onto Body's scale
+            const float rho = aux_rho(a);
+#pragma unroll
+            for (int j = 0; j < TMB; ++j) {
+                float r = rho;
+                if (a.x_per_token) r = aux_rho_tok(a)[min((tile_m * TMB + j) * 16 + (lane & 15), a.M - 1)];
+#pragma unroll
+                for (int i = 0; i < TNB; ++i)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[i][j][v] = (int)__builtin_rintf(r * (float)acc[i][j][v]);
+            }
         }
     }
+    auto multiply = [&](int d) {
+#pragma unroll
+        for (int i = 0; i < TNB; ++i)
+#pragma unroll
+            for (int j = 0; j < TMB; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[d][i], xf[d][j], acc[i][j], 0, 0, 0);
+    };
+    // (no condition on a request in the loop: where one may have been left out, the compiler waits for all of them)
+    int t = 0;
+    for (; t + 2 * DEPTH <= nk; t += DEPTH) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            multiply(d);
+            load(d, t + d + DEPTH);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+        if (t + d < nk) multiply(d);
+        if (t + d + DEPTH < nk) load(d, t + d + DEPTH);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d)
+        if (t + d + DEPTH < nk) multiply(d);
 
     // Partial sums to LDS.  A 16 x 16 fragment has its lane (token l % 16, n quad q = l / 16) in slot
     // 16 q + (token + 4 nb + q) % 16: free of bank conflicts for this store and for the reads below.
@@ -1471,22 +1527,23 @@ __global__ __launch_bounds__(W * 64) void k_gemm_i8_direct(const GemmArgs a, con
     }
     lds_barrier();
     uint32_t mx[4] = {0, 0, 0, 0};
-    for (int mt = m0; mt < TMB * 16; mt += MSTEP) {
+    const v4i cn = cn_raw - a.cn_bias;
+#pragma unroll
+    for (int k = 0; k < MT; ++k) {
+        const int mt = m0 + k * MSTEP;
+        if (mt >= TMB * 16) break;
         const int nb = nq >> 2, q = nq & 3, j = mt >> 4, m = tile_m * TMB * 16 + mt;
         const v4i *src = part + (nb * TMB + j) * 64 + q * 16 + (((mt & 15) + 4 * nb + q) & 15);
         v4i sum = src[0];
 #pragma unroll
         for (int w = 1; w < W; ++w) sum += src[w * FRAGS * 64];
         if (!n_in || m >= a.M) continue;
-        const int tok = a.x_per_token ? m : 0;
-        if (a.cn != nullptr) sum -= cn * a.zero_point[tok];
-        const float sx = a.x_scale[tok];
-        const float swv[4] = {sw.x, sw.y, sw.z, sw.w};
+        if (a.cn != nullptr) sum -= cn * zv[k];
         f16x4 out;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            float y = (sx * swv[i]) * (float)sum[i];      // Eq. 3
-            if (a.bias != nullptr) y = y + (float)bias[i];
+            float y = (sxv[k] * swv[i]) * (float)sum[i];  // Eq. 3
+            if (a.bias != nullptr) y = y + (float)__builtin_bit_cast(_Float16, bias[i]);
             out[i] = (_Float16)y;
             if (a.gelu) {
                 out[i] = (_Float16)gelu_tanh_f32((float)out[i]);
