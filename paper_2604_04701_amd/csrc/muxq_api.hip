@@ -321,10 +321,10 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
     g.aux_own_scale = aux_own;
     g.wg_ticks = (long long *)wg_ticks;
     g.gelu = gelu;
-    // the column maxima of the output, for the next layer: from the GEMM's own tiles when its
-    // form takes them and it has at most kMaxSlabs rows of tiles, else by a pass over Y
+    // the column maxima of the output, for the next layer: from the GEMM's own tiles when
+    // there are at most kMaxSlabs rows of tiles, else by a pass over Y
     const int tile_rows = muxq::gemm_tile_rows(M, N, k_pad);
-    const bool slabs_from_gemm = next_count > 0 && !next_hits_gemm && tile_rows > 0 &&
+    const bool slabs_from_gemm = next_count > 0 && !next_hits_gemm &&
                                  (M + tile_rows - 1) / tile_rows <= muxq::kMaxSlabs;
     if (slabs_from_gemm) {
         g.slab_out = (uint16_t *)next_slabs;
@@ -656,7 +656,7 @@ int muxq_linear_gelu_slabs(int M, int K, int N)
 {
     if (check_dims(M, K, N)) return 0;
     const int tile_rows = muxq::gemm_tile_rows(M, N, kpad(K));
-    if (tile_rows > 0 && (M + tile_rows - 1) / tile_rows <= muxq::kMaxSlabs) return (M + tile_rows - 1) / tile_rows;
+    if ((M + tile_rows - 1) / tile_rows <= muxq::kMaxSlabs) return (M + tile_rows - 1) / tile_rows;
     return muxq::absmax_slab_count(M, kpad(N));
 }
 

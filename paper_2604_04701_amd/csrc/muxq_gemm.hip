@@ -26,7 +26,7 @@
 // through, the epilogue removes it).  The weights are the first MFMA operand and the
 // narrow activation codes the second: the other way round draws more.
 //
-// Five kernels share that scheme:
+// Four kernels share that scheme:
 //   k_gemm_i8_persist8  256 x 256 tile, 8 waves (2 per SIMD), K step 64, one
 //                   persistent workgroup per CU.  Operand tiles go global -> LDS
 //                   directly (buffer_load_dwordx4 ... lds, no staging registers)
@@ -43,7 +43,6 @@
 //   k_gemm_i8_direct  small tiles (16 x 16 to 64 x 64), operands from memory straight to
 //                   registers, the waves of a workgroup split K: for problems
 //                   with too few larger tiles to fill the chip.
-//   k_gemm_i8_small register-staged tiles of 64 x 64 for short K loops.
 //
 // LDS rows are 64 bytes (one K step); the four 16-byte chunks of a row are
 // XOR-swizzled with row bits so that a ds_read_b128 of 32 rows x one chunk is
@@ -266,98 +265,10 @@ __device__ __forceinline__ void store_y(const GemmArgs &a, int m, int n, v4i v)
 // n = 8 * (v / 4) + 4 * (lane / 32) + v % 4 for register v of 16, so a lane holds
 // runs of 4 channels of ONE token: stored directly, a wave instruction would
 // touch 32 rows of Y with 16 bytes each.  Instead each wave transposes its
-// fp16 results through a private LDS patch, 32 tokens at a time, and writes
-// whole rows of its sub-tile (FN * 64 contiguous bytes per token, 16 B per lane).
-// `patch` is this wave's LDS area of 32 * (FN * 64 + 16) bytes; the row padding
+// fp16 results through a private LDS patch, 32 tokens at a time, whose row padding
 // of 16 B spreads the 8-byte writes of the 32 tokens over the banks.
-template <int FN, int FM>
-__device__ __forceinline__ void epilogue(const GemmArgs &a, const v16i (&acc)[FN][FM], int m_base,
-                                         int n_base, int lane, unsigned char *patch, int sub_bias)
-{
-    constexpr int ROW_BYTES = FN * 64 + 16;
-    constexpr int LANES_PER_ROW = FN * 4;              // 16-byte pieces per row
-    constexpr int ROWS_PER_PASS = 64 / LANES_PER_ROW;
-    const int fr = lane & 31, fh = lane >> 5;
-    const bool has_bias = a.bias != nullptr;
-
-#pragma unroll
-    for (int fm = 0; fm < FM; ++fm) {
-        // this lane's token: its own activation scale in the per-token setting
-        const int m_tok = a.x_per_token ? min(m_base + fm * 32 + fr, a.M - 1) : 0;
-        const float sx = a.x_scale[m_tok];
-        // ... and its zero point: z * cn[n] comes off the accumulators (|cn| < 2^23)
-        const int negz = a.cn != nullptr ? -a.zero_point[m_tok] : 0;
-        // registers -> LDS patch [token][channel]
-#pragma unroll
-        for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int nl = fn * 32 + 8 * g + 4 * fh;
-                const int n = n_base + nl;
-                const int ns = n < a.N ? n : 0;      // N % 8 == 0: a run of 4 is in or out as a whole
-                float sc[4], bs[4] = {0.f, 0.f, 0.f, 0.f};
-                // what comes off the accumulator: z * cn[n] and the explicit part of its start value
-                int zc[4] = {-sub_bias, -sub_bias, -sub_bias, -sub_bias};
-                if (a.cn != nullptr) {
-                    const int4 c4 = *(const int4 *)(a.cn + ns);
-                    zc[0] += __mul24(c4.x, negz); zc[1] += __mul24(c4.y, negz);
-                    zc[2] += __mul24(c4.z, negz); zc[3] += __mul24(c4.w, negz);
-                }
-                if (a.w_per_channel) {
-                    const float4 w4 = *(const float4 *)(a.w_scale + ns);
-                    sc[0] = sx * w4.x; sc[1] = sx * w4.y; sc[2] = sx * w4.z; sc[3] = sx * w4.w;
-                } else {
-                    const float s = sx * a.w_scale[0];
-                    sc[0] = sc[1] = sc[2] = sc[3] = s;
-                }
-                if (has_bias) {
-                    const f16x4 b4 = *(const f16x4 *)(a.bias + ns);
-                    bs[0] = (float)b4[0]; bs[1] = (float)b4[1]; bs[2] = (float)b4[2]; bs[3] = (float)b4[3];
-                }
-                f16x4 out;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float y = sc[i] * (float)(acc[fn][fm][4 * g + i] + zc[i]);
-                    if (has_bias) y = y + bs[i];
-                    out[i] = (_Float16)y;
-                    // fused activation: on the fp16 value the layer would have stored
-                    if (a.gelu) out[i] = (_Float16)gelu_tanh_f32((float)out[i]);
-                }
-                *(f16x4 *)(patch + fr * ROW_BYTES + nl * 2) = out;
-            }
-        // LDS patch -> Y, whole rows
-#pragma unroll
-        for (int p = 0; p < 32 / ROWS_PER_PASS; ++p) {
-            const int row = p * ROWS_PER_PASS + lane / LANES_PER_ROW;
-            const int piece = lane % LANES_PER_ROW;
-            const v4i v = *(const v4i *)(patch + row * ROW_BYTES + piece * 16);
-            const int m = m_base + fm * 32 + row, n = n_base + piece * 8;
-            if (m < a.M && n < a.N) store_y<false>(a, m, n, v);
-        }
-    }
-
-    if (a.dbg_acc != nullptr) {        // raw accumulators, debugging aid: plain per-lane stores
-#pragma unroll
-        for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int n = n_base + fn * 32 + 8 * g + 4 * fh;
-#pragma unroll
-                for (int fm = 0; fm < FM; ++fm) {
-                    const int m = m_base + fm * 32 + fr;
-                    if (n >= a.N || m >= a.M) continue;
-                    v4i raw = {acc[fn][fm][4 * g], acc[fn][fm][4 * g + 1], acc[fn][fm][4 * g + 2],
-                               acc[fn][fm][4 * g + 3]};
-                    if (a.cn != nullptr)
-                        raw -= *(const v4i *)(a.cn + n) * a.zero_point[a.x_per_token ? m : 0];
-                    raw -= sub_bias;
-                    *(v4i *)(a.dbg_acc + (size_t)m * a.N + n) = raw;
-                }
-            }
-    }
-}
-
-// Epilogue of the persistent kernel, with a smaller patch: the wave's LDS patch
+//
+// Epilogue of the persistent kernels: the wave's LDS patch
 // holds 32 tokens x 64 channels (two fragments), so a tile's epilogue runs
 // FM x FN/2 rounds of { 8 ds_write_b64, 4 ds_read_b128, 4 stores of 8 rows x 128 B }.
 // Exactly FM * (FN / 2) * 4 store instructions are issued for a tile, partial or not.
@@ -1076,268 +987,6 @@ __global__ __launch_bounds__(256, EPI == kEpiAny ? 2 : 1) void k_gemm_i8_persist
 #if MUXQ_GEMM_PART == 0
 
 // --------------------------------------------------------------------------
-// Small tiles (64 x 64), 4 waves, register staging.
-// --------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_gemm_i8_small(const GemmArgs a, const TileMap tm)
-{
-    fetch_arguments();
-    constexpr int TN = 64, TM = 64, WN = 2, WM = 2, NT = 256, CH = BK / 16, SWZ = 1;
-    constexpr int FN = TN / WN / 32, FM = TM / WM / 32;
-    constexpr int ROWS_PER_PASS = NT / CH;
-    constexpr int W_LD = TN / ROWS_PER_PASS, X_LD = TM / ROWS_PER_PASS;
-    constexpr int BUF_BYTES = (TN + TM) * BK;
-    __shared__ __attribute__((aligned(16))) unsigned char lds[2 * BUF_BYTES];
-
-    int tile_m, tile_n;
-    if (!tile_of_workgroup(tm, tile_m, tile_n)) return;
-    const int m0 = tile_m * TM, n0 = tile_n * TN;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wave_n = (wave % WN) * (TN / WN), wave_m = (wave / WN) * (TM / WM);
-    const int t_aux = aux_tiles(a);
-    const int t_all = t_aux + a.k_pad / BK;
-    // where the accumulators start (see kCnBias), and what the Aux weighting has to take off
-    const int fold_bias = (a.cn != nullptr && !a.x_per_token) ? a.zero_point[0] * a.cn_bias : 0;
-    const int sub_bias = fold_bias != 0 ? 0 : kAccBias;    // comes off by itself (see kAccBias)
-    const int acc_bias = fold_bias + sub_bias, acc_fix = ((1 << a.exp_shift) - 2) * acc_bias;
-    const float rho = aux_rho(a);
-
-    const int ld_chunk = tid % CH, ld_row = tid / CH;
-    int w_row[W_LD], x_row[X_LD], w_lds[W_LD], x_lds[X_LD];
-#pragma unroll
-    for (int i = 0; i < W_LD; ++i) {
-        int r = ld_row + i * ROWS_PER_PASS;
-        w_row[i] = min(n0 + r, a.N - 1);
-        w_lds[i] = r * BK + swizzle<SWZ>(r, ld_chunk) * 16;
-    }
-#pragma unroll
-    for (int i = 0; i < X_LD; ++i) {
-        int r = ld_row + i * ROWS_PER_PASS;
-        x_row[i] = min(m0 + r, a.M - 1);
-        x_lds[i] = TN * BK + r * BK + swizzle<SWZ>(r, ld_chunk) * 16;
-    }
-    v4i stage_w[W_LD], stage_x[X_LD];
-#define MUXQ_LOAD_TILE(t_)                                                                   \
-    do {                                                                                     \
-        const int tt_ = (t_);                                                                \
-        const bool aux_ = tt_ < t_aux;                                                       \
-        const int8_t *wp_ = aux_ ? a.w_aux : a.w_q;                                          \
-        const int8_t *xp_ = aux_ ? a.aux_q : a.a_q;                                          \
-        const size_t rb_ = (size_t)((aux_ ? a.r_cap : a.k_pad) / BK) * 1024; /* 16 packed rows */ \
-        const size_t k0_ = (size_t)(aux_ ? tt_ : tt_ - t_aux) * 1024 + ld_chunk * 16;        \
-        _Pragma("unroll") for (int i = 0; i < W_LD; ++i)                                     \
-            stage_w[i] = *(const v4i *)(wp_ + (size_t)(w_row[i] >> 4) * rb_ +                \
-                                        (w_row[i] & 15) * 64 + k0_);                         \
-        _Pragma("unroll") for (int i = 0; i < X_LD; ++i)                                     \
-            stage_x[i] = *(const v4i *)(xp_ + (size_t)(x_row[i] >> 4) * rb_ +                \
-                                        (x_row[i] & 15) * 64 + k0_);                         \
-    } while (0)
-#define MUXQ_STORE_TILE(buf_)                                                                \
-    do {                                                                                     \
-        unsigned char *sb_ = lds + (buf_) * BUF_BYTES;                                       \
-        _Pragma("unroll") for (int i = 0; i < W_LD; ++i) *(v4i *)(sb_ + w_lds[i]) = stage_w[i]; \
-        _Pragma("unroll") for (int i = 0; i < X_LD; ++i) *(v4i *)(sb_ + x_lds[i]) = stage_x[i]; \
-    } while (0)
-
-    const int fr = lane & 31, fh = lane >> 5;
-    v16i acc[FN][FM];
-#pragma unroll
-    for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-        for (int fm = 0; fm < FM; ++fm)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[fn][fm][v] = acc_bias;
-
-    MUXQ_LOAD_TILE(0);
-    MUXQ_STORE_TILE(0);
-    __syncthreads();
-    for (int t = 0; t < t_all; ++t) {
-        if (t == t_aux && t_aux > 0) {
-            if (a.aux_own_scale && a.x_per_token) {
-                float rho_t[FM];
-#pragma unroll
-                for (int fm = 0; fm < FM; ++fm)
-                    rho_t[fm] = aux_rho_tok(a)[min(m0 + wave_m + fm * 32 + (lane & 31), a.M - 1)];
-                scale_acc_rho_tok<FN, FM>(acc, rho_t, acc_bias);
-            } else if (a.aux_own_scale) scale_acc_rho<FN, FM>(acc, rho, acc_bias);
-            else scale_acc<FN, FM>(acc, a.exp_shift, acc_fix);
-        }
-        MUXQ_LOAD_TILE(min(t + 1, t_all - 1));   // the last tile re-reads itself, unused
-        __builtin_amdgcn_sched_barrier(0);       // keep the prefetch ahead of the MFMAs
-        const unsigned char *base = lds + (t & 1) * BUF_BYTES;
-#pragma unroll
-        for (int kk = 0; kk < BK / 32; ++kk) {
-            v4i wf[FN], xf[FM];
-#pragma unroll
-            for (int fn = 0; fn < FN; ++fn) {
-                int r = wave_n + fn * 32 + fr;
-                wf[fn] = *(const v4i *)(base + r * BK + swizzle<SWZ>(r, kk * 2 + fh) * 16);
-            }
-#pragma unroll
-            for (int fm = 0; fm < FM; ++fm) {
-                int r = wave_m + fm * 32 + fr;
-                xf[fm] = *(const v4i *)(base + TN * BK + r * BK + swizzle<SWZ>(r, kk * 2 + fh) * 16);
-            }
-#pragma unroll
-            for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-                for (int fm = 0; fm < FM; ++fm)
-                    acc[fn][fm] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[fn], xf[fm],
-                                                                        acc[fn][fm], 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        MUXQ_STORE_TILE((t + 1) & 1);
-        __syncthreads();
-    }
-#undef MUXQ_LOAD_TILE
-#undef MUXQ_STORE_TILE
-    // (the loop ends on a barrier: every wave is done with the operand tiles)
-    static_assert(4 * 32 * (FN * 64 + 16) <= 2 * BUF_BYTES, "epilogue patch does not fit");
-    epilogue<FN, FM>(a, acc, m0 + wave_m, n0 + wave_n, lane, lds + wave * (32 * (FN * 64 + 16)), sub_bias);
-}
-
-// --------------------------------------------------------------------------
-// The same tiles for problems with no more tiles than CUs.  Those are bound by memory round
-// trips, not by bytes or MFMAs (a kernel starts with cold caches, and a load that something
-// waits for costs 0.5-2 us): the operand loads of CS K steps are issued together and wait in
-// registers while the previous CS steps are computed out of LDS, so the loop waits once per CS
-// steps instead of once per step.  It costs registers and LDS (two workgroups per CU), which
-// is why problems with several workgroups per CU keep the kernel above.
-// --------------------------------------------------------------------------
-template <int CS>
-__global__ __launch_bounds__(256) void k_gemm_i8_small_deep(const GemmArgs a, const TileMap tm)
-{
-    fetch_arguments();
-    constexpr int TN = 64, TM = 64, WN = 2, WM = 2, NT = 256, CH = BK / 16, SWZ = 1;
-    constexpr int FN = TN / WN / 32, FM = TM / WM / 32;
-    constexpr int ROWS_PER_PASS = NT / CH;
-    constexpr int W_LD = TN / ROWS_PER_PASS, X_LD = TM / ROWS_PER_PASS;
-    constexpr int STEP_BYTES = (TN + TM) * BK;
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];     // CS * STEP_BYTES
-
-    int tile_m, tile_n;
-    if (!tile_of_workgroup(tm, tile_m, tile_n)) return;
-    const int m0 = tile_m * TM, n0 = tile_n * TN;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wave_n = (wave % WN) * (TN / WN), wave_m = (wave / WN) * (TM / WM);
-    const int t_aux = aux_tiles(a);
-    const int t_all = t_aux + a.k_pad / BK;
-    const int n_chunks = (t_all + CS - 1) / CS;
-    // where the accumulators start (see kCnBias), and what the Aux weighting has to take off
-    const int fold_bias = (a.cn != nullptr && !a.x_per_token) ? a.zero_point[0] * a.cn_bias : 0;
-    const int sub_bias = fold_bias != 0 ? 0 : kAccBias;    // comes off by itself (see kAccBias)
-    const int acc_bias = fold_bias + sub_bias, acc_fix = ((1 << a.exp_shift) - 2) * acc_bias;
-    const float rho = aux_rho(a);
-
-    const int ld_chunk = tid % CH, ld_row = tid / CH;
-    int w_row[W_LD], x_row[X_LD], w_lds[W_LD], x_lds[X_LD];
-#pragma unroll
-    for (int i = 0; i < W_LD; ++i) {
-        int r = ld_row + i * ROWS_PER_PASS;
-        w_row[i] = min(n0 + r, a.N - 1);
-        w_lds[i] = r * BK + swizzle<SWZ>(r, ld_chunk) * 16;
-    }
-#pragma unroll
-    for (int i = 0; i < X_LD; ++i) {
-        int r = ld_row + i * ROWS_PER_PASS;
-        x_row[i] = min(m0 + r, a.M - 1);
-        x_lds[i] = TN * BK + r * BK + swizzle<SWZ>(r, ld_chunk) * 16;
-    }
-    v4i stage_w[CS][W_LD], stage_x[CS][X_LD];
-    // the K steps [c * CS, c * CS + CS) of the tile (Aux steps first; past the end the last
-    // step is read again, unused) -> registers
-    auto load_chunk = [&](int c) {
-#pragma unroll
-        for (int sl = 0; sl < CS; ++sl) {
-            const int tt = min(c * CS + sl, t_all - 1);
-            const bool aux = tt < t_aux;
-            const int8_t *wp = aux ? a.w_aux : a.w_q;
-            const int8_t *xp = aux ? a.aux_q : a.a_q;
-            const size_t rb = (size_t)((aux ? a.r_cap : a.k_pad) / BK) * 1024;   // 16 packed rows
-            const size_t k0 = (size_t)(aux ? tt : tt - t_aux) * 1024 + ld_chunk * 16;
-#pragma unroll
-            for (int i = 0; i < W_LD; ++i)
-                stage_w[sl][i] = *(const v4i *)(wp + (size_t)(w_row[i] >> 4) * rb + (w_row[i] & 15) * 64 + k0);
-#pragma unroll
-            for (int i = 0; i < X_LD; ++i)
-                stage_x[sl][i] = *(const v4i *)(xp + (size_t)(x_row[i] >> 4) * rb + (x_row[i] & 15) * 64 + k0);
-        }
-    };
-    auto store_chunk = [&]() {
-#pragma unroll
-        for (int sl = 0; sl < CS; ++sl) {
-            unsigned char *sb = lds + sl * STEP_BYTES;
-#pragma unroll
-            for (int i = 0; i < W_LD; ++i) *(v4i *)(sb + w_lds[i]) = stage_w[sl][i];
-#pragma unroll
-            for (int i = 0; i < X_LD; ++i) *(v4i *)(sb + x_lds[i]) = stage_x[sl][i];
-        }
-    };
-
-    const int fr = lane & 31, fh = lane >> 5;
-    v16i acc[FN][FM];
-#pragma unroll
-    for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-        for (int fm = 0; fm < FM; ++fm)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[fn][fm][v] = acc_bias;
-
-    load_chunk(0);
-    store_chunk();
-    __syncthreads();
-    for (int c = 0; c < n_chunks; ++c) {
-        const bool more = c + 1 < n_chunks;
-        if (more) load_chunk(c + 1);
-        __builtin_amdgcn_sched_barrier(0);       // keep the prefetch ahead of the MFMAs
-#pragma unroll
-        for (int sl = 0; sl < CS; ++sl) {
-            const int t = c * CS + sl;
-            if (t >= t_all) break;
-            if (t == t_aux && t_aux > 0) {
-                if (a.aux_own_scale && a.x_per_token) {
-                    float rho_t[FM];
-#pragma unroll
-                    for (int fm = 0; fm < FM; ++fm)
-                        rho_t[fm] = aux_rho_tok(a)[min(m0 + wave_m + fm * 32 + (lane & 31), a.M - 1)];
-                    scale_acc_rho_tok<FN, FM>(acc, rho_t, acc_bias);
-                } else if (a.aux_own_scale) scale_acc_rho<FN, FM>(acc, rho, acc_bias);
-                else scale_acc<FN, FM>(acc, a.exp_shift, acc_fix);
-            }
-            const unsigned char *base = lds + sl * STEP_BYTES;
-#pragma unroll
-            for (int kk = 0; kk < BK / 32; ++kk) {
-                v4i wf[FN], xf[FM];
-#pragma unroll
-                for (int fn = 0; fn < FN; ++fn) {
-                    int r = wave_n + fn * 32 + fr;
-                    wf[fn] = *(const v4i *)(base + r * BK + swizzle<SWZ>(r, kk * 2 + fh) * 16);
-                }
-#pragma unroll
-                for (int fm = 0; fm < FM; ++fm) {
-                    int r = wave_m + fm * 32 + fr;
-                    xf[fm] = *(const v4i *)(base + TN * BK + r * BK + swizzle<SWZ>(r, kk * 2 + fh) * 16);
-                }
-#pragma unroll
-                for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-                    for (int fm = 0; fm < FM; ++fm)
-                        acc[fn][fm] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[fn], xf[fm],
-                                                                            acc[fn][fm], 0, 0, 0);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();                         // every wave is done with the tiles in LDS
-        if (more) {
-            store_chunk();
-            __syncthreads();
-        }
-    }
-    // (the loop ends on a barrier: every wave is done with the operand tiles)
-    static_assert(4 * 32 * (FN * 64 + 16) <= CS * STEP_BYTES, "epilogue patch does not fit");
-    epilogue<FN, FM>(a, acc, m0 + wave_m, n0 + wave_n, lane, lds + wave * (32 * (FN * 64 + 16)), sub_bias);
-}
-
-// --------------------------------------------------------------------------
 // Problems with too few tiles for the forms above: 16 TNB x 16 TMB tiles, and the waves of a
 // workgroup split K.  A block of the packed layout (16 rows x 64 codes, 1 KiB) is one operand of
 // v_mfma_i32_16x16x64_i8 as it lies there -- lane l takes the 16 bytes of row l % 16 at 16 (l / 16)
@@ -1727,9 +1376,6 @@ persist_kernel_t persist_kernel(int tile, int kind, int epi, int store)
                                           : persist_kernel_of_part<0>(tile, kind, epi, store));
 }
 
-// K steps whose loads a workgroup of k_gemm_i8_small_deep issues together (64 staging registers,
-// 64 KiB of LDS).
-constexpr int kDeepSteps = 8;
 
 // What the launcher needs to know about a device, found once per device (gemm_prepare_device).
 constexpr int kMaxDevices = 64;
@@ -1769,9 +1415,6 @@ hipError_t prepare_current_device(int dev)
     std::lock_guard<std::mutex> lock(g_prepare_mutex);
     if (g_device_cus[dev].load(std::memory_order_acquire) != 0) return hipSuccess;
     hipError_t e;
-    e = hipFuncSetAttribute((const void *)k_gemm_i8_small_deep<kDeepSteps>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kDeepSteps * 128 * BK);
-    if (e != hipSuccess) return e;
     if ((e = few_prepare_device()) != hipSuccess) return e;
     int cus = 0;
     if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
@@ -1821,19 +1464,6 @@ hipError_t launch_persist(const GemmArgs &a, hipStream_t s)
     return launch_kernel(kern, dim3(grid), dim3(waves_of(TILE) * 64), lds_bytes, s, a, tm);
 }
 
-hipError_t launch_small(const GemmArgs &a, hipStream_t s)
-{
-    int grid;
-    const TileMap tm = make_tile_map(a, 64, 64, grid);
-    int n_cu = 0, dev = 0;                    // (prepares the device on first use: LDS attribute)
-    const hipError_t e = current_device_cus(n_cu, dev);
-    if (e != hipSuccess) return e;
-    if ((long)tm.tiles_m * tm.tiles_n <= n_cu)
-        return launch_kernel(k_gemm_i8_small_deep<kDeepSteps>, dim3(grid), dim3(256),
-                             kDeepSteps * 128 * BK, s, a, tm);
-    return launch_kernel(k_gemm_i8_small, dim3(grid), dim3(256), 0, s, a, tm);
-}
-
 template <int TNB, int TMB, int DEPTH, int W>
 hipError_t launch_direct(const GemmArgs &a, hipStream_t s)
 {
@@ -1861,20 +1491,25 @@ hipError_t gemm_prepare_all()
 }
 
 enum GemmForm {
-    kSmall64,         // register-staged 64 x 64
     kPersist128, kPersist256, kPersistHalf,
     kDirect16x16, kDirect16x32, kDirect32x32, kDirect32x64, kDirect64x64       // channels x tokens
 };
 
 // Which form runs a shape fastest was measured over 289 shapes (M up to 16384, K 256..5120, N 256..16384,
 // each form forced in turn).  us per call, by form:
-//   32 x 768 -> 2304     16x32 4.1,  32x32 4.7,  small 7.8,  persistent 128 9.3
-//   24 x 5120 -> 1280    16x16 5.3,  16x32 6.0,  32x32 8.2,  small 24.0,  persistent 128 27.6
-//   512 x 1024 -> 1024   32x32 6.4,  32x64 6.6,  64x64 8.4,  small 9.3,  persistent 128 10.0
-//   512 x 4096 -> 1024   32x64 9.0,  32x32 10.2,  64x64 12.1,  small 20.5,  persistent 128 23.3
-//   1024 x 4096 -> 1024  64x64 12.3,  32x64 14.7,  persistent 128 22.5
-//   512 x 1024 -> 3072   persistent 128 10.4,  small 10.8,  32x32 13.0,  64x64 15.7
-//   1024 x 320 -> 1000   small 6.2,  64x64 8.2,  persistent 128 8.9
+//   24 x 5120 -> 1280    16x16 5.3,  16x32 6.0,  32x32 8.2,  persistent 128 27.6
+//   32 x 768 -> 2304     16x32 4.1,  32x32 4.7,  persistent 128 9.3
+// and since the direct forms' requests no longer wait, as whole calls:
+//   128 x 1024 -> 4096   32x32 14.6,  32x64 14.3,  64x64 15.7,  16x32 16.2,  persistent 128 17.5
+//   512 x 1024 -> 1024   32x32 14.8,  32x64 14.7,  64x64 15.7,  persistent 128 17.8
+//   768 x 768 -> 768     64x64 16.1,  32x32 17.3,  persistent 128 17.5
+//   512 x 4096 -> 1024   32x64 18.7,  32x32 20.1,  64x64 21.1,  persistent 128 31.1
+//   512 x 1024 -> 2048   64x64 15.9,  persistent 128 18.2,  32x32 19.0
+//   1024 x 512 -> 1024   64x64 15.6,  persistent 128 16.4,  32x32 18.8
+//   400 x 256 -> 2560    persistent 128 14.8,  64x64 20.1,  32x32 20.3
+//   512 x 1024 -> 3072   persistent 128 18.4,  64x64 21.9,  32x32 23.0
+// (a form with 64 x 64 tiles staged through registers, which was the choice up to K = 512, is 3 to 14 % slower than the
+// better of these on all of 31 shapes with K from 8 to 512, and gone)
 //
 // off_lines: rows of Y off 64-byte boundaries, no GELU (it matters for the tiles of 256 tokens alone, whose slabs are the same)
 static GemmForm gemm_form(int M, int N, int k_pad, bool off_lines = false)
@@ -1887,14 +1522,9 @@ static GemmForm gemm_form(int M, int N, int k_pad, bool off_lines = false)
     const bool short_k = k_pad <= 1536;
     if (!short_k && tiles(16, 16) <= 256) return kDirect16x16;
     if (tiles(16, 32) <= (short_k ? 320 : 256)) return kDirect16x32;
-    if (k_pad <= 512) {
-        if (t64 <= 96) return kDirect32x32;
-        if (t128 <= 192) return kSmall64;       // a few K steps: the ring of the persistent forms hides nothing
-    } else {
-        if (tiles(32, 32) <= (short_k ? 800 : 256)) return kDirect32x32;
-        if (!short_k && tiles(32, 64) <= 256) return kDirect32x64;
-        if (t64 <= 256) return kDirect64x64;
-    }
+    if (tiles(32, 32) <= (short_k ? 512 : 256)) return kDirect32x32;
+    if (!short_k && tiles(32, 64) <= 256) return kDirect32x64;
+    if (t64 <= 256) return kDirect64x64;
     // A round of 256 tiles of 256 x 256 takes as long as three of 256 tiles of 128 x 128 (1024 channels:
     // 20-23 us and 5.3 us + 5.3 us each; the ratio holds from K = 768 to 5120), so the larger tile
     // wins where its last round is full enough: 8192 x 1024 -> 1024 14 us against 19 us,
@@ -1936,8 +1566,8 @@ int gemm_tile_rows(int M, int N, int k_pad)
     case kDirect64x64: case kDirect32x64: return 64;
     case kDirect32x32: case kDirect16x32: return 32;
     case kDirect16x16: return 16;
-    default: return 0;
     }
+    return 0;
 }
 
 const char *gemm_kernel_name(int M, int N, int k_pad)
@@ -1946,7 +1576,6 @@ const char *gemm_kernel_name(int M, int N, int k_pad)
     case kPersist256: return "k_gemm_i8_persist8";
     case kPersist128: return "k_gemm_i8_persist4";
     case kPersistHalf: return "k_gemm_i8_persist_half";
-    case kSmall64: return "k_gemm_i8_small";
     default: return "k_gemm_i8_direct";
     }
 }
@@ -1963,8 +1592,8 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
     case kDirect32x32: return launch_direct<2, 2, 6, 4>(a, s);
     case kDirect32x64: return launch_direct<2, 4, 6, 4>(a, s);
     case kDirect64x64: return launch_direct<4, 4, 4, 4>(a, s);
-    default: return launch_small(a, s);
     }
+    return hipErrorInvalidValue;
 }
 
 #endif  // MUXQ_GEMM_PART == 0

@@ -170,7 +170,7 @@ struct GemmArgs {
     int w_per_channel;
     int x_per_token;        // one activation scale per row of a_q (per-vector setting)
     int gelu;               // the layer's output goes through the tanh GELU: Y = fp16(gelu(fp16(y)))
-    uint16_t *slab_out;     // with gelu, not the register-staged form, or nullptr: workgroups write the
+    uint16_t *slab_out;     // with gelu, or nullptr: workgroups write the
                             // column maxima |Y| of their tile, fp16 bits, to
                             // slab_out[tile_m][n] (row stride slab_ld, zeros for n >= N): the slab
                             // maxima the next layer's selection step folds
@@ -382,13 +382,12 @@ hipError_t launch_wquant_strip(const void *w_fp16, int K, int N, int ldw, int k_
 hipError_t launch_wscale_finalize(float *w_scale, int n, float qmax, hipStream_t s);
 
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s);
-// Rows per output tile of the form launch_gemm picks for this problem, or 0 when it picks the
-// register-staged form (which does not write slab_out).
+// Rows per output tile of the form launch_gemm picks for this problem.
 int gemm_tile_rows(int M, int N, int k_pad);
 const char *gemm_kernel_name(int M, int N, int k_pad);
 
 // Per-device set-up of the GEMM kernels for the CURRENT device: the CU count the persistent kernels' grid is
-// sized by, the LDS attributes of the small and few-token kernels.  Thread-safe, idempotent, and
+// sized by, the LDS attributes of the few-token kernels.  Thread-safe, idempotent, and
 // NOT to be called under capture (it queries the device and sets function attributes).
 // launch_gemm calls it itself when the current device has not been prepared yet, and sets the LDS attribute of a
 // persistent kernel before that kernel's first launch.
