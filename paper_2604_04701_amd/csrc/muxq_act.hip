@@ -343,9 +343,10 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_select(const ActArgs a
         sx = sh.sx;
         inv = sh.inv;
         z = sh.z;
+        if (tid < CA && store_share(wave))
+            store_selection(sel, mx, tid, C, CA, a.r_cap, true, inv, shrink, a.col_absmax, a.col_scale, a.col_slot, a.col_mask, a.idx);
         if (blockIdx.x == 0) {
-            store_selection(sel, mx, tid, C, CA, true, a.r_cap, true, inv, shrink, a.col_absmax, a.col_scale, a.col_slot,
-                            a.col_mask, a.idx, a.n_outliers);
+            store_list_rest(sel, a.r_cap, a.idx, a.n_outliers);
             if (tid == 0) {
                 a.x_scale[0] = sx;
                 a.x_scale[1] = inv;
@@ -443,9 +444,11 @@ __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
     const float shrink = __uint_as_float((uint32_t)(127 - a.exp) << 23);  // 2^-exp
     uint4 mx;
     const Selected sel = act_select<!STATIC, false>(a, sh, shrink, mx, load_first);
-    if (blockIdx.x == 0 && !STATIC)
-        store_selection(sel, mx, tid, C, CA, true, a.r_cap, false, 0.f, shrink, a.col_absmax, a.col_scale, a.col_slot,
-                        a.col_mask, a.idx, a.n_outliers);
+    if (!STATIC) {
+        if (tid < CA && store_share(wave))
+            store_selection(sel, mx, tid, C, CA, a.r_cap, false, 0.f, shrink, a.col_absmax, a.col_scale, a.col_slot, a.col_mask, a.idx);
+        if (blockIdx.x == 0) store_list_rest(sel, a.r_cap, a.idx, a.n_outliers);
+    }
     const int used = __builtin_amdgcn_readfirstlane(sel.used);       // (the same in every lane)
     const ActGather g = gather_request(a, sh, blockIdx.x * 64 + (tid >> 4), used);
     // magnitudes of the unlisted channels of each chunk (the parts of the fold have been read)

@@ -32,15 +32,16 @@ namespace {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kFewThreads = 1024, kFewWaves = kFewThreads / 64;
-constexpr int kFewMaxK = 8 * kFewThreads;                    // one 8-channel chunk per thread in the selection
+constexpr int kFewMaxWaves = 16;                             // of a workgroup, see few_waves
+constexpr int kFewMaxK = 8 * 64 * kFewMaxWaves;              // one 8-channel chunk per thread in the selection
 constexpr int kFewMaxM = 64;
 // Weight blocks of a wave, all in registers, by 16-row blocks of tokens: enough for the K that
 // few_tokens_fit lets through.  (Eight for all of them made the forms above 16 tokens spill to scratch.)
-constexpr int few_loads(int row_blocks) { return row_blocks == 1 ? kFewMaxK / 64 / kFewWaves : row_blocks == 2 ? 3 : 1; }
+constexpr int few_loads(int row_blocks) { return row_blocks == 1 ? kFewMaxK / 64 / kFewMaxWaves : row_blocks == 2 ? 3 : 1; }
 
 // What the kernel needs besides FewArgs, worked out on the host: the division of its waves and LDS.
 struct FewPlan {
+    int waves;               // of a workgroup
     int pieces, groups;      // a row of X is `pieces` pieces of 64 chunks (8 channels each); rows in flight at once
     int div;                 // wave / pieces == wave * div >> 16
     int share_parts, share_len;          // codes for the caller: a row in so many parts of so many 16-byte units
@@ -48,11 +49,12 @@ struct FewPlan {
     int cut;                 // the threshold, see chunk_candidates
 };
 
-FewPlan few_plan(int M, int K, int k_pad, int r_cap, int grid)
+FewPlan few_plan(int M, int K, int k_pad, int r_cap, int grid, int waves)
 {
     FewPlan P;
+    P.waves = waves;
     P.pieces = (k_pad / 8 + 63) / 64;
-    P.groups = kFewWaves / P.pieces;
+    P.groups = waves / P.pieces;
     P.div = 65536 / P.pieces + 1;
     P.share_parts = grid / M > 1 ? grid / M : 1;
     const int units = k_pad / 16;
@@ -65,7 +67,7 @@ FewPlan few_plan(int M, int K, int k_pad, int r_cap, int grid)
     P.idx = off;   off += r_cap * 4;                         // the list
     // partial column maxima, before there are codes or sums
     P.part = P.codes;
-    if (P.part + kFewThreads * 16 > off) off = P.part + kFewThreads * 16;
+    if (P.part + waves * 1024 > off) off = P.part + waves * 1024;
     P.total = off;
     return P;
 }
@@ -84,20 +86,21 @@ __device__ __forceinline__ int few_code_pos(int row, int col, int M, int cols)
 // (Loops over rows are kept rolled: a kernel starts with a cold instruction cache, and straight-line
 // code for eight rows takes longer to fetch than to run.)
 template <int MB, bool TOKEN>
-__global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, const FewPlan L)
+__global__ __launch_bounds__(kFewMaxWaves * 64) void k_linear_few(const FewArgs a, const FewPlan L)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     typedef __attribute__((address_space(3))) void *lptr_t;
     constexpr int LOADS = few_loads(MB);
-    __shared__ __attribute__((aligned(16))) int s_tot[kFewWaves];       // (each row group selects for itself)
-    __shared__ __attribute__((aligned(16))) uint32_t s_max[kFewWaves];
-    __shared__ uint32_t s_row[kFewMaxM * kFewWaves];     // per token: the maxima of a row's pieces
+    __shared__ __attribute__((aligned(16))) int s_tot[kFewMaxWaves];
+    __shared__ __attribute__((aligned(16))) uint32_t s_max[kFewMaxWaves];
+    __shared__ uint32_t s_row[kFewMaxM * kFewMaxWaves];     // per token: the maxima of a row's pieces
     __shared__ float s_sx[kFewMaxM], s_inv[kFewMaxM];
     __shared__ int s_z[kFewMaxM];
     __shared__ uint32_t s_pick[kFewMaxK / 8];            // per chunk: which channels are listed, rank of the first << 8
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int M = a.M, K = a.K, k_pad = a.k_pad, N = a.N, r_cap = a.r_cap;
+    const int W = L.waves, threads = W * 64;
     unsigned char *const codes = lds + L.codes;
     unsigned char *const aux = lds + L.aux;
     unsigned char *const waux = lds + L.waux;
@@ -139,7 +142,7 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
         const int8_t *src = a.w_q + (size_t)nblock * k_pad * 16 + ln * 64 + lq * 16;
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
-            const int kb = wave + i * kFewWaves;
+            const int kb = wave + i * W;
             if (kb < KB) w[i] = *(const v4i *)(src + (size_t)kb * 1024);
         }
     };
@@ -172,7 +175,7 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
     if (want_max && a.slabs == nullptr) {
         if (in_c)
             for (int row = row0; row < M; row += P) mx = absmax_step(mx, *(const uint4 *)(xc + row * K * 2));
-        if (P > 1) {                                     // the row groups' parts meet
+        if (min(P, M) > 1) {                             // the row groups' parts meet
             uint4 *const part = (uint4 *)(lds + L.part);
             part[tid] = mx;
             lds_barrier();
@@ -189,13 +192,13 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
         listed = chunk_candidates(mx, a.threshold, L.cut);
         if (!in_c) listed = 0;
     }
-    const Selected sel = select_channels<kFewWaves>(mx, listed, holds, seg, S, r_cap, !TOKEN, s_tot, s_max);
+    const Selected sel = select_channels<kFewMaxWaves>(mx, listed, holds, seg, S, r_cap, !TOKEN, s_tot, s_max);
     const int used = sel.used;
     const uint32_t call_max = sel.maxima;
     // (the parts of the maxima, which may lie here, were read before the barriers of the selection)
-    for (int i = tid * 4; i < M * r_cap; i += kFewThreads * 4) *(uint32_t *)(aux + i) = 0u;
-    for (int i = tid * 4; i < 16 * r_cap; i += kFewThreads * 4) *(uint32_t *)(waux + i) = 0u;
-    for (int i = tid; i < n_mb * 256; i += kFewThreads) red[i] = 0;
+    for (int i = tid * 4; i < M * r_cap; i += threads * 4) *(uint32_t *)(aux + i) = 0u;
+    for (int i = tid * 4; i < 16 * r_cap; i += threads * 4) *(uint32_t *)(waux + i) = 0u;
+    for (int i = tid; i < n_mb * 256; i += threads) red[i] = 0;
     if (holds) {
         int rank = sel.first;
         for (uint32_t mm = sel.listed; mm != 0; mm &= mm - 1, ++rank) idx_lds[rank] = c * 8 + __builtin_ctz(mm);
@@ -214,12 +217,12 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
             uint4 raw[1] = {make_uint4(0, 0, 0, 0)};
             if (in_c) raw[0] = *(const uint4 *)(xc + row * K * 2);
             const uint32_t m = wave_row_maxima(raw, listed);
-            if (lane == 63) s_row[row * kFewWaves + seg] = m;
+            if (lane == 63) s_row[row * kFewMaxWaves + seg] = m;
         }
         lds_barrier();
         if (tid < M) {
             uint32_t m = 0;
-            for (int s = 0; s < S; ++s) m = pk_max_u16(m, s_row[tid * kFewWaves + s]);
+            for (int s = 0; s < S; ++s) m = pk_max_u16(m, s_row[tid * kFewMaxWaves + s]);
             float sx, iv;
             int zz;
             call_scale(m, shrink, a.qmax, sx, iv, zz);
@@ -239,7 +242,8 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
 
     // Eq. 7: the weights of the listed channels, 16 per output channel and step; on their way while
     // the codes are formed (the lines have just been read, as part of the weight blocks)
-    const int g_row = tid & 15, g_slot = tid >> 4;       // 64 slots at a time
+    const int g_row = tid & 15, g_slot = tid >> 4;       // `slots` at a time
+    const int slots = threads >> 4;
     int g_w = 0;
     auto gather_weights = [&](int nblock, int j) -> int {
         return a.w_q[(size_t)nblock * k_pad * 16 + (size_t)(idx_lds[j] >> 6) * 1024 + g_row * 64 + (idx_lds[j] & 63)];
@@ -282,18 +286,19 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
             *(uint2 *)(codes + few_code_pos(row, c * 8, M, k_pad)) = packed;
         }
     }
-    auto keep_weights = [&](int nblock) {                // -> LDS; lists beyond 64 entries: the rest directly
+    auto keep_weights = [&](int nblock) {                // -> LDS; longer lists: the rest directly
         if (g_slot < used) waux[few_code_pos(g_row, g_slot, 16, r_cap)] = (uint8_t)g_w;
-        for (int j = g_slot + 64; j < used; j += 64)
+        for (int j = g_slot + slots; j < used; j += slots)
             waux[few_code_pos(g_row, j, 16, r_cap)] = (uint8_t)gather_weights(nblock, j);
     };
     keep_weights(nb);
     // ---- the selection results, for the caller ----
-    if (blockIdx.x == 0 && want_max) {
-        store_selection(sel, mx, c, C, CA, p == 0, r_cap, !TOKEN, inv, shrink, a.col_absmax, a.col_scale, a.col_slot,
-                        a.col_mask, a.idx, a.n_outliers);
-        if (tid == 0) {
-            if (!TOKEN) {
+    if (want_max) {
+        if (holds && (MB == 1 ? blockIdx.x == 0 : store_share(seg)))         // (with few rows the first has the time)
+            store_selection(sel, mx, c, C, CA, r_cap, !TOKEN, inv, shrink, a.col_absmax, a.col_scale, a.col_slot, a.col_mask, a.idx);
+        if (blockIdx.x == 0) {
+            store_list_rest(sel, r_cap, a.idx, a.n_outliers);
+            if (tid == 0 && !TOKEN) {
                 a.x_scale[0] = sx_call;
                 a.x_scale[1] = inv;
                 a.zero_point[0] = z;
@@ -305,7 +310,7 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
     if ((int)blockIdx.x < M * L.share_parts)
         for (int row = (int)blockIdx.x % M; row < M; row += gridDim.x) {
             const int u0 = ((int)blockIdx.x / M) * L.share_len, u1 = min(k_pad / 16, u0 + L.share_len);
-            for (int u = u0 + tid; u < u1; u += kFewThreads)
+            for (int u = u0 + tid; u < u1; u += threads)
                 *(uint4 *)(a.body_q + packed_index(row, u * 16, k_pad)) = *(const uint4 *)(codes + few_code_pos(row, u * 16, M, k_pad));
             if ((int)blockIdx.x < M && tid < r_cap / 16)
                 *(uint4 *)(a.aux_q + packed_index(row, tid * 16, r_cap)) = *(const uint4 *)(aux + few_code_pos(row, tid * 16, M, r_cap));
@@ -325,7 +330,7 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
         for (int mb = 0; mb < MB; ++mb) acc[mb] = v4i{0, 0, 0, 0};
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
-            const int kb = wave + i * kFewWaves;
+            const int kb = wave + i * W;
             if (kb >= KB) break;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
@@ -346,7 +351,7 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
 
         // the Aux weight rows, for the caller (a static block has them already)
         if (a.w_aux != nullptr)
-            for (int u = tid; u < r_cap; u += kFewThreads) {       // 16 rows x r_cap / 16 pieces
+            for (int u = tid; u < r_cap; u += threads) {       // 16 rows x r_cap / 16 pieces
                 const int row = u & 15, col = u & ~15;
                 if (nb * 16 + row < N)
                     *(uint4 *)(a.w_aux + packed_index(nb * 16 + row, col, r_cap)) =
@@ -414,17 +419,32 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
             load_consts(nb + gridDim.x);
             keep_weights(nb + gridDim.x);                // (waux is consumed: the barrier above)
             if (a.next_slabs != nullptr) lds_barrier();
-            for (int i = tid; i < n_mb * 256; i += kFewThreads) red[i] = 0;
+            for (int i = tid; i < n_mb * 256; i += threads) red[i] = 0;
             lds_barrier();
         }
     }
     // the K padding of the next layer's slabs past the last 16 channels of this one
     if (a.next_slabs != nullptr && blockIdx.x == 0)
-        for (int i = nblk * 16 + tid; i < a.next_ld; i += kFewThreads)
+        for (int i = nblk * 16 + tid; i < a.next_ld; i += threads)
             for (int sl = 0; sl < a.next_count; ++sl) a.next_slabs[(size_t)sl * a.next_ld + i] = 0;
 }
 
 }  // namespace
+
+// Waves of a workgroup.  Every wave walks through the whole kernel, much of which is not divided among them (about 800
+// instructions, 4 cycles each), so with four waves on a SIMD small calls are bound by their issue.  A long K, whose weights
+// want many loads in flight, takes 16 all the same, else many rows 12 and few rows 8; whole row groups of waves, since a thread has one
+// chunk of the rows, and no more weight blocks to a wave than it has registers for.  us a call with 8 / 12 / 16: 1 x 768 -> 2304 6.8 /
+// 7.1 / 7.4, 4 x 1024 -> 1024 7.2 / 7.6 / 8.0, 8 x 1280 -> 5120 10.9 / 10.0 / 10.4, 16 x 1280 -> 3840 14.5 / 11.4 / 12.0, 20 x 2000 -> 2048
+// 13.5 / 13.6 / 13.9, 3 x 3000 -> 8000 13.7 / 12.4 / 12.4, 8 x 4096 -> 4096 13.6 / 13.6 / 12.4.
+int few_waves(int M, int k_pad)
+{
+    const int pieces = (k_pad / 8 + 63) / 64, loads = few_loads((M + 15) / 16);
+    const int want = pieces > 4 ? 16 : M * pieces <= 20 ? 8 : 12;
+    int waves = max(want / pieces, 1) * pieces;
+    while (waves * loads * 64 < k_pad) waves += pieces;
+    return min(waves, kFewMaxWaves);
+}
 
 // X and its codes have to fit LDS together (about 42 K elements); below that the line against the separate
 // launches (selecting quantiser and GEMM) lies where two things that grow here outweigh the launch
@@ -439,7 +459,7 @@ __global__ __launch_bounds__(kFewThreads) void k_linear_few(const FewArgs a, con
 // the line over N takes in.
 bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token)
 {
-    if (M > kFewMaxM || k_pad > 64 * kFewWaves * few_loads((M + 15) / 16) || few_plan(M, K, k_pad, r_cap, 1).total > kFewLdsBytes)
+    if (M > kFewMaxM || k_pad > 64 * kFewMaxWaves * few_loads((M + 15) / 16) || few_plan(M, K, k_pad, r_cap, 1, kFewMaxWaves).total > kFewLdsBytes)
         return false;
     const bool fewest = M <= 8;
     if (N > (M > 32 ? 8192 : K > 1536 ? (fewest && K > 3072 ? 32768 : 24576) : fewest && (per_token || r_cap > 64) ? 16384 : 12288))
@@ -475,9 +495,9 @@ hipError_t launch_linear_few(const FewArgs &a, hipStream_t s)
     if (e != hipSuccess) return e;
     // every workgroup repeats the activation side: no more of them than are resident at once
     const int nblk = (a.N + 15) / 16, grid = nblk < 256 ? nblk : 256;
-    FewPlan plan = few_plan(a.M, a.K, a.k_pad, a.r_cap, grid);
+    FewPlan plan = few_plan(a.M, a.K, a.k_pad, a.r_cap, grid, few_waves(a.M, a.k_pad));
     plan.cut = magnitude_cut(a.threshold);
-    return launch_kernel(few_kernel((a.M + 15) / 16, a.x_per_token != 0), dim3(grid), dim3(kFewThreads), plan.total, s,
+    return launch_kernel(few_kernel((a.M + 15) / 16, a.x_per_token != 0), dim3(grid), dim3(plan.waves * 64), plan.total, s,
                          a, plan);
 }
 

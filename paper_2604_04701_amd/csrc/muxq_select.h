@@ -239,15 +239,16 @@ __device__ __forceinline__ Selected select_channels(uint4 mx, uint32_t cand, boo
     return r;
 }
 
-// The selection results of the call as the workspace keeps them, by the threads of one workgroup
-// (one chunk each): col_absmax, col_slot, col_mask and, with one scale per call, col_scale; the list,
-// its padding and counts.
-__device__ __forceinline__ void store_selection(const Selected &r, uint4 mx, int c, int C, int CA, bool mine, int r_cap,
+// The selection results of the call as the workspace keeps them: col_absmax, col_slot, col_mask and, with one scale per
+// call, col_scale; the list, its padding and counts.  Every workgroup has them, and each stores the chunks of few
+// waves (store_share): all by one workgroup, that one ended 0.5 to 1.5 us after the others.  Called by the waves that hold
+// chunks, `c` being the thread's; the padding and counts go out from the first workgroup.
+__device__ __forceinline__ bool store_share(int seg) { return seg % (int)gridDim.x == (int)blockIdx.x; }
+__device__ __forceinline__ void store_selection(const Selected &r, uint4 mx, int c, int C, int CA, int r_cap,
                                                 bool with_scale, float inv, float shrink, float *col_absmax,
-                                                float *col_scale, int32_t *col_slot, uint8_t *col_mask, int32_t *idx,
-                                                int32_t *n_outliers)
+                                                float *col_scale, int32_t *col_slot, uint8_t *col_mask, int32_t *idx)
 {
-    if (mine && c < CA) {
+    if (c < CA) {
         int slots[8];
         int rank = r.first;
         float v[8];
@@ -276,6 +277,9 @@ __device__ __forceinline__ void store_selection(const Selected &r, uint4 mx, int
             sc[1] = make_float4(v[4], v[5], v[6], v[7]);
         }
     }
+}
+__device__ __forceinline__ void store_list_rest(const Selected &r, int r_cap, int32_t *idx, int32_t *n_outliers)
+{
     for (int j = r.used + (int)threadIdx.x; j < max(r_cap, 1); j += (int)blockDim.x) idx[j] = -1;
     if (threadIdx.x == 0) {
         n_outliers[0] = r.used;

@@ -17,7 +17,9 @@ U = (20.0, 100.0)
 
 SHAPES = [(1, 8, 8), (1, 768, 2304), (1, 8192, 520), (2, 72, 24), (15, 4096, 136), (16, 1280, 1288),
           (17, 1000, 264), (24, 5120, 264), (31, 512, 8200), (33, 136, 520), (48, 2048, 72), (64, 64, 16),
-          (64, 1024, 264)]
+          (64, 1024, 264),
+          # workgroups of 15, 14, 9 and 13 waves: a row in 5, 7, 9 and 13 pieces
+          (3, 2400, 72), (3, 3400, 264), (2, 4360, 72), (5, 6400, 136)]
 
 
 @pytest.mark.parametrize("x_gran,w_gran", [("tensor", "tensor"), ("tensor", "channel"), ("token", "channel")])
