@@ -124,7 +124,7 @@ __device__ __forceinline__ Selected act_select(const ActArgs &a, ActShared &sh, 
     const bool holds = wave < n_seg;
     mx = make_uint4(0, 0, 0, 0);
     if (WANT_MAX) {
-        const int P = quotient(kActThreads, a.by_chunks), p = quotient(tid, a.by_chunks), c = tid - p * CA;
+        const int P = quotient(a.wg_waves * 64, a.by_chunks), p = quotient(tid, a.by_chunks), c = tid - p * CA;
         const bool on = p < P && c < C && p < a.n_slabs;
         if (a.n_slabs <= P) {
             mx = fold_slabs<1>(a, c, p, P, on, load_x);
@@ -181,11 +181,11 @@ __device__ __forceinline__ Selected act_select(const ActArgs &a, ActShared &sh, 
             sh.idx[rank] = k;
         }
     }
-    if (WANT_SCALE && wave == kActWaves - 1) {           // (as a rule a wave without chunks)
+    if (WANT_SCALE && wave == a.wg_waves - 1) {           // (as a rule a wave without chunks)
         float sx, inv;
         int z;
         call_scale(r.maxima, shrink, a.qmax, sx, inv, z);
-        if (tid == kActThreads - 1) {
+        if ((tid & 63) == 0) {
             sh.sx = sx;
             sh.inv = inv;
             sh.z = z;
@@ -196,7 +196,7 @@ __device__ __forceinline__ Selected act_select(const ActArgs &a, ActShared &sh, 
 }
 
 // Eq. 7: the weight rows that meet Aux, w_aux[n][j] = w_q[n][idx[j]], and cn[n], the sum of channel n's
-// other weight codes (+ cn_bias): 16 lanes per output channel, 64 channels per workgroup and step.  The
+// other weight codes (+ cn_bias): 16 lanes per output channel, 64 channels per step of a workgroup of 16 waves.  The
 // bytes of the first step are requested before the rows of X are worked on and written after it.
 struct ActGather {
     int v[4], row_sum;
@@ -238,11 +238,11 @@ __device__ __forceinline__ void gather_finish(const ActArgs &a, const ActShared 
 }
 __device__ __forceinline__ void gather_rest(const ActArgs &a, const ActShared &sh, int used, const ActGather &first)
 {
-    const int n0 = blockIdx.x * 64 + (threadIdx.x >> 4);
+    const int per = a.wg_waves * 4, n0 = (int)blockIdx.x * per + ((int)threadIdx.x >> 4);       // channels per workgroup and step
     gather_finish(a, sh, n0, used, first);
     if (a.cn == nullptr) return;
-    for (int nb = ((int)blockIdx.x + (int)gridDim.x) * 64; nb < a.N; nb += (int)gridDim.x * 64) {     // (N in the ten thousands)
-        const int n = nb + (threadIdx.x >> 4);
+    for (int nb = ((int)blockIdx.x + (int)gridDim.x) * per; nb < a.N; nb += (int)gridDim.x * per) {    // (N in the ten thousands)
+        const int n = nb + ((int)threadIdx.x >> 4);
         gather_finish(a, sh, n, used, gather_request(a, sh, n, used));
     }
 }
@@ -257,7 +257,7 @@ __device__ __forceinline__ void store_through(int8_t *dst, uint2 codes)
 __device__ __forceinline__ void zero_aux_rest(const ActArgs &a, int used)
 {
     const int per = (a.M + (int)gridDim.x - 1) / (int)gridDim.x, r1 = min(a.M, ((int)blockIdx.x + 1) * per);
-    for (int r = (int)blockIdx.x * per + ((int)threadIdx.x >> 4); r < r1; r += kActThreads / 16)
+    for (int r = (int)blockIdx.x * per + ((int)threadIdx.x >> 4); r < r1; r += a.wg_waves * 4)
         for (int j = ((int)threadIdx.x & 15) * 4; j < a.r_cap; j += 64) {
             int8_t *const dst = a.aux_q + packed_index(r, j, a.r_cap);
             if (j >= used)
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_select(const ActArgs a
         if (tid < CA) sh.mask[tid] = 0;
         if (tid == 0) sh.amax = 0.f;
         lds_barrier();
-        for (int j = tid; j < used; j += kActThreads) {
+        for (int j = tid; j < used; j += a.wg_waves * 64) {
             const int k = a.idx[j];
             if (k >= 0 && k < a.K) {
                 sh.slot[k] = (uint16_t)j;
@@ -354,7 +354,7 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_select(const ActArgs a
             }
         }
     }
-    const ActGather g_aux = gather_request(a, sh, blockIdx.x * 64 + (tid >> 4), used);
+    const ActGather g_aux = gather_request(a, sh, (int)blockIdx.x * a.wg_waves * 4 + (tid >> 4), used);
 
     const float inv_listed = inv * shrink, magic = 12582912.0f + (float)z;
     const uint32_t mask = rb < nb && in_c ? sh.mask[c] : 0u;
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
         if (blockIdx.x == 0) store_list_rest(sel, a.r_cap, a.idx, a.n_outliers);
     }
     const int used = __builtin_amdgcn_readfirstlane(sel.used);       // (the same in every lane)
-    const ActGather g = gather_request(a, sh, blockIdx.x * 64 + (tid >> 4), used);
+    const ActGather g = gather_request(a, sh, (int)blockIdx.x * a.wg_waves * 4 + (tid >> 4), used);
     // magnitudes of the unlisted channels of each chunk (the parts of the fold have been read)
     uint4 *const s_unlisted = sh.part;
     if (tid < C) {
@@ -634,22 +634,27 @@ hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool give
     a.by_chunks = divisor(a.k_pad / 8);
     a.cut = magnitude_cut(a.threshold);
     // every workgroup selects for itself, so no more of them than are resident at once, but enough for
-    // a share of the weight side each (64 output channels)
-    const int most = 256, weight_side = a.cn != nullptr ? (a.N + 63) / 64 : 1;
-    int grid, form = 0;
+    // a share of the weight side each (4 output channels a wave)
+    const int most = 256;
+    int units, form = 0;                                 // units: what a wave takes at a time
     if (!per_token) {
         // columns of 64 channels, and as many waves as there are blocks of 8 rows in them
         const int columns = a.k_pad / 64, blocks = (a.M + 7) / 8;
-        const long long units = (long long)columns * blocks;
         a.by_pieces = divisor(columns);
-        a.waves = (int)min((long long)kActWaves, (units + most - 1) / most);
-        grid = (int)min((long long)most, max((units + a.waves - 1) / a.waves, (long long)weight_side));
-        a.groups = min(grid * a.waves / columns, blocks);
+        a.waves = (int)min((long long)kActWaves, ((long long)columns * blocks + most - 1) / most);
+        units = (int)min((long long)most * a.waves, (long long)columns * blocks);
     } else {
-        const int groups = row_form(a.M, a.k_pad, form, a.pieces, a.groups);
+        units = row_form(a.M, a.k_pad, form, a.pieces, a.groups);
         a.by_pieces = divisor(a.pieces);
-        grid = min(max((groups + a.groups - 1) / a.groups, weight_side), most);
+        a.waves = a.groups * a.pieces;
     }
+    // A workgroup of 8 waves where they are enough, for the rows, the chunks and a step of the weight side: what all waves do, the
+    // selection above all, is bound by the issue of its instructions.  us a call with 16 / 8: 100 x 2000 -> 640 13.3 / 12.3, 1024 x 768
+    // -> 3072 17.9 / 17.7, 40 x 3000 -> 3000 14.4 / 14.1; 50 x 1000 -> 16384 (two steps of the weight side) 14.9 / 16.1.
+    a.wg_waves = max(a.waves, (a.k_pad + 511) / 512) <= 8 && (a.cn == nullptr || a.N <= most * 32) ? 8 : kActWaves;
+    const int weight_side = a.cn != nullptr ? (a.N + 4 * a.wg_waves - 1) / (4 * a.wg_waves) : 1;
+    const int grid = min(max((units + (per_token ? a.groups : a.waves) - 1) / (per_token ? a.groups : a.waves), weight_side), most);
+    if (!per_token) a.groups = min(grid * a.waves / (a.k_pad / 64), (a.M + 7) / 8);
     void (*kern)(const ActArgs);
     const bool is_static = a.static_mask != nullptr;
     if (!per_token)
@@ -660,7 +665,7 @@ hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool give
         kern = is_static ? k_rows_select<4, 16, true> : k_rows_select<4, 16, false>;
     else
         kern = is_static ? k_rows_select<5, 16, true> : k_rows_select<5, 16, false>;
-    return launch_kernel(kern, dim3(grid), dim3(kActThreads), 0, s, a);
+    return launch_kernel(kern, dim3(grid), dim3(a.wg_waves * 64), 0, s, a);
 }
 
 }  // namespace muxq

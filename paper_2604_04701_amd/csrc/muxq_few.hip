@@ -5,10 +5,10 @@
 // little it does, and a GEMM kernel made of 64 x 64 or 128 x 128 output tiles leaves most CUs
 // without a tile.  So here every workgroup does the activation side of ALL rows for itself --
 // column maxima, outlier selection, codes, kept in LDS -- and then the product for 16 output
-// channels at a time.  What bounds it now: latency up to about 8 K elements of X (1 x 768 -> 2304:
-// 6.5 us inside the kernel, of which 1.6 us until X has arrived and 1.6 us selection), the vector
-// ALU work of the codes, repeated on every CU, beyond (8 x 5120: 3.1 of 10.8 us).
-// Measured, us per call, four launches with a selection kernel against this kernel: 1 x 768 -> 2304 18.8 / 8.4,
+// channels at a time.  What bounds it now: the instructions that every wave repeats and the latencies between them, up to
+// about 8 K elements of X (1 x 768 -> 2304: 4.5 us inside the kernel), the vector ALU work of the codes, repeated on
+// every CU, beyond (8 x 5120: 3 of 9.5 us).
+// Measured, us per call, four launches with a selection kernel against this kernel with 16 waves (see few_waves): 1 x 768 -> 2304 18.8 / 8.4,
 // 1 x 8192 -> 1024 49.1 / 10.1, 8 x 1280 -> 5120 -> 1280 (an MLP, two launches instead of eight)
 // 61.5 / 24.7, 16 x 2560 -> 2560 28.8 / 11.2, 2 x 4096 -> 16384 36.8 / 20.5; against the launches that
 // would run here without it, see few_tokens_fit.
@@ -22,8 +22,8 @@
 // activation side runs in the shadow of their latency.
 //
 // Everything a caller may read from the workspace afterwards (the muxq_workspace_layout regions)
-// is written as by the separate launches: the selection results by workgroup 0, the codes in
-// shares by all workgroups, w_aux and cn by the workgroup that owns the channels.
+// is written as by the separate launches: the selection results and the codes in shares by
+// the workgroups, w_aux and cn by the workgroup that owns the channels.
 #include "muxq_select.h"
 
 namespace muxq {

@@ -219,7 +219,7 @@ struct ActArgs {
     int32_t *cn;
     int32_t cn_bias;
     Divisor by_chunks, by_pieces;        // these are set by the launch
-    int pieces, groups, waves, cut;
+    int pieces, groups, waves, wg_waves, cut;
 };
 // What every workgroup of the quantisers may as well read to select for itself, in bytes: the slabs a
 // producer of X left (more are folded into one by a launch of their own first: the quantiser of an MLP's
