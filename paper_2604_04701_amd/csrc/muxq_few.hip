@@ -446,27 +446,44 @@ int few_waves(int M, int k_pad)
     return min(waves, kFewMaxWaves);
 }
 
+// Whether two workgroups share a CU where there are more blocks of 16 output channels than CUs (two of 8 waves do not hinder each other
+// much while few rows' codes are to be formed): us a call, walking over N / so: 1 x 1600 -> 6400 9.1 / 8.0, 1 x 2048 -> 16384 15.6 / 12.1,
+// 4 x 1024 -> 12288 11.4 / 9.8, 4 x 512 -> 8192 8.6 / 8.0; 8 x 512 -> 8192 8.5 / 8.8, 16 x 512 -> 8192 9.4 / 10.2.
+bool few_two_on_a_cu(int M, int waves) { return M <= 4 && waves == 8; }
+
 // X and its codes have to fit LDS together (about 42 K elements); below that the line against the separate
-// launches (selecting quantiser and GEMM) lies where two things that grow here outweigh the launch
-// saved: the walk over N, 16 channels per workgroup at a time with barriers between, and the
-// codes, which every CU forms for all rows.  us per call, the separate launches / this kernel:
-//   N      1 x 768 -> 12288 12.5 / 11.4, -> 32768 17.7 / 19.6, -> 131072 39.6 / 65.7;  8 x 4096 -> 24576 34.5 / 29.8,
-//          -> 65536 59.5 / 65.4 (a longer K gives the walk more to hide its barriers behind);  1 x 8192 -> 32768 65.9 /
-//          51.3;  64 x 248 -> 4096 12.8 / 11.5, -> 12288 14.2 / 15.6;  8 x 1280 -> 16384 per token 15.4 / 14.2
-//   codes  20 x 2000 -> 2048 12.3 / 11.0;  32 x 1000 -> 2048 11.8 / 10.7, with one scale per token 12.4 / 12.5;  32 x 1248
-//          -> 2048 11.8 / 11.7 and 13.4 / 14.3;  40 x 800 -> 4096 12.1 / 11.7 and 12.7 / 13.6;  64 x 560 -> 2048 11.6 / 13.0
-// Long lists move it the other way (8 x 1280 -> 4096, 160 channels of at most 1024 listed: 19.6 / 11.0), which only
-// the line over N takes in.
+// launches (selecting quantiser and GEMM) lies where three things that grow here outweigh the launch
+// saved: the rows that a wave works on one after the other (`turns`), which every workgroup repeats; the walk over N, 16
+// channels per workgroup at a time with barriers between, from N = 4096 on; and rows in more than one block of 16.  us per
+// call, the separate launches / this kernel:
+//   turns  8 x 768 -> 3072 9.8 / 7.9 (2), 16 x 768 9.9 / 9.3 (3), 16 x 1280 -> 1280 10.0 / 9.7 (4), 8 x 3072 -> 768 10.7 / 10.0 (4), 5 x 6000
+//          -> 1000 11.5 / 11.3 (5), 12 x 3072 -> 768 11.2 / 11.6 (6), 8 x 5120 -> 1280 11.4 / 13.3 (8); the same number costs more with
+//          many elements in it: 8 x 4096 -> 1024 10.9 / 11.1 (4).  One scale per token: 8 x 2048 11.6 / 10.8 (3), 8 x 3072 -> 768 11.5 /
+//          11.7 (4), 12 x 1600 11.7 / 13.0 (4)
+//   N      4 x 1600 -> 6400 10.6 / 10.2 (2), 12 x 1024 -> 12288 12.8 / 12.8 (2), 8 x 2048 -> 8192 11.5 / 12.2 (3); a longer K: 1 x 4096 ->
+//          8192 13.6 / 12.2 (1), 4 x 4096 -> 16384 19.1 / 21.2 (2), but 8 x 4096 -> 24576 37.4 / 32.8, 1 x 5120 -> 20480 43.2 / 33.8
+//   rows   32 x 512 -> 2048 9.9 / 9.1 (3), 17 x 1024 9.9 / 9.8 (3), 20 x 768 -> 2304 9.9 / 10.2 (4), 48 x 256 -> 1024 10.2 / 11.1, 64 x 512 ->
+//          1024 10.1 / 12.6
+// Long lists move it the other way (8 x 1280 -> 4096, 160 channels of at most 1024 listed, 19.6 / 11.0 with the separate launches of
+// before): capacities above 64 keep wider lines.
 bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token)
 {
     if (M > kFewMaxM || k_pad > 64 * kFewMaxWaves * few_loads((M + 15) / 16) || few_plan(M, K, k_pad, r_cap, 1, kFewMaxWaves).total > kFewLdsBytes)
         return false;
     const bool fewest = M <= 8;
-    if (N > (M > 32 ? 8192 : K > 1536 ? (fewest && K > 3072 ? 32768 : 24576) : fewest && (per_token || r_cap > 64) ? 16384 : 12288))
-        return false;
-    if (M <= 20) return true;
-    if (M <= 32) return M * K <= (M <= 24 ? 36 : 32) * 1024;
-    return K <= 512 ? M <= (per_token ? 48 : 64) : M <= 40 && M * K <= 32 * 1024 && !per_token;
+    if (r_cap > 64) {
+        if (N > (M > 32 ? 8192 : K > 1536 ? (fewest && K > 3072 ? 32768 : 24576) : fewest ? 16384 : 12288)) return false;
+        if (M <= 20) return true;
+        if (M <= 32) return M * K <= (M <= 24 ? 36 : 32) * 1024;
+        return K <= 512 ? M <= (per_token ? 48 : 64) : M <= 40 && M * K <= 32 * 1024 && !per_token;
+    }
+    const int pieces = (k_pad / 8 + 63) / 64, waves = few_waves(M, k_pad), at_once = waves / pieces, turns = (M + at_once - 1) / at_once;
+    if (N > 4096) {
+        if (pieces > 4) return N <= 16384 ? turns == 1 : fewest && N <= (K > 3072 ? 32768 : 24576);
+        return N <= (few_two_on_a_cu(M, waves) ? 16384 : 12288) && turns <= 2 && (!per_token || fewest);
+    }
+    if (turns <= 3) return M <= (per_token ? 24 : 32);
+    return !per_token && M <= 16 && turns <= 5 && M * K <= 30 * 1024;
 }
 
 typedef void (*few_kernel_t)(const FewArgs, const FewPlan);
@@ -494,8 +511,8 @@ hipError_t launch_linear_few(const FewArgs &a, hipStream_t s)
     const hipError_t e = gemm_prepare_device();
     if (e != hipSuccess) return e;
     // every workgroup repeats the activation side: no more of them than are resident at once
-    const int nblk = (a.N + 15) / 16, grid = nblk < 256 ? nblk : 256;
-    FewPlan plan = few_plan(a.M, a.K, a.k_pad, a.r_cap, grid, few_waves(a.M, a.k_pad));
+    const int nblk = (a.N + 15) / 16, waves = few_waves(a.M, a.k_pad), grid = min(nblk, few_two_on_a_cu(a.M, waves) ? 512 : 256);
+    FewPlan plan = few_plan(a.M, a.K, a.k_pad, a.r_cap, grid, waves);
     plan.cut = magnitude_cut(a.threshold);
     return launch_kernel(few_kernel((a.M + 15) / 16, a.x_per_token != 0), dim3(grid), dim3(plan.waves * 64), plan.total, s,
                          a, plan);

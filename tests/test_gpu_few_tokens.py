@@ -38,6 +38,17 @@ def test_few_tokens_list_capacity(r_cap, r, x_gran):
         check_case(Case("few_cap", M, 520, 136, r, U, 640 + M), r_cap=r_cap, e=e, x_gran=x_gran)
 
 
+@pytest.mark.parametrize("x_gran", ["tensor", "token"])
+@pytest.mark.parametrize("shape", [(33, 136, 520), (48, 512, 72), (64, 248, 264), (24, 1400, 136), (1, 1600, 6416), (4, 2048, 8200)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_few_tokens_long_capacity_and_many_blocks(shape, x_gran):
+    """Capacities above 64, with which more rows stay in the one launch (three and four blocks of 16 of them), and more blocks
+    of 16 output channels than CUs with few rows, for which two workgroups share a CU."""
+    M, K, N = shape
+    for r_cap in (64, 128):
+        check_case(Case("few_rows", M, K, N, min(80, K // 8), U, 690 + M), r_cap=r_cap, x_gran=x_gran, w_gran="channel", bias_seed=4)
+
+
 @pytest.mark.parametrize("x_gran,w_gran", [("tensor", "channel"), ("token", "tensor")])
 def test_few_tokens_static_lists(x_gran, w_gran):
     for M, K, N in ((1, 264, 136), (24, 5120, 72), (50, 1032, 264)):
