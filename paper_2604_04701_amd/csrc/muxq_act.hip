@@ -560,6 +560,28 @@ __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
     gather_rest(a, sh, used, g);
 }
 
+// muxq_detect_outliers: the fold and the list by themselves, one workgroup.  Bound by latency (5120 channels 5.5 -> 4.7 us against
+// the kernel that also leaves what the separate quantisers read).
+__global__ __launch_bounds__(kActThreads) void k_detect_select(const ActArgs a)
+{
+    __shared__ ActShared sh;
+    const int tid = threadIdx.x;
+    uint4 mx;
+    const Selected sel = act_select<true, false>(a, sh, 1.f, mx, [] {});
+    if (tid < a.K / 8) {
+        float v[8];
+        widen8(mx, v);
+        if (((uintptr_t)a.col_absmax & 15) == 0) {
+            ((float4 *)(a.col_absmax + tid * 8))[0] = make_float4(v[0], v[1], v[2], v[3]);
+            ((float4 *)(a.col_absmax + tid * 8))[1] = make_float4(v[4], v[5], v[6], v[7]);
+        } else {
+            for (int i = 0; i < 8; ++i) a.col_absmax[tid * 8 + i] = v[i];
+        }
+    }
+    for (int j = tid; j < sel.used; j += kActThreads) a.idx[j] = sh.idx[j];
+    store_list_rest(sel, a.r_cap, a.idx, a.n_outliers);
+}
+
 }  // namespace
 
 bool act_select_fits(int k_pad, int r_cap) { return k_pad <= kActMaxK && r_cap <= kActMaxCap; }
@@ -625,6 +647,15 @@ int row_form(int M, int k_pad, int &form, int &pieces, int &at_once)
         at_once = P;
     }
     return groups;
+}
+
+hipError_t launch_detect_select(const ActArgs &args, hipStream_t s)
+{
+    ActArgs a = args;
+    a.by_chunks = divisor(a.k_pad / 8);
+    a.cut = magnitude_cut(a.threshold);
+    a.wg_waves = kActWaves;
+    return launch_kernel(k_detect_select, dim3(1), dim3(kActThreads), 0, s, a);
 }
 
 hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool given, hipStream_t s)

@@ -576,6 +576,20 @@ int muxq_detect_outliers(const void *X, int M, int K, int ldx, float threshold, 
         MUXQ_TRY(muxq::launch_col_absmax_narrow(X, M, K, ldx, kpad(K), (uint16_t *)scratch, &n_slabs, s));
     else
         MUXQ_TRY(muxq::launch_col_absmax_partial(X, M, K, ldx, kpad(K), (uint16_t *)scratch, &n_slabs, s));
+    if (muxq::act_select_fits(kpad(K), r_cap)) {
+        muxq::ActArgs d{};
+        d.K = K; d.k_pad = kpad(K);
+        d.r_cap = r_cap;
+        d.threshold = threshold;
+        d.slabs = (const uint16_t *)scratch;
+        d.n_slabs = n_slabs;
+        d.slab_ld = kpad(K);
+        d.col_absmax = col_absmax;
+        d.idx = outlier_idx;
+        d.n_outliers = n_outliers;
+        MUXQ_TRY(muxq::launch_detect_select(d, s));
+        return MUXQ_OK;
+    }
     MUXQ_TRY(muxq::launch_fold_select_scale((const uint16_t *)scratch, n_slabs, K, kpad(K), threshold,
                                             r_cap, 0, 127.0f, 0, col_absmax, outlier_idx, n_outliers, nullptr,
                                             nullptr, nullptr, nullptr, s));

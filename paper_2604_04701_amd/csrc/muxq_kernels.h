@@ -236,6 +236,7 @@ hipError_t launch_fold_slabs(uint16_t *partial, int n_slabs, int k_pad, hipStrea
 hipError_t launch_col_absmax_narrow(const void *x_fp16, int rows, int cols, int ld, int k_pad, uint16_t *partial,
                                     int *n_slabs, hipStream_t s);
 hipError_t launch_quantize_select(const ActArgs &a, bool per_token, bool given, hipStream_t s);
+hipError_t launch_detect_select(const ActArgs &a, hipStream_t s);     // x, M and what the quantisers write are not used
 
 // One layer in one launch, for few tokens (muxq_few.hip).  Pointers into the workspace as in
 // muxq_ws_layout; slabs (n_slabs x k_pad fp16 magnitudes) when a producer of X has left the column
