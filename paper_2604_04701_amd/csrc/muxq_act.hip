@@ -21,29 +21,28 @@ constexpr int kActMaxCap = 1024;
 // Column maxima of |X| per row slab, like k_col_absmax_partial, but a workgroup covers only 128
 // columns and many rows: the same number of workgroups leaves a quarter of the slabs.  (64 columns leave
 // an eighth, but 16384 x 5120 from HBM then takes 5 us more; 256 columns, 64-128 KB to fold, cost the
-// quantisers 1-2 us.)  The workgroups take turns at blocks of 32 rows, so that all of them walk through X together (a range of
-// rows for each: 16384 x 5120 39.6 -> 37.8 us = 4.4 TB/s, behind the write-back of the codes before, 8192 x 4096 13.8 -> 12.8).
+// quantisers 1-2 us.)
 constexpr int kNarrowLanes = 16;
 __global__ __launch_bounds__(512) void k_col_absmax_narrow(const uint16_t *__restrict__ x, int rows, int cols, int ld,
-                                                           int k_pad,
+                                                           int k_pad, int rows_per_block,
                                                            uint16_t *__restrict__ partial)
 {
     constexpr int LANES = kNarrowLanes, RW = 64 / LANES, RB = 8 * RW;    // rows of a wave's load, of a workgroup's
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col0 = blockIdx.x * LANES * 8 + (lane % LANES) * 8;
-    const int step = (int)gridDim.y * RB;
+    const int r0 = blockIdx.y * rows_per_block, r1 = min(rows, r0 + rows_per_block);
     uint4 mx = make_uint4(0, 0, 0, 0);
     if (col0 < cols) {
         const uint16_t *p = x + col0;
-        int row = (int)blockIdx.y * RB + wave * RW + lane / LANES;
-        for (; row + 3 * step < rows; row += 4 * step) {
+        int row = r0 + wave * RW + lane / LANES;
+        for (; row + 3 * RB < r1; row += 4 * RB) {
             const uint4 v0 = *(const uint4 *)(p + (size_t)row * ld);
-            const uint4 v1 = *(const uint4 *)(p + (size_t)(row + step) * ld);
-            const uint4 v2 = *(const uint4 *)(p + (size_t)(row + 2 * step) * ld);
-            const uint4 v3 = *(const uint4 *)(p + (size_t)(row + 3 * step) * ld);
+            const uint4 v1 = *(const uint4 *)(p + (size_t)(row + RB) * ld);
+            const uint4 v2 = *(const uint4 *)(p + (size_t)(row + 2 * RB) * ld);
+            const uint4 v3 = *(const uint4 *)(p + (size_t)(row + 3 * RB) * ld);
             mx = absmax_step(absmax_step(absmax_step(absmax_step(mx, v0), v1), v2), v3);
         }
-        for (; row < rows; row += step) mx = absmax_step(mx, *(const uint4 *)(p + (size_t)row * ld));
+        for (; row < r1; row += RB) mx = absmax_step(mx, *(const uint4 *)(p + (size_t)row * ld));
     }
     __shared__ uint4 red[512];
     red[threadIdx.x] = mx;
@@ -613,9 +612,11 @@ hipError_t launch_col_absmax_narrow(const void *x_fp16, int rows, int cols, int 
     const int gx = (k_pad / 8 + kNarrowLanes - 1) / kNarrowLanes;
     int gy = max(1, min(kMaxSlabs, 256 / gx));
     gy = max(1, min(gy, (rows + 63) / 64));
+    const int rpb = ((rows + gy - 1) / gy + 63) & ~63;
+    gy = (rows + rpb - 1) / rpb;
     *n_slabs = gy;
     return launch_kernel(k_col_absmax_narrow, dim3(gx, gy), dim3(512), 0, s,
-                         (const uint16_t *)x_fp16, rows, cols, ld, k_pad, partial);
+                         (const uint16_t *)x_fp16, rows, cols, ld, k_pad, rpb, partial);
 }
 
 hipError_t launch_fold_slabs(uint16_t *partial, int n_slabs, int k_pad, hipStream_t s)
