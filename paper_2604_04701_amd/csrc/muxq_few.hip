@@ -452,38 +452,37 @@ int few_waves(int M, int k_pad)
 bool few_two_on_a_cu(int M, int waves) { return M <= 4 && waves == 8; }
 
 // X and its codes have to fit LDS together (about 42 K elements); below that the line against the separate
-// launches (selecting quantiser and GEMM) lies where three things that grow here outweigh the launch
-// saved: the rows that a wave works on one after the other (`turns`), which every workgroup repeats; the walk over N, 16
-// channels per workgroup at a time with barriers between, from N = 4096 on; and rows in more than one block of 16.  us per
-// call, the separate launches / this kernel:
-//   turns  8 x 768 -> 3072 9.8 / 7.9 (2), 16 x 768 9.9 / 9.3 (3), 16 x 1280 -> 1280 10.0 / 9.7 (4), 8 x 3072 -> 768 10.7 / 10.0 (4), 5 x 6000
-//          -> 1000 11.5 / 11.3 (5), 12 x 3072 -> 768 11.2 / 11.6 (6), 8 x 5120 -> 1280 11.4 / 13.3 (8); the same number costs more with
-//          many elements in it: 8 x 4096 -> 1024 10.9 / 11.1 (4).  One scale per token: 8 x 2048 11.6 / 10.8 (3), 8 x 3072 -> 768 11.5 /
-//          11.7 (4), 12 x 1600 11.7 / 13.0 (4)
-//   N      4 x 1600 -> 6400 10.6 / 10.2 (2), 12 x 1024 -> 12288 12.8 / 12.8 (2), 8 x 2048 -> 8192 11.5 / 12.2 (3); a longer K: 1 x 4096 ->
-//          8192 13.6 / 12.2 (1), 4 x 4096 -> 16384 19.1 / 21.2 (2), but 8 x 4096 -> 24576 37.4 / 32.8, 1 x 5120 -> 20480 43.2 / 33.8
-//   rows   32 x 512 -> 2048 9.9 / 9.1 (3), 17 x 1024 9.9 / 9.8 (3), 20 x 768 -> 2304 9.9 / 10.2 (4), 48 x 256 -> 1024 10.2 / 11.1, 64 x 512 ->
-//          1024 10.1 / 12.6
+// launches (selecting quantiser and GEMM, two or three of them, which cost the host alone 9.8 us) lies where what grows here
+// outweighs the launches saved: the rows that a wave works on one after the other (`turns`) and the elements in them, which every
+// workgroup repeats, and the walk over N, 16 channels per workgroup at a time with barriers between, from N = 4096 on.  us per
+// call, the separate launches / this kernel (turns):
+//   N <= 4096  16 x 2048 -> 2048 10.9 / 8.7 (6), 24 x 1536 10.3 / 9.1 (6), 64 x 512 -> 1024 10.4 / 9.1 (6), 12 x
+//          3072 -> 768 10.7 / 9.5 (6), 8 x 4096 -> 1024 10.5 / 9.6 (4), 4 x 8192 -> 1024 12.4 / 10.9 (4), 40 x 800 10.4 / 9.9 (7), 8 x 5120 -> 1280 11.0 /
+//          11.0 (8; with the maxima given by the layer before 11.0 / 11.5).  One scale per token, whose maxima are one more walk over the
+//          rows: 8 x 3072 -> 768 11.1 / 10.5 (24 K elements), 16 x 1600 11.5 / 11.2 (25 K), 8 x 4096 -> 1024 11.3 / 11.7 (32 K), 6 x 5120 12.1 / 12.7
+//   beyond 16 x 768 -> 12288 12.1 / 10.8 (3), 32 x 768 -> 8192 10.6 / 10.2 (6), 8 x 2048 -> 8192 10.8 / 10.6 (3), 16 x 1600 -> 6400 10.6 / 10.8 (6),
+//          12 x 1600 -> 6400 per token 11.4 / 12.2 (4), 4 x 2048 -> 24000 20.8 / 15.9; a longer K: 8 x 4096 -> 8192 13.4 / 14.2 (4), 4 x 4096
+//          -> 16384 18.9 / 20.3 (2), but 8 x 4096 -> 24576 37.4 / 32.8
 // Long lists move it the other way (8 x 1280 -> 4096, 160 channels of at most 1024 listed, 19.6 / 11.0 with the separate launches of
 // before): capacities above 64 keep wider lines.
 bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token)
 {
     if (M > kFewMaxM || k_pad > 64 * kFewMaxWaves * few_loads((M + 15) / 16) || few_plan(M, K, k_pad, r_cap, 1, kFewMaxWaves).total > kFewLdsBytes)
         return false;
-    const bool fewest = M <= 8;
-    if (r_cap > 64) {
-        if (N > (M > 32 ? 8192 : K > 1536 ? (fewest && K > 3072 ? 32768 : 24576) : fewest ? 16384 : 12288)) return false;
-        if (M <= 20) return true;
-        if (M <= 32) return M * K <= (M <= 24 ? 36 : 32) * 1024;
-        return K <= 512 ? M <= (per_token ? 48 : 64) : M <= 40 && M * K <= 32 * 1024 && !per_token;
+    const bool fewest = M <= 8, long_lists = r_cap > 64;
+    if (N > (M > 32 ? 8192 : K > 1536 ? (fewest && K > 3072 ? 32768 : 24576) : fewest ? 16384 : 12288)) return false;
+    if (!long_lists) {
+        const int pieces = (k_pad / 8 + 63) / 64, waves = few_waves(M, k_pad), at_once = waves / pieces, turns = (M + at_once - 1) / at_once;
+        if (N > 4096) {
+            if (pieces > 4) return N <= 16384 ? turns == 1 : fewest;
+            if (N > 16384) return few_two_on_a_cu(M, waves);
+            return turns <= (per_token ? 2 : N > 8192 ? (pieces > 2 ? 2 : 3) : pieces > 2 ? 3 : 6) && M * K <= 24 * 1024;
+        }
+        if (per_token ? M * K > 26 * 1024 : turns > 7 && fewest) return false;
     }
-    const int pieces = (k_pad / 8 + 63) / 64, waves = few_waves(M, k_pad), at_once = waves / pieces, turns = (M + at_once - 1) / at_once;
-    if (N > 4096) {
-        if (pieces > 4) return N <= 16384 ? turns == 1 : fewest && N <= (K > 3072 ? 32768 : 24576);
-        return N <= (few_two_on_a_cu(M, waves) ? 16384 : 12288) && turns <= 2 && (!per_token || fewest);
-    }
-    if (turns <= 3) return M <= (per_token ? 24 : 32);
-    return !per_token && M <= 16 && turns <= 5 && M * K <= 30 * 1024;
+    if (M <= 20) return true;
+    if (M <= 32) return M * K <= (M <= 24 ? 36 : 32) * 1024;
+    return K <= 512 ? M <= (per_token ? 48 : 64) : M <= 40 && M * K <= 32 * 1024 && !per_token;
 }
 
 typedef void (*few_kernel_t)(const FewArgs, const FewPlan);
