@@ -333,8 +333,8 @@ int muxq_gelu_absmax(const void *Y_fp16, int M, int K, int ldy, void *X_fp16, in
  * maxima of H, so that the next muxq_linear_opts / muxq_linear_static starts at its selection
  * step with opts.absmax_ready = 1 and opts.absmax_slabs = muxq_linear_gelu_slabs(M, K, N).
  * The GEMM's workgroups take those maxima from the tiles they store (one slab per row of
- * tiles); where the problem runs on a form of the GEMM that does not, or has more than 64 rows of
- * tiles, one plain pass over H takes them instead (same result, same interface).  One workspace may
+ * tiles); where there are more than 64 rows of tiles one plain pass over H takes them instead
+ * (same result, same interface).  One workspace may
  * serve both layers (large enough for either): next_slabs then lies inside `workspace`, and the
  * maxima come from that pass where its layout has something there that the GEMM still needs.
  * opts: as muxq_linear_opts (aux_own_scale is not combined with the fused GELU: MUXQ_ERR_PARAM). */
