@@ -19,7 +19,9 @@ SHAPES = [(1, 8, 8), (1, 768, 2304), (1, 8192, 520), (2, 72, 24), (15, 4096, 136
           (17, 1000, 264), (24, 5120, 264), (31, 512, 8200), (33, 136, 520), (48, 2048, 72), (64, 64, 16),
           (64, 1024, 264),
           # workgroups of 15, 14, 9 and 13 waves: a row in 5, 7, 9 and 13 pieces
-          (3, 2400, 72), (3, 3400, 264), (2, 4360, 72), (5, 6400, 136)]
+          (3, 2400, 72), (3, 3400, 264), (2, 4360, 72), (5, 6400, 136),
+          # either side of the line to the separate launches: rows in turn, elements with one scale per token, the walk over N
+          (7, 5120, 136), (8, 5120, 136), (6, 4400, 72), (6, 4480, 72), (16, 768, 12280), (20, 768, 12280)]
 
 
 @pytest.mark.parametrize("x_gran,w_gran", [("tensor", "tensor"), ("tensor", "channel"), ("token", "channel")])
