@@ -35,6 +35,7 @@ typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 constexpr int kFewMaxWaves = 16;                             // of a workgroup, see few_waves
 constexpr int kFewMaxK = 8 * 64 * kFewMaxWaves;              // one 8-channel chunk per thread in the selection
 constexpr int kFewMaxM = 64;
+constexpr int kFewGrid = 256;                               // workgroups, one to a CU (see few_two_on_a_cu)
 // Weight blocks of a wave, all in registers, by 16-row blocks of tokens: enough for the K that
 // few_tokens_fit lets through.  (Eight for all of them made the forms above 16 tokens spill to scratch.)
 constexpr int few_loads(int row_blocks) { return row_blocks == 1 ? kFewMaxK / 64 / kFewMaxWaves : row_blocks == 2 ? 3 : 1; }
@@ -435,11 +436,15 @@ __global__ __launch_bounds__(kFewMaxWaves * 64) void k_linear_few(const FewArgs 
 // instructions, 4 cycles each), so with four waves on a SIMD small calls are bound by their issue.  A long K, whose weights
 // want many loads in flight, takes 16 all the same, else many rows 12 and few rows 8; whole row groups of waves, since a thread has one
 // chunk of the rows, and no more weight blocks to a wave than it has registers for.  us a call with 8 / 12 / 16: 1 x 768 -> 2304 6.8 /
-// 7.1 / 7.4, 4 x 1024 -> 1024 7.2 / 7.6 / 8.0, 8 x 1280 -> 5120 10.9 / 10.0 / 10.4, 16 x 1280 -> 3840 14.5 / 11.4 / 12.0, 20 x 2000 -> 2048
-// 13.5 / 13.6 / 13.9, 3 x 3000 -> 8000 13.7 / 12.4 / 12.4, 8 x 4096 -> 4096 13.6 / 13.6 / 12.4.
-int few_waves(int M, int k_pad)
+// 7.1 / 7.4, 4 x 1024 -> 1024 7.2 / 7.6 / 8.0, 8 x 1280 -> 5120 10.9 / 10.0 / 10.4, 16 x 1280 -> 3840 14.5 / 11.4 / 12.0, 3 x 3000 -> 8000
+// 13.7 / 12.4 / 12.4, 8 x 4096 -> 4096 13.6 / 13.6 / 12.4.
+// Whole row groups are 9 to 15 waves with a K beyond 4096.  Where the workgroups walk over N, the weights decide, and 16 it is, the rest of
+// them for the weights alone: whole groups / 16, 1 x 4368 -> 6424 13.2 / 12.3, 1 x 4608 -> 14336 22.0 / 20.2, 4 x 3072 -> 10240 15.0 / 14.5; with
+// one block of 16 channels to a workgroup 8 x 4608 -> 1280 11.0 / 11.2, 4 x 6144 -> 1280 9.5 / 9.5.
+int few_waves(int M, int N, int k_pad)
 {
     const int pieces = (k_pad / 8 + 63) / 64, loads = few_loads((M + 15) / 16);
+    if (pieces > 4 && N > 16 * kFewGrid) return kFewMaxWaves;
     const int want = pieces > 4 ? 16 : M * pieces <= 20 ? 8 : 12;
     int waves = max(want / pieces, 1) * pieces;
     while (waves * loads * 64 < k_pad) waves += pieces;
@@ -472,7 +477,7 @@ bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token)
     const bool fewest = M <= 8, long_lists = r_cap > 64;
     if (N > (M > 32 ? 8192 : K > 1536 ? (fewest && K > 3072 ? 32768 : 24576) : fewest ? 16384 : 12288)) return false;
     if (!long_lists) {
-        const int pieces = (k_pad / 8 + 63) / 64, waves = few_waves(M, k_pad), at_once = waves / pieces, turns = (M + at_once - 1) / at_once;
+        const int pieces = (k_pad / 8 + 63) / 64, waves = few_waves(M, N, k_pad), at_once = waves / pieces, turns = (M + at_once - 1) / at_once;
         if (N > 4096) {
             if (pieces > 4) return N <= 16384 ? turns == 1 : fewest;
             if (N > 16384) return few_two_on_a_cu(M, waves);
@@ -510,7 +515,7 @@ hipError_t launch_linear_few(const FewArgs &a, hipStream_t s)
     const hipError_t e = gemm_prepare_device();
     if (e != hipSuccess) return e;
     // every workgroup repeats the activation side: no more of them than are resident at once
-    const int nblk = (a.N + 15) / 16, waves = few_waves(a.M, a.k_pad), grid = min(nblk, few_two_on_a_cu(a.M, waves) ? 512 : 256);
+    const int nblk = (a.N + 15) / 16, waves = few_waves(a.M, a.N, a.k_pad), grid = min(nblk, few_two_on_a_cu(a.M, waves) ? 2 * kFewGrid : kFewGrid);
     FewPlan plan = few_plan(a.M, a.K, a.k_pad, a.r_cap, grid, waves);
     plan.cut = magnitude_cut(a.threshold);
     return launch_kernel(few_kernel((a.M + 15) / 16, a.x_per_token != 0), dim3(grid), dim3(plan.waves * 64), plan.total, s,
