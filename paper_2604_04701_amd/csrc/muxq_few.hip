@@ -36,6 +36,7 @@ constexpr int kFewMaxWaves = 16;                             // of a workgroup, 
 constexpr int kFewMaxK = 8 * 64 * kFewMaxWaves;              // one 8-channel chunk per thread in the selection
 constexpr int kFewMaxM = 64;
 constexpr int kFewGrid = 256;                               // workgroups, one to a CU (see few_two_on_a_cu)
+constexpr int kFewTwoM = 4;                                  // most rows with which two share a CU
 // Weight blocks of a wave, all in registers, by 16-row blocks of tokens: enough for the K that
 // few_tokens_fit lets through.  (Eight for all of them made the forms above 16 tokens spill to scratch.)
 constexpr int few_loads(int row_blocks) { return row_blocks == 1 ? kFewMaxK / 64 / kFewMaxWaves : row_blocks == 2 ? 3 : 1; }
@@ -440,21 +441,25 @@ __global__ __launch_bounds__(kFewMaxWaves * 64) void k_linear_few(const FewArgs 
 // 13.7 / 12.4 / 12.4, 8 x 4096 -> 4096 13.6 / 13.6 / 12.4.
 // Whole row groups are 9 to 15 waves with a K beyond 4096.  Where the workgroups walk over N, the weights decide, and 16 it is, the rest of
 // them for the weights alone: whole groups / 16, 1 x 4368 -> 6424 13.2 / 12.3, 1 x 4608 -> 14336 22.0 / 20.2, 4 x 3072 -> 10240 15.0 / 14.5; with
-// one block of 16 channels to a workgroup 8 x 4608 -> 1280 11.0 / 11.2, 4 x 6144 -> 1280 9.5 / 9.5.
+// one block of 16 channels to a workgroup 8 x 4608 -> 1280 11.0 / 11.2, 4 x 6144 -> 1280 9.5 / 9.5.  Where 8 would be 6, as three pieces make
+// them, 12 walk over N faster unless two workgroups share the CU (6 / 12 waves): 5 x 1280 -> 12288 12.7 / 11.8, per token 13.4 / 12.3, 6 x
+// 1536 -> 8192 10.2 / 9.8; one block of channels 6 x 1536 -> 4096 7.2 / 7.5.
 int few_waves(int M, int N, int k_pad)
 {
     const int pieces = (k_pad / 8 + 63) / 64, loads = few_loads((M + 15) / 16);
     if (pieces > 4 && N > 16 * kFewGrid) return kFewMaxWaves;
-    const int want = pieces > 4 ? 16 : M * pieces <= 20 ? 8 : 12;
+    const bool few = M * pieces <= 20 && !(pieces == 3 && M > kFewTwoM && N > 16 * kFewGrid);
+    const int want = pieces > 4 ? 16 : few ? 8 : 12;
     int waves = max(want / pieces, 1) * pieces;
     while (waves * loads * 64 < k_pad) waves += pieces;
     return min(waves, kFewMaxWaves);
 }
 
-// Whether two workgroups share a CU where there are more blocks of 16 output channels than CUs (two of 8 waves do not hinder each other
-// much while few rows' codes are to be formed): us a call, walking over N / so: 1 x 1600 -> 6400 9.1 / 8.0, 1 x 2048 -> 16384 15.6 / 12.1,
-// 4 x 1024 -> 12288 11.4 / 9.8, 4 x 512 -> 8192 8.6 / 8.0; 8 x 512 -> 8192 8.5 / 8.8, 16 x 512 -> 8192 9.4 / 10.2.
-bool few_two_on_a_cu(int M, int waves) { return M <= 4 && waves == 8; }
+// Whether two workgroups share a CU where there are more blocks of 16 output channels than CUs (two of at most 8 waves do not hinder each
+// other much while few rows' codes are to be formed): us a call, walking over N / so: 1 x 1600 -> 6400 9.1 / 8.0, 1 x 2048 -> 16384 15.6 / 12.1,
+// 4 x 1024 -> 12288 11.4 / 9.8, 4 x 512 -> 8192 8.6 / 8.0; with 6 waves 1 x 1280 -> 5120 8.2 / 7.4, 4 x 1536 -> 12288 12.8 / 10.6; 8 x 512 -> 8192
+// 8.5 / 8.8, 16 x 512 -> 8192 9.4 / 10.2.
+bool few_two_on_a_cu(int M, int waves) { return M <= kFewTwoM && waves <= 8; }
 
 // X and its codes have to fit LDS together (about 42 K elements); below that the line against the separate
 // launches (selecting quantiser and GEMM, two or three of them, which cost the host alone 9.8 us) lies where what grows here

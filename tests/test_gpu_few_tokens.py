@@ -20,8 +20,10 @@ SHAPES = [(1, 8, 8), (1, 768, 2304), (1, 8192, 520), (2, 72, 24), (15, 4096, 136
           (64, 1024, 264),
           # workgroups of 15, 14, 9 and 13 waves: a row in 5, 7, 9 and 13 pieces
           (3, 2400, 72), (3, 3400, 264), (2, 4360, 72), (5, 6400, 136),
-          # the same rows with more blocks of output channels than CUs: 16 waves, of which 1, 4, 7 and 3 hold no row
+          # the same rows with more blocks of output channels than CUs: 16 waves, of which 1, 2, 7 and 3 hold no row
           (3, 2400, 4104), (2, 3400, 6424), (1, 4360, 4120), (1, 6400, 6424),
+          # three pieces to a row: two workgroups of 6 waves on a CU, and 12 waves that walk over N
+          (1, 1032, 4104), (4, 1536, 8216), (5, 1032, 4104), (6, 1536, 8200),
           # either side of the line to the separate launches: rows in turn, elements with one scale per token, the walk over N
           (7, 5120, 136), (8, 5120, 136), (6, 4400, 72), (6, 4480, 72), (16, 768, 12280), (20, 768, 12280)]
 
