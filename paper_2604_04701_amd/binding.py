@@ -24,7 +24,7 @@ EXPORTS = ["muxq_version", "muxq_status_string", "muxq_k_pad", "muxq_wq_bytes",
            "muxq_noalloc_max_bytes", "muxq_linear_noalloc", "muxq_linear_gelu", "muxq_linear_gelu_slabs",
            "muxq_mlp", "muxq_mlp_workspace_bytes",
            "muxq_quantize_weight_smooth", "muxq_smooth_absmax",
-           "muxq_probe_mfma_rate", "muxq_gemm_kernel", "muxq_static_bytes", "muxq_static_layout_of",
+           "muxq_probe_mfma_rate", "muxq_gemm_kernel", "muxq_code_kernel", "muxq_static_bytes", "muxq_static_layout_of",
            "muxq_prepare_static", "muxq_linear_static", "muxq_gelu_absmax"]
 
 
@@ -130,6 +130,8 @@ def lib():
         L.muxq_smooth_absmax.argtypes = [vp, i, i, i, vp, vp, i, vp, vp]
         L.muxq_gemm_kernel.restype = C.c_char_p
         L.muxq_gemm_kernel.argtypes = [i, i, i]
+        L.muxq_code_kernel.restype = C.c_char_p
+        L.muxq_code_kernel.argtypes = [i, i, i, i, C.POINTER(ActOpts)]
         L.muxq_linear_gelu_slabs.restype = i
         L.muxq_linear_gelu_slabs.argtypes = [i, i, i]
         L.muxq_linear_gelu.restype = i
@@ -445,6 +447,12 @@ def muxq_linear_timed(X, w_q, w_scale, N, gemm_start, gemm_stop, w_gran="tensor"
 def gemm_kernel(M: int, K: int, N: int) -> str:
     """Name of the kernel that runs the GEMM of an M x K -> N layer (include/muxq_measure.h)."""
     return lib().muxq_gemm_kernel(M, K, N).decode()
+
+
+def code_kernel(M: int, K: int, N: int, r_cap=64, x_gran="tensor", absmax_ready=False, aux_scale="shared") -> str:
+    """Name of the kernel that forms the codes of X in an M x K -> N layer (include/muxq_measure.h)."""
+    opts = ActOpts(_XGRAN[x_gran], 8, int(absmax_ready), {"shared": 0, "own": 1}[aux_scale], 0)
+    return lib().muxq_code_kernel(M, K, N, r_cap, C.byref(opts)).decode()
 
 
 def wq_row_sums(w_q, K: int, N: int):

@@ -463,32 +463,41 @@ bool few_two_on_a_cu(int M, int waves) { return M <= kFewTwoM && waves <= 8; }
 
 // X and its codes have to fit LDS together (about 42 K elements); below that the line against the separate
 // launches (selecting quantiser and GEMM, two or three of them, which cost the host alone 9.8 us) lies where what grows here
-// outweighs the launches saved: the rows that a wave works on one after the other (`turns`) and the elements in them, which every
-// workgroup repeats, and the walk over N, 16 channels per workgroup at a time with barriers between, from N = 4096 on.  us per
-// call, the separate launches / this kernel (turns):
-//   N <= 4096  16 x 2048 -> 2048 10.9 / 8.7 (6), 24 x 1536 10.3 / 9.1 (6), 64 x 512 -> 1024 10.4 / 9.1 (6), 12 x
-//          3072 -> 768 10.7 / 9.5 (6), 8 x 4096 -> 1024 10.5 / 9.6 (4), 4 x 8192 -> 1024 12.4 / 10.9 (4), 40 x 800 10.4 / 9.9 (7), 8 x 5120 -> 1280 11.0 /
-//          11.0 (8; with the maxima given by the layer before 11.0 / 11.5).  One scale per token, whose maxima are one more walk over the
-//          rows: 8 x 3072 -> 768 11.1 / 10.5 (24 K elements), 16 x 1600 11.5 / 11.2 (25 K), 8 x 4096 -> 1024 11.3 / 11.7 (32 K), 6 x 5120 12.1 / 12.7
-//   beyond 16 x 768 -> 12288 12.1 / 10.8 (3), 32 x 768 -> 8192 10.6 / 10.2 (6), 8 x 2048 -> 8192 10.8 / 10.6 (3), 16 x 1600 -> 6400 10.6 / 10.8 (6),
-//          12 x 1600 -> 6400 per token 11.4 / 12.2 (4), 4 x 2048 -> 24000 20.8 / 15.9; a longer K: 8 x 4096 -> 8192 13.4 / 14.2 (4), 4 x 4096
-//          -> 16384 18.9 / 20.3 (2), but 8 x 4096 -> 24576 37.4 / 32.8
+// outweighs the launches saved: the rows that a wave works on one after the other (`turns`, counted for 12 waves and 16 whatever few_waves
+// gives, so that a row more never brings a call back) and the elements in them, which every workgroup repeats, and the walk over N, 16
+// channels per workgroup at a time with barriers between, from N = 4096 on.  us per call, the separate launches / this kernel (turns):
+//   N <= 4096  16 x 2056 -> 2048 11.5 / 10.0, 24 x 1536 10.1 / 9.1, 64 x 512 10.4 / 9.2, 12 x 3096 -> 2048 11.5 / 10.4, 40 x 800 10.9 /
+//          10.1, 8 x 4608 -> 2048 11.9 / 11.1, 9 x 4608 -> 4096 13.1 / 12.6, 10 x 4104 -> 4096 12.7 / 12.5.  With the maxima given, which leaves
+//          the separate launches one thing less to wait for: 8 x 5120 -> 1280 10.8 / 10.7, -> 3072 11.7 / 12.0, 9 x 4608 -> 2560 11.1 / 11.0,
+//          -> 3072 11.3 / 11.8, 6 x 6656 -> 3072 12.2 / 12.9, but two rows at a time 12 x 3400 -> 4096 11.1 / 11.0, 16 x 2600 -> 4096 11.0 / 10.1, and
+//          8 x 4104 (32 K elements) -> 4096 11.5 / 11.5.  One scale per token, whose maxima are one more walk over the rows: 10 x 2600 12.3 / 11.2
+//          (25 K elements), 8 x 3608 12.0 / 11.6 (28 K), 8 x 4104 12.3 / 13.4 (32 K), 7 x 4608 12.3 / 13.2, 6 x 4608 12.3 / 12.5
+//   to 12288, K <= 2048  32 x 768 -> 12288 13.1 / 12.2 (6), 16 x 1280 -> 12288 13.1 / 12.9 (4), 12 x 1600 -> 8192 11.5 / 10.8 (4), -> 12288 13.4 /
+//          13.7; per token 48 x 512 -> 8192 13.1 / 11.9 (4), 32 x 768 -> 8192 12.6 / 12.7 (6), 24 x 1024 -> 8192 12.1 / 11.7 (4), -> 12288 14.0 / 14.2,
+//          9 x 1600 -> 8192 12.3 / 11.9 (3), -> 12288 14.0 / 14.6, 12 x 1600 -> 5120 11.8 / 12.1 (4)
+//   to 12288 with a longer K  8 x 2560 -> 8192 12.3 / 11.9 (3), 6 x 4096 -> 8192 14.0 / 14.0 (3), 3 x 4608 -> 8192 14.3 / 13.7 (3), 8 x 4096 14.1 / 14.6
+//          (4), 5 x 4608 14.3 / 14.6 (5), 3 x 8192 -> 4104 16.1 / 16.7 (3); per token 5 x 2560 -> 8192 12.9 / 12.3 (2), 2 x 6144 16.3 / 15.9 (2), 6 x
+//          4096 14.7 / 15.3 (3), 3 x 4608 14.6 / 15.0, 2 x 8192 -> 4104 16.6 / 17.3 (2)
+//   to 16384, where the GEMM still has direct tiles and this kernel takes a step more  1 x 2056 14.4 / 15.4, 1 x 4096 19.0 / 19.1, 8 x 1024
+//          13.3 / 13.8, but 8 x 512 12.3 / 10.9; two workgroups on a CU 4 x 1536 13.3 / 12.2
+//   beyond, where it has not  4 x 2048 -> 24000 20.8 / 15.9, 1 x 2560 -> 20000 23.3 / 18.8, 8 x 2056 21.6 / 19.7, 8 x 4096 -> 24576 38.0 / 32.6
 // Long lists move it the other way (8 x 1280 -> 4096, 160 channels of at most 1024 listed, 19.6 / 11.0 with the separate launches of
 // before): capacities above 64 keep wider lines.
-bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token)
+bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token, bool maxima_given)
 {
     if (M > kFewMaxM || k_pad > 64 * kFewMaxWaves * few_loads((M + 15) / 16) || few_plan(M, K, k_pad, r_cap, 1, kFewMaxWaves).total > kFewLdsBytes)
         return false;
     const bool fewest = M <= 8, long_lists = r_cap > 64;
     if (N > (M > 32 ? 8192 : K > 1536 ? (fewest && K > 3072 ? 32768 : 24576) : fewest ? 16384 : 12288)) return false;
     if (!long_lists) {
-        const int pieces = (k_pad / 8 + 63) / 64, waves = few_waves(M, N, k_pad), at_once = waves / pieces, turns = (M + at_once - 1) / at_once;
+        const int pieces = (k_pad / 8 + 63) / 64, at_once = max((pieces > 4 ? 16 : 12) / pieces, 1), turns = (M + at_once - 1) / at_once;
+        if (N > 12288) return pieces > 4 ? N > 16384 && fewest : pieces == 1 || few_two_on_a_cu(M, few_waves(M, N, k_pad));
         if (N > 4096) {
-            if (pieces > 4) return N <= 16384 ? turns == 1 : fewest;
-            if (N > 16384) return few_two_on_a_cu(M, waves);
-            return turns <= (per_token ? 2 : N > 8192 ? (pieces > 2 ? 2 : 3) : pieces > 2 ? 3 : 6) && M * K <= 24 * 1024;
+            if (pieces > 4) return turns <= (per_token ? 2 : 3) - (K > 6144);
+            const int most = per_token ? (pieces <= 3 ? 4 : 3) - (N > 8192) : pieces <= 2 ? 6 : N <= 8192 || pieces == 3 ? 4 : 3;
+            return turns <= most && M * K <= 24 * 1024;
         }
-        if (per_token ? M * K > 26 * 1024 : turns > 7 && fewest) return false;
+        if (per_token ? M * K > 26 * 1024 : maxima_given && pieces > 8 && M * K > 34 * 1024 && N > 2560) return false;
     }
     if (M <= 20) return true;
     if (M <= 32) return M * K <= (M <= 24 ? 36 : 32) * 1024;

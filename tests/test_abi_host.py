@@ -25,6 +25,7 @@ def test_library_exports_every_declared_symbol():
     # the product header carries no measurement hook
     product = re.sub(r"/\*.*?\*/", "", open(os.path.join(inc, "muxq.h")).read(), flags=re.S)
     assert "muxq_probe_mfma_rate" not in product and "muxq_linear_timed" not in product and "muxq_gemm_kernel" not in product
+    assert "muxq_code_kernel" not in product
     assert declared == set(B.EXPORTS)
     L = B.lib()
     for name in declared:
@@ -236,3 +237,34 @@ def test_gemm_kernels_by_size():
         assert B.gemm_kernel(M, K, N) == "k_gemm_i8_persist4"
         assert B.lib().muxq_linear_gelu_slabs(M, K, N) == (M + 127) // 128
     assert B.gemm_kernel(0, 64, 64) == B.gemm_kernel(64, 64, 9) == ""
+
+
+@pytest.mark.parametrize("x_gran", ["tensor", "token"])
+@pytest.mark.parametrize("absmax_ready", [False, True])
+def test_a_row_more_never_brings_a_call_back_to_the_one_launch(x_gran, absmax_ready):
+    """The one launch for few tokens repeats the work of every row on every CU: the numbers of tokens that take it are
+    1 to some most, for every row length, width and capacity, with the column maxima given or not."""
+    Ks = sorted(set(range(8, 8200, 168)) | {8, 512, 520, 1024, 1032, 1536, 1544, 2048, 2056, 3072, 4096, 4104, 4352, 4608, 5120, 8192})
+    for r_cap in (0, 64, 128):
+        for K in Ks:
+            if r_cap > B.k_pad(K):
+                continue
+            for N in (8, 2560, 2568, 4096, 4104, 8192, 8200, 12288, 12296, 16384, 16392, 24576, 32768):
+                few = [B.code_kernel(M, K, N, r_cap, x_gran, absmax_ready) == "k_linear_few" for M in range(1, 70)]
+                assert not few[-1] and few == sorted(few, reverse=True), (K, N, r_cap, [m + 1 for m in range(69) if few[m]])
+
+
+def test_code_kernels_by_size():
+    """Both sides of the lines between the routes."""
+    assert B.code_kernel(8, 4608, 1280) == B.code_kernel(9, 4608, 1280) == B.code_kernel(8, 5120, 1280) == "k_linear_few"
+    assert B.code_kernel(8, 5120, 1280, absmax_ready=True) == B.code_kernel(10, 4104, 2560, absmax_ready=True) == "k_linear_few"
+    assert B.code_kernel(8, 5120, 2568, absmax_ready=True) == B.code_kernel(10, 4104, 4096, absmax_ready=True) == "k_quantize_select"
+    assert B.code_kernel(16, 2600, 4096, absmax_ready=True) == B.code_kernel(8, 4104, 4096, absmax_ready=True) == "k_linear_few"
+    assert B.code_kernel(5, 1032, 5120, x_gran="token") == B.code_kernel(16, 1280, 8192, x_gran="token") == "k_linear_few"
+    assert B.code_kernel(12, 1600, 5120, x_gran="token") == B.code_kernel(24, 1024, 12288, x_gran="token") == "k_rows_select"
+    assert B.code_kernel(1, 4096, 12288) == B.code_kernel(1, 4096, 16392) == "k_linear_few"
+    assert B.code_kernel(1, 4096, 12296) == B.code_kernel(1, 4096, 16384) == "k_quantize_select"
+    assert B.code_kernel(30000, 4096, 64) == B.code_kernel(70, 8200, 64) == "k_quantize_body"
+    assert B.code_kernel(4, 512, 64, aux_scale="own") == "k_quantize_body"
+    assert B.code_kernel(70, 8200, 64, x_gran="token") == "k_quantize_rows_token"
+    assert B.code_kernel(0, 64, 64) == B.code_kernel(64, 64, 64, r_cap=32) == ""
