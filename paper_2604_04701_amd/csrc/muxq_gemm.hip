@@ -1525,6 +1525,10 @@ static GemmForm gemm_form(int M, int N, int k_pad, bool off_lines = false)
     if (tiles(32, 32) <= (short_k ? 512 : 256)) return kDirect32x32;
     if (!short_k && tiles(32, 64) <= 256) return kDirect32x64;
     if (t64 <= 256) return kDirect64x64;
+    // One row of tiles: half of a 64 x 64 tile and three quarters of a persistent one would be empty.  To three workgroups of 32 x 32 on a
+    // CU, with one K step or from 12 on (us a call, 32 x 32 / persistent 128): 16 x 64 -> 20000 12.9 / 13.9, 32 x 768 -> 16392 15.1 / 16.1, 16 x 1536
+    // -> 24576 17.7 / 20.8; 32 x 256 -> 20000 15.9 / 14.3, 32 x 512 -> 20000 15.9 / 15.0, with 800 tiles 32 x 768 -> 25600 17.9 / 16.3.
+    if (tiles(32, 32) <= 768 && short_k && (k_pad <= 64 || k_pad >= 768)) return kDirect32x32;
     // A round of 256 tiles of 256 x 256 takes as long as three of 256 tiles of 128 x 128 (1024 channels:
     // 20-23 us and 5.3 us + 5.3 us each; the ratio holds from K = 768 to 5120), so the larger tile
     // wins where its last round is full enough: 8192 x 1024 -> 1024 14 us against 19 us,

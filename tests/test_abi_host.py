@@ -236,6 +236,11 @@ def test_gemm_kernels_by_size():
     for M, K, N in ((1040, 2072, 6968), (1642, 5024, 4744), (1402, 2560, 5456), (2850, 5120, 2696)):
         assert B.gemm_kernel(M, K, N) == "k_gemm_i8_persist4"
         assert B.lib().muxq_linear_gelu_slabs(M, K, N) == (M + 127) // 128
+    # one row of 32 x 32 tiles, three workgroups on a CU
+    for M, K, N in ((9, 1416, 20600), (32, 768, 24576), (16, 64, 16400)):
+        assert B.gemm_kernel(M, K, N) == "k_gemm_i8_direct" and B.lib().muxq_linear_gelu_slabs(M, K, N) == 1
+    for M, K, N in ((32, 512, 20600), (32, 768, 24584), (33, 768, 16400)):
+        assert B.gemm_kernel(M, K, N) == "k_gemm_i8_persist4"
     assert B.gemm_kernel(0, 64, 64) == B.gemm_kernel(64, 64, 9) == ""
 
 

@@ -17,7 +17,7 @@ U = (20.0, 100.0)
 FORMS = {
     "direct 16x16": (100, 2112, 264, 16), "direct 16x32": (130, 520, 1000, 32), "direct 16x32, one K step": (70, 64, 72, 32),
     "direct 32x32": (333, 1032, 1096, 32), "direct 32x64": (500, 2112, 776, 64), "direct 64x64": (700, 1600, 1400, 64),
-    "direct 64x64, long K": (390, 3008, 1992, 64), "register-staged": (2049, 264, 776, None),
+    "direct 64x64, long K": (390, 3008, 1992, 64), "direct 32x32, three on a CU": (31, 776, 16424, 32), "register-staged": (2049, 264, 776, None),
     # no more tiles than are worked on at one time: split evenly, or one block per XCD
     "persistent 128, even split": (2100, 520, 1544, 128), "persistent 128, block per XCD": (2245, 72, 1288, 128),
     "persistent 256, even split": (3077, 136, 4808, 256), "persistent 256, block per XCD": (4100, 72, 2560, 256),
