@@ -461,17 +461,41 @@ int few_waves(int M, int N, int k_pad)
 // 8.5 / 8.8, 16 x 512 -> 8192 9.4 / 10.2.
 bool few_two_on_a_cu(int M, int waves) { return M <= kFewTwoM && waves <= 8; }
 
+// Most rows in turn (see few_tokens_fit) with the maxima given by the layer before.  The separate launches then are one less, and what
+// they cost the host is hidden by that layer, so the line lies at fewer turns than without.  us of both layers of an MLP (the first one a
+// quarter of the second's K wide), the second in separate launches / in this kernel (turns):
+//   N <= 4096  32 x 512 -> 128 18.8 / 17.9 (3), 48 x 512 20.1 / 21.1 (4), 16 x 1024 -> 256 17.7 / 17.1 (3), 20 x 1024 18.3 / 18.4 (4), 16 x 1536 -> 384
+//          17.8 / 17.3 (4), 20 x 1536 18.2 / 18.4 (5), 12 x 2048 -> 512 18.6 / 18.3 (4), 14 x 2048 18.7 / 18.8 (5); a longer K 10 x 3072 -> 768 18.7 / 18.3 (5),
+//          12 x 3072 19.3 / 19.7 (6), 5 x 5120 -> 1280 21.7 / 20.9, 8 x 5120 21.9 / 22.7, 5 x 4608 -> 1152 21.4 / 21.1, 8 x 4608 22.0 / 23.0, 5 x 4608 -> 4096
+//          22.1 / 22.5, 4 x 5120 -> 4096 21.3 / 21.2
+//   per token  24 x 512 -> 128 19.5 / 19.0 (2), 12 x 1024 -> 256 18.5 / 18.2 (2), 16 x 1024 19.1 / 19.2 (3), 9 x 2048 -> 512 19.6 / 19.3 (3), 10 x 2048 19.9 /
+//          19.9 (4), 8 x 3072 -> 768 20.0 / 19.8 (4), 9 x 3072 20.4 / 20.5 (5), 6 x 4096 -> 1024 20.0 / 19.7, -> 4096 20.6 / 21.1, 3 x 4608 -> 2560 21.5 /
+//          21.0, 4 x 4608 22.2 / 22.4
+//   beyond 24 x 512 -> 8192 18.9 / 18.8 (2), 32 x 512 19.2 / 19.3 (3), 12 x 1024 18.3 / 18.1 (2), 16 x 1024 18.5 / 18.7 (3), -> 5120 19.1 / 18.5, 6 x 1024 ->
+//          12288 20.0 / 19.8 (1), 10 x 1024 20.7 / 20.9 (2), 5 x 2048 -> 8192 18.6 / 19.2 (2), two workgroups on a CU 4 x 2048 18.6 / 18.3; 4 x 3072 -> 8192
+//          19.7 / 19.4 (2), 4 x 3072 -> 5120 19.1 / 19.3, 2 x 6400 -> 5120 24.5 / 25.2 (2), per token 3 x 4096 -> 8192 22.0 / 21.7, 4 x 4096 21.9 / 22.5 (2)
+int given_turns(int M, int K, int N, int k_pad, int pieces, bool per_token)
+{
+    if (N > 4096) {
+        if (few_two_on_a_cu(M, few_waves(M, N, k_pad))) return M;
+        if (pieces <= 3) return pieces > 1 && N > 8192 ? 1 : per_token || N > 6400 ? 2 : 3;
+        return pieces > 4 && N > 6400 && K <= 6144 && !(per_token && M * K > 12 * 1024) ? 2 : 1;
+    }
+    if (!per_token) return pieces <= 2 ? 3 : pieces > 4 && N <= 2560 ? 5 : 4;
+    if (M * K > (N > 2560 ? 20 : 24) * 1024) return 0;
+    return pieces <= 2 ? 2 : pieces > 4 && pieces <= 8 ? 4 : 3;
+}
+
 // X and its codes have to fit LDS together (about 42 K elements); below that the line against the separate
 // launches (selecting quantiser and GEMM, two or three of them, which cost the host alone 9.8 us) lies where what grows here
 // outweighs the launches saved: the rows that a wave works on one after the other (`turns`, counted for 12 waves and 16 whatever few_waves
 // gives, so that a row more never brings a call back) and the elements in them, which every workgroup repeats, and the walk over N, 16
-// channels per workgroup at a time with barriers between, from N = 4096 on.  us per call, the separate launches / this kernel (turns):
+// channels per workgroup at a time with barriers between, from N = 4096 on.  us per call, the separate launches / this kernel (turns), with
+// the maxima not given:
 //   N <= 4096  16 x 2056 -> 2048 11.5 / 10.0, 24 x 1536 10.1 / 9.1, 64 x 512 10.4 / 9.2, 12 x 3096 -> 2048 11.5 / 10.4, 40 x 800 10.9 /
-//          10.1, 8 x 4608 -> 2048 11.9 / 11.1, 9 x 4608 -> 4096 13.1 / 12.6, 10 x 4104 -> 4096 12.7 / 12.5.  With the maxima given, which leaves
-//          the separate launches one thing less to wait for: 8 x 5120 -> 1280 10.8 / 10.7, -> 3072 11.7 / 12.0, 9 x 4608 -> 2560 11.1 / 11.0,
-//          -> 3072 11.3 / 11.8, 6 x 6656 -> 3072 12.2 / 12.9, but two rows at a time 12 x 3400 -> 4096 11.1 / 11.0, 16 x 2600 -> 4096 11.0 / 10.1, and
-//          8 x 4104 (32 K elements) -> 4096 11.5 / 11.5.  One scale per token, whose maxima are one more walk over the rows: 10 x 2600 12.3 / 11.2
-//          (25 K elements), 8 x 3608 12.0 / 11.6 (28 K), 8 x 4104 12.3 / 13.4 (32 K), 7 x 4608 12.3 / 13.2, 6 x 4608 12.3 / 12.5
+//          10.1, 8 x 4608 -> 2048 11.9 / 11.1, 9 x 4608 -> 4096 13.1 / 12.6, 10 x 4104 -> 4096 12.7 / 12.5.  One scale per token, whose
+//          maxima are one more walk over the rows: 10 x 2600 12.3 / 11.2 (25 K elements), 8 x 3608 12.0 / 11.6 (28 K), 8 x 4104 12.3 / 13.4 (32 K), 7 x
+//          4608 12.3 / 13.2, 6 x 4608 12.3 / 12.5
 //   to 12288, K <= 2048  32 x 768 -> 12288 13.1 / 12.2 (6), 16 x 1280 -> 12288 13.1 / 12.9 (4), 12 x 1600 -> 8192 11.5 / 10.8 (4), -> 12288 13.4 /
 //          13.7; per token 48 x 512 -> 8192 13.1 / 11.9 (4), 32 x 768 -> 8192 12.6 / 12.7 (6), 24 x 1024 -> 8192 12.1 / 11.7 (4), -> 12288 14.0 / 14.2,
 //          9 x 1600 -> 8192 12.3 / 11.9 (3), -> 12288 14.0 / 14.6, 12 x 1600 -> 5120 11.8 / 12.1 (4)
@@ -492,12 +516,16 @@ bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token, b
     if (!long_lists) {
         const int pieces = (k_pad / 8 + 63) / 64, at_once = max((pieces > 4 ? 16 : 12) / pieces, 1), turns = (M + at_once - 1) / at_once;
         if (N > 12288) return pieces > 4 ? N > 16384 && fewest : pieces == 1 || few_two_on_a_cu(M, few_waves(M, N, k_pad));
+        if (maxima_given && N <= 12288) {
+            if (turns > given_turns(M, K, N, k_pad, pieces, per_token)) return false;
+            if (N > 4096) return true;
+        }
         if (N > 4096) {
             if (pieces > 4) return turns <= (per_token ? 2 : 3) - (K > 6144);
             const int most = per_token ? (pieces <= 3 ? 4 : 3) - (N > 8192) : pieces <= 2 ? 6 : N <= 8192 || pieces == 3 ? 4 : 3;
             return turns <= most && M * K <= 24 * 1024;
         }
-        if (per_token ? M * K > 26 * 1024 : maxima_given && pieces > 8 && M * K > 34 * 1024 && N > 2560) return false;
+        if (per_token && M * K > 26 * 1024) return false;
     }
     if (M <= 20) return true;
     if (M <= 32) return M * K <= (M <= 24 ? 36 : 32) * 1024;

@@ -262,9 +262,15 @@ def test_a_row_more_never_brings_a_call_back_to_the_one_launch(x_gran, absmax_re
 def test_code_kernels_by_size():
     """Both sides of the lines between the routes."""
     assert B.code_kernel(8, 4608, 1280) == B.code_kernel(9, 4608, 1280) == B.code_kernel(8, 5120, 1280) == "k_linear_few"
-    assert B.code_kernel(8, 5120, 1280, absmax_ready=True) == B.code_kernel(10, 4104, 2560, absmax_ready=True) == "k_linear_few"
-    assert B.code_kernel(8, 5120, 2568, absmax_ready=True) == B.code_kernel(10, 4104, 4096, absmax_ready=True) == "k_quantize_select"
-    assert B.code_kernel(16, 2600, 4096, absmax_ready=True) == B.code_kernel(8, 4104, 4096, absmax_ready=True) == "k_linear_few"
+    # with the column maxima given by the layer before: (M, K, N) of the last calls in the one launch, and a row more
+    for x_gran, last in (("tensor", [(36, 512, 128), (18, 1024, 4096), (16, 1536, 384), (12, 2048, 512), (12, 2560, 4096), (15, 2560, 640), (5, 5120, 1280),
+                                     (4, 5120, 4096), (24, 512, 8192), (12, 1024, 8192), (6, 1024, 12288), (4, 2048, 8192), (4, 3072, 8192),
+                                     (2, 3072, 5120), (1, 6400, 8192), (4, 2048, 16384)]),
+                         ("token", [(24, 512, 4096), (12, 1024, 256), (12, 1536, 4096), (9, 2048, 512), (6, 4096, 1024), (5, 4096, 4096),
+                                    (3, 6400, 2560), (24, 512, 8192), (8, 1536, 8192), (4, 2048, 5120), (1, 6400, 5120)])):
+        for M, K, N in last:
+            assert B.code_kernel(M, K, N, x_gran=x_gran, absmax_ready=True) == "k_linear_few", (M, K, N, x_gran)
+            assert B.code_kernel(M + 1, K, N, x_gran=x_gran, absmax_ready=True) != "k_linear_few", (M, K, N, x_gran)
     assert B.code_kernel(5, 1032, 5120, x_gran="token") == B.code_kernel(16, 1280, 8192, x_gran="token") == "k_linear_few"
     assert B.code_kernel(12, 1600, 5120, x_gran="token") == B.code_kernel(24, 1024, 12288, x_gran="token") == "k_rows_select"
     assert B.code_kernel(1, 4096, 12288) == B.code_kernel(1, 4096, 16392) == "k_linear_few"
