@@ -26,12 +26,16 @@ SHAPES = [(1, 8, 8), (1, 768, 2304), (1, 8192, 520), (2, 72, 24), (15, 4096, 136
           (1, 1032, 4104), (4, 1536, 8216), (5, 1032, 4104), (6, 1536, 8200),
           # either side of the line to the separate launches: rows in turn, elements with one scale per token, the walk over N
           (7, 5120, 136), (8, 5120, 136), (6, 4400, 72), (6, 4480, 72), (16, 768, 12280), (20, 768, 12280)]
+# those of them beyond that line, with one scale per call and per token
+SEPARATE = [(15, 4096, 136), (24, 5120, 264), (48, 2048, 72), (64, 1024, 264)]
+SEPARATE_TOKEN = SEPARATE + [(64, 64, 16), (5, 6400, 136), (7, 5120, 136), (8, 5120, 136), (6, 4480, 72), (20, 768, 12280)]
 
 
 @pytest.mark.parametrize("x_gran,w_gran", [("tensor", "tensor"), ("tensor", "channel"), ("token", "channel")])
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_few_tokens_all_stages(shape, x_gran, w_gran):
     M, K, N = shape
+    assert (B.code_kernel(M, K, N, x_gran=x_gran) == "k_linear_few") == (shape not in (SEPARATE if x_gran == "tensor" else SEPARATE_TOKEN))
     case = Case("few", M, K, N, min(6, K // 8), U, 600 + M)
     check_case(case, x_gran=x_gran, w_gran=w_gran, bias_seed=M if M % 2 else None)
     check_plain_y(case, x_gran=x_gran, w_gran=w_gran, bias_seed=3)
@@ -170,14 +174,28 @@ def test_one_workspace_for_both_layers(M, K, N1, N2, x_gran):
         assert torch.equal(H, H1) and torch.equal(Y, Y1)
 
 
-@pytest.mark.parametrize("x_gran", ["tensor", "token"])
-@pytest.mark.parametrize("M,K,N", [(16, 2624, 4360), (20, 2048, 24576), (24, 1536, 4360), (32, 1024, 12288), (33, 992, 264),
-                                   (40, 816, 264), (48, 512, 8192), (64, 512, 8192)])
-def test_longest_rows_and_widest_outputs(M, K, N, x_gran):
-    """The longest rows that each number of tokens runs with (every weight block of a wave is held), the
-    widest outputs; one row more, eight channels more of either, take the separate launches."""
-    check_case(Case("few_longest", M, K, N, 5, U, 680 + M), x_gran=x_gran, w_gran="channel", bias_seed=2)
-    if N in (8192, 12288, 24576):
-        check_plain_y(Case("few_wider", M, K, N + 8, 5, U, 690 + M), x_gran=x_gran, w_gran="channel")
-    else:
-        check_case(Case("few_longer", M + 1, K + 8, N, 5, U, 690 + M), x_gran=x_gran, w_gran="channel")
+# (M, K, N), then what makes it a call for the separate launches: one row ("M"), eight channels of K or of N more
+LIMITS = {
+    (64, "tensor"): [(8, 5328, 264, "MK"), (16, 2648, 264, "MK"), (20, 2104, 136, "MK"), (24, 1536, 264, "MK"), (32, 1024, 264, "MK"),
+                     (33, 992, 264, "MK"), (40, 816, 264, "MK"), (64, 512, 264, "MK"), (9, 2560, 8192, "MK"), (24, 1024, 12288, "MKN"),
+                     (48, 512, 8192, "MKN"), (1, 4096, 12288, "N"), (4, 2048, 16384, "MK"), (1, 1544, 24576, "N")],
+    (64, "token"): [(4, 6656, 264, "MK"), (8, 3328, 264, "MK"), (16, 1664, 264, "MK"), (24, 1104, 264, "MK"), (32, 832, 264, "MK"),
+                    (48, 512, 264, "MK"), (2, 6144, 8192, "MK"), (9, 2048, 8192, "MKN"), (16, 1024, 12288, "KN"), (48, 512, 8192, "MKN")],
+    (128, "tensor"): [(16, 2608, 4360, "MK"), (20, 2048, 24576, "MKN"), (24, 1536, 4360, "MK"), (32, 1024, 12288, "MKN"), (40, 816, 264, "MK"),
+                      (48, 512, 8192, "KN"), (64, 512, 8192, "MKN")],
+    (128, "token"): [(16, 2608, 4360, "MK"), (20, 2048, 24576, "MKN"), (24, 1536, 4360, "MK"), (32, 1024, 12288, "MKN"), (48, 512, 8192, "MKN")],
+}
+
+
+@pytest.mark.parametrize("r_cap,x_gran,M,K,N,ends", [(r, g, *s) for (r, g), shapes in LIMITS.items() for s in shapes])
+def test_longest_rows_and_widest_outputs(r_cap, x_gran, M, K, N, ends):
+    """The longest rows that each number of tokens runs with (with capacities above 64 every weight block of a wave is held and LDS is
+    full), the widest outputs; one row more, eight channels more take the separate launches."""
+    beyond = [(M + (e == "M"), K + 8 * (e == "K"), N + 8 * (e == "N")) for e in ends]
+    assert B.code_kernel(M, K, N, r_cap, x_gran) == "k_linear_few"
+    assert all(B.code_kernel(*s, r_cap, x_gran) in ("k_quantize_select", "k_rows_select") for s in beyond)
+    kw = dict(x_gran=x_gran, w_gran="channel", r_cap=r_cap)
+    check = check_plain_y if K * N > 10_000_000 else check_case        # (every stage, unless the weight is large)
+    check(Case("few_longest", M, K, N, 70 if r_cap > 64 else 5, U, 680 + M), bias_seed=2, **kw)
+    if N < 16384:
+        check(Case("few_longer", *beyond[-1], 5, U, 690 + M), **kw)
