@@ -443,11 +443,12 @@ __global__ __launch_bounds__(kFewMaxWaves * 64) void k_linear_few(const FewArgs 
 // them for the weights alone: whole groups / 16, 1 x 4368 -> 6424 13.2 / 12.3, 1 x 4608 -> 14336 22.0 / 20.2, 4 x 3072 -> 10240 15.0 / 14.5; with
 // one block of 16 channels to a workgroup 8 x 4608 -> 1280 11.0 / 11.2, 4 x 6144 -> 1280 9.5 / 9.5.  Where 8 would be 6, as three pieces make
 // them, 12 walk over N faster unless two workgroups share the CU (6 / 12 waves): 5 x 1280 -> 12288 12.7 / 11.8, per token 13.4 / 12.3, 6 x
-// 1536 -> 8192 10.2 / 9.8; one block of channels 6 x 1536 -> 4096 7.2 / 7.5.
+// 1536 -> 8192 10.2 / 9.8; one block of channels 6 x 1536 -> 4096 7.2 / 7.5.  Rows of four pieces take 16 from the fifth block of channels on (12
+// / 16): 5 x 2048 -> 24576 21.1 / 19.6, per token 22.1 / 20.4, 6 x 1600 -> 24576 19.8 / 18.9; 8 x 2048 -> 12288 13.2 / 13.4.
 int few_waves(int M, int N, int k_pad)
 {
     const int pieces = (k_pad / 8 + 63) / 64, loads = few_loads((M + 15) / 16);
-    if (pieces > 4 && N > 16 * kFewGrid) return kFewMaxWaves;
+    if (pieces > 4 ? N > 16 * kFewGrid : pieces == 4 && M > kFewTwoM && N > 4 * 16 * kFewGrid) return kFewMaxWaves;
     const bool few = M * pieces <= 20 && !(pieces == 3 && M > kFewTwoM && N > 16 * kFewGrid);
     const int want = pieces > 4 ? 16 : few ? 8 : 12;
     int waves = max(want / pieces, 1) * pieces;
@@ -502,9 +503,10 @@ int given_turns(int M, int K, int N, int k_pad, int pieces, bool per_token)
 //   to 12288 with a longer K  8 x 2560 -> 8192 12.3 / 11.9 (3), 6 x 4096 -> 8192 14.0 / 14.0 (3), 3 x 4608 -> 8192 14.3 / 13.7 (3), 8 x 4096 14.1 / 14.6
 //          (4), 5 x 4608 14.3 / 14.6 (5), 3 x 8192 -> 4104 16.1 / 16.7 (3); per token 5 x 2560 -> 8192 12.9 / 12.3 (2), 2 x 6144 16.3 / 15.9 (2), 6 x
 //          4096 14.7 / 15.3 (3), 3 x 4608 14.6 / 15.0, 2 x 8192 -> 4104 16.6 / 17.3 (2)
-//   to 16384, where the GEMM still has direct tiles and this kernel takes a step more  1 x 2056 14.4 / 15.4, 1 x 4096 19.0 / 19.1, 8 x 1024
-//          13.3 / 13.8, but 8 x 512 12.3 / 10.9; two workgroups on a CU 4 x 1536 13.3 / 12.2
-//   beyond, where it has not  4 x 2048 -> 24000 20.8 / 15.9, 1 x 2560 -> 20000 23.3 / 18.8, 8 x 2056 21.6 / 19.7, 8 x 4096 -> 24576 38.0 / 32.6
+//   to 16384, where the GEMM still has direct tiles and this kernel takes a step more  3 x 2560 15.4 / 16.7, 5 x 1024 12.6 / 13.1, 5 x 2048 14.2 /
+//          15.8, but 8 x 512 12.1 / 10.8; two workgroups on a CU 4 x 2048 14.1 / 12.7
+//   beyond, where it has not  8 x 4096 -> 24576 38.1 / 32.9, 10 x 4096 38.3 / 33.4, 12 x 3072 26.9 / 25.1, 12 x 2560 -> 20480 23.7 / 20.9, per token 9 x 2560
+//          -> 24576 24.8 / 24.2, 12 x 2560 24.9 / 25.3 (4); four pieces 9 x 2048 -> 24576 21.5 / 20.3 (3), per token 22.6 / 21.4, 9 x 1600 19.3 / 19.4
 // Long lists move it the other way (8 x 1280 -> 4096, 160 channels of at most 1024 listed, 19.6 / 11.0 with the separate launches of
 // before): capacities above 64 keep wider lines.
 bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token, bool maxima_given)
@@ -515,8 +517,11 @@ bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token, b
     if (N > (M > 32 ? 8192 : K > 1536 ? (fewest && K > 3072 ? 32768 : 24576) : fewest ? 16384 : 12288)) return false;
     if (!long_lists) {
         const int pieces = (k_pad / 8 + 63) / 64, at_once = max((pieces > 4 ? 16 : 12) / pieces, 1), turns = (M + at_once - 1) / at_once;
-        if (N > 12288) return pieces > 4 ? N > 16384 && fewest : pieces == 1 || few_two_on_a_cu(M, few_waves(M, N, k_pad));
-        if (maxima_given && N <= 12288) {
+        if (N > 12288) {
+            if (pieces > 4) return N > 16384 && !(per_token && pieces == 5 && turns > 3);
+            return pieces == 1 || few_two_on_a_cu(M, few_waves(M, N, k_pad)) || (pieces == 4 && N > 16384 && turns <= 3);
+        }
+        if (maxima_given) {
             if (turns > given_turns(M, K, N, k_pad, pieces, per_token)) return false;
             if (N > 4096) return true;
         }

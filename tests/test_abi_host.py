@@ -275,6 +275,12 @@ def test_code_kernels_by_size():
     assert B.code_kernel(12, 1600, 5120, x_gran="token") == B.code_kernel(24, 1024, 12288, x_gran="token") == "k_rows_select"
     assert B.code_kernel(1, 4096, 12288) == B.code_kernel(1, 4096, 16392) == "k_linear_few"
     assert B.code_kernel(1, 4096, 12296) == B.code_kernel(1, 4096, 16384) == "k_quantize_select"
+    # beyond N = 16384, where the GEMM has no direct tiles: whatever fits with a long K, rows in three turns with four pieces
+    for x_gran in ("tensor", "token"):
+        assert B.code_kernel(10, 4096, 24576, x_gran=x_gran) == B.code_kernel(13, 3072, 24576, x_gran=x_gran) == "k_linear_few"
+        assert B.code_kernel(9, 2560, 20000, x_gran=x_gran) == B.code_kernel(9, 2048, 24576, x_gran=x_gran) == "k_linear_few"
+        assert B.code_kernel(10, 2048, 24576, x_gran=x_gran) != "k_linear_few" != B.code_kernel(9, 2048, 16384, x_gran=x_gran)
+    assert B.code_kernel(12, 2560, 20000) == "k_linear_few" and B.code_kernel(10, 2560, 20000, x_gran="token") == "k_rows_select"
     assert B.code_kernel(30000, 4096, 64) == B.code_kernel(70, 8200, 64) == "k_quantize_body"
     assert B.code_kernel(4, 512, 64, aux_scale="own") == "k_quantize_body"
     assert B.code_kernel(70, 8200, 64, x_gran="token") == "k_quantize_rows_token"

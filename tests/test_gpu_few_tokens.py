@@ -24,6 +24,8 @@ SHAPES = [(1, 8, 8), (1, 768, 2304), (1, 8192, 520), (2, 72, 24), (15, 4096, 136
           (3, 2400, 4104), (2, 3400, 6424), (1, 4360, 4120), (1, 6400, 6424),
           # three pieces to a row: two workgroups of 6 waves on a CU, and 12 waves that walk over N
           (1, 1032, 4104), (4, 1536, 8216), (5, 1032, 4104), (6, 1536, 8200),
+          # rows of four pieces and of more beyond N = 16384: 16 waves
+          (5, 1544, 16392), (9, 2048, 16456), (9, 2064, 16392),
           # either side of the line to the separate launches: rows in turn, elements with one scale per token, the walk over N
           (7, 5120, 136), (8, 5120, 136), (6, 4400, 72), (6, 4480, 72), (16, 768, 12280), (20, 768, 12280)]
 # those of them beyond that line, with one scale per call and per token
