@@ -493,16 +493,20 @@ int given_turns(int M, int K, int N, int k_pad, int pieces, bool per_token)
 // gives, so that a row more never brings a call back) and the elements in them, which every workgroup repeats, and the walk over N, 16
 // channels per workgroup at a time with barriers between, from N = 4096 on.  us per call, the separate launches / this kernel (turns), with
 // the maxima not given:
-//   N <= 4096  16 x 2056 -> 2048 11.5 / 10.0, 24 x 1536 10.1 / 9.1, 64 x 512 10.4 / 9.2, 12 x 3096 -> 2048 11.5 / 10.4, 40 x 800 10.9 /
-//          10.1, 8 x 4608 -> 2048 11.9 / 11.1, 9 x 4608 -> 4096 13.1 / 12.6, 10 x 4104 -> 4096 12.7 / 12.5.  One scale per token, whose
-//          maxima are one more walk over the rows: 10 x 2600 12.3 / 11.2 (25 K elements), 8 x 3608 12.0 / 11.6 (28 K), 8 x 4104 12.3 / 13.4 (32 K), 7 x
-//          4608 12.3 / 13.2, 6 x 4608 12.3 / 12.5
-//   to 12288, K <= 2048  32 x 768 -> 12288 13.1 / 12.2 (6), 16 x 1280 -> 12288 13.1 / 12.9 (4), 12 x 1600 -> 8192 11.5 / 10.8 (4), -> 12288 13.4 /
-//          13.7; per token 48 x 512 -> 8192 13.1 / 11.9 (4), 32 x 768 -> 8192 12.6 / 12.7 (6), 24 x 1024 -> 8192 12.1 / 11.7 (4), -> 12288 14.0 / 14.2,
-//          9 x 1600 -> 8192 12.3 / 11.9 (3), -> 12288 14.0 / 14.6, 12 x 1600 -> 5120 11.8 / 12.1 (4)
-//   to 12288 with a longer K  8 x 2560 -> 8192 12.3 / 11.9 (3), 6 x 4096 -> 8192 14.0 / 14.0 (3), 3 x 4608 -> 8192 14.3 / 13.7 (3), 8 x 4096 14.1 / 14.6
-//          (4), 5 x 4608 14.3 / 14.6 (5), 3 x 8192 -> 4104 16.1 / 16.7 (3); per token 5 x 2560 -> 8192 12.9 / 12.3 (2), 2 x 6144 16.3 / 15.9 (2), 6 x
-//          4096 14.7 / 15.3 (3), 3 x 4608 14.6 / 15.0, 2 x 8192 -> 4104 16.6 / 17.3 (2)
+//   N <= 4096  18 x 2048 10.9 / 9.7, 30 x 1024 9.9 / 8.8, 60 x 512 9.9 / 9.2; from the ninth piece on the elements decide 8 x 4608 -> 2560 11.6 / 11.3,
+//          7 x 4608 -> 4096 12.0 / 12.1, 8 x 4608 12.0 / 12.4, 8 x 5120 -> 4096 12.2 / 12.7, 4 x 8192 13.7 / 13.4
+//   per token, whose maxima are one more walk over the rows  48 x 512 11.0 / 10.3 (4), 60 x 512 10.9 / 11.3 (5), 24 x 768 10.6 / 10.1 (4), 30 x 768 10.7 /
+//          10.9 (5), 16 x 1536 10.7 / 10.4 (4), 15 x 2048 11.8 / 11.3 (5), 18 x 2048 11.6 / 12.4 (6), 12 x 2560 12.2 / 12.0 (4, 30 K elements), 15 x 2560
+//          12.2 / 13.2, 10 x 3072 -> 2560 12.3 / 11.6 (5), 6 x 4096 -> 2560 11.7 / 11.3 (3), -> 4096 12.0 / 12.1, 8 x 4096 11.8 / 12.2; from the ninth piece on
+//          5 x 4608 -> 2560 12.2 / 11.8, 6 x 4608 12.3 / 12.6, 3 x 4608 -> 4096 12.3 / 11.6, 4 x 4608 12.4 / 12.4, 4 x 8192 -> 768 13.6 / 12.6
+//   to 12288, up to four pieces  36 x 768 -> 8192 12.4 / 11.0 (6), -> 12288 13.1 / 13.1, 12 x 1536 -> 12288 12.8 / 12.7 (3), 16 x 1536 12.9 / 13.1, 12 x 1600 ->
+//          8192 11.2 / 10.8 (4), 15 x 1600 11.1 / 11.2, 9 x 1600 -> 12288 13.0 / 13.0 (3), 12 x 1600 13.2 / 13.4; per token 48 x 512 -> 8192 12.7 / 11.7
+//          (4), 24 x 768 11.4 / 11.5 (4), 18 x 768 -> 12288 13.0 / 12.4 (3), 12 x 1536 -> 8192 11.9 / 11.8 (3), 16 x 1536 12.0 / 12.7, -> 5120 12.0 / 12.1, 8
+//          x 1536 -> 12288 13.5 / 13.3 (2), 12 x 1536 13.7 / 14.2, 9 x 1600 -> 5120 11.5 / 11.2 (3), 12 x 1600 11.6 / 12.1, 6 x 2048 -> 8192 11.7 / 11.7 (2)
+//   to 12288, more pieces  2 x 3072 -> 5120 11.0 / 11.2 (1), 4 x 3072 11.2 / 11.5, 4 x 4096 12.3 / 12.8: up to N = 6400 the GEMM does not fill the CUs and
+//          this kernel walks two steps all the same; 9 x 2560 -> 8192 12.4 / 12.1 (3), 12 x 2560 12.4 / 12.6, 3 x 4608 13.7 / 13.7 (3), 4 x 4608 13.9 / 14.1,
+//          3 x 5120 -> 12288 18.6 / 18.2 (3), 2 x 8192 -> 8192 17.7 / 17.6 (2); per token 2 x 3072 12.7 / 12.1 (1), 4 x 3072 12.7 / 12.8, 2 x 5120 15.1 /
+//          14.7 (2), 3 x 5120 15.1 / 15.4, 1 x 6400 16.5 / 15.8, 2 x 6400 16.4 / 16.7
 //   to 16384, where the GEMM still has direct tiles and this kernel takes a step more  3 x 2560 15.4 / 16.7, 5 x 1024 12.6 / 13.1, 5 x 2048 14.2 /
 //          15.8, but 8 x 512 12.1 / 10.8; two workgroups on a CU 4 x 2048 14.1 / 12.7
 //   beyond, where it has not  8 x 4096 -> 24576 38.1 / 32.9, 10 x 4096 38.3 / 33.4, 12 x 3072 26.9 / 25.1, 12 x 2560 -> 20480 23.7 / 20.9, per token 9 x 2560
@@ -524,13 +528,18 @@ bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token, b
         if (maxima_given) {
             if (turns > given_turns(M, K, N, k_pad, pieces, per_token)) return false;
             if (N > 4096) return true;
-        }
-        if (N > 4096) {
-            if (pieces > 4) return turns <= (per_token ? 2 : 3) - (K > 6144);
-            const int most = per_token ? (pieces <= 3 ? 4 : 3) - (N > 8192) : pieces <= 2 ? 6 : N <= 8192 || pieces == 3 ? 4 : 3;
+        } else if (N > 4096) {
+            if (pieces > 4) return turns <= (N <= 6400 ? 1 : per_token ? 1 + (pieces > 8 && K <= 6144) : 3 - (K > 6144));
+            const int most = !per_token ? (pieces <= 2 ? 6 : N <= 8192 || pieces == 3 ? 4 : 3)
+                           : pieces <= 2 ? 4 - (N > 8192) : pieces == 3 ? 4 - (N > 6400) - (N > 8192) : 3 - (N > 6400);
             return turns <= most && M * K <= 24 * 1024;
+        } else if (!per_token) {
+            if (pieces > 8 && M * K > 34 * 1024 && N > 2560) return false;
+        } else if (pieces > 8) {
+            if (N > 2560 ? turns > 3 : M * K > 26 * 1024 && (N > 1536 || turns > 4)) return false;
+        } else if (turns > (pieces <= 3 ? 4 : pieces <= 6 ? 5 : 3) || M * K > 31 * 1024) {
+            if (pieces <= 3 || M * K > 26 * 1024 || (pieces > 6 && N > 2560)) return false;
         }
-        if (per_token && M * K > 26 * 1024) return false;
     }
     if (M <= 20) return true;
     if (M <= 32) return M * K <= (M <= 24 ? 36 : 32) * 1024;

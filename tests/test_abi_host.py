@@ -271,7 +271,16 @@ def test_code_kernels_by_size():
         for M, K, N in last:
             assert B.code_kernel(M, K, N, x_gran=x_gran, absmax_ready=True) == "k_linear_few", (M, K, N, x_gran)
             assert B.code_kernel(M + 1, K, N, x_gran=x_gran, absmax_ready=True) != "k_linear_few", (M, K, N, x_gran)
-    assert B.code_kernel(5, 1032, 5120, x_gran="token") == B.code_kernel(16, 1280, 8192, x_gran="token") == "k_linear_few"
+    assert B.code_kernel(5, 1032, 5120, x_gran="token") == B.code_kernel(12, 1280, 8192, x_gran="token") == "k_linear_few"
+    # (M, K, N) of the last calls in the one launch, and a row more
+    for x_gran, last in (("tensor", [(7, 4608, 4096), (6, 5120, 4096), (8, 5120, 2560), (12, 1600, 8192), (16, 1536, 12288), (16, 1280, 8192),
+                                     (3, 2560, 5120), (2, 4096, 6400), (9, 2560, 8192), (2, 6400, 8192)]),
+                         ("token", [(48, 512, 4096), (24, 768, 4096), (16, 1536, 768), (15, 2048, 4096), (12, 2560, 4096), (10, 3072, 768),
+                                    (6, 4096, 4096), (3, 4608, 4096), (5, 4608, 2560), (4, 8192, 768), (24, 768, 8192), (12, 1536, 8192),
+                                    (9, 2048, 5120), (6, 2048, 8192), (3, 2560, 12288), (2, 5120, 12288), (1, 6400, 12288), (1, 8192, 4104)])):
+        for M, K, N in last:
+            assert B.code_kernel(M, K, N, x_gran=x_gran) == "k_linear_few", (M, K, N, x_gran)
+            assert B.code_kernel(M + 1, K, N, x_gran=x_gran) != "k_linear_few", (M, K, N, x_gran)
     assert B.code_kernel(12, 1600, 5120, x_gran="token") == B.code_kernel(24, 1024, 12288, x_gran="token") == "k_rows_select"
     assert B.code_kernel(1, 4096, 12288) == B.code_kernel(1, 4096, 16392) == "k_linear_few"
     assert B.code_kernel(1, 4096, 12296) == B.code_kernel(1, 4096, 16384) == "k_quantize_select"

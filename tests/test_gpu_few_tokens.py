@@ -181,8 +181,8 @@ LIMITS = {
     (64, "tensor"): [(8, 5328, 264, "MK"), (16, 2648, 264, "MK"), (20, 2104, 136, "MK"), (24, 1536, 264, "MK"), (32, 1024, 264, "MK"),
                      (33, 992, 264, "MK"), (40, 816, 264, "MK"), (64, 512, 264, "MK"), (9, 2560, 8192, "MK"), (24, 1024, 12288, "MKN"),
                      (48, 512, 8192, "MKN"), (1, 4096, 12288, "N"), (4, 2048, 16384, "MK"), (1, 1544, 24576, "N")],
-    (64, "token"): [(4, 6656, 264, "MK"), (8, 3328, 264, "MK"), (16, 1664, 264, "MK"), (24, 1104, 264, "MK"), (32, 832, 264, "MK"),
-                    (48, 512, 264, "MK"), (2, 6144, 8192, "MK"), (9, 2048, 8192, "MKN"), (16, 1024, 12288, "KN"), (48, 512, 8192, "MKN")],
+    (64, "token"): [(4, 8192, 264, "MK"), (8, 3328, 264, "MK"), (12, 2560, 264, "MK"), (16, 1664, 264, "MK"), (24, 1024, 264, "MK"),
+                    (48, 512, 264, "MK"), (2, 6144, 8192, "MK"), (6, 2048, 8192, "MK"), (16, 1024, 12288, "KN"), (48, 512, 8192, "MKN")],
     (128, "tensor"): [(16, 2608, 4360, "MK"), (20, 2048, 24576, "MKN"), (24, 1536, 4360, "MK"), (32, 1024, 12288, "MKN"), (40, 816, 264, "MK"),
                       (48, 512, 8192, "KN"), (64, 512, 8192, "MKN")],
     (128, "token"): [(16, 2608, 4360, "MK"), (20, 2048, 24576, "MKN"), (24, 1536, 4360, "MK"), (32, 1024, 12288, "MKN"), (48, 512, 8192, "MKN")],
