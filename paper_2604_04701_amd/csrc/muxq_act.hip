@@ -663,7 +663,8 @@ hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool give
 {
     ActArgs a = args;
     a.by_chunks = divisor(a.k_pad / 8);
-    a.cut = magnitude_cut(a.threshold);
+    const bool is_static = a.static_mask != nullptr;
+    if (!given && !is_static) a.cut = magnitude_cut(a.threshold);
     // every workgroup selects for itself, so no more of them than are resident at once, but enough for
     // a share of the weight side each (4 output channels a wave)
     const int most = 256;
@@ -687,7 +688,6 @@ hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool give
     const int grid = min(max((units + (per_token ? a.groups : a.waves) - 1) / (per_token ? a.groups : a.waves), weight_side), most);
     if (!per_token) a.groups = min(grid * a.waves / (a.k_pad / 64), (a.M + 7) / 8);
     void (*kern)(const ActArgs);
-    const bool is_static = a.static_mask != nullptr;
     if (!per_token)
         kern = given ? k_quantize_select<true> : k_quantize_select<false>;
     else if (form == 0)

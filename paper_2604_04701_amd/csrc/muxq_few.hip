@@ -573,7 +573,7 @@ hipError_t launch_linear_few(const FewArgs &a, hipStream_t s)
     // every workgroup repeats the activation side: no more of them than are resident at once
     const int nblk = (a.N + 15) / 16, waves = few_waves(a.M, a.N, a.k_pad), grid = min(nblk, few_two_on_a_cu(a.M, waves) ? 2 * kFewGrid : kFewGrid);
     FewPlan plan = few_plan(a.M, a.K, a.k_pad, a.r_cap, grid, waves);
-    plan.cut = magnitude_cut(a.threshold);
+    plan.cut = a.static_mask != nullptr ? 0 : magnitude_cut(a.threshold);
     return launch_kernel(few_kernel((a.M + 15) / 16, a.x_per_token != 0), dim3(grid), dim3(plan.waves * 64), plan.total, s,
                          a, plan);
 }

@@ -159,19 +159,13 @@ __device__ __forceinline__ uint32_t chunk_candidates(uint4 mx, float threshold, 
     }
     return (m | m >> 15) & 0xffu;
 }
+// (On the host, in every call with a threshold: the conversion to fp16, rounded towards zero.  A search over the values took 0.11 us.)
 inline int magnitude_cut(float threshold)
 {
     if (!(threshold >= 0.f)) return -1;
-    int lo = 0, hi = 0x7c00;                             // +0 is not over it; bits of fp16 order like the values
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) / 2;
-        const float v = mid == 0x7c00 ? __builtin_inff()
-                      : mid < 0x400 ? __builtin_ldexpf((float)mid, -24)
-                                    : __builtin_ldexpf((float)(0x400 | (mid & 0x3ff)), (mid >> 10) - 25);
-        if (v <= threshold) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
+    if (threshold > 65504.f) return threshold == __builtin_inff() ? 0x7c00 : 0x7bff;
+    if (threshold < 0x1p-14f) return (int)(threshold * 0x1p24f);         // subnormal: in units of 2^-24 (and -0)
+    return (int)(__builtin_bit_cast(uint32_t, threshold) >> 13) - ((127 - 15) << 10);
 }
 
 // Sec. III-C with the capacity rule: the r_cap lowest candidates are listed.  The first `n_seg` pieces

@@ -30,7 +30,8 @@ def test_select_and_quantise_capacity(r_cap, r, x_gran):
     check_case(Case("act_cap", 333, 712, 136, r, U, 940 + r), r_cap=r_cap, e=3, x_gran=x_gran)
 
 
-@pytest.mark.parametrize("threshold", [-1.0, 0.0, 2.0 ** -25, 2.0 ** -24, 3.5e-5, 6.0, 6.001, 65504.0, float("inf")])
+@pytest.mark.parametrize("threshold", [-1.0, -0.0, 0.0, 1e-40, 2.0 ** -25, 2.0 ** -24, 3.5e-5, 2.0 ** -14 - 2.0 ** -25, 2.0 ** -14, 6.0, 6.001,
+                                       65503.9, 65504.0, 65519.0, 65520.0, 1e30, float("inf")])
 @pytest.mark.parametrize("M", [3, 300])
 def test_thresholds(M, threshold):
     """The threshold is any binary32 value, also between two fp16 values, below the smallest or above the largest
