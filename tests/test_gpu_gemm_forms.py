@@ -12,12 +12,14 @@ from paper_2604_04701_amd.synth import Case
 pytestmark = pytest.mark.gpu
 U = (20.0, 100.0)
 
-# Rows of the output tile of each form; the register-staged form takes no column maxima, so the count
-# it leaves is that of a pass over the output.
+# M, K, N and the rows of the output tile of each form.
 FORMS = {
     "direct 16x16": (100, 2112, 264, 16), "direct 16x32": (130, 520, 1000, 32), "direct 16x32, one K step": (70, 64, 72, 32),
     "direct 32x32": (333, 1032, 1096, 32), "direct 32x64": (500, 2112, 776, 64), "direct 64x64": (700, 1600, 1400, 64),
-    "direct 64x64, long K": (390, 3008, 1992, 64), "direct 32x32, three on a CU": (31, 776, 16424, 32), "register-staged": (2049, 264, 776, None),
+    "direct 64x64, long K": (390, 3008, 1992, 64), "direct 32x32, three on a CU": (31, 776, 16424, 32),
+    # fewer K steps than waves (with several Aux steps: the list below), or not many more
+    "direct 64x64, one K step": (1016, 64, 1024, 64), "direct 64x64, five K steps": (1024, 264, 1000, 64),
+    "persistent 128, short K": (2049, 264, 776, 128), "persistent 128, one K step": (1536, 64, 1536, 128),
     # no more tiles than are worked on at one time: split evenly, or one block per XCD
     "persistent 128, even split": (2100, 520, 1544, 128), "persistent 128, block per XCD": (2245, 72, 1288, 128),
     "persistent 256, even split": (3077, 136, 4808, 256), "persistent 256, block per XCD": (4100, 72, 2560, 256),
@@ -32,8 +34,8 @@ FORMS = {
 @pytest.mark.parametrize("form", FORMS)
 def test_gemm_forms(form, x_gran, w_gran, bias_seed):
     M, K, N, tile_rows = FORMS[form]
-    if tile_rows is not None:
-        assert B.lib().muxq_linear_gelu_slabs(M, K, N) == (M + tile_rows - 1) // tile_rows
+    assert B.lib().muxq_linear_gelu_slabs(M, K, N) == (M + tile_rows - 1) // tile_rows
+    assert B.gemm_kernel(M, K, N) == {64: "k_gemm_i8_direct", 128: "k_gemm_i8_persist4", 256: "k_gemm_i8_persist8"}[max(tile_rows, 64)]
     case = Case("form", M, K, N, min(6, K // 8), U, 800 + M)
     if M * N <= 2000 * 1600:
         check_case(case, x_gran=x_gran, w_gran=w_gran, bias_seed=bias_seed)
@@ -51,10 +53,11 @@ def test_one_k_step_per_tile_and_several_tiles_per_workgroup(M, N, tile_rows, x_
 
 
 @pytest.mark.parametrize("x_gran", ["tensor", "token"])
-@pytest.mark.parametrize("shape", [(100, 2112, 264), (130, 520, 1000), (333, 1032, 1096), (500, 2112, 776)],
-                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", [(100, 2112, 264), (130, 520, 1000), (333, 1032, 1096), (500, 2112, 776), (700, 1600, 1400),
+                                   (1000, 200, 1024)], ids=lambda s: "x".join(map(str, s)))
 def test_direct_forms_several_aux_steps_and_own_scale(shape, x_gran):
     M, K, N = shape
+    assert B.gemm_kernel(M, K, N) == "k_gemm_i8_direct"
     check_case(Case("form_aux", M, K, N, 150, U, 820 + M), r_cap=192, e=3, x_gran=x_gran)
     X = np.random.default_rng(M).uniform(-5.0, 5.0, size=(M, K)).astype(np.float32)
     X[:, ::K // 8] *= 1.5
@@ -66,6 +69,18 @@ def test_direct_forms_several_aux_steps_and_own_scale(shape, x_gran):
                          ids=lambda s: "x".join(map(str, s)))
 def test_direct_forms_hand_the_column_maxima_over(shape):
     check_mlp(*shape, 840 + shape[0])
+
+
+@pytest.mark.parametrize("w_gran,x_gran", [("tensor", "tensor"), ("channel", "token")])
+@pytest.mark.parametrize("shape,tile_rows", [((1040, 1544, 48, 72), 16), ((2080, 72, 64, 136), 32), ((1041, 1600, 40, 24), 16)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else f"tile_rows_{v}")
+def test_more_than_64_rows_of_tiles(shape, tile_rows, w_gran, x_gran):
+    """More rows of tiles than the next layer takes slabs: the column maxima come from a pass over H."""
+    M, K, N, N2 = shape
+    assert (M + tile_rows - 1) // tile_rows > 64
+    assert B.gemm_kernel(M, K, N) == "k_gemm_i8_direct"
+    n = check_mlp(M, K, N, N2, 850 + M, w_gran=w_gran, x_gran=x_gran)
+    assert n <= 64 and n != (M + tile_rows - 1) // tile_rows
 
 
 @pytest.mark.parametrize("N,ldy", [(4808, 4808), (4816, 4816), (4832, 4832), (4864, 4864), (4808, 4832), (4832, 4840)])

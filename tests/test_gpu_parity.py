@@ -362,7 +362,7 @@ def test_large_tile_path_several_aux_steps(r_cap, r):
 # Middle sizes.  The 128 x 128 form of the DMA-ring GEMM runs where its rounds of 256 tiles are fewer than
 # three times those of the 256 x 256 form and there are too many tiles for the direct forms: here the
 # second case (one tile per workgroup).  The first runs direct 16 x 32 tiles, the third (K = 64) the
-# register-staged form.
+# 128 x 128 form with one K step to a tile.
 MID = [
     Case("mid_long_k", 300, 2112, 264, 7, U, 41),
     Case("mid_one_round", 1500, 1032, 1544, 5, U, 42),
@@ -810,14 +810,14 @@ def test_own_scale_aux_per_token_full_size_and_loud_outliers():
     ((2049, 512, 2048, 512), 128),
     ((4096, 64, 4096, 72), 256),                           # one-step K loop
     ((4096, 520, 4104, 72), 128),                          # several tiles per workgroup
-    ((1500, 512, 1544, 136), None),                        # register-staged: maxima by a pass over H
+    ((1500, 512, 1544, 136), 128),                         # one tile per workgroup
+    ((1000, 264, 1000, 136), 64),                          # direct 64 x 64 with a short K
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else f"tile_rows_{v}")
 @pytest.mark.parametrize("w_gran,x_gran", [("tensor", "tensor"), ("channel", "token")])
 def test_mlp_gelu_fused_into_the_first_gemm(shape, tile_rows, w_gran, x_gran):
     M, K, N1, N2 = shape
     n = check_mlp(M, K, N1, N2, seed=M + K, w_gran=w_gran, x_gran=x_gran)
-    if tile_rows is not None:                              # one slab per row of tiles
-        assert n == (M + tile_rows - 1) // tile_rows
+    assert n == (M + tile_rows - 1) // tile_rows           # one slab per row of tiles
 
 
 def test_mlp_full_size_gpt2_medium():
