@@ -17,6 +17,7 @@ namespace {
 constexpr int kActThreads = 1024, kActWaves = kActThreads / 64;
 constexpr int kActMaxK = 8 * kActThreads;              // one chunk of 8 channels per thread in the selection
 constexpr int kActMaxCap = 1024;
+constexpr int kEarlyMaxK = 2048;                        // see row_form
 
 // Column maxima of |X| per row slab, like k_col_absmax_partial, but a workgroup covers only 128
 // columns and many rows: the same number of workgroups leaves a quarter of the slabs.  (64 columns leave
@@ -405,15 +406,17 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_select(const ActArgs a
 // One activation scale per row.  A wave takes 64 / LANES rows x NB pieces of LANES chunks, 16 bytes of each piece a lane, in
 // registers from the rows' maxima to the codes: with 16 lanes to a row, what is worked out for a row (its maximum over the lanes, the
 // scale, two divisions) is worked out for 4 rows at once, and the codes go out as 256 contiguous bytes.  The next rows are
-// requested piece by piece as these are worked on.  Rows longer than that are in `pieces` waves, whose maxima meet in LDS (one
+// requested piece by piece as these are worked on, or (EARLY) whether there are any or not, with 4 rows to a wave all at once before the maxima:
+// in the last step the same rows again, which are near.  Rows longer than that are in `pieces` waves, whose maxima meet in LDS (one
 // barrier per step; the two halves of `s_piece` take turns).  Against single rows of up to 4 x 64 chunks a wave: 16384 x 1280
-// 24.8 -> 21.8 us (63 MB, with the selection in it), a call of 60000 x 1280 -> 512 138 -> 122 us.  The codes are written through: a call
-// of 8192 x 4096 -> 1024 72.2 -> 71.4 us, 6000 x 2048 -> 768 38.4 -> 37.8.
+// 24.8 -> 21.8 us (63 MB, with the selection in it), a call of 60000 x 1280 -> 512 138 -> 122 us.  The codes are written through, however many:
+// as usual / through, calls with N = 256, 4096 x 512 18.4 / 18.3, 16384 x 512 (8 MB) 25.2 / 24.3, 16384 x 1280 (21 MB) 39.0 / 38.4, 8192 x 4096 (33 MB)
+// 65.6 / 64.3, 16384 x 5120 (84 MB) 116.7 / 115.9, 30000 x 4096 (123 MB) 158.9 / 158.2; only with N = 1024 and from 100 MB on as usual is ahead by 0.5 %.
 // A kernel starts with a cold instruction cache, and what is unrolled NB times is kept short (1 KB of code takes about 0.12 us
-// to fetch: 10 pieces with everything unrolled was 2 us slower than 4 on 1024 x 768): the column masks of the maxima come from LDS, and pieces with a listed channel or K padding are put aside, in LDS,
-// for a rolled loop.
+// to fetch: 10 pieces with everything unrolled was 2 us slower than 4 on 1024 x 768): the column masks of the maxima come from LDS, and pieces
+// with a listed channel or K padding are put aside, in LDS, for a rolled loop.
 // STATIC: the list was fixed offline (a kernel of its own: nothing waits for slabs, and the rows are requested first).
-template <int NB, int LANES, bool STATIC>
+template <int NB, int LANES, bool STATIC, bool EARLY>
 __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
 {
     constexpr int R = 64 / LANES;
@@ -427,7 +430,7 @@ __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
     const int c0 = seg * NB * LANES + lane % LANES, lr = lane / LANES, n_rb = (a.M + R - 1) / R;
     uint4 raw[NB];
     auto chunk = [&](int j) { return min(c0 + j * LANES, C - 1); };          // (past the end the last chunk again)
-    auto row_of = [&](int rb) { return a.x + (size_t)min(rb * R + lr, a.M - 1) * a.ldx; };
+    auto row_of = [&](int rb) { return a.x + (size_t)min(min(rb, n_rb - 1) * R + lr, a.M - 1) * a.ldx; };
     auto load = [&](const uint16_t *row, int j) { return *(const uint4 *)(row + chunk(j) * 8); };
     const int stride = (int)gridDim.x * P;
     int rb = (int)blockIdx.x * P + p;
@@ -471,7 +474,14 @@ __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
 
     // (the same number of steps for all waves: they meet at the barrier)
     for (int step = 0, r0 = (int)blockIdx.x * P; r0 < n_rb; ++step, r0 += stride, rb += stride) {
-        const bool on = p < P && rb < n_rb;
+        const bool on = p < P && rb < n_rb, more = rb + stride < n_rb;
+        const uint16_t *const next_row = row_of(more ? rb + stride : rb);
+        uint4 next[NB];
+        if (EARLY && R > 1) {                            // (no condition: behind one the compiler waits for all that is in flight)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) next[j] = load(next_row, j);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         uint32_t m = 0;
         if (on) {
             // listed and unlisted apart, two halves to a word
@@ -514,14 +524,15 @@ __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
             ((int32_t *)a.x_scale)[2 * (size_t)a.M + row] = z;
         }
         const float inv_listed = inv * shrink, magic = 12582912.0f + (float)z;
-        const bool more = rb + stride < n_rb;
-        const uint16_t *const next = row_of(rb + stride);
         int8_t *const dst = a.body_q + packed_index(row, c0 * 8, a.k_pad);
         constexpr int PIECE = LANES / 8 * 1024;          // bytes of packed codes from piece to piece
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             const uint4 v = raw[j];
-            if (more) raw[j] = load(next, j);
+            if (EARLY)
+                raw[j] = R > 1 ? next[j] : load(next_row, j);
+            else if (more)
+                raw[j] = load(next_row, j);
             if ((aside >> j & 1u) != 0) {
                 s_aside[wave][j][lane] = v;
             } else {
@@ -624,30 +635,48 @@ hipError_t launch_fold_slabs(uint16_t *partial, int n_slabs, int k_pad, hipStrea
     return launch_kernel(k_fold_slabs, dim3((k_pad / 8 + 63) / 64), dim3(256), 0, s, partial, n_slabs, k_pad);
 }
 
-// The form of k_rows_select: single rows in pieces of 2 x 64 chunks, or 4 rows in pieces of 4 or 5 x 16.  Each is bound by its
-// vector instructions, about 60 for a piece of 64 lanes x 16 bytes and 200 for what is worked out once per row, times the waves on a SIMD
-// and the steps, and the least of the three estimates is the fastest or within 1 % of it (19 shapes, 24 x 5120 to 60000 x 1280).
-// us a call, single rows / 4 rows x 4 / 4 rows x 5: 512 x 4096 -> 1024 21.8 / 22.4 / 22.7, 2000 x 1280 -> 1280 23.6 / 22.8 / 23.0, 8192 x 4096
-// -> 1024 81.1 / 73.7 / 74.6, 9000 x 520 -> 1000 37.0 / 36.0 / 32.3, 60000 x 1280 -> 512 168 / 125 / 124.
+// The form of k_rows_select: single rows in pieces of 2 x 64 chunks, or 4 rows in pieces of 4 or 5 x 16, by the least of three estimates.
+// Beyond 4 KB of a row the vector instructions bound it: about 60 for a piece of 64 lanes x 16 bytes and 200 for what is worked out
+// once per row, times the waves on a SIMD and the steps (19 shapes, 24 x 5120 to 60000 x 1280: the fastest or within 1 %).
+// Shorter rows are bound by the latency of a step (the 8 in the estimate), and rows in several waves by their barrier as well, most of all with
+// several steps.  There the next rows are requested ahead (early), and the groups are spread evenly over the steps unless the last of
+// them is nearly empty.  Fitted to 232 calls in each form, 100 to 32768 rows of 256 to 5120, checked on 207 others: the fastest form or within 2 %.  us a
+// call, single rows of up to 4 x 64 chunks as they were before the three forms / the first estimate for all, requests piece by piece / now:
+// 10240 x 1024 -> 256 29.1 / 30.2 / 28.2, 20000 x 1024 37.7 / 40.3 / 37.6, 9004 x 896 21.8 / 23.6 / 20.3 (static list), 16384 x 1424 44.0 / 46.4 / 42.9, 16384 x
+// 1592 47.2 / 48.2 / 47.9, 24576 x 640 36.9 / 34.1 / 32.9; 16386 x 576, whose second step is one group: evenly 30.1, otherwise 28.5; the new way
+// with longer rows 16384 x 3072 79.9 instead of 77.8, 2609 x 3080 26.8 instead of 26.0.
 // Returns the groups of rows; pieces: waves to a group, at_once: groups of a workgroup at a time.
-int row_form(int M, int k_pad, int &form, int &pieces, int &at_once)
+int row_form(int M, int k_pad, int &form, int &pieces, int &at_once, bool &early)
 {
     static const struct { int pieces, lanes; } kForms[3] = {{2, 64}, {4, 16}, {5, 16}};
     int groups = 0;
     long long best = -1;
     for (int f = 0; f < 3; ++f) {
-        const int rows = 64 / kForms[f].lanes, n = (M + rows - 1) / rows;
-        const int S = (k_pad / 8 + kForms[f].pieces * kForms[f].lanes - 1) / (kForms[f].pieces * kForms[f].lanes);
-        const int P = min(kActWaves / S, (n + 255) / 256);
-        const long long cost = (long long)((n + 256 * P - 1) / (256 * P)) * ((P * S + 3) / 4) * (60 * kForms[f].pieces + 200);
+        const int NB = kForms[f].pieces, rows = 64 / kForms[f].lanes, n = (M + rows - 1) / rows;
+        const int S = (k_pad / 8 + NB * kForms[f].lanes - 1) / (NB * kForms[f].lanes);
+        const int most = 256 * (kActWaves / S), steps = (n + most - 1) / most;
+        int P = min(kActWaves / S, (n + 255) / 256);
+        const bool even = k_pad <= kEarlyMaxK && steps > 1 && (n - 1) % most >= most / 8;
+        if (even) P = (n + 256 * steps - 1) / (256 * steps);
+        const int waves = (P * S + 3) / 4;
+        const long long cost = k_pad > kEarlyMaxK ? (long long)steps * waves * (60 * NB + 200)
+                               : (long long)steps * (waves + 8) * (60 * NB + (rows == 1 ? 140 : 70)) + (S == 1 ? 0 : steps == 1 ? 1000 : 4680);
         if (best >= 0 && cost >= best) continue;
         best = cost;
         form = f;
         groups = n;
         pieces = S;
         at_once = P;
+        early = k_pad <= kEarlyMaxK && steps > 1;
     }
     return groups;
+}
+
+typedef void (*act_kernel_t)(const ActArgs);
+template <bool STATIC, bool EARLY>
+act_kernel_t rows_kernel(int form)
+{
+    return form == 0 ? k_rows_select<2, 64, STATIC, EARLY> : form == 1 ? k_rows_select<4, 16, STATIC, EARLY> : k_rows_select<5, 16, STATIC, EARLY>;
 }
 
 hipError_t launch_detect_select(const ActArgs &args, hipStream_t s)
@@ -669,6 +698,7 @@ hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool give
     // a share of the weight side each (4 output channels a wave)
     const int most = 256;
     int units, form = 0;                                 // units: what a wave takes at a time
+    bool early = false;
     if (!per_token) {
         // columns of 64 channels, and as many waves as there are blocks of 8 rows in them
         const int columns = a.k_pad / 64, blocks = (a.M + 7) / 8;
@@ -676,7 +706,7 @@ hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool give
         a.waves = (int)min((long long)kActWaves, ((long long)columns * blocks + most - 1) / most);
         units = (int)min((long long)most * a.waves, (long long)columns * blocks);
     } else {
-        units = row_form(a.M, a.k_pad, form, a.pieces, a.groups);
+        units = row_form(a.M, a.k_pad, form, a.pieces, a.groups, early);
         a.by_pieces = divisor(a.pieces);
         a.waves = a.groups * a.pieces;
     }
@@ -687,15 +717,13 @@ hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool give
     const int weight_side = a.cn != nullptr ? (a.N + 4 * a.wg_waves - 1) / (4 * a.wg_waves) : 1;
     const int grid = min(max((units + (per_token ? a.groups : a.waves) - 1) / (per_token ? a.groups : a.waves), weight_side), most);
     if (!per_token) a.groups = min(grid * a.waves / (a.k_pad / 64), (a.M + 7) / 8);
-    void (*kern)(const ActArgs);
+    act_kernel_t kern;
     if (!per_token)
         kern = given ? k_quantize_select<true> : k_quantize_select<false>;
-    else if (form == 0)
-        kern = is_static ? k_rows_select<2, 64, true> : k_rows_select<2, 64, false>;
-    else if (form == 1)
-        kern = is_static ? k_rows_select<4, 16, true> : k_rows_select<4, 16, false>;
+    else if (is_static)
+        kern = early ? rows_kernel<true, true>(form) : rows_kernel<true, false>(form);
     else
-        kern = is_static ? k_rows_select<5, 16, true> : k_rows_select<5, 16, false>;
+        kern = early ? rows_kernel<false, true>(form) : rows_kernel<false, false>(form);
     return launch_kernel(kern, dim3(grid), dim3(a.wg_waves * 64), 0, s, a);
 }
 

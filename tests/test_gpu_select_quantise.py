@@ -47,7 +47,10 @@ def test_thresholds(M, threshold):
 # one scale per row: single rows (2 x 64 chunks to a wave), and 4 rows at a time in pieces of 4 and of 5 x 16 chunks, each with one
 # wave to the rows and with several, whole pieces and K padding, M off the groups of 4
 ROW_SHAPES = [(40, 1024, 24), (70, 3080, 24), (255, 8192, 24), (8195, 512, 24), (6001, 1032, 24), (2003, 5120, 24), (5002, 640, 24),
-              (9001, 600, 24), (12001, 1280, 24), (9999, 8, 24)]
+              (9001, 600, 24), (12001, 1280, 24), (9999, 8, 24),
+              # several steps with rows up to 4 KB, requested ahead: single rows, and 4 rows in one wave and in several, spread evenly over
+              # the steps or with a last step of few rows
+              (9001, 1000, 24), (16390, 640, 24), (16400, 240, 24), (5125, 1536, 24), (5001, 2040, 24), (12289, 1024, 24)]
 
 
 @pytest.mark.parametrize("shape", ROW_SHAPES, ids=lambda s: "x".join(map(str, s)))
@@ -55,11 +58,11 @@ def test_rows_of_each_form(shape):
     M, K, N = shape
     check_case(Case("act_rows", M, K, N, min(9, K // 8), U, 990), x_gran="token")
     case = Case("act_rows_static", M, K, N, min(5, K // 8), U, 991)
-    if M * K < 4_000_000:
+    if M * K < 10_300_000:
         T._check_static(case, [int(k) for k in synth.make_case(case)[2]], "token", "channel", with_bias=True)
 
 
-@pytest.mark.parametrize("M,K", [(40, 1024), (6001, 520), (9001, 600)])
+@pytest.mark.parametrize("M,K", [(40, 1024), (6001, 520), (9001, 600), (9001, 1000), (5125, 1536)])
 def test_rows_with_nan_and_infinity(M, K):
     """A NaN sets no scale (and hides its channel from the list), an infinity makes its row's scale infinite; the codes
     and scales of all other rows are those of the list that results, by the formulas in binary32."""
