@@ -6,7 +6,7 @@
 // can fetch (~100 GB/s), and the launch.  Here the abs-max pass leaves few slabs (narrow blocks of
 // columns, 64 KB in all), and every workgroup of the quantiser folds them and selects for itself,
 // while its first rows of X are on their way.  With few tokens the abs-max pass goes as well: the
-// workgroups fold X itself (`slabs` are its rows).  Workgroup 0 leaves the results in the workspace.
+// workgroups fold X itself (`slabs` are its rows).  The results go into the workspace in shares of the workgroups.
 //
 // Bound by memory: X twice (the second time mostly out of the memory-side cache), the codes once.
 #include "muxq_select.h"
@@ -95,7 +95,8 @@ struct ActShared {
 // This thread's part of the fold, of N slabs p, p + P, ... at most.  The loads of N slabs are all
 // requested at once, and the workgroup's first rows of X behind them (load_x): loads come back in the order they
 // were issued, and the fold would wait for X as well.  (Past the end the last slab again: a branch per load would
-// serialise the loads.  N fits the slabs there are, because what 16 waves read twice counts: always eight of them, 0.2-0.4 us.)
+// serialise the loads.  N fits the slabs there are, because what 16 waves read twice counts: always eight of them, 0.2-0.4 us; a form for five as
+// well, 0.0 us.)
 template <int N, typename LoadX>
 __device__ __forceinline__ uint4 fold_slabs(const ActArgs &a, int c, int p, int P, bool on, LoadX &&load_x)
 {
@@ -133,8 +134,6 @@ __device__ __forceinline__ Selected act_select(const ActArgs &a, ActShared &sh, 
             mx = fold_slabs<2>(a, c, p, P, on, load_x);
         } else if (a.n_slabs <= 4 * P) {
             mx = fold_slabs<4>(a, c, p, P, on, load_x);
-        } else if (a.n_slabs <= 5 * P) {
-            mx = fold_slabs<5>(a, c, p, P, on, load_x);
         } else {
             mx = fold_slabs<8>(a, c, p, P, on, load_x);
             for (int sl = p + 8 * P; on && sl < a.n_slabs; sl += 8 * P) {
@@ -172,7 +171,7 @@ __device__ __forceinline__ Selected act_select(const ActArgs &a, ActShared &sh, 
             if (tid >= C) cand = 0;
         }
     }
-    const Selected r = select_channels<kActWaves>(mx, cand, holds, wave, n_seg, a.r_cap, WANT_SCALE, sh.tot, sh.max);
+    const Selected r = select_channels(mx, cand, holds, wave, n_seg, a.r_cap, WANT_SCALE, sh.tot, sh.max);
     if (holds) {
         if (tid < CA) sh.mask[tid] = (uint8_t)r.listed;
         int rank = r.first;

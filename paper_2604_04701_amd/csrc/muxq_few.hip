@@ -9,7 +9,7 @@
 // about 8 K elements of X (1 x 768 -> 2304: 4.5 us inside the kernel), the vector ALU work of the codes, repeated on
 // every CU, beyond (8 x 5120: 3 of 9.5 us).
 // Measured, us per call, four launches with a selection kernel against this kernel with 16 waves (see few_waves): 1 x 768 -> 2304 18.8 / 8.4,
-// 1 x 8192 -> 1024 49.1 / 10.1, 8 x 1280 -> 5120 -> 1280 (an MLP, two launches instead of eight)
+// 1 x 8192 -> 1024 49.1 / 10.1, 8 x 1280 -> 5120 -> 1280 (an MLP with both layers in this kernel, two launches instead of eight)
 // 61.5 / 24.7, 16 x 2560 -> 2560 28.8 / 11.2, 2 x 4096 -> 16384 36.8 / 20.5; against the launches that
 // would run here without it, see few_tokens_fit.
 //
@@ -194,10 +194,10 @@ __global__ __launch_bounds__(kFewMaxWaves * 64) void k_linear_few(const FewArgs 
         listed = chunk_candidates(mx, a.threshold, L.cut);
         if (!in_c) listed = 0;
     }
-    const Selected sel = select_channels<kFewMaxWaves>(mx, listed, holds, seg, S, r_cap, !TOKEN, s_tot, s_max);
+    const Selected sel = select_channels(mx, listed, holds, seg, S, r_cap, !TOKEN, s_tot, s_max);
     const int used = sel.used;
     const uint32_t call_max = sel.maxima;
-    // (the parts of the maxima, which may lie here, were read before the barriers of the selection)
+    // (the parts of the maxima, which may lie here, were read before the barrier of the selection)
     for (int i = tid * 4; i < M * r_cap; i += threads * 4) *(uint32_t *)(aux + i) = 0u;
     for (int i = tid * 4; i < 16 * r_cap; i += threads * 4) *(uint32_t *)(waux + i) = 0u;
     for (int i = tid; i < n_mb * 256; i += threads) red[i] = 0;
@@ -216,8 +216,8 @@ __global__ __launch_bounds__(kFewMaxWaves * 64) void k_linear_few(const FewArgs 
     if (TOKEN) {
         // ---- max|Body| of every row: a wave's piece first ----
         for (int row = row0; row < M; row += P) {
-            uint4 raw[1] = {make_uint4(0, 0, 0, 0)};
-            if (in_c) raw[0] = *(const uint4 *)(xc + row * K * 2);
+            uint4 raw = make_uint4(0, 0, 0, 0);
+            if (in_c) raw = *(const uint4 *)(xc + row * K * 2);
             const uint32_t m = wave_row_maxima(raw, listed);
             if (lane == 63) s_row[row * kFewMaxWaves + seg] = m;
         }

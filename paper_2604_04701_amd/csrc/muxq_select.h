@@ -94,26 +94,14 @@ __device__ __forceinline__ uint4 drop_nan(uint4 mx)
     return make_uint4(d[0], d[1], d[2], d[3]);
 }
 
-// chunk_maxima over the NC chunks that each lane of a wave holds of a row, in lane 63, without NaNs.
-// (`mk`: the chunks' masks of listed channels, one to a byte; every lane of the wave calls.)  A NaN wins
-// the integer comparison, so it shows in the result, and only then -- one scalar test per row in the
-// streaming kernels -- the maxima are taken again without it, chunk by chunk to need few registers.
-template <int NC>
-__device__ __forceinline__ uint32_t wave_row_maxima(const uint4 (&raw)[NC], uint32_t mk)
+// chunk_maxima over the chunks that the lanes of a wave hold of a row, in lane 63, without NaNs.  (Every lane of the wave
+// calls.)  A NaN wins the integer comparison, so it shows in the result, and only then the maxima are taken again without it.
+__device__ __forceinline__ uint32_t wave_row_maxima(uint4 raw, uint32_t listed)
 {
-    uint32_t m = 0;
-#pragma unroll
-    for (int i = 0; i < NC; ++i) m = pk_max_u16(m, chunk_maxima(raw[i], (mk >> (8 * i)) & 0xffu));
-    m = wave_max_u16x2_to_lane63(m);
+    const uint32_t m = wave_max_u16x2_to_lane63(chunk_maxima(raw, listed));
     const uint32_t top = (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
     if ((top & 0xffffu) <= 0x7c00u && (top >> 16) <= 0x7c00u) return m;
-    m = 0;
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-        m = pk_max_u16(m, chunk_maxima(drop_nan(raw[i]), (mk >> (8 * i)) & 0xffu));
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    return wave_max_u16x2_to_lane63(m);
+    return wave_max_u16x2_to_lane63(chunk_maxima(drop_nan(raw), listed));
 }
 
 // Whether a lane of the wave has a NaN among its magnitudes.
@@ -170,16 +158,15 @@ inline int magnitude_cut(float threshold)
 
 // Sec. III-C with the capacity rule: the r_cap lowest candidates are listed.  The first `n_seg` pieces
 // of 64 chunks are in one wave each; a thread of those (`holds`, the same in a wave) brings the column maxima `mx`
-// (magnitudes) of chunk 64 seg + lane and its candidates.  All NW waves of the workgroup call; two
-// barriers at least; the caller's LDS writes before are visible after.
+// (magnitudes) of chunk 64 seg + lane and its candidates.  All waves of the workgroup call, 16 at most; one
+// barrier, two more where the list overflows: the caller's LDS writes before are visible after, what it read before may be overwritten
+// after, and s_tot and s_max (16 entries each) not before another barrier.
 // A chain of latencies that every workgroup walks: 16 waves that all work out everything are bound by
 // their instructions (four waves on a SIMD), so only the waves that hold chunks do, and what all need of the waves' results
 // is read by 16 lanes side by side (8192 x 1024, from the column maxima to the list 1.5 -> 0.9 us).
-template <int NW>
 __device__ __forceinline__ Selected select_channels(uint4 mx, uint32_t cand, bool holds, int seg, int n_seg, int r_cap,
                                                     bool want_max, int *s_tot, uint32_t *s_max)
 {
-    static_assert(NW == 16, "a row of 16 lanes reads the waves' results");
     const int lane = threadIdx.x & 63;
     Selected r;
     r.listed = cand;
