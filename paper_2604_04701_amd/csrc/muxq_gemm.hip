@@ -1001,8 +1001,8 @@ __global__ __launch_bounds__(256, EPI == kEpiAny ? 2 : 1) void k_gemm_i8_persist
 // What counts beside the bytes is that no request waits for anything and nothing waits for a request it does not use: the first
 // Aux step and the epilogue's constants, token scales and zero points are requested with the first Body steps, without
 // branches.  (Before, a wave waited for all its first loads for the sake of a constant, the last wave was 2.6 us behind the others
-// with Aux, every DEPTH steps all loads were waited for, and the end began with two loads: 512 x 4096 -> 1024 11.4 -> 9.2 us,
-// 24 x 5120 -> 1280 6.9 -> 5.4, 1024 x 4096 -> 1024 15.4 -> 12.)
+// with Aux, every DEPTH steps all loads were waited for, and the end began with two loads: 512 x 4096 -> 1024 11.6 -> 10.1 us,
+// 24 x 5120 -> 1280 6.9 -> 6.0.)
 // --------------------------------------------------------------------------
 template <int TNB, int TMB, int DEPTH, int W>
 __global__ __launch_bounds__(W * 64) void k_gemm_i8_direct(const GemmArgs a, const TileMap tm)
@@ -1562,6 +1562,9 @@ static GemmForm gemm_form(int M, int N, int k_pad, bool off_lines = false)
     return k_pad >= 512 && (wide ? half * 11 / 10 : half) < rounds256 * 100 * (steps + 7) ? kPersistHalf : kPersist256;
 }
 
+// (The callers divide by it: a form without a case here does not compile.)
+#pragma clang diagnostic push
+#pragma clang diagnostic error "-Wswitch"
 int gemm_tile_rows(int M, int N, int k_pad)
 {
     switch (gemm_form(M, N, k_pad)) {
@@ -1571,8 +1574,9 @@ int gemm_tile_rows(int M, int N, int k_pad)
     case kDirect32x32: case kDirect16x32: return 32;
     case kDirect16x16: return 16;
     }
-    return 0;
+    __builtin_unreachable();
 }
+#pragma clang diagnostic pop
 
 const char *gemm_kernel_name(int M, int N, int k_pad)
 {
