@@ -17,7 +17,6 @@ namespace {
 constexpr int kActThreads = 1024, kActWaves = kActThreads / 64;
 constexpr int kActMaxK = 8 * kActThreads;              // one chunk of 8 channels per thread in the selection
 constexpr int kActMaxCap = 1024;
-constexpr int kEarlyMaxK = 2048;                        // see row_form
 
 // Column maxima of |X| per row slab, like k_col_absmax_partial, but a workgroup covers only 128
 // columns and many rows: the same number of workgroups leaves a quarter of the slabs.  (64 columns leave
@@ -275,10 +274,12 @@ __device__ __forceinline__ void zero_aux_rest(const ActArgs &a, int used)
 // time is one contiguous piece of memory.  (A range of rows for each workgroup puts all of them on the same few memory
 // channels where a range is a multiple of a large power of two: 16384 x 5120 from HBM 65 us instead of 45 us.)
 // Few codes (up to 10 MB) are written through: stored as usual they all are dirty in the L2s when the kernel ends, and
-// wait to be written back then.  With more of them the L2s write while the kernel runs anyway, and do it better by themselves (us a call, through / as usual: 9000 x 520 -> 1000 28.8 / 29.3, 8192 x 1024 -> 1024
-// 28.3 / 28.4, 6000 x 2048 -> 1024 35.1 / 34.9, 8192 x 4096 -> 4096 139.6 / 137.2, 20000 x 4096 -> 512 130.9 / 126.6).
+// wait to be written back then (us a call, through / as usual: 4096 x 512 -> 256 17.1 / 17.3, 16384 x 512 (8 MB) -> 256 21.5 / 22.0, 16384 x 512 -> 1024
+// 28.7 / 29.1, 8192 x 1024 (8 MB) -> 256 22.4 / 22.6, 2048 x 4096 -> 256 21.8 / 22.0).  With more of them the L2s write while the kernel runs anyway, and do it
+// better by themselves: from 10 to 20 MB no difference (24576 x 512 25.5 / 25.6, 12288 x 1024 25.5 / 25.5), then up to 2 % (8192 x 4096 61.3 / 60.0, 40000 x 1024
+// 59.4 / 58.5), once none (16384 x 5120 112.3 / 112.6).
 // Against rows of 64 chunks to a wave, four rows requested at a time (64-byte pieces of the codes): 8192 x 1024 11.8 -> 9.4 us, 8192
-// x 4096 30.2 -> 24 us (100 MB, 4.2 TB/s with the selection in it), a call of 9000 x 520 -> 1000 38.4 -> 28.8 us.  U = 2; 3, 4, 6
+// x 4096 30.2 -> 25.3 us (100 MB, 4.0 TB/s with the selection in it), a call of 9000 x 520 -> 1000 38.4 -> 28.8 us.  U = 2; 3, 4, 6
 // and 8 are up to 2 % slower.
 // GIVEN: the list and the column maxima are the caller's (muxq_build_aux): any list of channels, each
 // named once, and any binary32 maxima.
@@ -405,8 +406,9 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_select(const ActArgs a
 // One activation scale per row.  A wave takes 64 / LANES rows x NB pieces of LANES chunks, 16 bytes of each piece a lane, in
 // registers from the rows' maxima to the codes: with 16 lanes to a row, what is worked out for a row (its maximum over the lanes, the
 // scale, two divisions) is worked out for 4 rows at once, and the codes go out as 256 contiguous bytes.  The next rows are
-// requested piece by piece as these are worked on, or (EARLY) whether there are any or not, with 4 rows to a wave all at once before the maxima:
-// in the last step the same rows again, which are near.  Rows longer than that are in `pieces` waves, whose maxima meet in LDS (one
+// requested piece by piece as these are worked on.  (All at once before the maxima, whether there are any or not: calls with several steps of
+// rows up to 4 KB 1-2 % faster, with one step 0.5 us slower; and as a kernel of its own for several steps an MLP, whose two layers then run
+// different ones, 2-3 us slower: 8192 x 440 -> 1760 -> 440 66.0 / 68.6, 9000 x 264 58.2 / 60.2.)  Rows longer than that are in `pieces` waves, whose maxima meet in LDS (one
 // barrier per step; the two halves of `s_piece` take turns).  Against single rows of up to 4 x 64 chunks a wave: 16384 x 1280
 // 24.8 -> 21.8 us (63 MB, with the selection in it), a call of 60000 x 1280 -> 512 138 -> 122 us.  The codes are written through, however many:
 // as usual / through, calls with N = 256, 4096 x 512 18.4 / 18.3, 16384 x 512 (8 MB) 25.2 / 24.3, 16384 x 1280 (21 MB) 39.0 / 38.4, 8192 x 4096 (33 MB)
@@ -415,7 +417,7 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_select(const ActArgs a
 // to fetch: 10 pieces with everything unrolled was 2 us slower than 4 on 1024 x 768): the column masks of the maxima come from LDS, and pieces
 // with a listed channel or K padding are put aside, in LDS, for a rolled loop.
 // STATIC: the list was fixed offline (a kernel of its own: nothing waits for slabs, and the rows are requested first).
-template <int NB, int LANES, bool STATIC, bool EARLY>
+template <int NB, int LANES, bool STATIC>
 __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
 {
     constexpr int R = 64 / LANES;
@@ -473,14 +475,7 @@ __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
 
     // (the same number of steps for all waves: they meet at the barrier)
     for (int step = 0, r0 = (int)blockIdx.x * P; r0 < n_rb; ++step, r0 += stride, rb += stride) {
-        const bool on = p < P && rb < n_rb, more = rb + stride < n_rb;
-        const uint16_t *const next_row = row_of(more ? rb + stride : rb);
-        uint4 next[NB];
-        if (EARLY && R > 1) {                            // (no condition: behind one the compiler waits for all that is in flight)
-#pragma unroll
-            for (int j = 0; j < NB; ++j) next[j] = load(next_row, j);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        const bool on = p < P && rb < n_rb;
         uint32_t m = 0;
         if (on) {
             // listed and unlisted apart, two halves to a word
@@ -523,15 +518,14 @@ __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
             ((int32_t *)a.x_scale)[2 * (size_t)a.M + row] = z;
         }
         const float inv_listed = inv * shrink, magic = 12582912.0f + (float)z;
+        const bool more = rb + stride < n_rb;
+        const uint16_t *const next = row_of(rb + stride);
         int8_t *const dst = a.body_q + packed_index(row, c0 * 8, a.k_pad);
         constexpr int PIECE = LANES / 8 * 1024;          // bytes of packed codes from piece to piece
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             const uint4 v = raw[j];
-            if (EARLY)
-                raw[j] = R > 1 ? next[j] : load(next_row, j);
-            else if (more)
-                raw[j] = load(next_row, j);
+            if (more) raw[j] = load(next, j);
             if ((aside >> j & 1u) != 0) {
                 s_aside[wave][j][lane] = v;
             } else {
@@ -570,7 +564,8 @@ __global__ __launch_bounds__(kActThreads) void k_rows_select(const ActArgs a)
 }
 
 // muxq_detect_outliers: the fold and the list by themselves, one workgroup.  Bound by latency (5120 channels 5.5 -> 4.7 us against
-// the kernel that also leaves what the separate quantisers read).
+// the kernel that also leaves what the separate quantisers read).  8 waves instead of 16 would do up to 4096 channels and are neither better nor
+// worse: both kernels of a call replayed 20 times, 1 x 256 5.0 / 5.0 us, 64 x 2048 5.1 / 5.1, 1 x 4096 5.3 / 5.2, 1024 x 1024 5.5 / 5.8, 300 x 3072 5.6 / 5.4.
 __global__ __launch_bounds__(kActThreads) void k_detect_select(const ActArgs a)
 {
     __shared__ ActShared sh;
@@ -635,19 +630,21 @@ hipError_t launch_fold_slabs(uint16_t *partial, int n_slabs, int k_pad, hipStrea
 }
 
 // The form of k_rows_select: single rows in pieces of 2 x 64 chunks, or 4 rows in pieces of 4 or 5 x 16, by the least of three estimates.
-// Beyond 4 KB of a row the vector instructions bound it: about 60 for a piece of 64 lanes x 16 bytes and 200 for what is worked out
-// once per row, times the waves on a SIMD and the steps (19 shapes, 24 x 5120 to 60000 x 1280: the fastest or within 1 %).
-// Shorter rows are bound by the latency of a step (the 8 in the estimate), and rows in several waves by their barrier as well, most of all with
-// several steps.  There the next rows are requested ahead (early), and the groups are spread evenly over the steps unless the last of
-// them is nearly empty.  Fitted to 232 calls in each form, 100 to 32768 rows of 256 to 5120, checked on 207 others: the fastest form or within 2 %.  us a
-// call, single rows of up to 4 x 64 chunks as they were before the three forms / the first estimate for all, requests piece by piece / now:
-// 10240 x 1024 -> 256 29.1 / 30.2 / 28.2, 20000 x 1024 37.7 / 40.3 / 37.6, 9004 x 896 21.8 / 23.6 / 20.3 (static list), 16384 x 1424 44.0 / 46.4 / 42.9, 16384 x
-// 1592 47.2 / 48.2 / 47.9, 24576 x 640 36.9 / 34.1 / 32.9; 16386 x 576, whose second step is one group: evenly 30.1, otherwise 28.5; the new way
-// with longer rows 16384 x 3072 79.9 instead of 77.8, 2609 x 3080 26.8 instead of 26.0.
+// One step, or rows beyond 4 KB: bound by the vector instructions, about 60 for a piece of 64 lanes x 16 bytes and 200 for what is worked
+// out once per row, times the waves on a SIMD and the steps (19 shapes, 24 x 5120 to 60000 x 1280: the fastest or within 1 %; us a call, single
+// rows / 4 rows x 4 / 4 rows x 5: 512 x 4096 -> 1024 21.8 / 22.4 / 22.7, 2000 x 1280 -> 1280 23.6 / 22.8 / 23.0, 8192 x 4096 -> 1024 81.1 / 73.7 / 74.6).
+// Several steps of shorter rows: the latency of a step counts as well (the 8 in the estimate), and the barrier of rows in several waves, most of
+// all from step to step; fitted to 232 calls in each form.  There the groups are also spread evenly over the steps, unless the last one is
+// nearly empty.  us a call, single rows of up to 4 x 64 chunks as before the three forms / the first estimate for all / now: 10240 x 1024 -> 256
+// 29.1 / 30.4 / 28.2, 20000 x 1024 38.3 / 40.7 / 38.4, 9004 x 896 static 21.7 / 23.5 / 20.3, 16384 x 1424 44.4 / 46.6 / 43.5, 16384 x 1592 47.5 / 50.2 / 48.6; 16386 x 576,
+// whose second step is one group, evenly 30.1, otherwise 28.3.  With one step the second estimate takes single rows up to 4096 x 1000, no
+// faster by themselves, and an MLP of them is slower: 4096 x 768 -> 3072 -> 768 per token 69.0 / 71.2.
 // Returns the groups of rows; pieces: waves to a group, at_once: groups of a workgroup at a time.
-int row_form(int M, int k_pad, int &form, int &pieces, int &at_once, bool &early)
+int row_form(int M, int k_pad, int &form, int &pieces, int &at_once)
 {
     static const struct { int pieces, lanes; } kForms[3] = {{2, 64}, {4, 16}, {5, 16}};
+    // (more than one step: of 4 rows to a wave in pieces of 4 x 16 chunks)
+    const bool short_rows = k_pad <= 2048 && M > 4 * 256 * (kActWaves / ((k_pad / 8 + 63) / 64));
     int groups = 0;
     long long best = -1;
     for (int f = 0; f < 3; ++f) {
@@ -655,10 +652,9 @@ int row_form(int M, int k_pad, int &form, int &pieces, int &at_once, bool &early
         const int S = (k_pad / 8 + NB * kForms[f].lanes - 1) / (NB * kForms[f].lanes);
         const int most = 256 * (kActWaves / S), steps = (n + most - 1) / most;
         int P = min(kActWaves / S, (n + 255) / 256);
-        const bool even = k_pad <= kEarlyMaxK && steps > 1 && (n - 1) % most >= most / 8;
-        if (even) P = (n + 256 * steps - 1) / (256 * steps);
+        if (short_rows && steps > 1 && (n - 1) % most >= most / 8) P = (n + 256 * steps - 1) / (256 * steps);
         const int waves = (P * S + 3) / 4;
-        const long long cost = k_pad > kEarlyMaxK ? (long long)steps * waves * (60 * NB + 200)
+        const long long cost = !short_rows ? (long long)steps * waves * (60 * NB + 200)
                                : (long long)steps * (waves + 8) * (60 * NB + (rows == 1 ? 140 : 70)) + (S == 1 ? 0 : steps == 1 ? 1000 : 4680);
         if (best >= 0 && cost >= best) continue;
         best = cost;
@@ -666,16 +662,8 @@ int row_form(int M, int k_pad, int &form, int &pieces, int &at_once, bool &early
         groups = n;
         pieces = S;
         at_once = P;
-        early = k_pad <= kEarlyMaxK && steps > 1;
     }
     return groups;
-}
-
-typedef void (*act_kernel_t)(const ActArgs);
-template <bool STATIC, bool EARLY>
-act_kernel_t rows_kernel(int form)
-{
-    return form == 0 ? k_rows_select<2, 64, STATIC, EARLY> : form == 1 ? k_rows_select<4, 16, STATIC, EARLY> : k_rows_select<5, 16, STATIC, EARLY>;
 }
 
 hipError_t launch_detect_select(const ActArgs &args, hipStream_t s)
@@ -697,7 +685,6 @@ hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool give
     // a share of the weight side each (4 output channels a wave)
     const int most = 256;
     int units, form = 0;                                 // units: what a wave takes at a time
-    bool early = false;
     if (!per_token) {
         // columns of 64 channels, and as many waves as there are blocks of 8 rows in them
         const int columns = a.k_pad / 64, blocks = (a.M + 7) / 8;
@@ -705,7 +692,7 @@ hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool give
         a.waves = (int)min((long long)kActWaves, ((long long)columns * blocks + most - 1) / most);
         units = (int)min((long long)most * a.waves, (long long)columns * blocks);
     } else {
-        units = row_form(a.M, a.k_pad, form, a.pieces, a.groups, early);
+        units = row_form(a.M, a.k_pad, form, a.pieces, a.groups);
         a.by_pieces = divisor(a.pieces);
         a.waves = a.groups * a.pieces;
     }
@@ -716,13 +703,15 @@ hipError_t launch_quantize_select(const ActArgs &args, bool per_token, bool give
     const int weight_side = a.cn != nullptr ? (a.N + 4 * a.wg_waves - 1) / (4 * a.wg_waves) : 1;
     const int grid = min(max((units + (per_token ? a.groups : a.waves) - 1) / (per_token ? a.groups : a.waves), weight_side), most);
     if (!per_token) a.groups = min(grid * a.waves / (a.k_pad / 64), (a.M + 7) / 8);
-    act_kernel_t kern;
+    void (*kern)(const ActArgs);
     if (!per_token)
         kern = given ? k_quantize_select<true> : k_quantize_select<false>;
-    else if (is_static)
-        kern = early ? rows_kernel<true, true>(form) : rows_kernel<true, false>(form);
+    else if (form == 0)
+        kern = is_static ? k_rows_select<2, 64, true> : k_rows_select<2, 64, false>;
+    else if (form == 1)
+        kern = is_static ? k_rows_select<4, 16, true> : k_rows_select<4, 16, false>;
     else
-        kern = early ? rows_kernel<false, true>(form) : rows_kernel<false, false>(form);
+        kern = is_static ? k_rows_select<5, 16, true> : k_rows_select<5, 16, false>;
     return launch_kernel(kern, dim3(grid), dim3(a.wg_waves * 64), 0, s, a);
 }
 

@@ -48,8 +48,8 @@ def test_thresholds(M, threshold):
 # wave to the rows and with several, whole pieces and K padding, M off the groups of 4
 ROW_SHAPES = [(40, 1024, 24), (70, 3080, 24), (255, 8192, 24), (8195, 512, 24), (6001, 1032, 24), (2003, 5120, 24), (5002, 640, 24),
               (9001, 600, 24), (12001, 1280, 24), (9999, 8, 24),
-              # several steps with rows up to 4 KB, requested ahead: single rows, and 4 rows in one wave and in several, spread evenly over
-              # the steps or with a last step of few rows
+              # several steps with rows up to 4 KB: single rows, and 4 rows in one wave and in several, spread evenly over the steps or
+              # with a last step of few rows
               (9001, 1000, 24), (16390, 640, 24), (16400, 240, 24), (5125, 1536, 24), (5001, 2040, 24), (12289, 1024, 24)]
 
 
