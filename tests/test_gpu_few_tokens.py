@@ -176,6 +176,19 @@ def test_one_workspace_for_both_layers(M, K, N1, N2, x_gran):
         assert torch.equal(H, H1) and torch.equal(Y, Y1)
 
 
+@pytest.mark.parametrize("x_gran", ["tensor", "token"])
+@pytest.mark.parametrize("M,K,N", [(16, 2624, 4360), (20, 2048, 24576), (24, 1536, 4360), (32, 1024, 12288), (33, 992, 264),
+                                   (40, 816, 264), (48, 512, 8192), (64, 512, 8192)])
+def test_longest_rows_and_widest_outputs(M, K, N, x_gran):
+    """The longest rows that each number of tokens can run with in the one launch (every weight block of a wave is held), the
+    widest outputs, and one row more, eight channels more of either, whichever launches the line gives them to."""
+    check_case(Case("few_longest", M, K, N, 5, U, 680 + M), x_gran=x_gran, w_gran="channel", bias_seed=2)
+    if N in (8192, 12288, 24576):
+        check_plain_y(Case("few_wider", M, K, N + 8, 5, U, 690 + M), x_gran=x_gran, w_gran="channel")
+    else:
+        check_case(Case("few_longer", M + 1, K + 8, N, 5, U, 690 + M), x_gran=x_gran, w_gran="channel")
+
+
 # (M, K, N), then what makes it a call for the separate launches: one row ("M"), eight channels of K or of N more
 LIMITS = {
     (64, "tensor"): [(8, 5328, 264, "MK"), (16, 2648, 264, "MK"), (20, 2104, 136, "MK"), (24, 1536, 264, "MK"), (32, 1024, 264, "MK"),
@@ -190,7 +203,7 @@ LIMITS = {
 
 
 @pytest.mark.parametrize("r_cap,x_gran,M,K,N,ends", [(r, g, *s) for (r, g), shapes in LIMITS.items() for s in shapes])
-def test_longest_rows_and_widest_outputs(r_cap, x_gran, M, K, N, ends):
+def test_ends_of_the_one_launch(r_cap, x_gran, M, K, N, ends):
     """The longest rows that each number of tokens runs with (with capacities above 64 every weight block of a wave is held and LDS is
     full), the widest outputs; one row more, eight channels more take the separate launches."""
     beyond = [(M + (e == "M"), K + 8 * (e == "K"), N + 8 * (e == "N")) for e in ends]
