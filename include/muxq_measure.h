@@ -33,10 +33,10 @@ int muxq_linear_timed(const void *X_fp16, int M, int K, int ldx, const int8_t *w
 const char *muxq_gemm_kernel(int M, int K, int N);
 
 /* Name of the kernel that forms the codes of X in an M x K -> N layer ("" for shapes that are refused; opts as in
- * muxq_linear_opts, NULL allowed): k_linear_few, the whole layer in one launch, where X, Y and the next layer's maxima lie apart,
- * k_quantize_select or k_rows_select, which select the channels themselves, or k_quantize_body or k_quantize_rows_token
+ * muxq_linear_opts, NULL allowed; hands_maxima: a layer follows that takes the column maxima of Y): k_linear_few, the
+ * whole layer in one launch, where X, Y and the next layer's maxima lie apart, k_quantize_select or k_rows_select, which select the channels themselves, or k_quantize_body or k_quantize_rows_token
  * behind a selection kernel. */
-const char *muxq_code_kernel(int M, int K, int N, int r_cap, const muxq_act_opts *opts);
+const char *muxq_code_kernel(int M, int K, int N, int r_cap, const muxq_act_opts *opts, int hands_maxima);
 
 /* The issue rate of the INT8 MFMA instruction the GEMM uses (v_mfma_i32_32x32x32_i8) with
  * operands held in registers and nothing else running, on operand codes sampled from

@@ -131,7 +131,7 @@ def lib():
         L.muxq_gemm_kernel.restype = C.c_char_p
         L.muxq_gemm_kernel.argtypes = [i, i, i]
         L.muxq_code_kernel.restype = C.c_char_p
-        L.muxq_code_kernel.argtypes = [i, i, i, i, C.POINTER(ActOpts)]
+        L.muxq_code_kernel.argtypes = [i, i, i, i, C.POINTER(ActOpts), i]
         L.muxq_linear_gelu_slabs.restype = i
         L.muxq_linear_gelu_slabs.argtypes = [i, i, i]
         L.muxq_linear_gelu.restype = i
@@ -449,10 +449,11 @@ def gemm_kernel(M: int, K: int, N: int) -> str:
     return lib().muxq_gemm_kernel(M, K, N).decode()
 
 
-def code_kernel(M: int, K: int, N: int, r_cap=64, x_gran="tensor", absmax_ready=False, aux_scale="shared") -> str:
+def code_kernel(M: int, K: int, N: int, r_cap=64, x_gran="tensor", absmax_ready=False, aux_scale="shared",
+                hands_maxima=False) -> str:
     """Name of the kernel that forms the codes of X in an M x K -> N layer (include/muxq_measure.h)."""
     opts = ActOpts(_XGRAN[x_gran], 8, int(absmax_ready), {"shared": 0, "own": 1}[aux_scale], 0)
-    return lib().muxq_code_kernel(M, K, N, r_cap, C.byref(opts)).decode()
+    return lib().muxq_code_kernel(M, K, N, r_cap, C.byref(opts), int(hands_maxima)).decode()
 
 
 def wq_row_sums(w_q, K: int, N: int):

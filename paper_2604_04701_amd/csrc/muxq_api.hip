@@ -101,10 +101,10 @@ hipError_t noalloc_scratch_ptr(void **out)
 
 // What forms the codes of X: the one launch for few tokens, a quantiser that selects for itself, or the separate launches.
 enum Route { kFew, kSelect, kSeparate };
-Route route_of(int M, int K, int N, int k_pad, int r_cap, bool per_token, bool aux_own, bool maxima_given, bool few_allowed)
+Route route_of(int M, int K, int N, int k_pad, int r_cap, bool per_token, bool aux_own, bool maxima_given, bool hands_maxima, bool few_allowed)
 {
     if (aux_own) return kSeparate;
-    if (few_allowed && muxq::few_tokens_fit(M, K, N, k_pad, r_cap, per_token, maxima_given)) return kFew;
+    if (few_allowed && muxq::few_tokens_fit(M, K, N, k_pad, r_cap, per_token, maxima_given, hands_maxima)) return kFew;
     return muxq::act_select_fits(k_pad, r_cap) && (per_token || muxq::act_select_pays(M, K)) ? kSelect : kSeparate;
 }
 
@@ -196,7 +196,7 @@ int linear_impl(const void *X, int M, int K, int ldx, const int8_t *w_q, const f
     // the separate launches, as does Aux on a scale of its own; X is addressed with 32-bit offsets)
     // (a Y that shares memory with X is written while other workgroups still read X: separate launches)
     const bool apart = !touch(X, ((size_t)(M - 1) * ldx + K) * 2, Y, ((size_t)(M - 1) * ldy + N) * 2);
-    const Route route = route_of(M, K, N, k_pad, r_cap, per_token, aux_own, absmax_ready,
+    const Route route = route_of(M, K, N, k_pad, r_cap, per_token, aux_own, absmax_ready, next_count > 0,
                                  gemm_start == nullptr && apart && !next_hits_few && (size_t)M * (size_t)ldx < (1u << 30));
     if (route == kFew) {
         muxq::FewArgs f{};
@@ -676,11 +676,11 @@ const char *muxq_gemm_kernel(int M, int K, int N)
     return check_dims(M, K, N) ? "" : muxq::gemm_kernel_name(M, N, kpad(K));
 }
 
-const char *muxq_code_kernel(int M, int K, int N, int r_cap, const muxq_act_opts *opts)
+const char *muxq_code_kernel(int M, int K, int N, int r_cap, const muxq_act_opts *opts, int hands_maxima)
 {
     if (check_dims(M, K, N) || check_rcap(K, r_cap)) return "";
     const bool per_token = opts && opts->x_gran == MUXQ_X_PER_TOKEN, own = opts && opts->aux_own_scale && r_cap > 0;
-    switch (route_of(M, K, N, kpad(K), r_cap, per_token, own, opts && opts->absmax_ready, true)) {
+    switch (route_of(M, K, N, kpad(K), r_cap, per_token, own, opts && opts->absmax_ready, hands_maxima != 0, true)) {
     case kFew: return "k_linear_few";
     case kSelect: return per_token ? "k_rows_select" : "k_quantize_select";
     case kSeparate: break;

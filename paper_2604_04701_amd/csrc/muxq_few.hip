@@ -487,6 +487,23 @@ int given_turns(int M, int K, int N, int k_pad, int pieces, bool per_token)
     return pieces <= 2 ? 2 : pieces > 4 && pieces <= 8 ? 4 : 3;
 }
 
+// Most rows in turn where a layer follows that takes the column maxima from this one, with more than one block of 16 output channels to a
+// workgroup.  What the separate launches cost the host is hidden by that layer, which leaves the time of the kernels.  us of an MLP of widths K,
+// 4 K, K, its second layer in separate launches, the first one in separate launches / in this kernel (turns):
+//   N <= 5120  16 x 1040 23.0 / 22.2 (4), 13 x 1280 23.1 / 22.7 (4), 16 x 1280 23.4 / 23.0 (4)
+//   beyond 13 x 1440 23.2 / 23.5 (4), 16 x 1520 23.5 / 24.1 (4), 10 x 1600 23.7 / 24.2 (4)
+//   per token  9 x 1120 23.9 / 23.2 (3), 12 x 1120 24.0 / 23.9 (3), 9 x 1280 23.9 / 23.7 (3), 12 x 1280 24.0 / 24.2 (3), 16 x 1120 24.3 / 24.7 (4); beyond 6
+//          x 1520 23.7 / 23.8 (2), 9 x 1440 24.0 / 24.3 (3), 16 x 1520 24.4 / 26.0 (4), four pieces 5 x 1600 24.2 / 24.6 (2), 9 x 1600 24.5 / 25.3 (3)
+// (two rows in turn beyond N = 8192, and one with more than four pieces, are what ran before the line of calls by themselves went further.)
+int handing_turns(int M, int K, int N, int k_pad, int pieces, bool per_token)
+{
+    if (pieces <= 2) return M;
+    if (pieces > 4) return 1;
+    if (!per_token) return N <= 5120 ? 4 : N <= 8192 ? 3 : 2;
+    if (N <= 5120) return M * K <= 14 * 1024 ? 3 : 2;
+    return pieces == 3 ? 2 : few_two_on_a_cu(M, few_waves(M, N, k_pad)) ? 2 : 1;
+}
+
 // X and its codes have to fit LDS together (about 42 K elements); below that the line against the separate
 // launches (selecting quantiser and GEMM, two or three of them, which cost the host alone 9.8 us) lies where what grows here
 // outweighs the launches saved: the rows that a wave works on one after the other (`turns`, counted for 12 waves and 16 whatever few_waves
@@ -513,7 +530,7 @@ int given_turns(int M, int K, int N, int k_pad, int pieces, bool per_token)
 //          -> 24576 24.8 / 24.2, 12 x 2560 24.9 / 25.3 (4); four pieces 9 x 2048 -> 24576 21.5 / 20.3 (3), per token 22.6 / 21.4, 9 x 1600 19.3 / 19.4
 // Long lists move it the other way (8 x 1280 -> 4096, 160 channels of at most 1024 listed, 19.6 / 11.0 with the separate launches of
 // before): capacities above 64 keep wider lines.
-bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token, bool maxima_given)
+bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token, bool maxima_given, bool hands_maxima)
 {
     if (M > kFewMaxM || k_pad > 64 * kFewMaxWaves * few_loads((M + 15) / 16) || few_plan(M, K, k_pad, r_cap, 1, kFewMaxWaves).total > kFewLdsBytes)
         return false;
@@ -529,6 +546,7 @@ bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token, b
             if (turns > given_turns(M, K, N, k_pad, pieces, per_token)) return false;
             if (N > 4096) return true;
         } else if (N > 4096) {
+            if (hands_maxima && turns > handing_turns(M, K, N, k_pad, pieces, per_token)) return false;
             if (pieces > 4) return turns <= (N <= 6400 ? 1 : per_token ? 1 + (pieces > 8 && K <= 6144) : 3 - (K > 6144));
             const int most = !per_token ? (pieces <= 2 ? 6 : N <= 8192 || pieces == 3 ? 4 : 3)
                            : pieces <= 2 ? 4 - (N > 8192) : pieces == 3 ? 4 - (N > 6400) - (N > 8192) : 3 - (N > 6400);

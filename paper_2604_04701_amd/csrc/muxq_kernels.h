@@ -272,7 +272,7 @@ struct FewArgs {
 };
 constexpr int kFewLdsBytes = 128 * 1024;
 // Whether launch_linear_few takes a call (and is the faster way): a function of the sizes only.
-bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token, bool maxima_given);
+bool few_tokens_fit(int M, int K, int N, int k_pad, int r_cap, bool per_token, bool maxima_given, bool hands_maxima);
 hipError_t launch_linear_few(const FewArgs &a, hipStream_t s);
 hipError_t few_prepare_device();      // LDS attributes, from gemm_prepare_device
 

@@ -245,8 +245,8 @@ def test_gemm_kernels_by_size():
 
 
 @pytest.mark.parametrize("x_gran", ["tensor", "token"])
-@pytest.mark.parametrize("absmax_ready", [False, True])
-def test_a_row_more_never_brings_a_call_back_to_the_one_launch(x_gran, absmax_ready):
+@pytest.mark.parametrize("absmax_ready,hands_maxima", [(False, False), (True, False), (False, True)])
+def test_a_row_more_never_brings_a_call_back_to_the_one_launch(x_gran, absmax_ready, hands_maxima):
     """The one launch for few tokens repeats the work of every row on every CU: the numbers of tokens that take it are
     1 to some most, for every row length, width and capacity, with the column maxima given or not."""
     Ks = sorted(set(range(8, 8200, 168)) | {8, 512, 520, 1024, 1032, 1536, 1544, 2048, 2056, 3072, 4096, 4104, 4352, 4608, 5120, 8192})
@@ -255,7 +255,7 @@ def test_a_row_more_never_brings_a_call_back_to_the_one_launch(x_gran, absmax_re
             if r_cap > B.k_pad(K):
                 continue
             for N in (8, 2560, 2568, 4096, 4104, 8192, 8200, 12288, 12296, 16384, 16392, 24576, 32768):
-                few = [B.code_kernel(M, K, N, r_cap, x_gran, absmax_ready) == "k_linear_few" for M in range(1, 70)]
+                few = [B.code_kernel(M, K, N, r_cap, x_gran, absmax_ready, hands_maxima=hands_maxima) == "k_linear_few" for M in range(1, 70)]
                 assert not few[-1] and few == sorted(few, reverse=True), (K, N, r_cap, [m + 1 for m in range(69) if few[m]])
 
 
@@ -271,6 +271,14 @@ def test_code_kernels_by_size():
         for M, K, N in last:
             assert B.code_kernel(M, K, N, x_gran=x_gran, absmax_ready=True) == "k_linear_few", (M, K, N, x_gran)
             assert B.code_kernel(M + 1, K, N, x_gran=x_gran, absmax_ready=True) != "k_linear_few", (M, K, N, x_gran)
+    # a layer follows that takes the column maxima: the last of the first layers in the one launch, and a row more
+    for x_gran, last in (("tensor", [(16, 1040, 4160), (16, 1280, 5120), (12, 1440, 5760), (12, 1536, 6144), (9, 1600, 6400), (3, 2560, 10240)]),
+                         ("token", [(12, 1120, 4480), (11, 1280, 5120), (8, 1440, 5760), (8, 1536, 6144), (4, 1600, 6400), (8, 1400, 12288)])):
+        for M, K, N in last:
+            assert B.code_kernel(M, K, N, x_gran=x_gran, hands_maxima=True) == "k_linear_few", (M, K, N, x_gran)
+            assert B.code_kernel(M + 1, K, N, x_gran=x_gran, hands_maxima=True) != "k_linear_few", (M, K, N, x_gran)
+    assert B.code_kernel(16, 1536, 6144) == B.code_kernel(12, 1600, 6400) == "k_linear_few"
+    assert B.code_kernel(36, 512, 4096, hands_maxima=True) == B.code_kernel(36, 512, 4096) == "k_linear_few"
     assert B.code_kernel(5, 1032, 5120, x_gran="token") == B.code_kernel(12, 1280, 8192, x_gran="token") == "k_linear_few"
     # (M, K, N) of the last calls in the one launch, and a row more
     for x_gran, last in (("tensor", [(7, 4608, 4096), (6, 5120, 4096), (8, 5120, 2560), (12, 1600, 8192), (16, 1536, 12288), (16, 1280, 8192),
